@@ -212,3 +212,51 @@ def tolerance(case):
     if case["kind"] == "map":
         return {"rel": 1e-6}   # gates only
     return {"rel": 1e-2, "max": 0.15 if case["kind"] != "train" else 0.4}
+
+
+def _gates(s, c):
+    """Selected experts (ties to the lower id) and their gates in 64 bits."""
+    v, idx = torch.sort(s["logits"].double(), dim=1, descending=True, stable=True)
+    return idx[:, :c["k"]], torch.softmax(v[:, :c["k"]], dim=1)
+
+
+def exact(case, seed):
+    """What run returns for these inputs as plain torch computes it in 64 bits, without any rounding
+    between the stages.  None for the index arrays, which are whole numbers."""
+    c = case
+    s = prepare(case, seed)
+    idx, gate = _gates(s, c)
+    tables = dict.fromkeys(("topk_idx", "topk_w", "counts", "offsets", "perm", "inv_perm"))
+    tables["topk_w"] = gate
+    if c["kind"] == "map":
+        names = ("dst_rank", "dst_expert", "dst_off", "dst_row", "send", "n_dst_ranks", "recv_offsets")
+        return {"routing": tables, "map": dict.fromkeys(names)}
+    train = c["kind"] == "train"
+    y = torch.zeros((c["T"], c["d"]), dtype=torch.float64, device="cuda")
+    if train:
+        dx, dgate = torch.zeros_like(y), torch.zeros_like(gate)
+        dw = [torch.zeros(w.shape, dtype=torch.float64, device="cuda") for w in s["w"]]
+    for e in range(c["E_loc"]):
+        tok, slot = torch.nonzero(idx == e, as_tuple=True)
+        if tok.numel() == 0:
+            continue
+        wg, wu, wd = (w[e].double() for w in s["w"])
+        x, p = s["x"][tok].double(), gate[tok, slot][:, None]
+        g, u = x @ wg, x @ wu
+        sig = torch.sigmoid(g)
+        h = g * sig * u
+        y.index_add_(0, tok, p * (h @ wd))
+        if train:
+            dy = s["dy"][tok].double()
+            raw = dy @ wd.T
+            dgate[tok, slot] = (raw * h).sum(1)
+            dh = p * raw
+            dg, du = dh * u * sig * (1.0 + g * (1.0 - sig)), dh * g * sig
+            dw[0][e], dw[1][e], dw[2][e] = x.T @ dg, x.T @ du, h.T @ (p * dy)
+            dx.index_add_(0, tok, dg @ wg.T + du @ wu.T)
+    if not train:
+        return {"routing": tables, "y": y}
+    dlogits = torch.zeros((c["T"], c["E"]), dtype=torch.float64, device="cuda")
+    dlogits.scatter_(1, idx, gate * (dgate - (gate * dgate).sum(1, keepdim=True)))
+    grads = {"dx": dx, "dtopk_w": dgate, "dw_gate": dw[0], "dw_up": dw[1], "dw_down": dw[2]}
+    return {"routing": tables, "y": y, "grads": grads, "dlogits": dlogits}
