@@ -78,133 +78,75 @@ __device__ __forceinline__ int wgrad_parts(int idx) { return (idx >> 20) & 0xfff
 constexpr int kMaxSplitParts = 0xfff;
 constexpr size_t kPartialTileBytes = (size_t)BMAX * BN * sizeof(float);
 
-// ------------------------------------------------------------- row metadata
-// row_tok[r] = token of expert row r, row_w[r] = its gate (the backward
-// "dispatch" of dY is a gather through these).
-__global__ void __launch_bounds__(256) row_meta_kernel(BwdParams p) {
-    const int A = p.offsets[p.s.e_count];
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r < A) {
-        const int f = p.perm[r];
-        p.row_tok[r] = f / p.s.k;
-        p.row_w[r] = p.topk_w[f];
+// ------------------------------------------------------------- first launch
+// The first kPlanBlocks workgroups make the work queue: row tiles, per-XCD task lists, cleared
+// scoreboard.  List order per XCD (experts i = 0..n-1 of that list): [dH_0], [dH_1],
+// [dXp_0, dWgu_0, dWdown_0], [dH_2], [dXp_1, dWgu_1, dWdown_1], ...: the consumers of expert i sit
+// `lag` experts behind its producers.  All three consumer kinds read what the dH tiles wrote
+// (dG|dU, and gate * h for dW_down).  Beside them, one thread per routed row: row_tok[r] = token of
+// expert row r, row_w[r] = its gate (the backward "dispatch" of dY is a gather through these).
+__global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
+    __shared__ QueuePlan P;
+    const int ec = p.s.e_count, bm = p.bm;
+    if (blockIdx.x >= kPlanBlocks) {
+        const int r = ((int)blockIdx.x - kPlanBlocks) * kPlanThreads + threadIdx.x;
+        if (r < p.offsets[ec]) {
+            const int f = p.perm[r];
+            p.row_tok[r] = f / p.s.k;
+            p.row_w[r] = p.topk_w[f];
+        }
+        return;
     }
-}
-
-// One workgroup: row tiles, per-XCD task lists, cleared scoreboard.  List order
-// per XCD (experts i = 0..n-1 of that list): [dH_0], [dH_1], [dXp_0, dWgu_0, dWdown_0],
-// [dH_2], [dXp_1, dWgu_1, dWdown_1], ...: the consumers of expert i sit `lag` experts
-// behind its producers.  All three consumer kinds read what the dH tiles wrote
-// (dG|dU, and gate * h for dW_down).
-template <int BM>
-__global__ void __launch_bounds__(1024) bwd_prologue_kernel(BwdParams p) {
-    __shared__ int32_t s_scan[kMaxExperts];
-    __shared__ int32_t s_ga[kMaxExperts];
-    __shared__ int32_t s_gb[kMaxExperts];
-    __shared__ int32_t s_rt0[kMaxExperts];
-    __shared__ int32_t s_r0[kMaxExperts];
-    __shared__ int32_t s_ta[kMaxExperts];
-    __shared__ int32_t s_tb[kMaxExperts];
-    __shared__ int32_t s_qbase[kQueues + 1];
-    __shared__ int32_t s_qlen[kQueues];
-    __shared__ int32_t s_lag;
-    __shared__ ListPlan s_plan;
-    const int e = threadIdx.x;
-    const int ec = p.s.e_count;
+    const int block = blockIdx.x;
     const int per_dwd = p.mt_dwd * p.nt_dwd, per_dwgu = p.mt_dwgu * p.nt_dwgu;
-    int cnt = 0, nt = 0;
-    if (e < ec) {
-        cnt = p.offsets[e + 1] - p.offsets[e];
-        nt = (cnt + BM - 1) / BM;
-    }
     // Section 6.3 prices bitwise reproducibility in the backward pass: the order of the
     // weight-gradient reduction is fixed.  An expert with more than split_rows rows has that
     // reduction cut at the fixed points r0 + j * split_rows (a function of the counts only) into
     // `parts` tasks per output tile; their fp32 partial tiles are added in the order of j.
-    const int parts = (p.split_rows > 0 && cnt > p.split_rows) ? (cnt + p.split_rows - 1) / p.split_rows : 1;
-    __shared__ int32_t s_parts[kMaxExperts];
-    s_parts[e] = parts;
-    s_plan.cost[e] = cnt;
-    s_scan[e] = nt;
-    s_ga[e] = (e < ec) ? nt * p.nct_dh : 0;
-    s_gb[e] = (e < ec) ? nt * p.nct_dxp + (per_dwgu + per_dwd) * parts : 0;
-    __syncthreads();
-    for (int off = 1; off < kMaxExperts; off <<= 1) {
-        const int32_t add = (e >= off) ? s_scan[e - off] : 0;
-        __syncthreads();
-        s_scan[e] += add;
-        __syncthreads();
-    }
-    const int nrt = s_scan[kMaxExperts - 1];
-    if (p.split_rows > 0) {   // slots of the split experts: output tiles, and partial tiles
-        __shared__ int32_t s_st[kMaxExperts];
-        __shared__ int32_t s_sp[kMaxExperts];
-        const int tiles = (e < ec && parts > 1) ? per_dwgu + per_dwd : 0;
-        s_st[e] = tiles;
-        s_sp[e] = tiles * parts;
-        __syncthreads();
-        for (int off = 1; off < kMaxExperts; off <<= 1) {
-            const int32_t a0 = (e >= off) ? s_st[e - off] : 0, a1 = (e >= off) ? s_sp[e - off] : 0;
-            __syncthreads();
-            s_st[e] += a0;
-            s_sp[e] += a1;
-            __syncthreads();
+    auto parts_of = [&](int rows) {
+        return (p.split_rows > 0 && rows > p.split_rows) ? (rows + p.split_rows - 1) / p.split_rows : 1;
+    };
+    // (an expert without rows still has its weight gradients written)
+    make_plan(P, p.offsets, ec, 0, bm, p.nct_dh, [&](int rows) { return row_tiles(rows, bm) * p.nct_dh; },
+              [&](int rows) { return row_tiles(rows, bm) * p.nct_dxp + (per_dwgu + per_dwd) * parts_of(rows); });
+    const int lane = threadIdx.x & 63;
+    for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {   // one wave, one expert
+        const int rows_x = P.rows[x], nt_x = row_tiles(rows_x, bm), parts_x = parts_of(rows_x);
+        const int rt0 = plan_rt0(P, x), r0 = p.offsets[x];
+        const int n_dxp = nt_x * p.nct_dxp;
+        for (int i = lane; i < nt_x; i += 64) p.flag_rt[rt0 + i] = 0;
+        if (lane == 0) p.flag_e[x] = 0;
+        if (p.split_rows > 0) {   // slots of the split experts in front of this one: output tiles, and partial tiles
+            int st = 0, sp = 0;
+            for (int e = lane; e < x; e += 64) {
+                const int n = parts_of(P.rows[e]);
+                st += n > 1 ? 1 : 0;
+                sp += n > 1 ? n : 0;
+            }
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) {
+                st += __shfl_xor(st, o);
+                sp += __shfl_xor(sp, o);
+            }
+            st *= per_dwgu + per_dwd;
+            if (lane == 0) {
+                p.split_tile0[x] = st;
+                p.split_base[x] = sp * (per_dwgu + per_dwd);
+            }
+            if (parts_x > 1)
+                for (int i = lane; i < per_dwgu + per_dwd; i += 64) p.split_cnt[st + i] = 0;
         }
-        if (e < ec) {
-            p.split_tile0[e] = s_st[e] - tiles;
-            p.split_base[e] = s_sp[e] - tiles * parts;
-            for (int i = 0; i < tiles; ++i) p.split_cnt[s_st[e] - tiles + i] = 0;
-        }
-    }
-    plan_lists(s_plan, ec);
-    if (e < kQueues) {   // length of list e
-        int len = 0;
-        for (int j = 0; j < s_plan.size[e]; ++j) {
-            const int x = s_plan.member[e][j];
-            len += s_ga[x] + s_gb[x];
-        }
-        s_qlen[e] = len;
-    }
-    __syncthreads();
-    if (e == 0) {
-        int base = 0;
-        for (int q = 0; q < kQueues; ++q) {
-            s_qbase[q] = base;
-            base += s_qlen[q];
-        }
-        s_qbase[kQueues] = base;
-        s_lag = queue_lag(nrt * p.nct_dh, ec);
-    }
-    __syncthreads();
-    if (e < ec) {
-        const int rt0 = s_scan[e] - nt;
-        s_r0[e] = p.offsets[e];
-        for (int i = 0; i < nt; ++i) p.flag_rt[rt0 + i] = 0;
-        p.flag_e[e] = 0;
-        int pa, pb;
-        queue_positions(s_plan, s_ga, s_gb, e, s_lag, pa, pb);
-        s_rt0[e] = rt0;
-        s_ta[e] = s_qbase[s_plan.list_of[e]] + pa;
-        s_tb[e] = s_qbase[s_plan.list_of[e]] + pb;
-    }
-    __syncthreads();
-    for (int x = e >> 6; x < ec; x += 16) {   // one wave writes the two blocks of an expert
-        const int rt0 = s_rt0[x], lane = e & 63;
-        const int parts_x = s_parts[x];
-        const int n_dxp = s_gb[x] - (per_dwgu + per_dwd) * parts_x;
-        Task* ta = p.tasks + s_ta[x];
-        Task* tb = p.tasks + s_tb[x];
-        const int r0 = s_r0[x], rows_x = s_plan.cost[x];
+        Task* ta = p.tasks + plan_a(P, x);
+        Task* tb = p.tasks + plan_b(P, x);
         // every block in the grouped order of block_pos(): row-tile GEMMs over (row tile, column
         // tile), weight-gradient GEMMs over (output row tile, output column tile)
-        const int nt_x = (rows_x + BM - 1) / BM;
         for_each_tile(lane, nt_x, p.nct_dh, [&](int j, int ct) {
             ta[block_pos<true>(j, ct, nt_x, p.nct_dh)] =
-                Task{rt0 + j, task_code(B_DH, x, ct), r0 + j * BM, min(BM, rows_x - j * BM)};
+                Task{rt0 + j, task_code(B_DH, x, ct), r0 + j * bm, min(bm, rows_x - j * bm)};
         });
         for_each_tile(lane, nt_x, p.nct_dxp, [&](int j, int ct) {
             tb[block_pos<true>(j, ct, nt_x, p.nct_dxp)] =
-                Task{rt0 + j, task_code(B_DXP, x, ct), r0 + j * BM, min(BM, rows_x - j * BM)};
+                Task{rt0 + j, task_code(B_DXP, x, ct), r0 + j * bm, min(bm, rows_x - j * bm)};
         });
         // weight-gradient tasks: idx = output row tile | part << 8 | parts << 20; row0 / rows = the part's rows
         for_each_tile(lane, p.mt_dwgu, p.nt_dwgu, [&](int mt, int nt) {
@@ -224,15 +166,7 @@ __global__ void __launch_bounds__(1024) bwd_prologue_kernel(BwdParams p) {
             }
         });
     }
-    if (e < CTRL_WORDS) {
-        int v = 0;
-        if (e == CTRL_NRT) v = nrt;
-        if (e == CTRL_NTAIL) v = (p.s.T + kDxTokens - 1) / kDxTokens;
-        if (e == CTRL_NWAIT) v = p.workers;
-        if (e >= CTRL_QLEN && e < CTRL_QLEN + kQueues) v = s_qbase[e - CTRL_QLEN + 1] - s_qbase[e - CTRL_QLEN];
-        if (e >= CTRL_QBASE && e < CTRL_QBASE + kQueues) v = s_qbase[e - CTRL_QBASE];
-        p.ctrl[e] = v;
-    }
+    if (block == 0) write_ctrl(P, p.ctrl, (p.s.T + kDxTokens - 1) / kDxTokens, p.workers);
 }
 
 // ------------------------------------------------------------- phase 0: dH
@@ -829,19 +763,17 @@ static void launch_worker(bool acc, bool split, const BwdParams& p, int workers,
     hipLaunchKernelGGL(bwd_worker_fn(acc, split), dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, phase);
 }
 
-template <int BM>
-static int bwd_launch_bm(BwdParams& p, const moe_opts_t& opts, hipStream_t st) {
+static int bwd_launch_bm(BwdParams& p, const moe_opts_t& opts, int bm, hipStream_t st) {
     const bool acc = opts.dw_accumulate != 0, split = opts.dw_split_rows > 0;
     int resident = 0;
     int rc = bwd_resident_workers(acc, split, &resident);
     if (rc != MOE_OK) return rc;
     const int workers = opts.workers > 0 ? min(opts.workers, resident) : resident;
     p.workers = workers;
-    p.bm = BM;
+    p.bm = bm;
     const int A_cap = p.s.T * p.s.k;
-    if (A_cap > 0)
-        hipLaunchKernelGGL(row_meta_kernel, dim3((A_cap + 255) / 256), dim3(256), 0, st, p);
-    hipLaunchKernelGGL(bwd_prologue_kernel<BM>, dim3(1), dim3(1024), 0, st, p);
+    hipLaunchKernelGGL(bwd_first_kernel, dim3(kPlanBlocks + (A_cap + kPlanThreads - 1) / kPlanThreads), dim3(kPlanThreads),
+                       0, st, p);
     if (opts.schedule == 2) {
         for (int phase = 0; phase < 5; ++phase) launch_worker(acc, split, p, workers, phase, st);
     } else if (opts.schedule != 1) {   // 0 (default) and 3: GEMM MegaKernel, then the tail tasks
@@ -907,7 +839,7 @@ int bwd_launch(const moe_shape_t& s, const void* dy, const void* x, const void* 
     p.nt_dwgu = L.nt_dwgu;
     const int ms = opts.spin_limit_ms > 0 ? opts.spin_limit_ms : 2000;
     p.spin_ticks = (long long)ms * 100000ll;
-    return nw == 4 ? bwd_launch_bm<128>(p, opts, st) : bwd_launch_bm<256>(p, opts, st);
+    return bwd_launch_bm(p, opts, nw == 4 ? 128 : 256, st);
 }
 
 }  // namespace uniep

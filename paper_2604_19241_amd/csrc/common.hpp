@@ -206,79 +206,38 @@ __device__ __forceinline__ void for_each_tile(int lane, int nt, int nct, F f) {
         }
 }
 
-// Which expert goes to which list.  The lists should end at the same time:
-// work that one XCD steals from another list has lost the L2 sharing between
-// the tiles of a row tile and of an expert, and runs about half as fast.  So the
-// experts are sorted by cost (rows, descending; ties by id) and dealt to the
-// lists in boustrophedon order (ranks 0..7 to lists 0..7, ranks 8..15 to lists
-// 7..0, ...).  Big experts come first in every list, small ones fill the end.
-// The plan depends only on the counts, so it is the same on every run.
-struct ListPlan {
-    int32_t cost[kMaxExperts];              // in: cost of every local expert (0 beyond e_count)
-    uint16_t order[kMaxExperts];            // experts by descending cost
-    uint16_t member[kQueues][kMaxExperts];  // member[q][i] = i-th expert of list q
-    uint16_t list_of[kMaxExperts];
-    uint16_t slot_of[kMaxExperts];
-    int32_t size[kQueues];                  // experts per list
+// Which expert goes to which list, and where its blocks stand in it.  The lists should end at the
+// same time: work that one XCD steals from another list has lost the L2 sharing between the
+// tiles of a row tile and of an expert, and runs about half as fast.  So the experts are sorted
+// by rows (descending, in 64 classes of equal width; ties by id) and dealt to the lists in
+// boustrophedon order (ranks 0..7 to lists 0..7, ranks 8..15 to lists 7..0, ...).  Big experts
+// come first in every list, small ones fill the end.  The producer block of a list's (i + lag)-th
+// expert comes before the consumer block of its i-th: A0, A1, B0, A2, B1, ..., A(n-1), B(n-2),
+// B(n-1) for a lag of 1.  The plan depends only on the counts, so it is the same on every run.
+//
+// Latency is all that counts here (one launch in front of every pass, nothing else can run), so
+// every one of kPlanBlocks workgroups makes the whole plan for itself, without a word to
+// the others (ranks from ballots, positions from scans: five barriers), and writes the tasks
+// of its share of the experts.  One workgroup of 1024 threads with a loop over the experts per
+// thread took 11 us for 128 experts of which 8 have rows, 15 us for 128 with 512 rows each and
+// 45 us for 512 experts.
+constexpr int kPlanThreads = 256;
+constexpr int kPlanBlocks = 32;   // 128 waves: up to 128 experts, one wave writes one expert's tasks
+constexpr int kPlanWaves = kPlanThreads / kWave;
+constexpr int kListSlots = kMaxExperts / kQueues;
+struct QueuePlan {
+    int32_t a[kQueues][kListSlots + 1];   // producer tasks in front of slot i of a list, without the other blocks
+    int32_t b[kQueues][kListSlots + 1];   // consumer tasks likewise
+    int32_t rows[kMaxExperts];
+    int32_t rt0[kMaxExperts];             // first row tile of the expert
+    int32_t sums[1][kPlanWaves];          // row tiles of each wave's experts
+    int32_t most[kPlanWaves];
+    int32_t hist[kPlanWaves][64];
+    int32_t first[kPlanWaves][64];
+    uint16_t slot[kMaxExperts];           // list * kListSlots + slot
+    int32_t base[kQueues + 1];            // first entry of each list
+    int32_t lag, n_row_tiles, pad_[2];
 };
-
-// Called by all 1024 threads of the prologue workgroup after plan.cost is written
-// (and a barrier).  Ends with a barrier.
-__device__ __forceinline__ void plan_lists(ListPlan& plan, int ec) {
-    const int e = threadIdx.x;
-    if (e < ec) {
-        const int32_t mine = plan.cost[e];
-        int r = 0;
-        for (int j = 0; j < ec; ++j) {
-            const int32_t c = plan.cost[j];
-            r += (c > mine || (c == mine && j < e)) ? 1 : 0;
-        }
-        plan.order[r] = (uint16_t)e;
-    }
-    __syncthreads();
-    if (e < ec) {
-        const int x = plan.order[e];
-        const int i = e / kQueues, c = e % kQueues;
-        const int q = (i & 1) ? kQueues - 1 - c : c;
-        plan.member[q][i] = (uint16_t)x;
-        plan.list_of[x] = (uint16_t)q;
-        plan.slot_of[x] = (uint16_t)i;
-    }
-    if (e < kQueues) {
-        int n = 0;
-        for (int i = 0; i * kQueues < ec; ++i) {
-            const int c = (i & 1) ? kQueues - 1 - e : e;
-            n += (i * kQueues + c < ec) ? 1 : 0;
-        }
-        plan.size[e] = n;
-    }
-    __syncthreads();
-}
-
-// Position of expert e's producer block (pos_a) and consumer block (pos_b)
-// inside its list, given the block sizes ga[], gb[] of all experts (shared
-// memory) and the lag L >= 1: the consumer block of the list's i-th expert
-// follows the producer block of its (i+L)-th.  List order for L = 1:
-// A0, A1, B0, A2, B1, ..., A(n-1), B(n-2), B(n-1).
-__device__ __forceinline__ void queue_positions(const ListPlan& plan, const int* ga, const int* gb, int e,
-                                                int lag, int& pos_a, int& pos_b) {
-    const int q = plan.list_of[e], i = plan.slot_of[e];
-    const int nq = plan.size[q];
-    int sa_i = 0, sb_i = 0, sb_lag = 0, sa_n = 0;
-    const int lim = min(i + lag + 1, nq);
-    for (int j = 0; j < lim; ++j) {
-        const int ej = plan.member[q][j];
-        if (j < i) {
-            sa_i += ga[ej];
-            sb_i += gb[ej];
-            if (j < i - lag) sb_lag += gb[ej];
-        }
-        sa_n += ga[ej];
-    }
-    pos_a = sa_i + sb_lag;
-    pos_b = sa_n + sb_i;
-}
-
 // Lag (in experts) between an expert's producer and consumer blocks: enough
 // producer tasks in between (about four rounds of one XCD's workgroups) that a
 // consumer's inputs are complete when it is fetched, also near the end of the
@@ -286,6 +245,173 @@ __device__ __forceinline__ void queue_positions(const ListPlan& plan, const int*
 __device__ __forceinline__ int queue_lag(int total_producer_tasks, int ec) {
     const int per = max(1, total_producer_tasks / max(1, ec));
     return min(16, max(1, (128 + per - 1) / per));
+}
+
+
+// Row tiles of an expert; tiles have 256 or 128 rows.
+__device__ __forceinline__ int row_tiles(int rows, int bm) { return (rows + bm - 1) >> (bm == 256 ? 8 : 7); }
+// The plan of this workgroup (kPlanThreads threads, all of them call; ends with a barrier).
+// Experts with up to `skip_rows` rows have no tasks.  a_of(rows) / b_of(rows): tasks of an
+// expert's producer and consumer block; `per_row_tile` producer tasks for each row tile of bm rows.
+template <class FA, class FB>
+__device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, int ec, int skip_rows, int bm,
+                                          int per_row_tile, FA a_of, FB b_of) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint64_t below = (1ull << lane) - 1ull;
+    constexpr int kRounds = kMaxExperts / kPlanThreads;
+    int rows[kRounds], run = 0, most = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {   // wave w looks at experts 256 w + 64 r + lane
+        const int e = 256 * w + 64 * r + lane;
+        rows[r] = offsets[min(e + 1, ec)] - offsets[min(e, ec)];
+        if (rows[r] <= skip_rows) rows[r] = 0;
+    }
+    for (int i = tid; i < kQueues * (kListSlots + 1); i += kPlanThreads) (&P.a[0][0])[i] = (&P.b[0][0])[i] = 0;
+    P.hist[w][lane] = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int e = 256 * w + 64 * r + lane, nt = row_tiles(rows[r], bm);
+        int incl = nt;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(incl, o);
+            if (lane >= o) incl += v;
+        }
+        P.rows[e] = rows[r];
+        P.rt0[e] = run + incl - nt;   // inside the wave; the waves before are added by the reader (plan_rt0)
+        run += __shfl(incl, 63);
+        most = max(most, rows[r]);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) most = max(most, __shfl_xor(most, o));
+    if (lane == 0) {
+        P.sums[0][w] = run;
+        P.most[w] = most;
+    }
+    __syncthreads();
+    // rank inside the class: the wave's experts of the class so far + the lanes below
+#pragma unroll
+    for (int i = 0; i < kPlanWaves; ++i) most = max(most, P.most[i]);
+    const float scale = most > 0 ? 63.f / (float)most : 0.f;
+    int cls[kRounds], rank[kRounds];
+    volatile int32_t* hist = P.hist[w];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const bool in = 256 * w + 64 * r + lane < ec;
+        cls[r] = min(63, (int)((float)rows[r] * scale));
+        uint64_t m = __ballot(in);
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            const uint64_t bb = __ballot((cls[r] >> b) & 1);
+            m &= ((cls[r] >> b) & 1) ? bb : ~bb;
+        }
+        if (in) rank[r] = hist[cls[r]] + __popcll(m & below);
+        __builtin_amdgcn_wave_barrier();
+        if (in && (m >> lane) <= 1ull) hist[cls[r]] = rank[r] + 1;   // the class's last lane moves its count
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    {   // lane l: class 63 - l.  Experts in higher classes, then those of the class in the waves before
+        const int c = 63 - lane;
+        int mine = 0, tot = 0;
+#pragma unroll
+        for (int i = 0; i < kPlanWaves; ++i) {
+            if (i < w) mine += P.hist[i][c];
+            tot += P.hist[i][c];
+        }
+        int incl = tot;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(incl, o);
+            if (lane >= o) incl += v;
+        }
+        P.first[w][c] = incl - tot + mine;
+    }
+    __builtin_amdgcn_wave_barrier();
+    volatile int32_t* first = P.first[w];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int e = 256 * w + 64 * r + lane;
+        if (e < ec) {
+            const int k = first[cls[r]] + rank[r], i = k / kQueues, c = k % kQueues;
+            const int q = (i & 1) ? kQueues - 1 - c : c;
+            P.slot[e] = (uint16_t)(q * kListSlots + i);
+            P.a[q][i] = a_of(rows[r]);
+            P.b[q][i] = b_of(rows[r]);
+        }
+    }
+    __syncthreads();
+    {   // exclusive sums along each list: 32 threads a list, 4 slots a thread
+        const int q = tid >> 5, i0 = (tid & 31) * 4;
+        int va[4], vb[4], sa = 0, sb = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            va[j] = P.a[q][i0 + j];
+            vb[j] = P.b[q][i0 + j];
+            sa += va[j];
+            sb += vb[j];
+        }
+        int ia = sa, ib = sb;
+#pragma unroll
+        for (int o = 1; o < 32; o <<= 1) {
+            const int x = __shfl_up(ia, o, 32), y = __shfl_up(ib, o, 32);
+            if ((tid & 31) >= o) {
+                ia += x;
+                ib += y;
+            }
+        }
+        int xa = ia - sa, xb = ib - sb;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            P.a[q][i0 + j] = xa;
+            P.b[q][i0 + j] = xb;
+            xa += va[j];
+            xb += vb[j];
+        }
+        if (i0 + 4 == kListSlots) {
+            P.a[q][kListSlots] = xa;
+            P.b[q][kListSlots] = xb;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int base = 0, n = 0;
+        for (int q = 0; q < kQueues; ++q) {
+            P.base[q] = base;
+            base += P.a[q][kListSlots] + P.b[q][kListSlots];
+        }
+        P.base[kQueues] = base;
+        for (int i = 0; i < kPlanWaves; ++i) n += P.sums[0][i];
+        P.n_row_tiles = n;
+        P.lag = queue_lag(n * per_row_tile, ec);
+    }
+    __syncthreads();
+}
+// First entries of expert e's two blocks in the task array, and its first row tile.
+__device__ __forceinline__ int plan_a(const QueuePlan& P, int e) {
+    const int q = P.slot[e] / kListSlots, i = P.slot[e] % kListSlots;
+    return P.base[q] + P.a[q][i] + P.b[q][max(0, i - P.lag)];
+}
+__device__ __forceinline__ int plan_b(const QueuePlan& P, int e) {
+    const int q = P.slot[e] / kListSlots, i = P.slot[e] % kListSlots;
+    return P.base[q] + P.a[q][min(i + P.lag + 1, kListSlots)] + P.b[q][i];
+}
+__device__ __forceinline__ int plan_rt0(const QueuePlan& P, int e) {
+    int r = P.rt0[e];
+    for (int i = 0; i < e / 256; ++i) r += P.sums[0][i];
+    return r;
+}
+// The control words of a pass, by one workgroup.
+__device__ __forceinline__ void write_ctrl(const QueuePlan& P, int* ctrl, int n_tail, int n_wait) {
+    for (int i = threadIdx.x; i < CTRL_WORDS; i += kPlanThreads) {
+        int v = 0;
+        if (i == CTRL_NRT) v = P.n_row_tiles;
+        if (i == CTRL_NTAIL) v = n_tail;
+        if (i == CTRL_NWAIT) v = n_wait;
+        if (i >= CTRL_QLEN && i < CTRL_QLEN + kQueues) v = P.base[i - CTRL_QLEN + 1] - P.base[i - CTRL_QLEN];
+        if (i >= CTRL_QBASE && i < CTRL_QBASE + kQueues) v = P.base[i - CTRL_QBASE];
+        ctrl[i] = v;
+    }
 }
 
 // Bounded wait for *p >= need.  Returns false (and raises the status word) if

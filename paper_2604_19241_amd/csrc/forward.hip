@@ -10,8 +10,9 @@
 // written to HBM; the scoreboard that remains orders GEMM1 -> GEMM2 per row
 // tile and GEMM2 -> combine.  SwiGLU runs in the GEMM1 epilogue on the fp32
 // accumulators.
-#include "mma.hpp"
+#include "thin.hpp"
 
+#include <algorithm>
 #include <mutex>
 
 namespace uniep {
@@ -43,102 +44,60 @@ struct FwdParams {
     int nct1, nct2;   // column tiles of GEMM1 (128 h-columns each) and GEMM2 (256 each)
     int max_rt;
     int workers;   // workgroups of the worker launch (the tail waits for all of them)
+    int bm;            // rows per row tile (256, or 128)
+    int thin_rows;     // experts with 1..thin_rows rows are run outside the work queue
+    int plan_blocks;   // workgroups of the first launch that make the queue: kPlanBlocks, or 0 if there is none
     long long spin_ticks;
 };
 
-// ------------------------------------------------------------- prologue
-// One workgroup: row-tile table from the expert offsets, the per-XCD task lists
-// (GEMM1 block of expert i+1 ahead of the GEMM2 block of expert i) and a
-// cleared scoreboard.
-template <int BM>
-__global__ void __launch_bounds__(1024) fwd_prologue_kernel(FwdParams p) {
-    __shared__ int32_t s_scan[kMaxExperts];
-    __shared__ int32_t s_g1[kMaxExperts];
-    __shared__ int32_t s_g2[kMaxExperts];
-    __shared__ int32_t s_nt[kMaxExperts];
-    __shared__ int32_t s_qbase[kQueues + 1];
-    __shared__ int32_t s_qlen[kQueues];
-    __shared__ int32_t s_lag;
-    __shared__ ListPlan s_plan;
-    const int e = threadIdx.x;
-    const int ec = p.s.e_count;
-    int cnt = 0, nt = 0;
-    if (e < ec) {
-        cnt = p.offsets[e + 1] - p.offsets[e];
-        nt = (cnt + BM - 1) / BM;
-    }
-    s_plan.cost[e] = cnt;
-    s_scan[e] = nt;
-    s_nt[e] = nt;
-    s_g1[e] = nt * p.nct1;
-    s_g2[e] = nt * p.nct2;
-    __syncthreads();
-    for (int off = 1; off < kMaxExperts; off <<= 1) {
-        const int32_t add = (e >= off) ? s_scan[e - off] : 0;
-        __syncthreads();
-        s_scan[e] += add;
-        __syncthreads();
-    }
-    const int nrt = s_scan[kMaxExperts - 1];
-    plan_lists(s_plan, ec);
-    if (e < kQueues) {   // length of list e
-        int len = 0;
-        for (int j = 0; j < s_plan.size[e]; ++j) {
-            const int x = s_plan.member[e][j];
-            len += s_g1[x] + s_g2[x];
-        }
-        s_qlen[e] = len;
-    }
-    __syncthreads();
-    if (e == 0) {
-        int base = 0;
-        for (int q = 0; q < kQueues; ++q) {
-            s_qbase[q] = base;
-            base += s_qlen[q];
-        }
-        s_qbase[kQueues] = base;
-        s_lag = queue_lag(nrt * p.nct1, ec);
-    }
-    __syncthreads();
-    __shared__ int32_t s_rt0[kMaxExperts];
-    __shared__ int32_t s_r0[kMaxExperts];
-    __shared__ int32_t s_t1[kMaxExperts];
-    __shared__ int32_t s_t2[kMaxExperts];
-    if (e < ec) {
-        const int rt0 = s_scan[e] - nt;
-        s_r0[e] = p.offsets[e];
-        for (int i = 0; i < nt; ++i) p.flag1[rt0 + i] = 0;
-        int pos1, pos2;
-        queue_positions(s_plan, s_g1, s_g2, e, s_lag, pos1, pos2);
-        s_rt0[e] = rt0;
-        s_t1[e] = s_qbase[s_plan.list_of[e]] + pos1;
-        s_t2[e] = s_qbase[s_plan.list_of[e]] + pos2;
-    }
-    __syncthreads();
-    for (int x = e >> 6; x < ec; x += 16) {   // one wave writes the two blocks of an expert
-        const int rt0 = s_rt0[x], lane = e & 63;
-        Task* t1 = p.tasks + s_t1[x];
-        Task* t2 = p.tasks + s_t2[x];
-        const int r0 = s_r0[x], rows_x = s_plan.cost[x];
-        const int nt_x = s_nt[x];
+// ------------------------------------------------------------- first launch
+// The work queue of the experts with more than kThinRows rows, made by the first kPlanBlocks
+// workgroups: row-tile table from the expert offsets, the per-XCD task lists (GEMM1 block of
+// expert i+1 ahead of the GEMM2 block of expert i) and a cleared scoreboard.
+__device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePlan& P) {
+    const int ec = p.s.e_count, bm = p.bm;
+    make_plan(P, p.offsets, ec, kThinRows, bm, p.nct1, [&](int rows) { return row_tiles(rows, bm) * p.nct1; },
+              [&](int rows) { return row_tiles(rows, bm) * p.nct2; });
+    const int lane = threadIdx.x & 63;
+    for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {
+        const int rows_x = P.rows[x], nt_x = row_tiles(rows_x, bm);
+        if (nt_x == 0) continue;
+        const int rt0 = plan_rt0(P, x), r0 = p.offsets[x];
+        for (int i = lane; i < nt_x; i += 64) p.flag1[rt0 + i] = 0;
+        Task* t1 = p.tasks + plan_a(P, x);
+        Task* t2 = p.tasks + plan_b(P, x);
         for_each_tile(lane, nt_x, p.nct1, [&](int j, int ct) {
             t1[block_pos<true>(j, ct, nt_x, p.nct1)] =
-                Task{rt0 + j, task_code(TASK_GEMM1, x, ct), r0 + j * BM, min(BM, rows_x - j * BM)};
+                Task{rt0 + j, task_code(TASK_GEMM1, x, ct), r0 + j * bm, min(bm, rows_x - j * bm)};
         });
         for_each_tile(lane, nt_x, p.nct2, [&](int j, int ct) {
             t2[block_pos<true>(j, ct, nt_x, p.nct2)] =
-                Task{rt0 + j, task_code(TASK_GEMM2, x, ct), r0 + j * BM, min(BM, rows_x - j * BM)};
+                Task{rt0 + j, task_code(TASK_GEMM2, x, ct), r0 + j * bm, min(bm, rows_x - j * bm)};
         });
     }
-    if (e < CTRL_WORDS) {
-        int v = 0;
-        if (e == CTRL_NRT) v = nrt;
-        if (e == CTRL_NTAIL) v = (p.s.T + kCombineTokens - 1) / kCombineTokens;
-        if (e == CTRL_NWAIT) v = p.workers;
-        if (e >= CTRL_QLEN && e < CTRL_QLEN + kQueues) v = s_qbase[e - CTRL_QLEN + 1] - s_qbase[e - CTRL_QLEN];
-        if (e >= CTRL_QBASE && e < CTRL_QBASE + kQueues) v = s_qbase[e - CTRL_QBASE];
-        p.ctrl[e] = v;
+    if (block == 0) write_ctrl(P, p.ctrl, (p.s.T + kCombineTokens - 1) / kCombineTokens, p.workers);
+}
+
+__device__ __forceinline__ ThinParams thin_params(const FwdParams& p) {
+    return ThinParams{p.s, p.x, p.w_gate, p.w_up, p.w_down, p.offsets, p.perm, p.gu, p.h, p.o, p.thin_rows};
+}
+// The queue (unless every expert is thin) and the thin experts' GEMM1, side by side: neither reads
+// what the other writes.
+__global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(3)))
+fwd_first_kernel(FwdParams p) {
+    __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared) > sizeof(QueuePlan) ? sizeof(ThinShared) : sizeof(QueuePlan)];
+    const int block = (int)blockIdx.x - p.plan_blocks;
+    if (block < 0) {
+        fwd_setup(p, (int)blockIdx.x, *(QueuePlan*)smem);
+        return;
     }
+    if (p.plan_blocks == 0 && block == 0 && threadIdx.x < CTRL_WORDS) p.ctrl[threadIdx.x] = 0;
+    thin_run<1>(thin_params(p), block, (int)gridDim.x - p.plan_blocks, *(ThinShared*)smem);
+}
+__global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(3)))
+fwd_second_kernel(FwdParams p) {
+    __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared)];
+    thin_run<2>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
 }
 
 // ------------------------------------------------------------- GEMM1 task
@@ -340,6 +299,7 @@ fwd_worker_kernel(FwdParams p, int phase) {
     const bool publishes = phase == -1 || phase == TASK_GEMM2;
     bool arrived = false;
     unsigned exhausted = 0;
+    if (phase == -2 && ctrl[CTRL_NRT] == 0) return;   // every expert was thin
     if (threadIdx.x == 0) {
         if (phase == -1) worker_started(ctrl, home);
         s_task = fetch_task(ctrl, pass, home, exhausted, use_lists, use_tail);
@@ -476,28 +436,43 @@ static int resident_workers(int* out) {
     return MOE_OK;
 }
 
+static void launch_tail(const FwdParams& p, int n_tail, hipStream_t st) {
+    if (p.s.k <= 8)
+        hipLaunchKernelGGL((fwd_tail_kernel<8, 8>), dim3(n_tail), dim3(kMmaThreads), 0, st, p);
+    else
+        hipLaunchKernelGGL((fwd_tail_kernel<8, kMaxTopK>), dim3(n_tail), dim3(kMmaThreads), 0, st, p);
+}
+
 // BM = rows per row tile: 256, or 128 (every tile then leaves the upper half of the workgroup's
 // rows empty; kept as an option because results must not depend on it).
-template <int BM>
-static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, hipStream_t st) {
+static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream_t st) {
     int resident = 0;
     int rc = resident_workers(&resident);
     if (rc != MOE_OK) return rc;
     int workers = opts.workers > 0 ? min(opts.workers, resident) : resident;
     p.workers = workers;
-    hipLaunchKernelGGL(fwd_prologue_kernel<BM>, dim3(1), dim3(1024), 0, st, p);
+    p.bm = bm;
+    const int n_tail = (p.s.T + kCombineTokens - 1) / kCombineTokens;
+    // A token selects an expert at most once, so up to kThinRows tokens no expert has more rows than
+    // that: every expert is thin and no work queue is set up.
+    const bool all_thin = p.s.T <= kThinRows;
+    p.thin_rows = all_thin ? INT_MAX : kThinRows;
+    p.plan_blocks = all_thin ? 0 : kPlanBlocks;
+    const size_t most = std::min<size_t>(p.s.e_count, (size_t)p.s.T * p.s.k);   // experts with rows
+    const size_t slots = (size_t)kThinGroupsPerCu * resident;
+    const size_t n1 = std::min(slots, most * (p.s.I / 64)), n2 = std::min(slots, most * ((p.s.d + kThinCols - 1) / kThinCols));
+    hipLaunchKernelGGL(fwd_first_kernel, dim3((unsigned)(n1 + p.plan_blocks)), dim3(kThinThreads), 0, st, p);
+    hipLaunchKernelGGL(fwd_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);
+    if (all_thin) {
+        if (!opts.skip_tail || opts.schedule == 1 || opts.schedule == 2) launch_tail(p, n_tail, st);
+        return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+    }
     if (opts.schedule == 2) {
         for (int phase = 0; phase < 3; ++phase)
             hipLaunchKernelGGL(fwd_worker_kernel, dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, phase);
     } else if (opts.schedule != 1) {   // 0 (default) and 3: GEMM MegaKernel, then the tail tasks
         hipLaunchKernelGGL(fwd_worker_kernel, dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, -2);
-        const int n_tail = (p.s.T + kCombineTokens - 1) / kCombineTokens;
-        if (n_tail > 0 && !opts.skip_tail) {
-            if (p.s.k <= 8)
-                hipLaunchKernelGGL((fwd_tail_kernel<8, 8>), dim3(n_tail), dim3(kMmaThreads), 0, st, p);
-            else
-                hipLaunchKernelGGL((fwd_tail_kernel<8, kMaxTopK>), dim3(n_tail), dim3(kMmaThreads), 0, st, p);
-        }
+        if (!opts.skip_tail) launch_tail(p, n_tail, st);
     } else {
         hipLaunchKernelGGL(fwd_worker_kernel, dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, -1);
     }
@@ -530,7 +505,7 @@ int fwd_launch(const moe_shape_t& s, const void* x, const void* w_gate, const vo
     p.max_rt = L.max_rt;
     const int ms = opts.spin_limit_ms > 0 ? opts.spin_limit_ms : 2000;
     p.spin_ticks = (long long)ms * 100000ll;   // wall_clock64 ticks at 100 MHz
-    return nw == 4 ? fwd_launch_bm<128>(p, opts, st) : fwd_launch_bm<256>(p, opts, st);
+    return fwd_launch_bm(p, opts, nw == 4 ? 128 : 256, st);
 }
 
 
