@@ -5,215 +5,284 @@
 // one rank the global offset base is zero, so the destination row of a
 // (token, slot) pair is  offsets[e] + rank of the pair among the pairs of e.
 //
-// No position is ever handed out by an atomic: the flat slots are cut into
-// fixed chunks, each chunk counts its experts, a scan over chunks gives every
-// chunk its starting row per expert, and inside a chunk ranks come from wave
-// ballots in lane order.  The result is therefore the same on every run.
+// No position is ever handed out by an atomic: the tokens are cut into fixed chunks, a slot's
+// rank inside its chunk comes from wave ballots in flat-slot order, and a scan over the chunks
+// gives every chunk its starting row per expert.  The result is therefore the same on every run.
 #include "common.hpp"
 
 #include <mutex>
 
 namespace uniep {
 
-constexpr int kChunk = 256;        // flat slots per wave-chunk (4 wave iterations)
+constexpr int kChunk = 256;        // flat slots per chunk, rounded up to whole tokens
 constexpr int kRouteThreads = 256; // 4 waves per workgroup
+constexpr int kChunkThreads = 1024;
+constexpr int kPieces = (kChunk + kMaxTopK - 1 + 63) / 64;   // 64-slot pieces of a chunk
+// Up to this many chunks every workgroup of the last kernel adds the chunks in front of its own
+// by itself (one launch less): 40 chunks of 512 experts are 80 KB from L2 for each of 40 workgroups.
+constexpr int kFewChunks = 64;
 
-// ---------------------------------------------------------------- top-k + gates
-// One wave per token.  Lane l holds experts l, l+64, ...  k rounds of arg-max
-// under the order (value desc, expert id asc); gates from the k selected logits
-// (the softmax denominator over all E cancels in the renormalisation).
-template <int EPL>
-__global__ void __launch_bounds__(kRouteThreads)
-topk_gate_kernel(const float* __restrict__ logits, int T, int E, int k,
-                 int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    const int lane = threadIdx.x & 63;
-    const int t = blockIdx.x * (kRouteThreads / 64) + (threadIdx.x >> 6);
-    if (t >= T) return;
-    const float* row = logits + (size_t)t * E;
-    float v[EPL];
+static int chunk_tokens(int k) { return (kChunk + k - 1) / k; }
+static int chunks_of(const moe_shape_t& s) { return (s.T + chunk_tokens(s.k) - 1) / chunk_tokens(s.k); }
+
+// Largest value over the wave, on the data-parallel-primitive path of the vector ALU: six
+// instructions; six shuffles through LDS took ten times as long.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+#define UNIEP_DPP_MAX(ctrl, rows) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false))
+    UNIEP_DPP_MAX(0x111, 0xf);   // row_shr:1
+    UNIEP_DPP_MAX(0x112, 0xf);   // row_shr:2
+    UNIEP_DPP_MAX(0x114, 0xf);   // row_shr:4
+    UNIEP_DPP_MAX(0x118, 0xf);   // row_shr:8  -> lane 15 of every row of 16 has the row's
+    UNIEP_DPP_MAX(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+    UNIEP_DPP_MAX(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef UNIEP_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// Unsigned integers in the order of the floats.  0 stands for a NaN (which is never selected),
+// an expert already taken and the padding; both zeros get one key, as they compare equal.
+__device__ __forceinline__ uint32_t logit_key(float x) {
+    const uint32_t u = __float_as_uint(x + 0.f);
+    return x == x ? ((u & 0x80000000u) ? ~u : u | 0x80000000u) : 0u;
+}
+__device__ __forceinline__ float key_logit(uint32_t k) {
+    return __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k);
+}
+
+// Exclusive sum over the workgroup's threads (W waves); `total` = sum over all of them.
+// s_wave: W words of LDS that nobody uses across the call's two barriers.
+template <int W>
+__device__ __forceinline__ int block_exclusive_sum(int v, int32_t* s_wave, int* total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int incl = v;
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-        const int e = lane + 64 * i;
-        v[i] = (e < E) ? row[e] : -INFINITY;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(incl, o);
+        if (lane >= o) incl += x;
     }
-    uint32_t taken = 0;
+    __syncthreads();
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int before = 0, all = 0;
 #pragma unroll
-    for (int i = 0; i < EPL; ++i)
-        if (lane + 64 * i >= E) taken |= 1u << i;   // padding lanes never win
-    float my_val = 0.f;
-    int my_idx = 0;
-    float top1 = 0.f;
-    for (int j = 0; j < k; ++j) {
-        float bv = -INFINITY;
-        int be = 0x7fffffff;
+    for (int w = 0; w < W; ++w) {
+        const int x = s_wave[w];
+        if (w < wave) before += x;
+        all += x;
+    }
+    *total = all;
+    return before + incl - v;
+}
+
+// ------------------------------------------- top-k, gates and ranks inside a chunk
+// One workgroup per chunk, one wave per token at a time.  Lane l holds experts l, l+64, ... as
+// sortable keys; a round of arg-max under the order (value desc, expert id asc) is one wave
+// maximum and one ballot per key, whose first set bit is the lowest expert id.  Gates come from
+// the k selected logits (the softmax denominator over all E cancels in the renormalisation).
+// Then wave i ranks the chunk's slots [64 i, 64 i + 64): lanes that share an expert are the
+// intersection of the ballots of the expert id's bits.  chunk_cnt[c][e] = slots of chunk c
+// routed to local expert e; inv_perm[f] = rank of slot f among its chunk's slots of that expert.
+// Bound by instruction issue.  With the maximum by shuffles and counts, scan and positions in three
+// launches of their own the whole routing took 101 us for 32768 tokens of 256 experts, 8 selected
+// (now 45 us), and 14 us in four launches for one token of 128 experts (now one launch of 4 us).
+//
+// ONE: the batch is a single chunk (a generation step): the ranks are complete, and the same
+// workgroup scans the counts and writes the rows.
+template <int EPL, bool ONE>
+__global__ void __launch_bounds__(kChunkThreads)
+topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_chunk, int e_start, int e_count,
+                 int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ chunk_cnt,
+                 int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+                 int32_t* __restrict__ inv_perm) {
+    __shared__ int32_t s_idx[kPieces * 64];
+    __shared__ int32_t s_cnt[kPieces][kMaxExperts];
+    __shared__ int32_t s_off[ONE ? kMaxExperts : 1];
+    __shared__ int32_t s_wave[kChunkThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t0 = blockIdx.x * per_chunk, nt = min(per_chunk, T - t0), n = nt * k;
+    const size_t f0 = (size_t)t0 * k;
+    if (tid < e_count)
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) s_cnt[i][tid] = 0;
+    for (int tt = wave; tt < nt; tt += kChunkThreads / 64) {
+        const float* row = logits + (size_t)(t0 + tt) * E;
+        uint32_t key[EPL];
 #pragma unroll
         for (int i = 0; i < EPL; ++i) {
             const int e = lane + 64 * i;
-            const bool free_ = !((taken >> i) & 1u);
-            if (free_ && (v[i] > bv || (v[i] == bv && e < be))) { bv = v[i]; be = e; }
+            key[i] = e < E ? logit_key(row[e]) : 0u;
         }
+        float my_val = 0.f, top1 = 0.f;
+        int my_idx = 0;
+        for (int j = 0; j < k; ++j) {
+            uint32_t best = key[0];
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            const float ov = __shfl_xor(bv, off);
-            const int oe = __shfl_xor(be, off);
-            if (ov > bv || (ov == bv && oe < be)) { bv = ov; be = oe; }
-        }
-        // every lane now agrees on (bv, be); the owner retires it
-        if ((be & 63) == lane) taken |= 1u << (be >> 6);
-        if (j == 0) top1 = bv;
-        if (lane == j) { my_val = bv; my_idx = be; }
-    }
-    float p = (lane < k) ? __expf(my_val - top1) : 0.f;
-    float s = p;
+            for (int i = 1; i < EPL; ++i) best = max(best, key[i]);
+            best = wave_max(best);
+            float bv = -INFINITY;
+            int be = 0x7fffffff;
+            if (best != 0u) {
+                bv = key_logit(best);
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    if (lane < k) {
-        topk_idx[(size_t)t * k + lane] = my_idx;
-        topk_w[(size_t)t * k + lane] = p / s;
-    }
-}
-
-// ------------------------------------------------------- per-chunk BinCount
-// chunk_cnt[c][e] = number of slots of chunk c routed to local expert e.
-// Also pre-fills perm with -1 (rows at and beyond A keep it).
-__global__ void __launch_bounds__(kRouteThreads)
-chunk_count_kernel(const int32_t* __restrict__ topk_idx, int F, int e_start, int e_count,
-                   int32_t* __restrict__ chunk_cnt, int32_t* __restrict__ perm) {
-    extern __shared__ int32_t s_cnt[];   // [4][e_count]
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int chunk = blockIdx.x * (kRouteThreads / 64) + wave;
-    int32_t* cnt = s_cnt + wave * e_count;
-    for (int e = lane; e < e_count; e += 64) cnt[e] = 0;
-    __syncthreads();
-    const int f0 = chunk * kChunk;
-    for (int it = 0; it < kChunk / 64; ++it) {
-        const int f = f0 + it * 64 + lane;
-        if (f < F) {
-            perm[f] = -1;
-            const int el = topk_idx[f] - e_start;
-            if (el >= 0 && el < e_count) atomicAdd(&cnt[el], 1);   // integer sum: order-free
-        }
-    }
-    __syncthreads();
-    if (f0 < F)
-        for (int e = lane; e < e_count; e += 64) chunk_cnt[(size_t)chunk * e_count + e] = cnt[e];
-}
-
-// ------------------------------------------- scan over chunks, then over experts
-// One workgroup.  In place: chunk_cnt[c][e] becomes the number of e-slots in
-// chunks before c.  counts[e] = total, offsets = exclusive CumSum(counts).
-// The chunks are cut into G = 1024 / e_pad contiguous groups (e_pad = e_count
-// rounded up to a power of two); thread (g, e) first sums its group, the group
-// sums are scanned over g, then the thread rewrites its chunks with the running value.
-__global__ void __launch_bounds__(1024)
-scan_kernel(int32_t* __restrict__ chunk_cnt, int n_chunks, int e_count,
-            int32_t* __restrict__ counts, int32_t* __restrict__ offsets) {
-    __shared__ int32_t s_tot[kMaxExperts];
-    __shared__ int32_t s_grp[kMaxExperts];   // [G][e_pad]
-    const int tid = threadIdx.x;
-    int e_pad = 1;
-    while (e_pad < e_count) e_pad <<= 1;
-    const int G = kMaxExperts / e_pad;
-    const int e = tid & (e_pad - 1), g = tid / e_pad;
-    const int per = (n_chunks + G - 1) / G;
-    const int c0 = min(g * per, n_chunks), c1 = min(c0 + per, n_chunks);
-    int32_t sum = 0;
-    if (e < e_count) {
-        int c = c0;
-        for (; c + 8 <= c1; c += 8) {
-            int32_t tmp[8];
+                for (int i = EPL - 1; i >= 0; --i) {
+                    const uint64_t m = __ballot(key[i] == best);
+                    if (m) be = 64 * i + (int)__builtin_ctzll(m);
+                }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) tmp[u] = chunk_cnt[(size_t)(c + u) * e_count + e];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) sum += tmp[u];
-        }
-        for (; c < c1; ++c) sum += chunk_cnt[(size_t)c * e_count + e];
-    }
-    s_grp[tid] = sum;
-    __syncthreads();
-    int32_t run = 0, total = 0;
-    for (int j = 0; j < G; ++j) {
-        const int32_t v = s_grp[j * e_pad + e];
-        if (j < g) run += v;
-        total += v;
-    }
-    if (e < e_count) {
-        int c = c0;
-        for (; c + 8 <= c1; c += 8) {
-            int32_t tmp[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) tmp[u] = chunk_cnt[(size_t)(c + u) * e_count + e];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                chunk_cnt[(size_t)(c + u) * e_count + e] = run;
-                run += tmp[u];
+                for (int i = 0; i < EPL; ++i) key[i] = (lane + 64 * i == be) ? 0u : key[i];
             }
+            if (j == 0) top1 = bv;
+            if (lane == j) { my_val = bv; my_idx = be; }
         }
-        for (; c < c1; ++c) {
-            const int32_t tmp = chunk_cnt[(size_t)c * e_count + e];
-            chunk_cnt[(size_t)c * e_count + e] = run;
-            run += tmp;
+        const float p = (lane < k) ? __expf(my_val - top1) : 0.f;
+        float s = p;
+#pragma unroll
+        for (int off = kMaxTopK / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+        if (lane < k) {
+            s_idx[tt * k + lane] = my_idx;
+            topk_idx[f0 + tt * k + lane] = my_idx;
+            topk_w[f0 + tt * k + lane] = p / s;
         }
-        if (g == 0) counts[e] = total;
     }
     __syncthreads();
-    s_tot[tid] = (g == 0 && e < e_count) ? total : 0;   // g == 0: tid == e
-    __syncthreads();
-    // inclusive Hillis-Steele scan over 1024 entries
-    for (int off = 1; off < kMaxExperts; off <<= 1) {
-        const int32_t add = (tid >= off) ? s_tot[tid - off] : 0;
-        __syncthreads();
-        s_tot[tid] += add;
-        __syncthreads();
-    }
-    if (tid < e_count) offsets[tid + 1] = s_tot[tid];
-    if (tid == 0) offsets[0] = 0;
-}
-
-// ------------------------------------------------------------ stable positions
-// Each wave walks its chunk 64 slots at a time.  cur[e] = next free row of
-// expert e for this chunk; lanes that share an expert take consecutive rows in
-// lane order (= flat-slot order): the set of such lanes is the intersection of
-// the ballots of the expert id's bits, a lane's rank the set bits below it.
-__global__ void __launch_bounds__(kRouteThreads)
-position_kernel(const int32_t* __restrict__ topk_idx, int F, int e_start, int e_count,
-                const int32_t* __restrict__ chunk_base, const int32_t* __restrict__ offsets,
-                int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
-    extern __shared__ int32_t s_cur_all[];   // [4][e_count]
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int chunk = blockIdx.x * (kRouteThreads / 64) + wave;
-    volatile int32_t* cur = s_cur_all + wave * e_count;
-    const int f0 = chunk * kChunk;
-    if (f0 >= F) return;   // whole wave leaves together; no workgroup barrier below
-    for (int e = lane; e < e_count; e += 64)
-        cur[e] = offsets[e] + chunk_base[(size_t)chunk * e_count + e];
-    __builtin_amdgcn_wave_barrier();
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int it = 0; it < kChunk / 64; ++it) {
-        const int f = f0 + it * 64 + lane;
-        int el = -1;
-        if (f < F) {
-            el = topk_idx[f] - e_start;
+    int el = -1, rank = -1;
+    if (wave < kPieces) {
+        if (tid < n) {
+            el = s_idx[tid] - e_start;
             if (el < 0 || el >= e_count) el = -1;
         }
-        // lanes with the same expert: intersect the ballots of the expert id's bits
         uint64_t m = __ballot(el >= 0);
         for (int b = 0; (1 << b) < e_count; ++b) {
             const uint64_t bb = __ballot((el >> b) & 1);
             m &= ((el >> b) & 1) ? bb : ~bb;
         }
-        int row = -1;
         if (el >= 0) {
-            row = cur[el] + __popcll(m & lt_mask);
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (el >= 0 && (m >> lane) <= 1ull) cur[el] = row + 1;   // the group's last lane moves the cursor
-        __builtin_amdgcn_wave_barrier();
-        if (f < F) {
-            inv_perm[f] = row;
-            if (row >= 0) perm[row] = f;
+            rank = __popcll(m & ((1ull << lane) - 1ull));
+            if ((m >> lane) <= 1ull) s_cnt[wave][el] = rank + 1;   // the group's last lane knows its size
         }
     }
+    __syncthreads();
+    if (el >= 0)
+        for (int w = 0; w < wave; ++w) rank += s_cnt[w][el];
+    int total = 0;
+    if (tid < e_count)
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) total += s_cnt[i][tid];
+    if (!ONE) {
+        if (tid < n) inv_perm[f0 + tid] = rank;
+        if (tid < e_count) chunk_cnt[(size_t)blockIdx.x * e_count + tid] = total;
+        return;
+    }
+    int rows;
+    const int off = block_exclusive_sum<kChunkThreads / 64>(total, s_wave, &rows);
+    if (tid < e_count) {
+        counts[tid] = total;
+        offsets[tid] = s_off[tid] = off;
+    }
+    if (tid == 0) offsets[e_count] = rows;
+    __syncthreads();
+    if (tid < n) {
+        const int row = el >= 0 ? s_off[el] + rank : -1;
+        inv_perm[tid] = row;
+        if (row >= 0) perm[row] = tid;
+        if (tid >= rows) perm[tid] = -1;   // rows at and beyond the routed ones
+    }
+}
+
+// ------------------------------------------------------------- scan over chunks
+// In place: chunk_cnt[c][e] becomes the number of e-slots in chunks before c; counts[e] = total.
+// A workgroup has 16 experts (64-byte row pieces) by 64 chunk lanes of 8 chunks: the table is read
+// once, 8 loads in flight a thread.
+constexpr int kScanExperts = 16, kScanLanes = kChunkThreads / kScanExperts, kScanPer = 8;
+__global__ void __launch_bounds__(kChunkThreads)
+chunk_scan_kernel(int32_t* __restrict__ chunk_cnt, int n_chunks, int e_count, int32_t* __restrict__ counts) {
+    __shared__ int32_t s_sum[kScanLanes][kScanExperts + 1];
+    const int col = threadIdx.x & (kScanExperts - 1), g = threadIdx.x / kScanExperts;
+    const int e = blockIdx.x * kScanExperts + col;
+    int32_t carry = 0;
+    for (int base = 0; base < n_chunks; base += kScanLanes * kScanPer) {
+        const int c0 = base + g * kScanPer;
+        int32_t v[kScanPer], sum = 0;
+#pragma unroll
+        for (int u = 0; u < kScanPer; ++u) {
+            v[u] = (e < e_count && c0 + u < n_chunks) ? chunk_cnt[(size_t)(c0 + u) * e_count + e] : 0;
+            sum += v[u];
+        }
+        s_sum[g][col] = sum;
+        __syncthreads();
+        int32_t run = carry;
+#pragma unroll 8
+        for (int i = 0; i < kScanLanes; ++i) {
+            const int32_t x = s_sum[i][col];
+            if (i < g) run += x;
+            carry += x;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kScanPer; ++u) {
+            if (e < e_count && c0 + u < n_chunks) chunk_cnt[(size_t)(c0 + u) * e_count + e] = run;
+            run += v[u];
+        }
+    }
+    if (g == 0 && e < e_count) counts[e] = carry;
+}
+
+// ------------------------------------------------------------ rows
+// One workgroup per chunk: row of a slot = first row of its expert (scan of the counts over the
+// experts, by every workgroup for itself) + the expert's slots in the chunks before + its rank
+// in the chunk.  SCANNED: chunk_cnt already holds the sums over the chunks before.
+template <bool SCANNED>
+__global__ void __launch_bounds__(kChunkThreads)
+rows_kernel(const int32_t* __restrict__ topk_idx, int T, int k, int per_chunk, int n_chunks, int e_start, int e_count,
+            const int32_t* __restrict__ chunk_cnt, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+            int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
+    __shared__ int32_t s_base[kMaxExperts];
+    __shared__ int32_t s_wave[kChunkThreads / 64];
+    const int tid = threadIdx.x, c = blockIdx.x;
+    const int t0 = c * per_chunk, n = min(per_chunk, T - t0) * k;
+    const int f = t0 * k + tid;
+    int el = -1, rank = 0;
+    if (tid < n) {
+        el = topk_idx[f] - e_start;
+        rank = inv_perm[f];
+    }
+    int before = 0, total = 0;
+    if (tid < e_count) {
+        if (SCANNED) {
+            before = chunk_cnt[(size_t)c * e_count + tid];
+            total = counts[tid];
+        } else {
+#pragma unroll 8
+            for (int i = 0; i < n_chunks; ++i) {
+                const int x = chunk_cnt[(size_t)i * e_count + tid];
+                if (i < c) before += x;
+                total += x;
+            }
+        }
+    }
+    int rows;
+    const int off = block_exclusive_sum<kChunkThreads / 64>(total, s_wave, &rows);
+    if (tid < e_count) {
+        s_base[tid] = off + before;
+        if (c == 0) {
+            if (!SCANNED) counts[tid] = total;
+            offsets[tid] = off;
+        }
+    }
+    if (c == 0 && tid == 0) offsets[e_count] = rows;
+    __syncthreads();
+    if (tid < n) {
+        const int row = rank >= 0 ? s_base[el] + rank : -1;
+        inv_perm[f] = row;
+        if (row >= 0) perm[row] = f;
+        if (f >= rows) perm[f] = -1;   // rows at and beyond the routed ones
+    }
+}
+
+// No tokens: no expert has rows.
+__global__ void __launch_bounds__(kChunkThreads) no_rows_kernel(int e_count, int32_t* counts, int32_t* offsets) {
+    if ((int)threadIdx.x < e_count) counts[threadIdx.x] = 0;
+    if ((int)threadIdx.x < e_count) offsets[threadIdx.x + 1] = 0;
+    if (threadIdx.x == 0) offsets[0] = 0;
 }
 
 // ------------------------------------------------------------ router gradient
@@ -351,6 +420,7 @@ int route_backward_launch(const moe_shape_t& s, const int32_t* topk_idx, const f
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
+// (a chunk has at least kChunk slots, so there are at most this many)
 size_t route_workspace_bytes(const moe_shape_t& s) {
     const size_t F = (size_t)s.T * s.k;
     const size_t n_chunks = (F + kChunk - 1) / kChunk;
@@ -358,38 +428,43 @@ size_t route_workspace_bytes(const moe_shape_t& s) {
 }
 
 template <int EPL>
-static void launch_topk(const moe_shape_t& s, const float* logits, int32_t* idx, float* w,
+static void launch_topk(const moe_shape_t& s, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
                         hipStream_t st) {
-    const int per = kRouteThreads / 64;
-    hipLaunchKernelGGL(topk_gate_kernel<EPL>, dim3((s.T + per - 1) / per), dim3(kRouteThreads), 0,
-                       st, logits, s.T, s.E, s.k, idx, w);
+    const int n = chunks_of(s);
+    if (n == 1)
+        hipLaunchKernelGGL((topk_rank_kernel<EPL, true>), dim3(1), dim3(kChunkThreads), 0, st, logits, s.T, s.E, s.k,
+                           chunk_tokens(s.k), s.e_start, s.e_count, (int32_t*)out.topk_idx, (float*)out.topk_w, chunk_cnt,
+                           (int32_t*)out.counts, (int32_t*)out.offsets, (int32_t*)out.perm, (int32_t*)out.inv_perm);
+    else
+        hipLaunchKernelGGL((topk_rank_kernel<EPL, false>), dim3(n), dim3(kChunkThreads), 0, st, logits, s.T, s.E, s.k,
+                           chunk_tokens(s.k), s.e_start, s.e_count, (int32_t*)out.topk_idx, (float*)out.topk_w, chunk_cnt,
+                           (int32_t*)out.counts, (int32_t*)out.offsets, (int32_t*)out.perm, (int32_t*)out.inv_perm);
 }
 
 int route_launch(const moe_shape_t& s, const float* logits, const moe_routing_t& out, void* ws,
                  hipStream_t st) {
     int32_t* chunk_cnt = (int32_t*)ws;
-    const int F = s.T * s.k;
-    const int n_chunks = (F + kChunk - 1) / kChunk;
-    if (s.T > 0) {
-        const int epl = (s.E + 63) / 64;
-        if (epl <= 1) launch_topk<1>(s, logits, (int32_t*)out.topk_idx, (float*)out.topk_w, st);
-        else if (epl <= 2) launch_topk<2>(s, logits, (int32_t*)out.topk_idx, (float*)out.topk_w, st);
-        else if (epl <= 4) launch_topk<4>(s, logits, (int32_t*)out.topk_idx, (float*)out.topk_w, st);
-        else if (epl <= 8) launch_topk<8>(s, logits, (int32_t*)out.topk_idx, (float*)out.topk_w, st);
-        else launch_topk<16>(s, logits, (int32_t*)out.topk_idx, (float*)out.topk_w, st);
-        const int per = kRouteThreads / 64;
-        const size_t sm = (size_t)per * s.e_count * sizeof(int32_t);
-        hipLaunchKernelGGL(chunk_count_kernel, dim3((n_chunks + per - 1) / per),
-                           dim3(kRouteThreads), sm, st, out.topk_idx, F, s.e_start, s.e_count,
-                           chunk_cnt, (int32_t*)out.perm);
+    const int n = chunks_of(s);
+    if (s.T == 0) {
+        hipLaunchKernelGGL(no_rows_kernel, dim3(1), dim3(kChunkThreads), 0, st, s.e_count, (int32_t*)out.counts,
+                           (int32_t*)out.offsets);
+        return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
     }
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, chunk_cnt, n_chunks, s.e_count,
-                       (int32_t*)out.counts, (int32_t*)out.offsets);
-    if (s.T > 0) {
-        const int per = kRouteThreads / 64;
-        const size_t sm = (size_t)per * s.e_count * sizeof(int32_t);
-        hipLaunchKernelGGL(position_kernel, dim3((n_chunks + per - 1) / per), dim3(kRouteThreads),
-                           sm, st, out.topk_idx, F, s.e_start, s.e_count, chunk_cnt, out.offsets,
+    const int epl = (s.E + 63) / 64;
+    if (epl <= 1) launch_topk<1>(s, logits, out, chunk_cnt, st);
+    else if (epl <= 2) launch_topk<2>(s, logits, out, chunk_cnt, st);
+    else if (epl <= 4) launch_topk<4>(s, logits, out, chunk_cnt, st);
+    else if (epl <= 8) launch_topk<8>(s, logits, out, chunk_cnt, st);
+    else launch_topk<16>(s, logits, out, chunk_cnt, st);
+    if (n > 1 && n <= kFewChunks) {
+        hipLaunchKernelGGL((rows_kernel<false>), dim3(n), dim3(kChunkThreads), 0, st, out.topk_idx, s.T, s.k, chunk_tokens(s.k),
+                           n, s.e_start, s.e_count, chunk_cnt, (int32_t*)out.counts, (int32_t*)out.offsets,
+                           (int32_t*)out.perm, (int32_t*)out.inv_perm);
+    } else if (n > 1) {
+        hipLaunchKernelGGL(chunk_scan_kernel, dim3((s.e_count + kScanExperts - 1) / kScanExperts), dim3(kChunkThreads), 0, st,
+                           chunk_cnt, n, s.e_count, (int32_t*)out.counts);
+        hipLaunchKernelGGL((rows_kernel<true>), dim3(n), dim3(kChunkThreads), 0, st, out.topk_idx, s.T, s.k, chunk_tokens(s.k),
+                           n, s.e_start, s.e_count, chunk_cnt, (int32_t*)out.counts, (int32_t*)out.offsets,
                            (int32_t*)out.perm, (int32_t*)out.inv_perm);
     }
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;

@@ -121,3 +121,33 @@ def test_route_backward_matches_oracle(kw):
     np.put_along_axis(mask, want_r["topk_idx"].astype(np.int64), True, axis=1)
     assert (got[~mask] == 0).all()
     assert np.allclose(got, want, rtol=1e-5, atol=2e-7), np.abs(got - want).max()
+
+
+# T k = 256, 257.. slots: one chunk of whole tokens / two; 64 / 65 chunks (the workgroups add the
+# chunks themselves / a scan does); a chunk of more than 256 slots; more chunks than one scan round
+@pytest.mark.parametrize("kw", [
+    dict(T=32, E=128, k=8), dict(T=33, E=128, k=8), dict(T=2048, E=40, k=8), dict(T=2049, E=40, k=8),
+    dict(T=18, E=1024, k=15), dict(T=18 * 65 + 7, E=65, k=15), dict(T=40000, E=24, k=4, e_start=5, e_count=17),
+    dict(T=16, E=64, k=16), dict(T=256, E=1, k=1),
+])
+def test_route_chunk_edges(kw):
+    cfg = moe_synth.small_config(d=64, I=64, **kw)
+    rng = np.random.default_rng(kw["T"] + kw["k"])
+    check(cfg, rng.integers(-4, 5, (cfg.T, cfg.E)).astype(np.float32) * np.float32(0.25), "chunk edge")
+
+
+@pytest.mark.parametrize("T", [20, 500])
+def test_route_special_values(T):
+    """-inf loses to every number and ties by id, both zeros and equal denormals tie by id, a NaN is
+    never selected: the order of a plain float comparison."""
+    cfg = moe_synth.small_config(T=T, d=64, E=80, k=6, I=64)
+    rng = np.random.default_rng(T)
+    pool = np.array([0.0, -0.0, -np.inf, 1e-42, -1e-42, 3e38, -3e38, 1.5, -1.5, np.nan], np.float32)
+    logits = pool[rng.integers(0, len(pool), (T, cfg.E))]
+    logits[0] = -np.inf
+    say(f"[route] special values {cfg.shape_dict()}")
+    got = run_route(cfg, logits)
+    # stable descending order with NaN behind everything; adding 0 makes the zeros one value
+    key = np.where(np.isnan(logits), -np.inf, logits).astype(np.float64) + 0.0
+    order = np.lexsort((np.broadcast_to(np.arange(cfg.E), key.shape), -key, np.isnan(logits)), axis=1)
+    assert np.array_equal(got["topk_idx"], order[:, :cfg.k])
