@@ -286,9 +286,13 @@ __global__ void __launch_bounds__(kChunkThreads) no_rows_kernel(int e_count, int
 }
 
 // ------------------------------------------------------------ router gradient
-// One wave per token.  Lanes j < k hold slot j; s = sum_j w_j g_j by a wave
-// reduction; then every lane writes its experts of the row: the value of the
-// slot that selected the expert, or zero.
+// One wave per token.  Lanes j < k hold slot j; s = sum_j w_j g_j by a wave reduction; then the
+// k experts and their values go to scalar registers and every lane writes its experts of the
+// row: the value of the slot that selected the expert, or zero.  Bound by the stores of the
+// [T,E] array: 60001 tokens of 256 experts 22 us (2.7 TB/s); with two shuffles through LDS per slot
+// and 64 experts 51 us.
+// KM = compile-time bound on k (8 or kMaxTopK).
+template <int KM>
 __global__ void __launch_bounds__(kRouteThreads)
 route_backward_kernel(const int32_t* __restrict__ topk_idx, const float* __restrict__ topk_w,
                       const float* __restrict__ dtopk_w, int T, int E, int k,
@@ -305,15 +309,20 @@ route_backward_kernel(const int32_t* __restrict__ topk_idx, const float* __restr
     }
     float s = w * g;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    for (int off = kMaxTopK / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off);
     const float mine = w * (g - s);
+    int ej[KM];
+    float vj[KM];
+#pragma unroll
+    for (int j = 0; j < KM; ++j) {   // (lanes from k on hold expert -1)
+        ej[j] = __builtin_amdgcn_readlane(idx, j);
+        vj[j] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(mine), j));
+    }
     for (int e = lane; e < E; e += 64) {
         float v = 0.f;
-        for (int j = 0; j < k; ++j) {
-            const int ej = __shfl(idx, j);
-            const float vj = __shfl(mine, j);
-            if (ej == e) v = vj;
-        }
+#pragma unroll
+        for (int j = 0; j < KM; ++j)
+            if (ej[j] == e) v = vj[j];
         dlogits[(size_t)t * E + e] = v;
     }
 }
@@ -332,27 +341,25 @@ __global__ void __launch_bounds__(1024)
 global_offsets_kernel(const int32_t* __restrict__ c_all, const int32_t* __restrict__ o_exp, int E,
                       int W, int rank, int n_epr, int32_t* __restrict__ off_base,
                       int32_t* __restrict__ row_base, int32_t* __restrict__ recv_offsets) {
-    __shared__ int32_t s_scan[1024];
+    __shared__ int32_t s_first[1024];
+    __shared__ int32_t s_wave[1024 / 64];
     const int e = threadIdx.x;
     int total = 0, before = 0;
     if (e < E) {
+#pragma unroll 8
         for (int r = 0; r < W; ++r) {
             const int c = c_all[(size_t)r * E + e];
             if (r < rank) before += c;
             total += c;
         }
     }
-    s_scan[e] = total;
+    int all;
+    const int first = block_exclusive_sum<1024 / 64>(total, s_wave, &all);
+    s_first[e] = first;
     __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {       // inclusive scan over all experts
-        const int add = (e >= off) ? s_scan[e - off] : 0;
-        __syncthreads();
-        s_scan[e] += add;
-        __syncthreads();
-    }
     if (e < E) {
         const int g0 = (e / n_epr) * n_epr;              // first expert of e's rank
-        const int start = (s_scan[e] - total) - (g0 > 0 ? s_scan[g0 - 1] : 0);
+        const int start = first - s_first[g0];
         const int ob = before - o_exp[e];
         off_base[e] = ob;
         row_base[e] = start + ob;
@@ -363,34 +370,45 @@ global_offsets_kernel(const int32_t* __restrict__ c_all, const int32_t* __restri
     }
 }
 
-// One thread per token: destination (rank, local expert, offset inside the expert's
-// segment, row of the destination buffer) of each of its k slots; `send` marks the first
+// One thread per slot: destination (rank, local expert, offset inside the expert's
+// segment, row of the destination buffer); `send` marks the first
 // slot, in slot order, that targets a rank (the copy that crosses the link; the relay
 // worker of Section 3.2 replicates it for the token's other experts on that rank).
+// A workgroup has per_group whole tokens and their slots' ranks in LDS, where a slot finds the
+// earlier slots of its token.  Bound by its seven arrays, which a
+// thread per token read and wrote with a stride: 8.3 us for 32768 tokens with 8 slots, now 4.7 us.
 __global__ void __launch_bounds__(kRouteThreads)
 global_map_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ m_loc, int T,
-                  int k, int n_epr, const int32_t* __restrict__ off_base,
+                  int k, int per_group, int n_epr, const int32_t* __restrict__ off_base,
                   const int32_t* __restrict__ row_base, int32_t* __restrict__ dst_rank,
                   int32_t* __restrict__ dst_expert, int32_t* __restrict__ dst_off,
                   int32_t* __restrict__ dst_row, int32_t* __restrict__ send,
                   int32_t* __restrict__ n_dst_ranks) {
-    const int t = blockIdx.x * kRouteThreads + threadIdx.x;
-    if (t >= T) return;
-    unsigned long long seen = 0ull;
-    for (int j = 0; j < k; ++j) {
-        const size_t f = (size_t)t * k + j;
-        const int e = topk_idx[f];
+    __shared__ int32_t s_rank[kRouteThreads];
+    const int tid = threadIdx.x;
+    const int t0 = blockIdx.x * per_group, nt = min(per_group, T - t0);
+    const size_t f = (size_t)t0 * k + tid;
+    const bool live = tid < nt * k;
+    if (live) {
+        const int e = topk_idx[f], loc = m_loc[f];
         const int r_tgt = e / n_epr;
-        const int loc = m_loc[f];
+        s_rank[tid] = r_tgt;
         dst_rank[f] = r_tgt;
         dst_expert[f] = e - r_tgt * n_epr;
         dst_off[f] = loc + off_base[e];
         dst_row[f] = loc + row_base[e];
-        const unsigned long long bit = 1ull << r_tgt;
-        send[f] = (seen & bit) ? 0 : 1;
-        seen |= bit;
     }
-    n_dst_ranks[t] = __popcll(seen);
+    __syncthreads();
+    if (live) {
+        bool first = true;
+        for (int i = tid - tid % k; i < tid; ++i) first = first && s_rank[i] != s_rank[tid];
+        send[f] = first ? 1 : 0;
+    }
+    if (tid < nt) {
+        unsigned long long seen = 0ull;
+        for (int j = 0; j < k; ++j) seen |= 1ull << s_rank[tid * k + j];
+        n_dst_ranks[t0 + tid] = __popcll(seen);
+    }
 }
 
 // ------------------------------------------------------------------ host side
@@ -402,11 +420,11 @@ int global_map_launch(const moe_shape_t& s, int W, int rank, const moe_routing_t
     const int n_epr = s.E / W;
     hipLaunchKernelGGL(global_offsets_kernel, dim3(1), dim3(1024), 0, st, c_all, r.offsets, s.E, W,
                        rank, n_epr, off_base, row_base, out.recv_offsets);
+    const int per_group = kRouteThreads / s.k;   // whole tokens whose slots fill a workgroup
     if (s.T > 0)
-        hipLaunchKernelGGL(global_map_kernel, dim3((s.T + kRouteThreads - 1) / kRouteThreads),
-                           dim3(kRouteThreads), 0, st, r.topk_idx, r.inv_perm, s.T, s.k, n_epr,
-                           off_base, row_base, out.dst_rank, out.dst_expert, out.dst_off,
-                           out.dst_row, out.send, out.n_dst_ranks);
+        hipLaunchKernelGGL(global_map_kernel, dim3((s.T + per_group - 1) / per_group), dim3(kRouteThreads), 0, st, r.topk_idx,
+                           r.inv_perm, s.T, s.k, per_group, n_epr, off_base, row_base, out.dst_rank, out.dst_expert,
+                           out.dst_off, out.dst_row, out.send, out.n_dst_ranks);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -415,8 +433,13 @@ int route_backward_launch(const moe_shape_t& s, const int32_t* topk_idx, const f
                           const float* dtopk_w, float* dlogits, hipStream_t st) {
     if (s.T == 0) return MOE_OK;
     const int per = kRouteThreads / 64;
-    hipLaunchKernelGGL(route_backward_kernel, dim3((s.T + per - 1) / per), dim3(kRouteThreads), 0, st,
-                       topk_idx, topk_w, dtopk_w, s.T, s.E, s.k, dlogits);
+    const dim3 grid((s.T + per - 1) / per);
+    if (s.k <= 8)
+        hipLaunchKernelGGL(route_backward_kernel<8>, grid, dim3(kRouteThreads), 0, st, topk_idx, topk_w, dtopk_w, s.T, s.E, s.k,
+                           dlogits);
+    else
+        hipLaunchKernelGGL(route_backward_kernel<kMaxTopK>, grid, dim3(kRouteThreads), 0, st, topk_idx, topk_w, dtopk_w, s.T,
+                           s.E, s.k, dlogits);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
