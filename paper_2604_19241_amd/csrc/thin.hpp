@@ -13,8 +13,6 @@
 
 namespace uniep {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
 constexpr int kThinRows = 32;       // rows up to which an expert takes this path
 constexpr int kThinThreads = 256;
 constexpr int kThinGroupsPerCu = 3;
