@@ -221,60 +221,77 @@ __device__ __forceinline__ void gemm2_task(const FwdParams& p, const RowTile rt,
 // bytes per lane, no LDS (Section 5.2 "Relay & Reduce Workers").
 // KM = compile-time bound on k (8 or kMaxTopK): the row loads of all KM slots are in flight
 // at once, so the smaller bound halves the registers and doubles the waves per SIMD.
-template <int NW, int KM = kMaxTopK>
-__device__ __forceinline__ void combine_task(const FwdParams& p, int block) {
-    const int d = p.s.d, k = p.s.k, T = p.s.T;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int tt = wave; tt < kCombineTokens; tt += NW) {
-        const int t = block * kCombineTokens + tt;
-        if (t >= T) break;
-        int rows[KM];
-        float w[KM];
+
+// Slots of one token: the o row of each local one (-1: not here) and its gate.
+template <int KM>
+struct CombineSlots {
+    int rows[KM];
+    float w[KM];
+    __device__ __forceinline__ void load(const FwdParams& p, int t) {
+        const int k = p.s.k;
 #pragma unroll
         for (int j = 0; j < KM; ++j) {
             rows[j] = (j < k) ? p.inv_perm[(size_t)t * k + j] : -1;
             w[j] = (j < k) ? p.topk_w[(size_t)t * k + j] : 0.f;
         }
-        // two 16-byte column pieces per lane and round: all 2k row loads are issued before the
-        // first is used, so a wave keeps up to 2k KB in flight
-        for (int c0 = lane * 8; c0 < d; c0 += 2 * 64 * 8) {
-            const int c1 = c0 + 64 * 8;
-            const bool two = c1 < d;
-            u32x4_t v0[KM], v1[KM];
+    }
+};
+
+// Two 16-byte column pieces of a lane, c0 (below d) and c0 + 512: all 2k row loads are issued before
+// the first is used, so a wave keeps up to 2k KB in flight.
+constexpr int kCombineCols = 2 * 64 * 8;   // columns of a wave's round
+template <int KM>
+__device__ __forceinline__ void combine_piece(const FwdParams& p, int t, int c0, const CombineSlots<KM>& slots) {
+    const int d = p.s.d, k = p.s.k;
+    const int (&rows)[KM] = slots.rows;
+    const float (&w)[KM] = slots.w;
+    const int c1 = c0 + 64 * 8;
+    const bool two = c1 < d;
+    u32x4_t v0[KM], v1[KM];
 #pragma unroll
-            for (int j = 0; j < KM; ++j) {
-                v0[j] = zero4();
-                v1[j] = zero4();
-                if (j < k && rows[j] >= 0) {
-                    const char* src = p.o + (size_t)rows[j] * d * 2;
-                    v0[j] = *(const u32x4_t*)(src + (size_t)c0 * 2);
-                    if (two) v1[j] = *(const u32x4_t*)(src + (size_t)c1 * 2);
-                }
-            }
-            float a0[8], a1[8];
+    for (int j = 0; j < KM; ++j) {
+        v0[j] = zero4();
+        v1[j] = zero4();
+        if (j < k && rows[j] >= 0) {
+            const char* src = p.o + (size_t)rows[j] * d * 2;
+            v0[j] = *(const u32x4_t*)(src + (size_t)c0 * 2);
+            if (two) v1[j] = *(const u32x4_t*)(src + (size_t)c1 * 2);
+        }
+    }
+    float a0[8], a1[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) a0[q] = a1[q] = 0.f;
+    for (int q = 0; q < 8; ++q) a0[q] = a1[q] = 0.f;
 #pragma unroll
-            for (int j = 0; j < KM; ++j) {
-                if (j < k && rows[j] >= 0) {   // slot order, local slots only
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        a0[2 * q] += w[j] * bf16_lo(v0[j][q]);
-                        a0[2 * q + 1] += w[j] * bf16_hi(v0[j][q]);
-                        a1[2 * q] += w[j] * bf16_lo(v1[j][q]);
-                        a1[2 * q + 1] += w[j] * bf16_hi(v1[j][q]);
-                    }
-                }
-            }
-            u32x4_t y0, y1;
+    for (int j = 0; j < KM; ++j) {
+        if (j < k && rows[j] >= 0) {   // slot order, local slots only
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                y0[q] = pack_bf16x2(a0[2 * q], a0[2 * q + 1]);
-                y1[q] = pack_bf16x2(a1[2 * q], a1[2 * q + 1]);
+                a0[2 * q] += w[j] * bf16_lo(v0[j][q]);
+                a0[2 * q + 1] += w[j] * bf16_hi(v0[j][q]);
+                a1[2 * q] += w[j] * bf16_lo(v1[j][q]);
+                a1[2 * q + 1] += w[j] * bf16_hi(v1[j][q]);
             }
-            store_stream16(p.y + ((size_t)t * d + c0) * 2, y0);
-            if (two) store_stream16(p.y + ((size_t)t * d + c1) * 2, y1);
         }
+    }
+    u32x4_t y0, y1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        y0[q] = pack_bf16x2(a0[2 * q], a0[2 * q + 1]);
+        y1[q] = pack_bf16x2(a1[2 * q], a1[2 * q + 1]);
+    }
+    store_stream16(p.y + ((size_t)t * d + c0) * 2, y0);
+    if (two) store_stream16(p.y + ((size_t)t * d + c1) * 2, y1);
+}
+
+template <int NW, int KM = kMaxTopK>
+__device__ __forceinline__ void combine_task(const FwdParams& p, int block) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int tt = wave; tt < kCombineTokens; tt += NW) {
+        const int t = block * kCombineTokens + tt;
+        if (t >= p.s.T) break;
+        CombineSlots<KM> slots;
+        slots.load(p, t);
+        for (int c0 = lane * 8; c0 < p.s.d; c0 += kCombineCols) combine_piece<KM>(p, t, c0, slots);
     }
 }
 
@@ -374,12 +391,22 @@ fwd_worker_kernel(FwdParams p, int phase) {
     }
 }
 
-// The combine as a plain grid launch, one workgroup per block of kCombineTokens tokens, for
-// the default schedule: it follows the GEMM MegaKernel in stream order, so it needs no
-// scoreboard wait, no task cursor and no LDS, and as many workgroups as fit share a CU.
-template <int NW, int KM>
-__global__ void __launch_bounds__(64 * NW) fwd_tail_kernel(FwdParams p) {
-    combine_task<NW, KM>(p, blockIdx.x);
+// The combine as a plain grid launch for the default schedule: it follows the GEMM MegaKernel in
+// stream order, so it needs no scoreboard wait, no task cursor and no LDS, and as many workgroups
+// as fit share a CU.  A wave is one token by one round of columns: a generation step has too few
+// tokens to fill the chip otherwise (32 tokens of width 2048 kept 2 CUs busy, four dependent
+// rounds a wave: 198 -> 191 us for the layer; one token 35.8 -> 34.8 us; 256 tokens of width 7168
+// 529 -> 518 us), and 8192 tokens gain a little as well (training step 2428 -> 2421 us).
+constexpr int kTailWaves = 4;
+template <int KM>
+__global__ void __launch_bounds__(64 * kTailWaves) fwd_tail_kernel(FwdParams p) {
+    const int rounds = (p.s.d + kCombineCols - 1) / kCombineCols;
+    const int id = rfl((int)blockIdx.x * kTailWaves + (int)(threadIdx.x >> 6));
+    const int t = id / rounds, c0 = (id - t * rounds) * kCombineCols + (int)(threadIdx.x & 63) * 8;
+    if (t >= p.s.T || c0 >= p.s.d) return;
+    CombineSlots<KM> slots;
+    slots.load(p, t);
+    combine_piece<KM>(p, t, c0, slots);
 }
 
 // ------------------------------------------------------------------ host side
@@ -436,11 +463,13 @@ static int resident_workers(int* out) {
     return MOE_OK;
 }
 
-static void launch_tail(const FwdParams& p, int n_tail, hipStream_t st) {
+static void launch_tail(const FwdParams& p, hipStream_t st) {
+    const size_t waves = (size_t)p.s.T * ((p.s.d + kCombineCols - 1) / kCombineCols);
+    const dim3 grid((unsigned)((waves + kTailWaves - 1) / kTailWaves)), block(64 * kTailWaves);
     if (p.s.k <= 8)
-        hipLaunchKernelGGL((fwd_tail_kernel<8, 8>), dim3(n_tail), dim3(kMmaThreads), 0, st, p);
+        hipLaunchKernelGGL((fwd_tail_kernel<8>), grid, block, 0, st, p);
     else
-        hipLaunchKernelGGL((fwd_tail_kernel<8, kMaxTopK>), dim3(n_tail), dim3(kMmaThreads), 0, st, p);
+        hipLaunchKernelGGL((fwd_tail_kernel<kMaxTopK>), grid, block, 0, st, p);
 }
 
 // BM = rows per row tile: 256, or 128 (every tile then leaves the upper half of the workgroup's
@@ -452,7 +481,6 @@ static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream
     int workers = opts.workers > 0 ? min(opts.workers, resident) : resident;
     p.workers = workers;
     p.bm = bm;
-    const int n_tail = (p.s.T + kCombineTokens - 1) / kCombineTokens;
     // A token selects an expert at most once, so up to kThinRows tokens no expert has more rows than
     // that: every expert is thin and no work queue is set up.
     const bool all_thin = p.s.T <= kThinRows;
@@ -464,7 +492,7 @@ static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream
     hipLaunchKernelGGL(fwd_first_kernel, dim3((unsigned)(n1 + p.plan_blocks)), dim3(kThinThreads), 0, st, p);
     hipLaunchKernelGGL(fwd_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);
     if (all_thin) {
-        if (!opts.skip_tail || opts.schedule == 1 || opts.schedule == 2) launch_tail(p, n_tail, st);
+        if (!opts.skip_tail || opts.schedule == 1 || opts.schedule == 2) launch_tail(p, st);
         return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
     }
     if (opts.schedule == 2) {
@@ -472,7 +500,7 @@ static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream
             hipLaunchKernelGGL(fwd_worker_kernel, dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, phase);
     } else if (opts.schedule != 1) {   // 0 (default) and 3: GEMM MegaKernel, then the tail tasks
         hipLaunchKernelGGL(fwd_worker_kernel, dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, -2);
-        if (!opts.skip_tail) launch_tail(p, n_tail, st);
+        if (!opts.skip_tail) launch_tail(p, st);
     } else {
         hipLaunchKernelGGL(fwd_worker_kernel, dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, -1);
     }

@@ -34,3 +34,11 @@ def test_forward_at_row_counts(rows, d, I):
         for name, got in (("y", to_f64(y)), ("G", gu[:, :I]), ("U", gu[:, I:]), ("h", to_f64(views["h"])), ("o", to_f64(views["o"]))):
             assert rel_l2(got, want[name]) <= REL_L2, name
             check_elementwise(name, got, want[name])
+
+
+# k axes of 18, 34 and 66 steps, dealt unevenly to the four waves of a task, more tasks than CUs, and
+# widths at which the combine's last round of columns is a full one, 64 columns or none
+@pytest.mark.parametrize("rows", [[1], [17, 15]])
+@pytest.mark.parametrize("d,I", [(576, 1088), (1024, 64), (1088, 576), (2112, 128), (192, 8256)])
+def test_forward_of_a_small_batch(rows, d, I):
+    test_forward_at_row_counts(rows, d, I)
