@@ -483,75 +483,89 @@ __device__ __forceinline__ void dwgu_task(const BwdParams& p, int e, int idx, in
 
 // ------------------------------------------------------------- phase 4: dX, dtopk_w
 // KM = compile-time bound on k (8 or kMaxTopK).
-template <int NW, int KM = kMaxTopK>
-__device__ __forceinline__ void dx_task(const BwdParams& p, int block) {
-    const int d = p.s.d, k = p.s.k, T = p.s.T;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool want_dots = p.dtopk_w != nullptr;
-    for (int tt = wave; tt < kDxTokens; tt += NW) {
-        const int t = block * kDxTokens + tt;
-        if (t >= T) break;
-        int rows[KM];
+template <int KM>
+__device__ __forceinline__ void dx_rows(const BwdParams& p, int t, int (&rows)[KM]) {
+    const int k = p.s.k;
 #pragma unroll
-        for (int j = 0; j < KM; ++j) rows[j] = (j < k) ? p.inv_perm[(size_t)t * k + j] : -1;
-        // two 16-byte column pieces per lane and round, as in the forward combine: all 2k row
-        // loads are issued before the first is used
-        for (int c0 = lane * 8; c0 < d; c0 += 2 * 64 * 8) {
-            const int c1 = c0 + 64 * 8;
-            const bool two = c1 < d;
-            u32x4_t v0[KM], v1[KM];
+    for (int j = 0; j < KM; ++j) rows[j] = (j < k) ? p.inv_perm[(size_t)t * k + j] : -1;
+}
+
+// Two 16-byte column pieces of a lane, c0 (below d) and c0 + 512, as in the forward combine: all
+// 2k row loads are issued before the first is used.
+constexpr int kDxCols = 2 * 64 * 8;   // columns of a wave's round
+template <int KM>
+__device__ __forceinline__ void dx_piece(const BwdParams& p, int t, int c0, const int (&rows)[KM]) {
+    const int d = p.s.d, k = p.s.k;
+    const int c1 = c0 + 64 * 8;
+    const bool two = c1 < d;
+    u32x4_t v0[KM], v1[KM];
 #pragma unroll
-            for (int j = 0; j < KM; ++j) {
-                v0[j] = zero4();
-                v1[j] = zero4();
-                if (j < k && rows[j] >= 0) {
-                    const char* src = p.dxp + (size_t)rows[j] * d * 2;
-                    v0[j] = *(const u32x4_t*)(src + (size_t)c0 * 2);
-                    if (two) v1[j] = *(const u32x4_t*)(src + (size_t)c1 * 2);
-                }
-            }
-            float a0[8], a1[8];
+    for (int j = 0; j < KM; ++j) {
+        v0[j] = zero4();
+        v1[j] = zero4();
+        if (j < k && rows[j] >= 0) {
+            const char* src = p.dxp + (size_t)rows[j] * d * 2;
+            v0[j] = *(const u32x4_t*)(src + (size_t)c0 * 2);
+            if (two) v1[j] = *(const u32x4_t*)(src + (size_t)c1 * 2);
+        }
+    }
+    float a0[8], a1[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) a0[q] = a1[q] = 0.f;
+    for (int q = 0; q < 8; ++q) a0[q] = a1[q] = 0.f;
 #pragma unroll
-            for (int j = 0; j < KM; ++j) {
-                if (j < k && rows[j] >= 0) {   // slot order, local slots only
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        a0[2 * q] += bf16_lo(v0[j][q]);
-                        a0[2 * q + 1] += bf16_hi(v0[j][q]);
-                        a1[2 * q] += bf16_lo(v1[j][q]);
-                        a1[2 * q + 1] += bf16_hi(v1[j][q]);
-                    }
-                }
-            }
-            u32x4_t o0, o1;
+    for (int j = 0; j < KM; ++j) {
+        if (j < k && rows[j] >= 0) {   // slot order, local slots only
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                o0[q] = pack_bf16x2(a0[2 * q], a0[2 * q + 1]);
-                o1[q] = pack_bf16x2(a1[2 * q], a1[2 * q + 1]);
+                a0[2 * q] += bf16_lo(v0[j][q]);
+                a0[2 * q + 1] += bf16_hi(v0[j][q]);
+                a1[2 * q] += bf16_lo(v1[j][q]);
+                a1[2 * q + 1] += bf16_hi(v1[j][q]);
             }
-            store_stream16(p.dx + ((size_t)t * d + c0) * 2, o0);
-            if (two) store_stream16(p.dx + ((size_t)t * d + c1) * 2, o1);
         }
-        if (want_dots && lane < k) {
-            // dtopk_w[t][j] = <dY[t], o[row]>: the partial sums of the row's dH column tiles (four
-            // per tile, one per wave column), added in column order; 0 for a slot whose expert is not
-            // local.  They stand side by side: 4 n_dots consecutive bytes a slot.  One cache line per partial
-            // sum made this kernel take 187 us instead of 128 us for 60001 tokens of width 2304.
-            const int r = p.inv_perm[(size_t)t * k + lane];
-            float s = 0.f;
-            if (r >= 0) {
-                const f32x4_t* part = (const f32x4_t*)(p.dots + (size_t)r * p.n_dots);
-#pragma unroll 4
-                for (int ct = 0; ct < p.n_dots / 4; ++ct) {
-                    const f32x4_t v = part[ct];
+    }
+    u32x4_t o0, o1;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) s += v[q];
-                }
-            }
-            p.dtopk_w[(size_t)t * k + lane] = s;
+    for (int q = 0; q < 4; ++q) {
+        o0[q] = pack_bf16x2(a0[2 * q], a0[2 * q + 1]);
+        o1[q] = pack_bf16x2(a1[2 * q], a1[2 * q + 1]);
+    }
+    store_stream16(p.dx + ((size_t)t * d + c0) * 2, o0);
+    if (two) store_stream16(p.dx + ((size_t)t * d + c1) * 2, o1);
+}
+
+// Lane j < k: the gradient of slot j's gate.
+__device__ __forceinline__ void dtopk_task(const BwdParams& p, int t) {
+    const int k = p.s.k, lane = threadIdx.x & 63;
+    if (lane >= k) return;
+    // dtopk_w[t][j] = <dY[t], o[row]>: the partial sums of the row's dH column tiles (four
+    // per tile, one per wave column), added in column order; 0 for a slot whose expert is not
+    // local.  They stand side by side: 4 n_dots consecutive bytes a slot.  One cache line per partial
+    // sum made this kernel take 187 us instead of 128 us for 60001 tokens of width 2304.
+    const int r = p.inv_perm[(size_t)t * k + lane];
+    float s = 0.f;
+    if (r >= 0) {
+        const f32x4_t* part = (const f32x4_t*)(p.dots + (size_t)r * p.n_dots);
+#pragma unroll 4
+        for (int ct = 0; ct < p.n_dots / 4; ++ct) {
+            const f32x4_t v = part[ct];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s += v[q];
         }
+    }
+    p.dtopk_w[(size_t)t * k + lane] = s;
+}
+
+template <int NW, int KM = kMaxTopK>
+__device__ __forceinline__ void dx_task(const BwdParams& p, int block) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int tt = wave; tt < kDxTokens; tt += NW) {
+        const int t = block * kDxTokens + tt;
+        if (t >= p.s.T) break;
+        int rows[KM];
+        dx_rows<KM>(p, t, rows);
+        for (int c0 = lane * 8; c0 < p.s.d; c0 += kDxCols) dx_piece<KM>(p, t, c0, rows);
+        if (p.dtopk_w) dtopk_task(p, t);
     }
 }
 
@@ -684,11 +698,29 @@ static BwdWorkerFn bwd_worker_fn(bool acc, bool split) {
                  : (acc ? bwd_worker_acc_kernel : bwd_worker_kernel);
 }
 
-// dX (and dtopk_w) as a plain grid launch behind the GEMM MegaKernel, one workgroup per block
-// of kDxTokens tokens: no scoreboard wait, no task cursor, no LDS.
-template <int NW, int KM>
-__global__ void __launch_bounds__(64 * NW) bwd_tail_kernel(BwdParams p) {
-    dx_task<NW, KM>(p, blockIdx.x);
+// dX (and dtopk_w) as a plain grid launch behind the GEMM MegaKernel: no scoreboard wait, no task
+// cursor, no LDS.  A wave is one token by one round of columns, or the token's gate gradients.
+// The gate gradients used to follow the columns in the same wave, two tokens a wave, and 256 tokens
+// filled 16 workgroups: training step of 256 tokens 139.6 -> 136.9 us, unchanged from 8192 tokens on.
+constexpr int kTailWaves = 4;
+static __host__ __device__ __forceinline__ int tail_units(const BwdParams& p) {   // waves a token
+    return (p.s.d + kDxCols - 1) / kDxCols + (p.dtopk_w ? 1 : 0);
+}
+template <int KM>
+__global__ void __launch_bounds__(64 * kTailWaves) bwd_tail_kernel(BwdParams p) {
+    const int units = tail_units(p);
+    const int id = rfl((int)blockIdx.x * kTailWaves + (int)(threadIdx.x >> 6));
+    const int t = id / units, unit = id - t * units;
+    if (t >= p.s.T) return;
+    if (unit * kDxCols >= p.s.d) {
+        dtopk_task(p, t);
+        return;
+    }
+    const int c0 = unit * kDxCols + (int)(threadIdx.x & 63) * 8;
+    if (c0 >= p.s.d) return;
+    int rows[KM];
+    dx_rows<KM>(p, t, rows);
+    dx_piece<KM>(p, t, c0, rows);
 }
 
 // ------------------------------------------------------------------ host side
@@ -786,12 +818,13 @@ static int bwd_launch_bm(BwdParams& p, const moe_opts_t& opts, int bm, hipStream
         for (int phase = 0; phase < 5; ++phase) launch_worker(acc, split, p, workers, phase, st);
     } else if (opts.schedule != 1) {   // 0 (default) and 3: GEMM MegaKernel, then the tail tasks
         launch_worker(acc, split, p, workers, -2, st);
-        const int n_tail = (p.s.T + kDxTokens - 1) / kDxTokens;
-        if (n_tail > 0 && !opts.skip_tail) {
+        if (p.s.T > 0 && !opts.skip_tail) {
+            const size_t waves = (size_t)p.s.T * tail_units(p);
+            const dim3 grid((unsigned)((waves + kTailWaves - 1) / kTailWaves)), block(64 * kTailWaves);
             if (p.s.k <= 8)
-                hipLaunchKernelGGL((bwd_tail_kernel<8, 8>), dim3(n_tail), dim3(kMmaThreads), 0, st, p);
+                hipLaunchKernelGGL((bwd_tail_kernel<8>), grid, block, 0, st, p);
             else
-                hipLaunchKernelGGL((bwd_tail_kernel<8, kMaxTopK>), dim3(n_tail), dim3(kMmaThreads), 0, st, p);
+                hipLaunchKernelGGL((bwd_tail_kernel<kMaxTopK>), grid, block, 0, st, p);
         }
     } else {
         launch_worker(acc, split, p, workers, -1, st);
