@@ -86,7 +86,7 @@ typedef struct {
                          task, 2 = staged: one launch per phase (same tile code; for profiling),
                          3 = one persistent MegaKernel for all GEMM tasks with scoreboard
                          waits, then a plain grid kernel for the tail tasks (combine / dX:
-                         fwd_tail_kernel / bwd_tail_kernel, one workgroup per 16 tokens),
+                         fwd_tail_kernel / bwd_tail_kernel, one wave per token and 1024 columns),
                          which may only start once every GEMM task is done.
                          Schedule 1 makes the tail tasks wait inside the kernel until EVERY
                          worker has started and run out of GEMM work, so it needs all
