@@ -3,21 +3,32 @@
 // from HBM and what a task costs before its first and after its last load.
 //
 // A workgroup is 4 waves and owns 128 weight columns (GEMM1: 64 gate columns and the same 64 up
-// columns) of one expert, with all of its rows; the k axis is dealt to the waves in steps of 32
-// and the four partial sums meet in LDS, added in wave order.  A lane loads 16 bytes (8 columns)
-// of 8 consecutive k rows straight into registers, and 32 byte permutes turn them into the 8
-// operands of v_mfma_f32_16x16x32_bf16 (one per column of the piece): no LDS staging, no barrier
-// in the loop, and two steps (16 KB a wave) on their way at any time.
+// columns) of one expert, with all of its rows.  K advances in stages of 64.  A stage is loaded into
+// registers (a wave: 16 k rows of the weights and 8 rows of activations, five 16-byte loads a lane in
+// whole 128- or 256-byte runs), kThinAhead stages ahead, and passes through one of two LDS images;
+// one barrier a stage.  Loads to registers and not the DMA of the big tiles: the loads of several
+// stages are on their way at any time, more than a CU's DMA path holds.
+//
+// Every output is ONE chain of v_mfma_f32_32x32x16_bf16 in ascending k, weights as the A operand,
+// with the same k in the same lane and element as in the 256-row tiles (mma.hpp): a row's results
+// are bit for bit those of the work queue, so they do not depend on how many rows its expert has, i.e.
+// on what else is in the batch.  That rules out a split of the k axis over waves: wave w multiplies
+// columns [32 w, +32) of the task over the whole k axis.  Measured against a form that dealt the k axis to the
+// four waves and added four partial sums (no LDS image, no barrier): 32 tokens of width 2048 on 128 experts of
+// inner width 768 185 -> 183 us for the layer, 1021 tokens on 512 experts of 512 728 -> 718 us, one token
+// 33.8 -> 33.6 us; and against 256-row tiles for these experts 258 -> 190, 755 -> 705 and 82 -> 34 us.
 #pragma once
 #include "mma.hpp"
 
 namespace uniep {
 
-constexpr int kThinRows = 32;       // rows up to which an expert takes this path
+constexpr int kThinRows = 32;       // rows up to which an expert takes this path: one fragment of the matrix instruction
 constexpr int kThinThreads = 256;
 constexpr int kThinGroupsPerCu = 3;
 constexpr int kThinCols = 128;      // weight columns of a task
-constexpr int kThinPad = kThinCols + 4;   // floats between two rows of a partial sum: all 64 banks in both directions
+constexpr int kThinAhead = 4;       // stages in flight (even: stage t is in registers t % 4 and in image t % 2)
+constexpr int kThinWBytes = BK * kThinCols * 2;                       // weights of a stage: image [64 k][256 B]
+constexpr int kThinImage = kThinWBytes + kThinRows * BK * 2;          // and the rows: image [32 rows][128 B]
 
 struct ThinParams {
     moe_shape_t s;
@@ -33,162 +44,179 @@ struct ThinParams {
     int max_rows;    // experts with 1..max_rows rows are run here
 };
 
-// Where a lane's next step comes from.  The pointers are advanced in place and kept opaque:
-// the compiler would otherwise carry one induction address per load and spill.
-typedef const __attribute__((address_space(1))) char* glb_ptr_t;   // an opaque generic pointer would be read with flat loads
+typedef const __attribute__((address_space(1))) char* glb_ptr_t;
 typedef const __attribute__((address_space(1))) u32x4_t* glb_vec_t;
-template <int NR>
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+typedef __attribute__((address_space(3))) char* lds_ptr_t;
+typedef __attribute__((address_space(3))) u32x4_t* lds_vec_t;
+typedef __attribute__((address_space(3))) bf16x4_t* lds_tr_t;
+
+// Where a wave's next stage comes from.  GEMM1: weight loads 0, 1 are 8 k rows each of 64 gate columns,
+// 2, 3 the same of the up columns; GEMM2: load i is 4 k rows of 128 columns.
+template <int GEMM>
 struct ThinSource {
-    glb_ptr_t w;       // k row 8 (l / 16) of the step, this lane's 8 columns
-    size_t ldw;          // bytes from one k row to the next (uniform)
-    glb_ptr_t x[NR];     // row 16 f + l % 16, the same 8 k
-    __device__ __forceinline__ void advance() {   // to this wave's next step, 4 steps on
-        w += 128 * ldw;
-        asm volatile("" : "+v"(w));
+    glb_ptr_t w[2];      // first k row of this wave in the stage to come (uniform); GEMM2: w[0] only
+    uint32_t off;        // this lane's k row and columns behind it
+    uint32_t ldw;        // bytes from one k row to the next (uniform)
+    glb_ptr_t x;         // this lane's row and chunk
+    // advance: 0 = stay on this stage (the last one).  The loads are never left out: behind a branch
+    // around them the compiler could not tell how many are in flight and would wait for all.
+    __device__ __forceinline__ void load(u32x4_t (&r)[5], int advance) {
 #pragma unroll
-        for (int f = 0; f < NR; ++f) {
-            x[f] += 256;
-            asm volatile("" : "+v"(x[f]));
+        for (int i = 0; i < 4; ++i) {
+            glb_ptr_t base = GEMM == 1 ? w[i >> 1] + (size_t)(8 * (i & 1)) * ldw : w[0] + (size_t)(4 * i) * ldw;
+            asm volatile("" : "+s"(base));   // scalar base + 32-bit lane offset, not one 64-bit lane address per load
+            r[i] = __builtin_nontemporal_load((glb_vec_t)(base + off));
         }
+        r[4] = *(glb_vec_t)x;
+        const size_t step = (size_t)(BK * advance) * ldw;
+        w[0] += step;
+        if (GEMM == 1) w[1] += step;
+        x += BK * 2 * advance;
     }
 };
 
-template <int NR>
-struct ThinStep {
-    u32x4_t w[8];
-    u32x4_t x[NR];
-    __device__ __forceinline__ void load(ThinSource<NR>& s) {
-        const glb_ptr_t p = s.w;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) w[j] = __builtin_nontemporal_load((glb_vec_t)(p + j * s.ldw));
-#pragma unroll
-        for (int f = 0; f < NR; ++f) x[f] = *(glb_vec_t)s.x[f];
-        s.advance();
-    }
-    // acc[f][c][v]: row 16 f + l % 16, column 32 (l / 16) + 8 v + c
-    __device__ __forceinline__ void mma(f32x4_t (&acc)[NR][8]) const {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
-            u32x4_t a;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) a[q] = __builtin_amdgcn_perm(w[2 * q + 1][c >> 1], w[2 * q][c >> 1], sel);
-#pragma unroll
-            for (int f = 0; f < NR; ++f)
-                acc[f][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                                    __builtin_bit_cast(bf16x8_t, x[f]), acc[f][c], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);   // not all 32 permutes ahead of the first product: no registers for that
+// The LDS images, with the swizzles of mma.hpp: weights, 16-byte chunk c of k row k at c ^ ((k & 3) << 2);
+// rows, chunk c of row r at c ^ ((r >> 1) & 7).  Chunks 4 w .. 4 w + 3 of a k row are wave w's 32 columns
+// (GEMM1: 16 gate columns, then the same 16 up columns).
+template <int GEMM>
+struct ThinLds {
+    lds_ptr_t wput, xput, wget, xget[4];
+    __device__ __forceinline__ ThinLds(lds_ptr_t base, const Lane& ln) {
+        const int l = ln.l, w = ln.w, kh = ln.hf, g = (l >> 4) & 1, e = (l & 15) >> 2, q = l & 3;
+        if (GEMM == 1) {
+            const int kr = l >> 3, p = l & 7;
+            wput = base + (16 * w + kr) * 256 + (((4 * (p >> 1) + (p & 1)) ^ ((kr & 3) << 2)) << 4);
+        } else {
+            const int kr = l >> 4, p = l & 15;
+            wput = base + (16 * w + kr) * 256 + ((p ^ (kr << 2)) << 4);
         }
+        const int row = 8 * w + (l >> 3);
+        xput = base + kThinWBytes + row * 128 + (((l & 7) ^ ((row >> 1) & 7)) << 4);
+        const int sq = ((q & 1) << 1) | (q >> 1);   // piece -> position of its 4 columns inside the 16
+        wget = base + (8 * kh + e) * 256 + (((4 * w + 2 * g + (sq >> 1)) ^ (e << 2)) << 4) + (sq & 1) * 8;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+            xget[kk] = base + kThinWBytes + ln.l31 * 128 + (((2 * kk + kh) ^ ((ln.l31 >> 1) & 7)) << 4);
+    }
+    __device__ __forceinline__ void put(int image, const u32x4_t (&r)[5]) const {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *(lds_vec_t)(wput + image * kThinImage + (GEMM == 1 ? (i & 1) * 2048 + (i >> 1) * 32 : i * 1024)) = r[i];
+        *(lds_vec_t)(xput + image * kThinImage) = r[4];
+    }
+    // acc[v]: row l % 32, column position 16 (v / 8) + 8 (l / 32) + v % 8 of the wave's 32
+    __device__ __forceinline__ void multiply(int image, f32x16_t& acc) const {
+        bf16x4_t lo[4], hi[4];
+        u32x4_t b[4];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const lds_ptr_t a = wget + image * kThinImage + kk * 4096;
+            b[kk] = *(lds_vec_t)(xget[kk] + image * kThinImage);
+            lo[kk] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)a);
+            hi[kk] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(a + 1024));
+        }
+        __builtin_amdgcn_sched_barrier(0);   // all reads on their way before the first product: one latency a stage, not four
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_shufflevector(lo[kk], hi[kk], 0, 1, 2, 3, 4, 5, 6, 7),
+                                                          __builtin_bit_cast(bf16x8_t, b[kk]), acc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
     }
 };
 
-// n steps (4 apart) of this wave; the loads of one step ahead of the matrix work of another
-template <int NR>
-__device__ __forceinline__ void thin_loop(ThinSource<NR>& src, int n, f32x4_t (&acc)[NR][8]) {
-#pragma unroll
-    for (int f = 0; f < NR; ++f)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            acc[f][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            asm volatile("" : "+v"(acc[f][c]));   // one copy, whatever the number of steps
-        }
-    if (n <= 0) return;
-    ThinStep<NR> a, b;
-    a.load(src);
-    int i = 0;
-    for (; i + 2 < n; i += 2) {
-        b.load(src);
-        __builtin_amdgcn_sched_barrier(0);
-        a.mma(acc);
-        __builtin_amdgcn_sched_barrier(0);
-        a.load(src);
-        __builtin_amdgcn_sched_barrier(0);
-        b.mma(acc);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (i + 1 < n) {
-        b.load(src);
-        __builtin_amdgcn_sched_barrier(0);
-        a.mma(acc);
-        a = b;
-    }
-    a.mma(acc);
+// LDS writes of this wave done, then all waves: what __syncthreads() does without its wait for the
+// loads in flight.
+__device__ __forceinline__ void thin_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
-// One block of up to 16 NR rows (row0 .., `rows` valid) by the task's columns.
-// GEMM 1: h = silu(x W_gate) * (x W_up), columns [64 ct, +64); GEMM 2: o = h W_down, columns [128 ct, +128).
-template <int GEMM, int NR>
-__device__ __forceinline__ void thin_block(const ThinParams& p, int e, int ct, int row0, int rows, float* red) {
-    const int d = p.s.d, I = p.s.I;
-    const Lane in;
-    const int n = in.l & 15, q = in.l >> 4, w = in.wave_uniform();
-    const int K = GEMM == 1 ? d : I;
-    ThinSource<NR> src;
-    src.ldw = (size_t)(GEMM == 1 ? I : d) * 2;
-    const char* wp;
-    if (GEMM == 1) {
-        wp = (n & 8 ? p.w_up : p.w_gate) + (size_t)e * d * src.ldw + (size_t)(64 * ct + 8 * (n & 7)) * 2;
-    } else {   // pieces past d alias the last one
-        wp = p.w_down + (size_t)e * I * src.ldw + (size_t)min(kThinCols * ct + 8 * n, d - 8) * 2;
-    }
-    src.w = (glb_ptr_t)(wp + (size_t)(32 * w + 8 * q) * src.ldw);
-#pragma unroll
-    for (int f = 0; f < NR; ++f) {
-        const int r = row0 + min(16 * f + n, rows - 1);   // rows past the last alias it
-        const char* row = GEMM == 1 ? p.x + (size_t)(p.perm[r] / p.s.k) * d * 2 : p.h + (size_t)r * I * 2;
-        src.x[f] = (glb_ptr_t)(row + 64 * w + 16 * q);
-    }
-    f32x4_t acc[NR][8];
-    thin_loop<NR>(src, (K / 32 - w + 3) / 4, acc);
+// One stage: registers -> image, the loads of the stage kThinAhead further on into the same registers,
+// barrier, matrix work.  An image is written again two stages later, behind the barrier that every wave
+// reaches with its reads of it done.
+template <int GEMM, bool LOAD>
+__device__ __forceinline__ void thin_stage(ThinSource<GEMM>& src, const ThinLds<GEMM>& lds, int image, u32x4_t (&r)[5],
+                                           f32x16_t& acc, int advance) {
+    lds.put(image, r);
+    __builtin_amdgcn_sched_barrier(0);
+    if (LOAD) src.load(r, advance);
+    thin_barrier();
+    lds.multiply(image, acc);
+}
 
+// n >= 1 stages: t is in registers t % kThinAhead and in image t % 2.
+template <int GEMM>
+__device__ __forceinline__ void thin_loop(ThinSource<GEMM>& src, const ThinLds<GEMM>& lds, int n, f32x16_t& acc) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    u32x4_t r[kThinAhead][5];
+    thin_barrier();   // the task before has read its last image
+#pragma unroll
+    for (int j = 0; j < kThinAhead; ++j) src.load(r[j], j + 1 < n ? 1 : 0);
+    int t = 0;
+    for (; t + kThinAhead < n; t += kThinAhead)
+#pragma unroll
+        for (int j = 0; j < kThinAhead; ++j)
+            thin_stage<GEMM, true>(src, lds, j & 1, r[j], acc, t + j + 1 + kThinAhead < n ? 1 : 0);
+#pragma unroll
+    for (int j = 0; j < kThinAhead; ++j)
+        if (t + j < n) thin_stage<GEMM, false>(src, lds, j & 1, r[j], acc, 0);
+}
+
+// One block of up to 32 rows (row0 .., `rows` valid) by the task's columns.
+// GEMM 1: h = silu(x W_gate) * (x W_up), columns [64 ct, +64); GEMM 2: o = h W_down, columns [128 ct, +128).
+template <int GEMM>
+__device__ __forceinline__ void thin_block(const ThinParams& p, int e, int ct, int row0, int rows, lds_ptr_t images) {
+    const int d = p.s.d, I = p.s.I;
+    f32x16_t acc;
+    {
+        const Lane in;
+        const int K = GEMM == 1 ? d : I;
+        ThinSource<GEMM> src;
+        src.ldw = (uint32_t)(GEMM == 1 ? I : d) * 2;
+        const size_t first = ((size_t)e * K + 16 * in.wave_uniform()) * src.ldw;
+        if (GEMM == 1) {
+            src.w[0] = (glb_ptr_t)(p.w_gate + first + (size_t)ct * 128);
+            src.w[1] = (glb_ptr_t)(p.w_up + first + (size_t)ct * 128);
+            src.off = (in.l >> 3) * src.ldw + (in.l & 7) * 16;
+        } else {   // pieces past d alias the last one
+            src.w[0] = src.w[1] = (glb_ptr_t)(p.w_down + first);
+            src.off = (in.l >> 4) * src.ldw + (uint32_t)min(kThinCols * ct + 8 * (in.l & 15), d - 8) * 2;
+        }
+        const int r = row0 + min(8 * in.w + (in.l >> 3), rows - 1);   // rows past the last alias it
+        const char* row = GEMM == 1 ? p.x + (size_t)(p.perm[r] / p.s.k) * d * 2 : p.h + (size_t)r * I * 2;
+        src.x = (glb_ptr_t)(row + (in.l & 7) * 16);
+        thin_loop<GEMM>(src, ThinLds<GEMM>(images, in), K / BK, acc);
+    }
     const Lane out;
-    const int tr = out.tid >> 4, tc = out.tid & 15;   // on the way out: row of the fragment, piece of its columns
-#pragma unroll
-    for (int f = 0; f < NR; ++f) {
-        __syncthreads();   // the partial sums of the fragment before (or of the task before) have been read
-        float* mine = red + (out.w * 16 + (out.l & 15)) * kThinPad + 32 * (out.l >> 4);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            *(f32x4_t*)(mine + 8 * v) = f32x4_t{acc[f][0][v], acc[f][1][v], acc[f][2][v], acc[f][3][v]};
-            *(f32x4_t*)(mine + 8 * v + 4) = f32x4_t{acc[f][4][v], acc[f][5][v], acc[f][6][v], acc[f][7][v]};
+    if (out.l31 >= rows) return;
+    const size_t row = (size_t)(row0 + out.l31);
+    if (GEMM == 1) {
+        const int col = 64 * ct + 16 * out.w + 8 * out.hf;
+        if (p.gu) {
+            *(u32x4_t*)(p.gu + (row * 2 * I + col) * 2) = pack8(acc, 0);
+            *(u32x4_t*)(p.gu + (row * 2 * I + I + col) * 2) = pack8(acc, 1);
         }
-        __syncthreads();
-        const int c0 = GEMM == 1 ? 4 * tc : 8 * tc, c1 = GEMM == 1 ? 64 + 4 * tc : 8 * tc + 4;
-        f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+        float hv[8];
 #pragma unroll
-        for (int ww = 0; ww < 4; ++ww) {
-            const float* src = red + (ww * 16 + tr) * kThinPad;
-            s0 += *(const f32x4_t*)(src + c0);
-            s1 += *(const f32x4_t*)(src + c1);
+        for (int j = 0; j < 8; ++j) {
+            const float g = acc[j], u = acc[8 + j];
+            hv[j] = g * sigmoid_f(g) * u;
         }
-        const int r = 16 * f + tr;
-        if (r < rows) {
-            const size_t row = (size_t)(row0 + r);
-            if (GEMM == 1) {
-                const int col = 64 * ct + 4 * tc;
-                if (p.gu) {
-                    char* g = p.gu + (row * 2 * I + col) * 2;
-                    __builtin_nontemporal_store(u32x2_t{pack_bf16x2(s0[0], s0[1]), pack_bf16x2(s0[2], s0[3])}, (u32x2_t*)g);
-                    __builtin_nontemporal_store(u32x2_t{pack_bf16x2(s1[0], s1[1]), pack_bf16x2(s1[2], s1[3])},
-                                                (u32x2_t*)(g + (size_t)I * 2));
-                }
-                float hv[4];
+        *(u32x4_t*)(p.h + (row * I + col) * 2) = u32x4_t{pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3]),
+                                                         pack_bf16x2(hv[4], hv[5]), pack_bf16x2(hv[6], hv[7])};
+    } else {
+        const int col = kThinCols * ct + 32 * out.w + 8 * out.hf;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) hv[j] = s0[j] * sigmoid_f(s0[j]) * s1[j];
-                *(u32x2_t*)(p.h + (row * I + col) * 2) = u32x2_t{pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3])};
-            } else {
-                const int col = kThinCols * ct + 8 * tc;
-                if (col < d)
-                    *(u32x4_t*)(p.o + (row * d + col) * 2) =
-                        u32x4_t{pack_bf16x2(s0[0], s0[1]), pack_bf16x2(s0[2], s0[3]), pack_bf16x2(s1[0], s1[1]),
-                                pack_bf16x2(s1[2], s1[3])};
-            }
-        }
+        for (int vg = 0; vg < 2; ++vg)
+            if (col + 16 * vg < d) *(u32x4_t*)(p.o + (row * d + col + 16 * vg) * 2) = pack8(acc, vg);
     }
 }
 
 struct ThinShared {
-    float red[4 * 16 * kThinPad];
+    __attribute__((aligned(16))) char images[2 * kThinImage];
     int32_t row0[kMaxExperts];
     int32_t rows[kMaxExperts];
     uint16_t expert[kMaxExperts];
@@ -246,11 +274,8 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
             ct = (id - even) % nct;
         }
         const int e = rfl(S.expert[x]), row0 = rfl(S.row0[x]), rows = rfl(S.rows[x]);
-        for (int r = 0; r < rows; r += kThinRows) {   // more than one round only where max_rows is larger
-            const int left = min(rows - r, kThinRows);
-            if (left <= 16) thin_block<GEMM, 1>(p, e, ct, row0 + r, left, S.red);
-            else thin_block<GEMM, 2>(p, e, ct, row0 + r, left, S.red);
-        }
+        for (int r = 0; r < rows; r += kThinRows)   // more than one round only where max_rows is larger
+            thin_block<GEMM>(p, e, ct, row0 + r, min(rows - r, kThinRows), (lds_ptr_t)S.images);
     }
 }
 
