@@ -10,6 +10,7 @@
 // gives every chunk its starting row per expert.  The result is therefore the same on every run.
 #include "common.hpp"
 
+#include <algorithm>
 #include <mutex>
 
 namespace uniep {
@@ -20,10 +21,28 @@ constexpr int kChunkThreads = 1024;
 constexpr int kPieces = (kChunk + kMaxTopK - 1 + 63) / 64;   // 64-slot pieces of a chunk
 // Up to this many chunks every workgroup of the last kernel adds the chunks in front of its own
 // by itself (one launch less): 40 chunks of 512 experts are 80 KB from L2 for each of 40 workgroups.
+// 44 chunks of 256 experts 13.6 us (with the scan's launch 15.7), 128 chunks 16.8 us (15.9).
 constexpr int kFewChunks = 64;
 
 static int chunk_tokens(int k) { return (kChunk + k - 1) / k; }
 static int chunks_of(const moe_shape_t& s) { return (s.T + chunk_tokens(s.k) - 1) / chunk_tokens(s.k); }
+// Whether the top-k is a launch of its own, one token a wave over the whole chip, ahead of the ranking
+// (one launch more), instead of part of the chunk's workgroup (up to 16 tokens a wave, one after the other,
+// on as many CUs as there are chunks).  Measured, us of the whole routing, in one launch with the ranking / apart:
+// up to 16 tokens a chunk have a wave each: 1 x 64 experts, 16 tokens 3.4 / 4.8 (tokens x experts x k below);
+// one chunk: 24 x 64 x 8 5.5 / 5.8, 32 x 256 x 1 5.1 / 5.4, but 32 x 256 x 8 8.9 / 6.9, 256 x 1024 x 1 51 / 8;
+// fewer chunks than CUs: 1024 x 128 x 8 10.4 / 9.6, 8192 x 1024 x 1 100 / 17, 4096 x 64 x 8 13.1 / 13.4,
+// 4096 x 256 x 8 16.0 / 15.2; as many: 8192 x 128 x 8 14.7 / 15.7, 8192 x 512 x 8 23.7 / 20.3, 65536 x 64 x 1
+// 21.1 / 19.8, 65536 x 1024 x 1 141 / 81; more, where the chip is full either way: 65536 x 256 x 2 31.4 / 34.8,
+// 32768 x 256 x 8 39.6 / 40.9.
+constexpr int kTopkGroups = 1 << 16;
+static bool topk_alone(const moe_shape_t& s) {
+    const int n = chunks_of(s), tokens = std::min(s.T, chunk_tokens(s.k));
+    const long long work = (long long)tokens * s.E;
+    if (tokens <= kChunkThreads / 64 && (n == 1 || s.E <= 256)) return false;
+    if (n == 1) return work * s.k > 13000;
+    return n < 128 || (n < 256 && work >= 4096) || (n < 512 && work >= 16384);
+}
 
 // Largest value over the wave, on the data-parallel-primitive path of the vector ALU: six
 // instructions; six shuffles through LDS took ten times as long.
@@ -73,6 +92,44 @@ __device__ __forceinline__ int block_exclusive_sum(int v, int32_t* s_wave, int* 
     return before + incl - v;
 }
 
+// Top-k of one token by one wave: lane j < k gets the j-th expert and its gate.
+template <int EPL>
+__device__ __forceinline__ void select_experts(const float* __restrict__ row, int E, int k, int lane, int& my_idx, float& gate) {
+    uint32_t key[EPL];
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+        const int e = lane + 64 * i;
+        key[i] = e < E ? logit_key(row[e]) : 0u;
+    }
+    float my_val = 0.f, top1 = 0.f;
+    my_idx = 0;
+    for (int j = 0; j < k; ++j) {
+        uint32_t best = key[0];
+#pragma unroll
+        for (int i = 1; i < EPL; ++i) best = max(best, key[i]);
+        best = wave_max(best);
+        float bv = -INFINITY;
+        int be = 0x7fffffff;
+        if (best != 0u) {
+            bv = key_logit(best);
+#pragma unroll
+            for (int i = EPL - 1; i >= 0; --i) {
+                const uint64_t m = __ballot(key[i] == best);
+                if (m) be = 64 * i + (int)__builtin_ctzll(m);
+            }
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) key[i] = (lane + 64 * i == be) ? 0u : key[i];
+        }
+        if (j == 0) top1 = bv;
+        if (lane == j) { my_val = bv; my_idx = be; }
+    }
+    const float p = (lane < k) ? __expf(my_val - top1) : 0.f;
+    float s = p;
+#pragma unroll
+    for (int off = kMaxTopK / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    gate = p / s;
+}
+
 // ------------------------------------------- top-k, gates and ranks inside a chunk
 // One workgroup per chunk, one wave per token at a time.  Lane l holds experts l, l+64, ... as
 // sortable keys; a round of arg-max under the order (value desc, expert id asc) is one wave
@@ -81,9 +138,10 @@ __device__ __forceinline__ int block_exclusive_sum(int v, int32_t* s_wave, int* 
 // Then wave i ranks the chunk's slots [64 i, 64 i + 64): lanes that share an expert are the
 // intersection of the ballots of the expert id's bits.  chunk_cnt[c][e] = slots of chunk c
 // routed to local expert e; inv_perm[f] = rank of slot f among its chunk's slots of that expert.
+// EPL = 0: topk_kernel has selected the experts already.
 // Bound by instruction issue.  With the maximum by shuffles and counts, scan and positions in three
 // launches of their own the whole routing took 101 us for 32768 tokens of 256 experts, 8 selected
-// (now 45 us), and 14 us in four launches for one token of 128 experts (now one launch of 4 us).
+// (now 45 us), and 11-15 us in four launches for up to 16 tokens of 128 experts (now one launch of 3.6-5 us).
 //
 // ONE: the batch is a single chunk (a generation step): the ranks are complete, and the same
 // workgroup scans the counts and writes the rows.
@@ -103,45 +161,19 @@ topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_
     if (tid < e_count)
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) s_cnt[i][tid] = 0;
-    for (int tt = wave; tt < nt; tt += kChunkThreads / 64) {
-        const float* row = logits + (size_t)(t0 + tt) * E;
-        uint32_t key[EPL];
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-            const int e = lane + 64 * i;
-            key[i] = e < E ? logit_key(row[e]) : 0u;
-        }
-        float my_val = 0.f, top1 = 0.f;
-        int my_idx = 0;
-        for (int j = 0; j < k; ++j) {
-            uint32_t best = key[0];
-#pragma unroll
-            for (int i = 1; i < EPL; ++i) best = max(best, key[i]);
-            best = wave_max(best);
-            float bv = -INFINITY;
-            int be = 0x7fffffff;
-            if (best != 0u) {
-                bv = key_logit(best);
-#pragma unroll
-                for (int i = EPL - 1; i >= 0; --i) {
-                    const uint64_t m = __ballot(key[i] == best);
-                    if (m) be = 64 * i + (int)__builtin_ctzll(m);
-                }
-#pragma unroll
-                for (int i = 0; i < EPL; ++i) key[i] = (lane + 64 * i == be) ? 0u : key[i];
+    if constexpr (EPL > 0) {
+        for (int tt = wave; tt < nt; tt += kChunkThreads / 64) {
+            int idx;
+            float gate;
+            select_experts<EPL>(logits + (size_t)(t0 + tt) * E, E, k, lane, idx, gate);
+            if (lane < k) {
+                s_idx[tt * k + lane] = idx;
+                topk_idx[f0 + tt * k + lane] = idx;
+                topk_w[f0 + tt * k + lane] = gate;
             }
-            if (j == 0) top1 = bv;
-            if (lane == j) { my_val = bv; my_idx = be; }
         }
-        const float p = (lane < k) ? __expf(my_val - top1) : 0.f;
-        float s = p;
-#pragma unroll
-        for (int off = kMaxTopK / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-        if (lane < k) {
-            s_idx[tt * k + lane] = my_idx;
-            topk_idx[f0 + tt * k + lane] = my_idx;
-            topk_w[f0 + tt * k + lane] = p / s;
-        }
+    } else if (tid < n) {
+        s_idx[tid] = topk_idx[f0 + tid];
     }
     __syncthreads();
     int el = -1, rank = -1;
@@ -185,6 +217,23 @@ topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_
         inv_perm[tid] = row;
         if (row >= 0) perm[row] = tid;
         if (tid >= rows) perm[tid] = -1;   // rows at and beyond the routed ones
+    }
+}
+
+// ------------------------------------------- top-k alone
+// One token a wave, over the whole chip; topk_rank_kernel<0, ..> then ranks what this wrote.
+template <int EPL>
+__global__ void __launch_bounds__(kRouteThreads)
+topk_kernel(const float* __restrict__ logits, int T, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+    const int lane = threadIdx.x & 63;
+    for (int t = blockIdx.x * (kRouteThreads / 64) + (threadIdx.x >> 6); t < T; t += gridDim.x * (kRouteThreads / 64)) {
+        int idx;
+        float gate;
+        select_experts<EPL>(logits + (size_t)t * E, E, k, lane, idx, gate);
+        if (lane < k) {
+            topk_idx[(size_t)t * k + lane] = idx;
+            topk_w[(size_t)t * k + lane] = gate;
+        }
     }
 }
 
@@ -451,7 +500,7 @@ size_t route_workspace_bytes(const moe_shape_t& s) {
 }
 
 template <int EPL>
-static void launch_topk(const moe_shape_t& s, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
+static void launch_rank(const moe_shape_t& s, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
                         hipStream_t st) {
     const int n = chunks_of(s);
     if (n == 1)
@@ -462,6 +511,16 @@ static void launch_topk(const moe_shape_t& s, const float* logits, const moe_rou
         hipLaunchKernelGGL((topk_rank_kernel<EPL, false>), dim3(n), dim3(kChunkThreads), 0, st, logits, s.T, s.E, s.k,
                            chunk_tokens(s.k), s.e_start, s.e_count, (int32_t*)out.topk_idx, (float*)out.topk_w, chunk_cnt,
                            (int32_t*)out.counts, (int32_t*)out.offsets, (int32_t*)out.perm, (int32_t*)out.inv_perm);
+}
+
+template <int EPL>
+static void launch_topk(const moe_shape_t& s, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
+                        hipStream_t st) {
+    if (!topk_alone(s)) return launch_rank<EPL>(s, logits, out, chunk_cnt, st);
+    const int grid = std::min((s.T + kRouteThreads / 64 - 1) / (kRouteThreads / 64), kTopkGroups);
+    hipLaunchKernelGGL(topk_kernel<EPL>, dim3(grid), dim3(kRouteThreads), 0, st, logits, s.T, s.E, s.k,
+                       (int32_t*)out.topk_idx, (float*)out.topk_w);
+    launch_rank<0>(s, logits, out, chunk_cnt, st);
 }
 
 int route_launch(const moe_shape_t& s, const float* logits, const moe_routing_t& out, void* ws,

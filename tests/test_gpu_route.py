@@ -151,3 +151,41 @@ def test_route_special_values(T):
     key = np.where(np.isnan(logits), -np.inf, logits).astype(np.float64) + 0.0
     order = np.lexsort((np.broadcast_to(np.arange(cfg.E), key.shape), -key, np.isnan(logits)), axis=1)
     assert np.array_equal(got["topk_idx"], order[:, :cfg.k])
+
+
+# Where the top-k is a launch of its own and where it is not: tokens of one chunk (a wave each, little work,
+# more work), fewer than 128, 256 and 512 chunks with little and with more work a chunk
+@pytest.mark.parametrize("kw", [
+    dict(T=16, E=1024, k=8), dict(T=17, E=300, k=8, e_start=3, e_count=290), dict(T=32, E=50, k=8), dict(T=32, E=51, k=8),
+    dict(T=256, E=50, k=1), dict(T=256, E=51, k=1, e_start=50, e_count=1), dict(T=257, E=4, k=1),
+    dict(T=33, E=256, k=16), dict(T=33, E=257, k=16), dict(T=127 * 256, E=8, k=1), dict(T=127 * 256 + 1, E=8, k=1),
+    dict(T=127 * 256 + 1, E=16, k=1), dict(T=255 * 256 + 1, E=63, k=1), dict(T=255 * 256 + 1, E=64, k=1, e_start=60, e_count=4),
+    dict(T=511 * 32 + 1, E=512, k=8), dict(T=510 * 32 + 1, E=512, k=8),
+])
+def test_route_with_the_topk_apart(kw):
+    cfg = moe_synth.small_config(d=64, I=64, **kw)
+    rng = np.random.default_rng(kw["T"] + kw["k"])
+    check(cfg, rng.integers(-40, 41, (cfg.T, cfg.E)).astype(np.float32) * np.float32(0.25), "top-k apart or not")
+
+
+def test_route_of_few_slots_is_spread_over_the_chip():
+    """One slot a token reads the same logits as eight with an eighth of the rounds: it takes no longer."""
+    import paper_2604_19241_amd as moe
+    T, E = 8192, 1024
+    logits = torch.randn((T, E), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    us = {}
+    for k in (1, 8):
+        shape = moe.make_shape(T=T, d=64, E=E, k=k, I=64, e_start=0, e_count=E)
+        routing = moe.alloc_routing(shape, "cuda")
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        times = []
+        for _ in range(8):
+            start.record()
+            for _ in range(20):
+                moe.moe_route_static(shape, logits, routing)
+            stop.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(stop) * 50.0)
+        us[k] = min(times)
+    say(f"[route] 8192 tokens of 1024 experts: {us}")
+    assert us[1] <= 1.3 * us[8], us
