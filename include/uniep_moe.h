@@ -88,6 +88,9 @@ typedef struct {
                          waits, then a plain grid kernel for the tail tasks (combine / dX:
                          fwd_tail_kernel / bwd_tail_kernel, one wave per token and 1024 columns),
                          which may only start once every GEMM task is done.
+                         With every schedule the forward GEMMs of experts with 1..32 rows run
+                         in two launches of their own ahead of the queue's, with the same
+                         results bit for bit; up to T = 32 nothing is left for the queue.
                          Schedule 1 makes the tail tasks wait inside the kernel until EVERY
                          worker has started and run out of GEMM work, so it needs all
                          `workers` workgroups co-resident: the occupancy query that bounds
@@ -96,14 +99,16 @@ typedef struct {
                          with MOE_ERR_DEVICE and partly written y / dx.  Schedules 0, 2, 3
                          have no such precondition. */
     int32_t workers;  /* persistent workgroups; 0 = one per resident slot (never more than
-                         can be co-resident: the deadlock-freedom condition of Section 3.1) */
+                         can be co-resident: the deadlock-freedom condition of Section 3.1).
+                         The launches for experts with few rows have at most as many.  Not
+                         bounded: the tail kernels and the 32 workgroups that write the queue */
     int32_t spin_limit_ms; /* bound on every scoreboard wait; 0 = 2000 ms.  A wait that
                               exceeds it sets MOE_ERR_DEVICE in the workspace and drains */
-    int32_t tile_rows;     /* rows per GEMM row tile: 0 = default (256), or 128 / 256 */
+    int32_t tile_rows;     /* rows per GEMM row tile of the queue: 0 = default (256), or 128 / 256 */
     int32_t skip_tail;     /* measurement aid, 0 or 1: with the default schedule, 1 leaves out the
                               tail kernel (combine / dX), so that y / dx and dtopk_w are not
                               written and a timer around the call sees the GEMM MegaKernel and
-                              its prologue alone */
+                              the launches ahead of it alone (plan; GEMMs of experts with few rows) */
     int32_t dw_accumulate; /* moe_fused_backward only, 0 or 1.  1: dw_gate, dw_up, dw_down are fp32
                               buffers of the same shapes (16-byte aligned) and the weight
                               gradients are ADDED to them in fp32, straight from the

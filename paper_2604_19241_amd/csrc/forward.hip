@@ -487,7 +487,8 @@ static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream
     p.thin_rows = all_thin ? INT_MAX : kThinRows;
     p.plan_blocks = all_thin ? 0 : kPlanBlocks;
     const size_t most = std::min<size_t>(p.s.e_count, (size_t)p.s.T * p.s.k);   // experts with rows
-    const size_t slots = (size_t)kThinGroupsPerCu * resident;
+    // A caller's bound on the workers leaves the rest of the chip to somebody else: as many workgroups here.
+    const size_t slots = workers < resident ? (size_t)workers : (size_t)kThinGroupsPerCu * resident;
     const size_t n1 = std::min(slots, most * (p.s.I / 64)), n2 = std::min(slots, most * ((p.s.d + kThinCols - 1) / kThinCols));
     hipLaunchKernelGGL(fwd_first_kernel, dim3((unsigned)(n1 + p.plan_blocks)), dim3(kThinThreads), 0, st, p);
     hipLaunchKernelGGL(fwd_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);

@@ -223,9 +223,9 @@ struct ThinShared {
     int32_t wave[4];
 };
 
-// Workgroup `block` of `blocks` (a multiple of 8, unless there are fewer tasks): it finds the
-// experts of this path by itself (their row counts come from the offsets) and takes every
-// `blocks`-th task.  Workgroups go to the XCDs in turn, so for as many experts as fill all eight
+// Workgroup `block` of `blocks` (a multiple of 8, unless there are fewer tasks or the caller bounds the
+// workers): it finds the experts of this path by itself (their row counts come from the offsets) and takes
+// every `blocks`-th task.  Workgroups go to the XCDs in turn, so for as many experts as fill all eight
 // the tasks of one expert share an XCD (its rows are then fetched by one L2); what is left over
 // is spread task by task.
 template <int GEMM>

@@ -1,0 +1,90 @@
+"""What the entry points launch, read from a captured (and never executed) graph: the grids of every kernel."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2604_19241_amd as moe
+from helpers import say
+
+pytestmark = pytest.mark.gpu
+
+
+class Dim3(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_uint32) for n in "xyz"]
+
+
+class KernelNodeParams(ctypes.Structure):
+    _fields_ = [("block", Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", Dim3),
+                ("params", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
+
+
+def hip():
+    with open("/proc/self/maps") as f:
+        lib = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    lib.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    lib.hipKernelNameRefByPtr.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    return lib
+
+
+def launches(call):
+    """[(kernel name, workgroups, threads a workgroup)] of call(stream), in order."""
+    lib = hip()
+    stream = torch.cuda.Stream()
+    st, graph = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p()
+    torch.cuda.synchronize()
+    assert lib.hipStreamBeginCapture(st, 2) == 0   # relaxed
+    rc = call(st)
+    ended = lib.hipStreamEndCapture(st, ctypes.byref(graph))
+    assert rc == moe.binding.MOE_OK, rc
+    assert ended == 0
+    n = ctypes.c_size_t()
+    assert lib.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert lib.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = KernelNodeParams()
+        assert lib.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        name = (lib.hipKernelNameRefByPtr(p.func, st) or b"?").decode()
+        out.append((name, p.grid.x * p.grid.y * p.grid.z, p.block.x * p.block.y * p.block.z))
+    assert lib.hipGraphDestroy(graph) == 0
+    return out
+
+
+# Any aligned address will do for a call whose kernels never run.
+def forward_launches(shape, opts):
+    p, lib = ctypes.c_void_p(4096), moe.load_library()
+    r = moe.binding.MoERoutingC(*([4096] * 6))
+    return launches(lambda st: lib.moe_fused_forward(
+        ctypes.byref(shape), p, p, p, p, ctypes.byref(r), p, None, p, ctypes.c_size_t(moe.moe_workspace_bytes(shape)["fwd"]),
+        ctypes.byref(opts), st))
+
+
+def first_call():
+    """What the library looks up once per device cannot be looked up during a capture."""
+    shape = moe.make_shape(T=40, d=64, E=2, k=1, I=64)
+    dev = {"device": "cuda"}
+    x, w = torch.zeros((40, 64), dtype=torch.bfloat16, **dev), torch.zeros((2, 64, 64), dtype=torch.bfloat16, **dev)
+    r = moe.moe_route(shape, torch.zeros((40, 2), **dev))
+    saved = moe.alloc_saved(shape, "cuda")
+    moe.moe_fused_forward(shape, x, w, w, w, r, saved=saved)
+    moe.moe_fused_backward(shape, x, x, w, w, w, r, saved)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("T", [20, 600])
+@pytest.mark.parametrize("workers", [1, 5, 0])
+def test_workers_bounds_every_launch_of_the_forward_gemms(T, workers):
+    first_call()
+    shape = moe.make_shape(T=T, d=1024, E=128, k=8, I=768)
+    got = forward_launches(shape, moe.make_opts(workers=workers))
+    say(f"[launches] T={T} workers={workers}: {got}")
+    gemms = [(name, groups) for name, groups, threads in got if "tail" not in name]
+    plan = 32 if T > 32 else 0   # workgroups of the first launch that write the queue
+    groups = [n - (plan if i == 0 else 0) for i, (_, n) in enumerate(gemms)]
+    assert len(groups) == (3 if plan else 2)
+    if workers:
+        assert max(groups) <= workers, gemms
+    else:
+        assert min(groups) >= 128, gemms
