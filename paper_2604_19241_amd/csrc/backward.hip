@@ -702,14 +702,13 @@ static BwdWorkerFn bwd_worker_fn(bool acc, bool split) {
 // cursor, no LDS.  A wave is one token by one round of columns, or the token's gate gradients.
 // The gate gradients used to follow the columns in the same wave, two tokens a wave, and 256 tokens
 // filled 16 workgroups: training step of 256 tokens 139.6 -> 136.9 us, unchanged from 8192 tokens on.
-constexpr int kTailWaves = 4;
 static __host__ __device__ __forceinline__ int tail_units(const BwdParams& p) {   // waves a token
     return (p.s.d + kDxCols - 1) / kDxCols + (p.dtopk_w ? 1 : 0);
 }
 template <int KM>
-__global__ void __launch_bounds__(64 * kTailWaves) bwd_tail_kernel(BwdParams p) {
-    const int units = tail_units(p);
-    const int id = rfl((int)blockIdx.x * kTailWaves + (int)(threadIdx.x >> 6));
+__global__ void __launch_bounds__(64 * kTailWaves) bwd_tail_kernel(BwdParams p, uint32_t first) {
+    const uint32_t units = tail_units(p);
+    const uint32_t id = first + rfl((int)blockIdx.x * kTailWaves + (int)(threadIdx.x >> 6));
     const int t = id / units, unit = id - t * units;
     if (t >= p.s.T) return;
     if (unit * kDxCols >= p.s.d) {
@@ -820,11 +819,12 @@ static int bwd_launch_bm(BwdParams& p, const moe_opts_t& opts, int bm, hipStream
         launch_worker(acc, split, p, workers, -2, st);
         if (p.s.T > 0 && !opts.skip_tail) {
             const size_t waves = (size_t)p.s.T * tail_units(p);
-            const dim3 grid((unsigned)((waves + kTailWaves - 1) / kTailWaves)), block(64 * kTailWaves);
-            if (p.s.k <= 8)
-                hipLaunchKernelGGL((bwd_tail_kernel<8>), grid, block, 0, st, p);
-            else
-                hipLaunchKernelGGL((bwd_tail_kernel<kMaxTopK>), grid, block, 0, st, p);
+            launch_tail_waves(waves, [&](dim3 grid, uint32_t first) {
+                if (p.s.k <= 8)
+                    hipLaunchKernelGGL((bwd_tail_kernel<8>), grid, dim3(64 * kTailWaves), 0, st, p, first);
+                else
+                    hipLaunchKernelGGL((bwd_tail_kernel<kMaxTopK>), grid, dim3(64 * kTailWaves), 0, st, p, first);
+            });
         }
     } else {
         launch_worker(acc, split, p, workers, -1, st);

@@ -21,6 +21,19 @@ constexpr int kWave = 64;
 constexpr int kMaxDevices = 64;                           // per-device host caches are indexed by the HIP device id
 constexpr size_t kRouteStaticScratchBytes = 4u << 20;     // file-scope scratch of moe_route_static
 
+// The tail kernels (combine, dX) have a wave for each piece of work.  A launch has to have fewer than 2^32
+// work-items (hipErrorInvalidConfiguration otherwise): beyond 2^22 workgroups of 256 threads another launch
+// goes on where the last one stopped.  (A loop in the kernel instead made it slower at every size: training
+// step of 60001 tokens 3186 -> 3296 us.)
+constexpr int kTailWaves = 4;   // of a workgroup
+constexpr size_t kTailGroups = 1u << 22;
+template <class F>
+inline void launch_tail_waves(size_t waves, F launch) {
+    const size_t groups = (waves + kTailWaves - 1) / kTailWaves;
+    for (size_t g = 0; g < groups; g += kTailGroups)
+        launch(dim3((unsigned)(groups - g < kTailGroups ? groups - g : kTailGroups)), (uint32_t)(g * kTailWaves));
+}
+
 // ---- bf16 <-> fp32 (round-to-nearest-even; gfx950 has a native packed convert)
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     f32x2_t v = {lo, hi};

@@ -397,11 +397,10 @@ fwd_worker_kernel(FwdParams p, int phase) {
 // tokens to fill the chip otherwise (32 tokens of width 2048 kept 2 CUs busy, four dependent
 // rounds a wave: 198 -> 191 us for the layer; one token 35.8 -> 34.8 us; 256 tokens of width 7168
 // 529 -> 518 us), and 8192 tokens gain a little as well (training step 2428 -> 2421 us).
-constexpr int kTailWaves = 4;
 template <int KM>
-__global__ void __launch_bounds__(64 * kTailWaves) fwd_tail_kernel(FwdParams p) {
-    const int rounds = (p.s.d + kCombineCols - 1) / kCombineCols;
-    const int id = rfl((int)blockIdx.x * kTailWaves + (int)(threadIdx.x >> 6));
+__global__ void __launch_bounds__(64 * kTailWaves) fwd_tail_kernel(FwdParams p, uint32_t first) {
+    const uint32_t rounds = (p.s.d + kCombineCols - 1) / kCombineCols;
+    const uint32_t id = first + rfl((int)blockIdx.x * kTailWaves + (int)(threadIdx.x >> 6));
     const int t = id / rounds, c0 = (id - t * rounds) * kCombineCols + (int)(threadIdx.x & 63) * 8;
     if (t >= p.s.T || c0 >= p.s.d) return;
     CombineSlots<KM> slots;
@@ -465,11 +464,12 @@ static int resident_workers(int* out) {
 
 static void launch_tail(const FwdParams& p, hipStream_t st) {
     const size_t waves = (size_t)p.s.T * ((p.s.d + kCombineCols - 1) / kCombineCols);
-    const dim3 grid((unsigned)((waves + kTailWaves - 1) / kTailWaves)), block(64 * kTailWaves);
-    if (p.s.k <= 8)
-        hipLaunchKernelGGL((fwd_tail_kernel<8>), grid, block, 0, st, p);
-    else
-        hipLaunchKernelGGL((fwd_tail_kernel<kMaxTopK>), grid, block, 0, st, p);
+    launch_tail_waves(waves, [&](dim3 grid, uint32_t first) {
+        if (p.s.k <= 8)
+            hipLaunchKernelGGL((fwd_tail_kernel<8>), grid, dim3(64 * kTailWaves), 0, st, p, first);
+        else
+            hipLaunchKernelGGL((fwd_tail_kernel<kMaxTopK>), grid, dim3(64 * kTailWaves), 0, st, p, first);
+    });
 }
 
 // BM = rows per row tile: 256, or 128 (every tile then leaves the upper half of the workgroup's

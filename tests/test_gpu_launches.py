@@ -88,3 +88,49 @@ def test_workers_bounds_every_launch_of_the_forward_gemms(T, workers):
         assert max(groups) <= workers, gemms
     else:
         assert min(groups) >= 128, gemms
+
+
+def every_launch_fits(got):
+    say(f"[launches] {got}")
+    assert all(0 < groups and groups * threads < 2 ** 32 for _, groups, threads in got), got
+
+
+# 2^32 work-items a launch are too many: one wave for each of these tokens and rounds of columns would be
+@pytest.mark.parametrize("T,d", [(2 ** 25, 1088), (2 ** 26, 64), (2 ** 27 - 16, 64)])
+def test_long_batches_of_narrow_tokens_can_be_launched(T, d):
+    first_call()
+    shape = moe.make_shape(T=T, d=d, E=2, k=1, I=64)
+    every_launch_fits(forward_launches(shape, moe.make_opts()))
+    p, lib = ctypes.c_void_p(4096), moe.load_library()
+    r = moe.binding.MoERoutingC(*([4096] * 6))
+    for gates in (p, None):
+        every_launch_fits(launches(lambda st: lib.moe_fused_backward(
+            ctypes.byref(shape), p, p, p, p, p, ctypes.byref(r), p, p, p, p, p, gates, p,
+            ctypes.c_size_t(moe.moe_workspace_bytes(shape)["bwd"]), None, st)))
+
+
+# more than the 2^24 waves of one launch: two for dX with the gates and one combine, three and two
+@pytest.mark.parametrize("T,d", [(2 ** 23 + 5, 64), (2 ** 24 + 37, 64)])
+def test_tail_kernels_of_several_launches(T, d):
+    g = torch.Generator(device="cuda").manual_seed(d)
+    I, E = 64, 2
+    x, dy = (torch.randn((T, d), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    w = [torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16) * 0.05 for s in ((E, d, I), (E, d, I), (E, I, d))]
+    logits = torch.randn((T, E), generator=g, device="cuda")
+
+    def both(sel):
+        n = len(x[sel])
+        shape = moe.make_shape(T=n, d=d, E=E, k=1, I=I)
+        r, saved = moe.moe_route(shape, logits[sel]), moe.alloc_saved(shape, "cuda")
+        y = moe.moe_fused_forward(shape, x[sel], *w, r, saved=saved)
+        out = moe.moe_fused_backward(shape, dy[sel], x[sel], *w, r, saved)
+        return {"y": y, "dx": out["dx"], "dtopk_w": out["dtopk_w"]}
+
+    say(f"[tail] T={T} d={d}")
+    whole = both(slice(0, T))
+    # a token's rows do not depend on the batch: the same tokens in pieces that one round of waves covers
+    step = 2 ** 22
+    for t in list(range(0, T, step)):
+        sel = slice(t, min(T, t + step))
+        for name, want in both(sel).items():
+            assert torch.equal(whole[name][sel], want), (name, t)
