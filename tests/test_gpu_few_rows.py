@@ -36,9 +36,74 @@ def test_forward_at_row_counts(rows, d, I):
             check_elementwise(name, got, want[name])
 
 
-# k axes of 18, 34 and 66 steps, dealt unevenly to the four waves of a task, more tasks than CUs, and
-# widths at which the combine's last round of columns is a full one, 64 columns or none
+# k axes of 9, 16, 17, 33 and 129 stages of 64, and widths at which the combine's last round of columns is a
+# full one, 64 columns or none
 @pytest.mark.parametrize("rows", [[1], [17, 15]])
 @pytest.mark.parametrize("d,I", [(576, 1088), (1024, 64), (1088, 576), (2112, 128), (192, 8256)])
 def test_forward_of_a_small_batch(rows, d, I):
     test_forward_at_row_counts(rows, d, I)
+
+
+# A generation step: no stash (h and o in the workspace, no G|U), several slots a token, an expert window; up to
+# 32 tokens without a queue, 33 with one.  The stash changes where the stages are kept and nothing else.
+@pytest.mark.parametrize("T", [1, 20, 32, 33])
+@pytest.mark.parametrize("kw", [dict(E=16, k=8, e_start=5, e_count=9), dict(E=16, k=12), dict(E=4, k=4)])
+def test_generation_step_without_a_stash(T, kw):
+    cfg = moe_synth.small_config(T=T, d=320, I=192, **kw)
+    inp = scaled_inputs(cfg, 9, 4.0)
+    b = bits(inp, ("x", "w_gate", "w_up", "w_down"))
+    r = oracle.route(cfg.shape_dict(), inp["logits"].numpy())
+    want = oracle.forward(cfg.shape_dict(), b["x"], b["w_gate"], b["w_up"], b["w_down"], r)["y"]
+    for schedule in (0, 1, 2):
+        say(f"[no stash] {cfg.shape_dict()} schedule={schedule}")
+        y, _, _ = gpu_forward(cfg, inp, schedule, 0, with_saved=False)
+        assert rel_l2(to_f64(y), want) <= REL_L2
+        check_elementwise("y", to_f64(y), want)
+        assert torch.equal(y, gpu_forward(cfg, inp, schedule, 0)[0])
+
+
+# More tasks than workgroups (768 of them): a workgroup's images are used for one task after the other
+@pytest.mark.parametrize("rows,I", [([2] * 16, 4096), ([1, 0, 3] * 5, 8256)])
+def test_workgroups_with_several_tasks(rows, I):
+    test_forward_at_row_counts(rows, 64, I)
+
+
+# A caller may bring a routing in which a token's slots share an expert: more than 32 rows of an expert in a batch
+# of up to 32 tokens are run in blocks of 32.  Against the same slots as tokens of their own, whose experts are on
+# the work queue: the rows have the same bits.
+@pytest.mark.parametrize("T,k", [(32, 2), (20, 5), (11, 3)])
+def test_slots_of_a_token_on_one_expert(T, k):
+    import paper_2604_19241_amd as moe
+    d, I, E = 320, 192, 6
+    F = T * k
+    rng = np.random.default_rng(F)
+    own = np.where(rng.random(F) < (0.9 if F > 40 else 1.0), 4, rng.integers(0, E, F)).astype(np.int32)   # slot f -> expert
+    perm = np.argsort(own, kind="stable").astype(np.int32)
+    inv = np.empty(F, np.int32)
+    inv[perm] = np.arange(F, dtype=np.int32)
+    counts = np.bincount(own, minlength=E).astype(np.int32)
+    assert counts.max() > 32
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    cfg = moe_synth.small_config(T=T, d=d, E=E, k=k, I=I)
+    dev = {key: v.cuda() for key, v in scaled_inputs(cfg, 13, 4.0).items()}
+    got = {}
+    for tokens, slots in ((T, k), (F, 1)):
+        say(f"[one expert] {tokens} tokens, {slots} slots, rows {counts.tolist()}")
+        shape = moe.make_shape(T=tokens, d=d, E=E, k=slots, I=I)
+        routing = moe.alloc_routing(shape, "cuda")
+        for name, v in (("topk_idx", own), ("counts", counts), ("offsets", offsets), ("perm", perm), ("inv_perm", inv)):
+            dst = getattr(routing, name)
+            dst.copy_(torch.from_numpy(v).view(dst.shape))
+        routing.topk_w.fill_(1.0)
+        x = dev["x"] if slots == k else dev["x"].repeat_interleave(k, dim=0)
+        saved = moe.alloc_saved(shape, "cuda")
+        y = moe.moe_fused_forward(shape, x, dev["w_gate"], dev["w_up"], dev["w_down"], routing, saved=saved)
+        got[slots] = dict(moe.saved_views(shape, saved), y=y)
+    for name in ("gu", "h", "o"):
+        assert torch.equal(got[k][name], got[1][name]), name
+    # gates of one: y is the sum of the token's rows in slot order, in fp32
+    o = got[k]["o"][torch.from_numpy(inv).cuda().long()].float().view(T, k, d)
+    want = torch.zeros((T, d), device="cuda")
+    for j in range(k):
+        want += o[:, j]
+    assert torch.equal(got[k]["y"], want.bfloat16())

@@ -24,8 +24,11 @@ def test_route_static_matches_route_on_two_calls_in_a_row():
     torch.cuda.set_device(0)
     big = moe_synth.small_config(T=4096, d=256, E=128, k=8, I=64, name="static-big")
     small = moe_synth.small_config(T=777, d=256, E=64, k=6, I=64, e_start=16, e_count=32, name="static-small")
+    # generation steps (one chunk): with the top-k apart, and in one launch
+    step = moe_synth.small_config(T=32, d=256, E=128, k=8, I=64, name="static-step")
+    few = moe_synth.small_config(T=16, d=256, E=128, k=8, I=64, name="static-few")
     calls = []
-    for cfg in (big, small):
+    for cfg in (big, small, step, few):
         shape = moe.make_shape(**cfg.shape_dict())
         assert moe.moe_workspace_bytes(shape)["route"] <= moe.ROUTE_STATIC_SCRATCH_BYTES
         logits = moe_synth.make_inputs(cfg, seed=5, with_dy=False, with_weights=False)["logits"].cuda()
