@@ -223,11 +223,14 @@ __device__ __forceinline__ void for_each_tile(int lane, int nt, int nct, F f) {
 // Which expert goes to which list, and where its blocks stand in it.  The lists should end at the
 // same time: work that one XCD steals from another list has lost the L2 sharing between the
 // tiles of a row tile and of an expert, and runs about half as fast.  So the experts are sorted
-// by rows (descending, in 64 classes of equal width; ties by id) and dealt to the lists in
+// by rows (descending, in 63 classes of equal width and one of those without rows; ties by id) and dealt to the lists in
 // boustrophedon order (ranks 0..7 to lists 0..7, ranks 8..15 to lists 7..0, ...).  Big experts
 // come first in every list, small ones fill the end.  The producer block of a list's (i + lag)-th
 // expert comes before the consumer block of its i-th: A0, A1, B0, A2, B1, ..., A(n-1), B(n-2),
 // B(n-1) for a lag of 1.  The plan depends only on the counts, so it is the same on every run.
+// Experts without rows never share a class with those of few rows: dealt together by id, one list could get
+// all of the latter (600 tokens under Zipf(1.2) routing, 80 of 512 experts of width 2048 and inner width 512 with
+// rows: backward 971 -> 847 us, 907 us where the experts were sorted exactly).
 //
 // Latency is all that counts here (one launch in front of every pass, nothing else can run), so
 // every one of kPlanBlocks workgroups makes the whole plan for itself, without a word to
@@ -306,13 +309,13 @@ __device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, 
     // rank inside the class: the wave's experts of the class so far + the lanes below
 #pragma unroll
     for (int i = 0; i < kPlanWaves; ++i) most = max(most, P.most[i]);
-    const float scale = most > 0 ? 63.f / (float)most : 0.f;
+    const float scale = most > 0 ? 62.f / (float)most : 0.f;
     int cls[kRounds], rank[kRounds];
     volatile int32_t* hist = P.hist[w];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const bool in = 256 * w + 64 * r + lane < ec;
-        cls[r] = min(63, (int)((float)rows[r] * scale));
+        cls[r] = rows[r] > 0 ? 1 + min(62, (int)((float)rows[r] * scale)) : 0;
         uint64_t m = __ballot(in);
 #pragma unroll
         for (int b = 0; b < 6; ++b) {
