@@ -89,8 +89,9 @@ typedef struct {
                          fwd_tail_kernel / bwd_tail_kernel, one wave per token and 1024 columns),
                          which may only start once every GEMM task is done.
                          With every schedule the forward GEMMs of experts with 1..32 rows run
-                         in two launches of their own ahead of the queue's, with the same
-                         results bit for bit; up to T = 32 nothing is left for the queue.
+                         in two launches of their own ahead of the queue's where the row
+                         counts say that this is faster, with the same results bit for bit;
+                         up to T = 32 nothing is left for the queue.
                          Schedule 1 makes the tail tasks wait inside the kernel until EVERY
                          worker has started and run out of GEMM work, so it needs all
                          `workers` workgroups co-resident: the occupancy query that bounds

@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
         return (p.split_rows > 0 && rows > p.split_rows) ? (rows + p.split_rows - 1) / p.split_rows : 1;
     };
     // (an expert without rows still has its weight gradients written)
-    make_plan(P, p.offsets, ec, 0, bm, p.nct_dh, [&](int rows) { return row_tiles(rows, bm) * p.nct_dh; },
+    make_plan(P, p.offsets, ec, 0, [](int) { return 0; }, bm, p.nct_dh, [&](int rows) { return row_tiles(rows, bm) * p.nct_dh; },
               [&](int rows) { return row_tiles(rows, bm) * p.nct_dxp + (per_dwgu + per_dwd) * parts_of(rows); });
     const int lane = threadIdx.x & 63;
     for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {   // one wave, one expert

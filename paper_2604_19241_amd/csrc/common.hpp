@@ -82,7 +82,7 @@ __device__ __forceinline__ void add_relaxed(int* p, int v) {
 
 // ---- work queues -----------------------------------------------------------
 // The GEMM tasks are cut into kQueues lists, one per XCD (each XCD has its own
-// L2): every expert belongs to one list (see ListPlan), so the tiles that share
+// L2): every expert belongs to one list (see QueuePlan), so the tiles that share
 // an expert's weights and rows run on one XCD and meet in its L2.  Inside a list
 // the experts are pipelined with a lag: the producer block of the list's
 // (i+L)-th expert comes before the consumer block of its i-th, so consumers
@@ -247,13 +247,14 @@ struct QueuePlan {
     int32_t b[kQueues][kListSlots + 1];   // consumer tasks likewise
     int32_t rows[kMaxExperts];
     int32_t rt0[kMaxExperts];             // first row tile of the expert
-    int32_t sums[1][kPlanWaves];          // row tiles of each wave's experts
+    int32_t sums[kPlanWaves];             // row tiles of each wave's experts
     int32_t most[kPlanWaves];
+    int32_t counts[kPlanWaves];           // experts with few and with many rows
     int32_t hist[kPlanWaves][64];
     int32_t first[kPlanWaves][64];
     uint16_t slot[kMaxExperts];           // list * kListSlots + slot
     int32_t base[kQueues + 1];            // first entry of each list
-    int32_t lag, n_row_tiles, pad_[2];
+    int32_t lag, n_row_tiles;
 };
 // Lag (in experts) between an expert's producer and consumer blocks: enough
 // producer tasks in between (about four rounds of one XCD's workgroups) that a
@@ -268,20 +269,32 @@ __device__ __forceinline__ int queue_lag(int total_producer_tasks, int ec) {
 // Row tiles of an expert; tiles have 256 or 128 rows.
 __device__ __forceinline__ int row_tiles(int rows, int bm) { return (rows + bm - 1) >> (bm == 256 ? 8 : 7); }
 // The plan of this workgroup (kPlanThreads threads, all of them call; ends with a barrier).
-// Experts with up to `skip_rows` rows have no tasks.  a_of(rows) / b_of(rows): tasks of an
-// expert's producer and consumer block; `per_row_tile` producer tasks for each row tile of bm rows.
-template <class FA, class FB>
-__device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, int ec, int skip_rows, int bm,
+// a_of(rows) / b_of(rows): tasks of an expert's producer and consumer block; `per_row_tile` producer tasks for
+// each row tile of bm rows.  limit > 0: experts with up to skip_of(counts) rows have no tasks, where counts is the
+// number of experts with 1..limit rows and, shifted left by 16, of those with more.
+template <class FS, class FA, class FB>
+__device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, int ec, int limit, FS skip_of, int bm,
                                           int per_row_tile, FA a_of, FB b_of) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
     constexpr int kRounds = kMaxExperts / kPlanThreads;
-    int rows[kRounds], run = 0, most = 0;
+    int rows[kRounds], run = 0, most = 0, counts = 0;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {   // wave w looks at experts 256 w + 64 r + lane
         const int e = 256 * w + 64 * r + lane;
         rows[r] = offsets[min(e + 1, ec)] - offsets[min(e, ec)];
-        if (rows[r] <= skip_rows) rows[r] = 0;
+        counts += __popcll(__ballot(rows[r] > 0 && rows[r] <= limit)) + (__popcll(__ballot(rows[r] > limit)) << 16);
+    }
+    if (limit > 0) {
+        if (lane == 0) P.counts[w] = counts;
+        __syncthreads();
+        counts = 0;
+#pragma unroll
+        for (int i = 0; i < kPlanWaves; ++i) counts += P.counts[i];
+        const int skip = skip_of(counts);
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r)
+            if (rows[r] <= skip) rows[r] = 0;
     }
     for (int i = tid; i < kQueues * (kListSlots + 1); i += kPlanThreads) (&P.a[0][0])[i] = (&P.b[0][0])[i] = 0;
     P.hist[w][lane] = 0;
@@ -302,7 +315,7 @@ __device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, 
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) most = max(most, __shfl_xor(most, o));
     if (lane == 0) {
-        P.sums[0][w] = run;
+        P.sums[w] = run;
         P.most[w] = most;
     }
     __syncthreads();
@@ -398,7 +411,7 @@ __device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, 
             base += P.a[q][kListSlots] + P.b[q][kListSlots];
         }
         P.base[kQueues] = base;
-        for (int i = 0; i < kPlanWaves; ++i) n += P.sums[0][i];
+        for (int i = 0; i < kPlanWaves; ++i) n += P.sums[i];
         P.n_row_tiles = n;
         P.lag = queue_lag(n * per_row_tile, ec);
     }
@@ -415,7 +428,7 @@ __device__ __forceinline__ int plan_b(const QueuePlan& P, int e) {
 }
 __device__ __forceinline__ int plan_rt0(const QueuePlan& P, int e) {
     int r = P.rt0[e];
-    for (int i = 0; i < e / 256; ++i) r += P.sums[0][i];
+    for (int i = 0; i < e / 256; ++i) r += P.sums[i];
     return r;
 }
 // The control words of a pass, by one workgroup.

@@ -19,10 +19,7 @@ namespace uniep {
 
 enum TaskType { TASK_GEMM1 = 0, TASK_GEMM2 = 1, TASK_COMBINE = 2 };
 
-// Where GEMM1 stages its A operand (the gathered rows of x): 1 = straight into registers,
-// 0 = through LDS with 128-byte coalesced row pieces.
-
-constexpr int kCombineTokens = 16;   // tokens per combine task (4 per wave)
+constexpr int kCombineTokens = 16;   // tokens per combine task (2 per wave)
 
 struct FwdParams {
     moe_shape_t s;
@@ -42,21 +39,21 @@ struct FwdParams {
     int* flag1;   // per row tile: GEMM1 column tiles finished
     Task* tasks;
     int nct1, nct2;   // column tiles of GEMM1 (128 h-columns each) and GEMM2 (256 each)
-    int max_rt;
     int workers;   // workgroups of the worker launch (the tail waits for all of them)
     int bm;            // rows per row tile (256, or 128)
-    int thin_rows;     // experts with 1..thin_rows rows are run outside the work queue
+    ThinRule rule;     // which experts are run outside the work queue; max_rows = 0: none
     int plan_blocks;   // workgroups of the first launch that make the queue: kPlanBlocks, or 0 if there is none
     long long spin_ticks;
 };
 
 // ------------------------------------------------------------- first launch
-// The work queue of the experts with more than kThinRows rows, made by the first kPlanBlocks
-// workgroups: row-tile table from the expert offsets, the per-XCD task lists (GEMM1 block of
-// expert i+1 ahead of the GEMM2 block of expert i) and a cleared scoreboard.
+// The work queue of the experts that thin_run leaves to it, made by the first kPlanBlocks workgroups:
+// row-tile table from the expert offsets, the per-XCD task lists (GEMM1 block of expert i+1 ahead of the
+// GEMM2 block of expert i) and a cleared scoreboard.
 __device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePlan& P) {
     const int ec = p.s.e_count, bm = p.bm;
-    make_plan(P, p.offsets, ec, kThinRows, bm, p.nct1, [&](int rows) { return row_tiles(rows, bm) * p.nct1; },
+    make_plan(P, p.offsets, ec, p.rule.max_rows, [&](int counts) { return p.rule.limit(counts); }, bm, p.nct1,
+              [&](int rows) { return row_tiles(rows, bm) * p.nct1; },
               [&](int rows) { return row_tiles(rows, bm) * p.nct2; });
     const int lane = threadIdx.x & 63;
     for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {
@@ -79,7 +76,7 @@ __device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePl
 }
 
 __device__ __forceinline__ ThinParams thin_params(const FwdParams& p) {
-    return ThinParams{p.s, p.x, p.w_gate, p.w_up, p.w_down, p.offsets, p.perm, p.gu, p.h, p.o, p.thin_rows};
+    return ThinParams{p.s, p.x, p.w_gate, p.w_up, p.w_down, p.offsets, p.perm, p.gu, p.h, p.o, p.rule};
 }
 // The queue (unless every expert is thin) and the thin experts' GEMM1, side by side: neither reads
 // what the other writes.
@@ -316,7 +313,7 @@ fwd_worker_kernel(FwdParams p, int phase) {
     const bool publishes = phase == -1 || phase == TASK_GEMM2;
     bool arrived = false;
     unsigned exhausted = 0;
-    if (phase == -2 && ctrl[CTRL_NRT] == 0) return;   // every expert was thin
+    if (phase == -2 && ctrl[CTRL_NRT] == 0) return;   // no expert with rows is left
     if (threadIdx.x == 0) {
         if (phase == -1) worker_started(ctrl, home);
         s_task = fetch_task(ctrl, pass, home, exhausted, use_lists, use_tail);
@@ -484,14 +481,22 @@ static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream
     // A token selects an expert at most once, so up to kThinRows tokens no expert has more rows than
     // that: every expert is thin and no work queue is set up.
     const bool all_thin = p.s.T <= kThinRows;
-    p.thin_rows = all_thin ? INT_MAX : kThinRows;
+    // Otherwise the counts decide, which only the device has.  But where the rows are more than kThinRows an expert and
+    // all experts are here, one has more, and few or small ones never spare the queue enough beside it: their launch
+    // without work took 2 us (256 tokens on 8 experts of 512 x 1024 48.3 us, without it 46.3 us).
+    const bool none_thin = !all_thin && p.s.e_count == p.s.E &&
+                           (long long)p.s.T * p.s.k > (long long)kThinRows * p.s.E &&
+                           !thin_may_pay(thin_rule(p.s, kThinRows), p.s);
+    p.rule = thin_rule(p.s, all_thin ? INT_MAX : none_thin ? 0 : kThinRows);
     p.plan_blocks = all_thin ? 0 : kPlanBlocks;
     const size_t most = std::min<size_t>(p.s.e_count, (size_t)p.s.T * p.s.k);   // experts with rows
     // A caller's bound on the workers leaves the rest of the chip to somebody else: as many workgroups here.
     const size_t slots = workers < resident ? (size_t)workers : (size_t)kThinGroupsPerCu * resident;
-    const size_t n1 = std::min(slots, most * (p.s.I / 64)), n2 = std::min(slots, most * ((p.s.d + kThinCols - 1) / kThinCols));
+    const size_t n1 = none_thin ? 0 : std::min(slots, most * (p.s.I / 64));
+    const size_t n2 = std::min(slots, most * ((p.s.d + kThinCols - 1) / kThinCols));
     hipLaunchKernelGGL(fwd_first_kernel, dim3((unsigned)(n1 + p.plan_blocks)), dim3(kThinThreads), 0, st, p);
-    hipLaunchKernelGGL(fwd_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);
+    if (!none_thin)
+        hipLaunchKernelGGL(fwd_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);
     if (all_thin) {
         if (!opts.skip_tail || opts.schedule == 1 || opts.schedule == 2) launch_tail(p, st);
         return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
@@ -531,7 +536,6 @@ int fwd_launch(const moe_shape_t& s, const void* x, const void* w_gate, const vo
     p.tasks = (Task*)(ws + L.tasks);
     p.nct1 = L.nct1;
     p.nct2 = L.nct2;
-    p.max_rt = L.max_rt;
     const int ms = opts.spin_limit_ms > 0 ? opts.spin_limit_ms : 2000;
     p.spin_ticks = (long long)ms * 100000ll;   // wall_clock64 ticks at 100 MHz
     return fwd_launch_bm(p, opts, nw == 4 ? 128 : 256, st);

@@ -30,6 +30,47 @@ constexpr int kThinAhead = 4;       // stages in flight (even: stage t is in reg
 constexpr int kThinWBytes = BK * kThinCols * 2;                       // weights of a stage: image [64 k][256 B]
 constexpr int kThinImage = kThinWBytes + kThinRows * BK * 2;          // and the rows: image [32 rows][128 B]
 
+// Whether the experts with few rows leave the queue.  Both paths give the same bits, so this is a matter of time
+// alone: the two launches of this path stand in front of the queue's, one after the other, and add their latency
+// where the queue would have had CUs to spare for the same experts.  In whole numbers and from the counts alone,
+// so that every workgroup of a pass comes to the same answer by itself.  It pays
+//  - where no expert has more rows: nothing is left for the queue (8 experts of 2048 x 1408 with 10 rows each 39 us,
+//    on the queue 69 us; 128 of 2048 x 768 with 4 rows each 201 and 247 us);
+//  - where nearly all have few or the others are bound by matrix work, and the queue is spared more time than this path
+//    takes.  The queue takes no less than a chain of GEMM1 and GEMM2 stages of 1 us each, else 30 us and the weights
+//    at 5.2 TB/s; this path 20 us and 6.4 TB/s (117 experts of 2048 x 768 with few rows beside 8 with 1900 each 346 us,
+//    on the queue 362 us; 63 beside 38 with 800 each 434 and 451 us).
+// It does not pay for 13 experts of 2048 x 1408 beside 3 with more rows (124 and 93 us), 14 beside 2 of 2048 x 768
+// (83 and 65 us), 43 beside 19 of 5120 x 1536 (749 and 687 us), 3 beside 5 of 4096 x 14336 (835 and 746 us).
+struct ThinRule {
+    int max_rows;              // an expert has few rows up to here
+    int many_most;             // up to so many experts with more rows have so many that matrix work bounds them
+    long long chain_ns;
+    int queue_ns, thin_ns;     // an expert's weights
+    __host__ __device__ __forceinline__ long long queue(int experts) const {
+        const long long stream = 30000 + (long long)experts * queue_ns;
+        return stream > chain_ns ? stream : chain_ns;
+    }
+    __host__ __device__ __forceinline__ bool pays(int few, int many) const {
+        if (many == 0) return true;
+        if (few < 8 * many && many > many_most) return false;
+        return queue(few + many) - queue(many) > 20000 + (long long)few * thin_ns;
+    }
+    // Rows up to which an expert of this batch takes this path (0 = none does); counts: experts with few rows and,
+    // shifted left by 16, with more.
+    __device__ __forceinline__ int limit(int counts) const {
+        const int c = rfl(counts);
+        return pays(c & 0xffff, c >> 16) ? max_rows : 0;
+    }
+};
+inline ThinRule thin_rule(const moe_shape_t& s, int max_rows) {
+    const long long bytes = 6ll * s.d * s.I;
+    return ThinRule{max_rows, (int)((long long)s.T * s.k * s.e_count / s.E / 512), 1000ll * ((s.d + s.I) / BK),
+                    (int)(bytes / 5200), (int)(bytes / 6400)};
+}
+// Whether it can pay beside an expert with many rows, whatever the counts.
+inline bool thin_may_pay(const ThinRule& r, const moe_shape_t& s) { return r.queue(s.e_count) - r.chain_ns > 20000; }
+
 struct ThinParams {
     moe_shape_t s;
     const char* x;
@@ -41,7 +82,7 @@ struct ThinParams {
     char* gu;
     char* h;
     char* o;
-    int max_rows;    // experts with 1..max_rows rows are run here
+    ThinRule rule;
 };
 
 typedef const __attribute__((address_space(1))) char* glb_ptr_t;
@@ -236,7 +277,10 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
 #pragma unroll
     for (int j = 0; j < 5; ++j) off[j] = p.offsets[min(4 * tid + j, ec)];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) mine += (off[j + 1] > off[j] && off[j + 1] - off[j] <= p.max_rows) ? 1 : 0;
+    for (int j = 0; j < 4; ++j) {   // few and, shifted left by 16, many rows
+        const int rows = off[j + 1] - off[j];
+        mine += rows <= 0 ? 0 : rows <= p.rule.max_rows ? 1 : 1 << 16;
+    }
     int pre = mine;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -251,10 +295,13 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
         if (w < wave) at += S.wave[w];
         count += S.wave[w];
     }
+    if (p.rule.limit(count) == 0) return;
+    at &= 0xffff;
+    count &= 0xffff;
     if (count == 0) return;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        if (off[j + 1] > off[j] && off[j + 1] - off[j] <= p.max_rows) {
+        if (off[j + 1] > off[j] && off[j + 1] - off[j] <= p.rule.max_rows) {
             S.expert[at] = (uint16_t)(4 * tid + j);
             S.row0[at] = off[j];
             S.rows[at] = off[j + 1] - off[j];
