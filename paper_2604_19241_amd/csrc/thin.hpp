@@ -22,9 +22,12 @@
 
 namespace uniep {
 
-constexpr int kThinRows = 32;       // rows up to which an expert takes this path: one fragment of the matrix instruction
+// Rows up to which an expert takes this path: one fragment of the matrix instruction.  More would be blocks of 32, each
+// with the weights again: 128 experts of 2048 x 768 with 16 / 32 / 40 rows each 207 / 223 / 419 us, on the queue
+// 252 / 259 / 262 us; 16 of 2048 x 1408 59 / 61 / 106 us, on the queue 88 / 88 / 92 us.
+constexpr int kThinRows = 32;
 constexpr int kThinThreads = 256;
-constexpr int kThinGroupsPerCu = 3;
+constexpr int kThinGroupsPerCu = 3;   // as many as the LDS holds (50 KB each); with 2 the same within 0.5 %
 constexpr int kThinCols = 128;      // weight columns of a task
 constexpr int kThinAhead = 4;       // stages in flight (even: stage t is in registers t % 4 and in image t % 2)
 constexpr int kThinWBytes = BK * kThinCols * 2;                       // weights of a stage: image [64 k][256 B]

@@ -142,7 +142,7 @@ def test_backward_without_dtopk_w():
 @pytest.mark.parametrize("tile_rows", [0, 256])
 def test_forward_backward_maximum_experts_and_topk(tile_rows):
     """The shape limits at once: E = 1024 experts, k = 16 slots, most experts empty or with a
-    handful of rows; exercises the 1024-expert scan, sort and list planning of the prologues."""
+    handful of rows; exercises the 1024-expert scan, sort and list planning of the first launches."""
     cfg = moe_synth.small_config(T=130, d=128, E=1024, k=16, I=64)
     check_backward(cfg, seed=21, schedule=1, tile_rows=tile_rows, wscale=4.0)
 

@@ -1,4 +1,4 @@
-"""Forward of experts with few rows (their own kernels) beside experts on the work queue, at the
+"""Forward of experts with few rows (their own kernels, or the work queue beside experts with more), at the
 row counts where fragments and paths change, against the oracle."""
 import numpy as np
 import pytest
