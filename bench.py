@@ -84,17 +84,18 @@ def event_ms(fn, n, before=None):
     return sum(ts) / len(ts), ts[len(ts) // 2], ts[0]
 
 
-def measured_traffic(cfg_name, kernel):
-    """HBM bytes per launch of `kernel` from the committed counter summary
+def measured_traffic(cfg_name, kernels):
+    """HBM bytes that one call's launches of `kernels` move, from the committed counter summary
     (profiles/hbm_traffic_<workload>.txt, written by profile_summary.py
     from a FETCH_SIZE and a WRITE_SIZE run scaled by the calibration copy), or None."""
     path = ROOT / "profiles" / f"hbm_traffic_{cfg_name.replace('-', '_')}.txt"
     if not path.exists():
         return None
+    found = {}
     for line in path.read_text().splitlines():
-        if line.startswith(kernel) and "traffic_bytes_per_launch=" in line:
-            return float(line.split("traffic_bytes_per_launch=")[1].split()[0])
-    return None
+        if "traffic_bytes_per_launch=" in line:
+            found[line.split()[0]] = float(line.split("traffic_bytes_per_launch=")[1].split()[0])
+    return sum(found.get(k, 0.0) for k in kernels) if kernels[-1] in found else None
 
 
 def cpu_model():
@@ -361,17 +362,17 @@ def main():
 
     ceilings = measured_ceilings(moe)
 
-    def roof(kernel, what, flops, ms, ms_call):
+    def roof(kernels, what, flops, ms, ms_call):
         tf = flops / (ms[0] * 1e-3) / 1e12
         return {
-            "kernel": f"{kernel} ({what}; the HIP events also span its prologue launches, "
-                      f"15-22 us, and with schedule 1 or 2 the tail tasks)",
+            "kernel": f"{kernels[-1]} ({what}; the HIP events also span {' and '.join(kernels[:-1])} ahead of it "
+                      f"and, with schedule 1 or 2, the tail tasks)",
             "bound": "mfma",
             "achieved": tf,
             "peak": MFMA_BF16_PEAK_TFLOPS,
             "unit": "TFLOP/s",
             "frac": tf / MFMA_BF16_PEAK_TFLOPS,
-            "traffic": measured_traffic(cfg.name, kernel),
+            "traffic": measured_traffic(cfg.name, kernels),
             "traffic_source": f"profiles/hbm_traffic_{cfg.name.replace('-', '_')}.txt (committed summary of "
                               f"rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command; not measured in this run)",
             "frac_of_measured_mfma": tf / ceilings["mfma_bf16_tflops"],
@@ -380,9 +381,10 @@ def main():
             "tail_kernel_ms": (ms_call[0] - ms[0]) if split else None,
         }
 
-    roof_fwd = roof("fwd_worker_kernel", "forward GEMM MegaKernel, 6*A*d*I flop per launch",
-                    f_fwd, ms_fwd_mega, ms_fwd)
-    roof_bwd = roof("bwd_worker_kernel", "backward GEMM MegaKernel, 12*A*d*I flop per launch",
+    roof_fwd = roof(("fwd_first_kernel", "fwd_second_kernel", "fwd_worker_kernel"),
+                    "forward GEMM MegaKernel, 6*A*d*I flop per launch; experts with few rows, if any, have their "
+                    "share of it run in the two launches ahead", f_fwd, ms_fwd_mega, ms_fwd)
+    roof_bwd = roof(("bwd_first_kernel", "bwd_worker_kernel"), "backward GEMM MegaKernel, 12*A*d*I flop per launch",
                     f_bwd, ms_bwd_mega, ms_bwd) if has_bwd else None
     roofline = roof_bwd if has_bwd else roof_fwd
     counts = state["r"].counts.cpu().tolist()
