@@ -99,6 +99,8 @@ def test_route_empty_batch():
     dict(T=65, d=64, E=1024, k=16, I=64),
     dict(T=129, d=64, E=5, k=5, I=64),
     dict(T=40, d=64, E=7, k=1, I=64),
+    dict(T=33, d=64, E=300, k=2, I=64), dict(T=33, d=64, E=65, k=3, I=64), dict(T=33, d=64, E=64, k=4, I=64),
+    dict(T=5, d=64, E=129, k=9, I=64),
 ])
 def test_route_backward_matches_oracle(kw):
     """dlogits from the gate gradients: parity with the oracle (fp32 arithmetic on the GPU, the
@@ -189,3 +191,27 @@ def test_route_of_few_slots_is_spread_over_the_chip():
         us[k] = min(times)
     say(f"[route] 8192 tokens of 1024 experts: {us}")
     assert us[1] <= 1.3 * us[8], us
+
+
+def test_route_backward_of_few_slots_takes_less_than_of_eight():
+    """One slot a token writes the same array as eight with an eighth of the comparisons."""
+    import paper_2604_19241_amd as moe
+    T, E = 32768, 1024
+    out = torch.empty((T, E), device="cuda")
+    us = {}
+    for k in (1, 8):
+        shape = moe.make_shape(T=T, d=64, E=E, k=k, I=64, e_start=0, e_count=E)
+        routing = moe.moe_route(shape, torch.randn((T, E), generator=torch.Generator(device="cuda").manual_seed(k), device="cuda"))
+        g = torch.ones((T, k), device="cuda")
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        times = []
+        for _ in range(8):
+            start.record()
+            for _ in range(20):
+                moe.moe_route_backward(shape, routing, g, out=out)
+            stop.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(stop) * 50.0)
+        us[k] = min(times)
+    say(f"[route-bwd] 32768 tokens of 1024 experts: {us}")
+    assert us[1] <= 0.92 * us[8], us
