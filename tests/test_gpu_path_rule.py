@@ -97,3 +97,43 @@ def test_few_rows_beside_many_take_no_longer_than_many():
         us[rows] = min(times)
     say(f"[path] {us}")
     assert us[16] <= 1.1 * us[48], us
+
+
+def test_a_captured_call_follows_the_counts_of_each_replay():
+    """The choice is the device's: one graph, replayed on batches that take either path and a mix of both."""
+    T, d, I, E = 3000, 1024, 1024, 128
+    shape = moe.make_shape(T=T, d=d, E=E, k=1, I=I)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randn((T, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    w = [torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16) * 0.05 for s in ((E, d, I), (E, d, I), (E, I, d))]
+    token = torch.arange(T, device="cuda")
+    batches = {"few": token % 128, "many": token % 60, "some": torch.where(token < 1000, token % 120, 120 + token % 8)}
+    logits, y = torch.zeros((T, E), device="cuda"), torch.empty_like(x)
+    routing = moe.alloc_routing(shape, "cuda")
+    ws = torch.empty(moe.moe_workspace_bytes(shape)["fwd"], dtype=torch.uint8, device="cuda")
+
+    def step():
+        moe.moe_route_static(shape, logits, routing)
+        moe.moe_fused_forward(shape, x, *w, routing, y=y, ws=ws)
+
+    def load(name):
+        logits.zero_()
+        logits[token, batches[name]] = 1.0
+
+    want, tiles = {}, {}
+    for name in batches:
+        load(name)
+        step()
+        want[name], tiles[name] = y.clone(), int(ws.view(torch.int32)[ROW_TILES])
+    assert tiles == {"few": 0, "many": 60, "some": 8}, tiles
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for name in ("many", "few", "some", "few", "many", "some"):
+        load(name)
+        y.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        say(f"[path] replay {name}")
+        assert int(ws.view(torch.int32)[ROW_TILES]) == tiles[name]
+        assert torch.equal(y, want[name]), name
