@@ -481,12 +481,12 @@ static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream
     // A token selects an expert at most once, so up to kThinRows tokens no expert has more rows than
     // that: every expert is thin and no work queue is set up.
     const bool all_thin = p.s.T <= kThinRows;
-    // Otherwise the counts decide, which only the device has.  But where the rows are more than kThinRows an expert and
-    // all experts are here, one has more, and few or small ones never spare the queue enough beside it: their launch
+    // Otherwise the counts decide, which only the device has.  But few or small experts never spare the queue enough
+    // beside one with more rows, and there is one where the rows are more than kThinRows an expert and all experts are
+    // here, or hardly ever none in a part of them with four times as many (the queue takes any counts).  Their launch
     // without work took 2 us (256 tokens on 8 experts of 512 x 1024 48.3 us, without it 46.3 us).
-    const bool none_thin = !all_thin && p.s.e_count == p.s.E &&
-                           (long long)p.s.T * p.s.k > (long long)kThinRows * p.s.E &&
-                           !thin_may_pay(thin_rule(p.s, kThinRows), p.s);
+    const long long enough = (long long)kThinRows * p.s.E * (p.s.e_count == p.s.E ? 1 : 4);
+    const bool none_thin = !all_thin && (long long)p.s.T * p.s.k > enough && !thin_may_pay(thin_rule(p.s, kThinRows), p.s);
     p.rule = thin_rule(p.s, all_thin ? INT_MAX : none_thin ? 0 : kThinRows);
     p.plan_blocks = all_thin ? 0 : kPlanBlocks;
     const size_t most = std::min<size_t>(p.s.e_count, (size_t)p.s.T * p.s.k);   // experts with rows

@@ -69,9 +69,11 @@ def test_the_same_bits_on_both_paths(few, many, rows, ahead):
 
 def test_no_launch_for_few_rows_where_the_sizes_rule_it_out():
     first_call()
-    small = forward_launches(moe.make_shape(T=256, d=512, E=8, k=2, I=1024), moe.make_opts())
-    say(f"[path] {small}")
-    assert [n for _, n, _ in small][0] == 32 and len(small) == 3   # plan, queue, combine
+    # more rows than 32 for each of all experts, or than 128 where only some are here
+    for shape in (moe.make_shape(T=256, d=512, E=8, k=2, I=1024), moe.make_shape(T=520, d=512, E=8, k=2, I=1024, e_start=4, e_count=4)):
+        got = forward_launches(shape, moe.make_opts())
+        say(f"[path] {got}")
+        assert got[0][1] == 32 and len(got) == 3   # plan, queue, combine
     # up to 32 rows an expert on average, or experts elsewhere: there may be no expert with more rows
     for shape in (moe.make_shape(T=128, d=512, E=8, k=2, I=1024), moe.make_shape(T=256, d=512, E=8, k=2, I=1024, e_start=0, e_count=4)):
         got = forward_launches(shape, moe.make_opts())
