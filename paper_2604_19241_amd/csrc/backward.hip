@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
     const int lane = threadIdx.x & 63;
     for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {   // one wave, one expert
         const int rows_x = P.rows[x], nt_x = row_tiles(rows_x, bm), parts_x = parts_of(rows_x);
-        const int rt0 = plan_rt0(P, x), r0 = p.offsets[x];
+        const int rt0 = plan_rt0(P, x), r0 = p.offsets[x], higher = higher_tiles(rows_x, bm);
         const int n_dxp = nt_x * p.nct_dxp;
         for (int i = lane; i < nt_x; i += 64) p.flag_rt[rt0 + i] = 0;
         if (lane == 0) p.flag_e[x] = 0;
@@ -142,11 +142,11 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
         // tile), weight-gradient GEMMs over (output row tile, output column tile)
         for_each_tile(lane, nt_x, p.nct_dh, [&](int j, int ct) {
             ta[block_pos<true>(j, ct, nt_x, p.nct_dh)] =
-                Task{rt0 + j, task_code(B_DH, x, ct), r0 + j * bm, min(bm, rows_x - j * bm)};
+                Task{rt0 + j, task_code(B_DH, x, ct), r0 + tile_first(j, higher, bm), tile_rows(j, higher, bm, rows_x)};
         });
         for_each_tile(lane, nt_x, p.nct_dxp, [&](int j, int ct) {
             tb[block_pos<true>(j, ct, nt_x, p.nct_dxp)] =
-                Task{rt0 + j, task_code(B_DXP, x, ct), r0 + j * bm, min(bm, rows_x - j * bm)};
+                Task{rt0 + j, task_code(B_DXP, x, ct), r0 + tile_first(j, higher, bm), tile_rows(j, higher, bm, rows_x)};
         });
         // weight-gradient tasks: idx = output row tile | part << 8 | parts << 20; row0 / rows = the part's rows
         for_each_tile(lane, p.mt_dwgu, p.nt_dwgu, [&](int mt, int nt) {
@@ -182,18 +182,12 @@ __device__ __forceinline__ void dh_task(const BwdParams& p, const RowTile rt, in
     const int n0 = ct * BN;
     const Lane ln;
     FragAddr fa;
-    frag_addresses<false, false>(fa, lds_addr(smem), ln);
-    KcLoader lb, la;
-    lb.n = KcLoader::blocks_for(ln, rt.rows);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = rt.row0 + min(KcGeom::row(ln, i), rt.rows - 1);   // rows past the tile alias its last row
-        lb.p[i] = p.dy + ((size_t)p.row_tok[row] * d + KcGeom::chunk(ln, i) * 8) * 2;
-        const int col = min(n0 + KcGeom::row(ln, i), I - 1);              // columns past I alias the last one
-        la.p[i] = p.w_down + (((size_t)rt.expert * I + col) * d + KcGeom::chunk(ln, i) * 8) * 2;
-    }
-    f32x16_t acc[4][2];
-    mma_tile<false, false>(lb, la, d / BK, rt.rows, smem, fa, acc);
+    frag_addresses<kKc, false>(fa, lds_addr(smem), ln);
+    KcLoader la;
+    la.init(ln, p.w_down + ((size_t)rt.expert * I + n0) * d * 2, I - n0, d * 2);
+    Acc acc;
+    row_tile_gemm<kKc>(ln, la, d / BK, rt.rows, smem, fa, acc,
+                       [&](int m) { return p.dy + (size_t)p.row_tok[rt.row0 + m] * d * 2; });
     after_mainloop();
     // epilogue, one row fragment (32 rows x the wave's 64 columns) at a time: the three outputs
     // pass through three 4 KB pieces of the wave's LDS region and leave as 8-byte write-through
@@ -202,67 +196,87 @@ __device__ __forceinline__ void dh_task(const BwdParams& p, const RowTile rt, in
     const int lane = le.l, wn = le.wn;
     const bool want_dots = p.dtopk_w != nullptr;
     WaveRepack<8> rg(smem, le), ru(smem + 4096, le), rh(smem + 8192, le);
-    const int rows_w = rt.rows - 128 * le.wm;      // rows of the tile inside this wave's 128
-    const int ocol = n0 + 64 * wn + 4 * rg.get8_piece();   // first of this lane's 4 columns on the way out
-#pragma unroll
-    for (int tf = 0; tf < 4; ++tf) {
-        const int m = acc_row(le, tf);
-        const float gt = p.row_w[rt.row0 + min(m, rt.rows - 1)];
+    // the lane's row m of the tile by column fragment af: outputs to piece pi0 of the three regions and further, and
+    // this lane half's part of the dot product
+    auto fragment = [&](const f32x16_t& a, int m, int af, int pi0, int row, float gt) {
         float dot = 0.f;
-        const size_t row = (size_t)(rt.row0 + min(m, rt.rows - 1));
 #pragma unroll
-        for (int af = 0; af < 2; ++af)
+        for (int vg = 0; vg < 2; ++vg) {
+            const int col = min(n0 + acc_col8(le, af, vg), I - 8);   // pieces past I alias a valid one, never stored
+            const size_t base = ((size_t)row * 2 * I + col) * 2;
+            const u32x4_t gv = *(const u32x4_t*)(p.gu + base);
+            const u32x4_t uv = *(const u32x4_t*)(p.gu + base + (size_t)I * 2);
+            // the h that GEMM2 multiplied (bf16), not silu(g) * u of the rounded g, u
+            const u32x4_t hv = *(const u32x4_t*)(p.h + ((size_t)row * I + col) * 2);
+            const bool live = m < rt.rows && n0 + acc_col8(le, af, vg) < I;
+            float dg[8], du[8], hs[8];
 #pragma unroll
-            for (int vg = 0; vg < 2; ++vg) {
-                const int col = min(n0 + acc_col8(le, af, vg), I - 8);   // pieces past I alias a valid one, never stored
-                const size_t base = (row * 2 * I + col) * 2;
-                const u32x4_t gv = *(const u32x4_t*)(p.gu + base);
-                const u32x4_t uv = *(const u32x4_t*)(p.gu + base + (size_t)I * 2);
-                // the h that GEMM2 multiplied (bf16), not silu(g) * u of the rounded g, u
-                const u32x4_t hv = *(const u32x4_t*)(p.h + (row * I + col) * 2);
-                const bool live = m < rt.rows && n0 + acc_col8(le, af, vg) < I;
-                float dg[8], du[8], hs[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float g = (e & 1) ? bf16_hi(gv[e >> 1]) : bf16_lo(gv[e >> 1]);
-                    const float u = (e & 1) ? bf16_hi(uv[e >> 1]) : bf16_lo(uv[e >> 1]);
-                    const float hh = (e & 1) ? bf16_hi(hv[e >> 1]) : bf16_lo(hv[e >> 1]);
-                    const float raw = acc[tf][af][8 * vg + e];
-                    const float dh = gt * raw;
-                    const float sg = sigmoid_f(g);
-                    if (live) dot += raw * hh;
-                    hs[e] = gt * hh;
-                    du[e] = dh * (g * sg);
-                    dg[e] = dh * u * (sg * (1.f + g * (1.f - sg)));
-                }
-                u32x4_t dgp, dup, hwp;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    dgp[q] = pack_bf16x2(dg[2 * q], dg[2 * q + 1]);
-                    dup[q] = pack_bf16x2(du[2 * q], du[2 * q + 1]);
-                    hwp[q] = pack_bf16x2(hs[2 * q], hs[2 * q + 1]);
-                }
-                const int pi = 4 * af + 2 * vg + le.hf;
-                rg.put(le.l31, pi, dgp);
-                ru.put(le.l31, pi, dup);
-                rh.put(le.l31, pi, hwp);
+            for (int e = 0; e < 8; ++e) {
+                const float g = (e & 1) ? bf16_hi(gv[e >> 1]) : bf16_lo(gv[e >> 1]);
+                const float u = (e & 1) ? bf16_hi(uv[e >> 1]) : bf16_lo(uv[e >> 1]);
+                const float hh = (e & 1) ? bf16_hi(hv[e >> 1]) : bf16_lo(hv[e >> 1]);
+                const float raw = a[8 * vg + e];
+                const float dh = gt * raw;
+                const float sg = sigmoid_f(g);
+                if (live) dot += raw * hh;
+                hs[e] = gt * hh;
+                du[e] = dh * (g * sg);
+                dg[e] = dh * u * (sg * (1.f + g * (1.f - sg)));
             }
-        // consumed by dXp / dW tiles on any XCD
+            u32x4_t dgp, dup, hwp;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                dgp[q] = pack_bf16x2(dg[2 * q], dg[2 * q + 1]);
+                dup[q] = pack_bf16x2(du[2 * q], du[2 * q + 1]);
+                hwp[q] = pack_bf16x2(hs[2 * q], hs[2 * q + 1]);
+            }
+            const int pi = pi0 + 2 * vg + le.hf;
+            rg.put(le.l31, pi, dgp);
+            ru.put(le.l31, pi, dup);
+            rh.put(le.l31, pi, hwp);
+        }
+        return dot;
+    };
+    // out of the regions: row `first` of the tile and further, columns from n0 + 64 wn on (consumed by dXp / dW tiles on
+    // any XCD); pieces outside [lo, hi) hold nothing
+    auto store = [&](int first, int lo, int hi) {
+        const int p8 = rg.get8_piece(), ocol = n0 + 64 * wn + 4 * p8;   // this lane's 4 columns
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int r = 32 * tf + rg.get8_row(j);
-            if (r < rows_w && ocol < I) {
-                const size_t orow = (size_t)(rt.row0 + 128 * le.wm + r);
+            const int r = first + rg.get8_row(j);
+            if (r < rt.rows && ocol < I && p8 >= lo && p8 < hi) {
+                const size_t orow = (size_t)(rt.row0 + r);
                 store_wt8(p.dgu + (orow * 2 * I + ocol) * 2, rg.get8(j));
                 store_wt8(p.dgu + (orow * 2 * I + I + ocol) * 2, ru.get8(j));
                 store_wt8(p.hw + (orow * I + ocol) * 2, rh.get8(j));
             }
         }
-        if (want_dots) {
-            // the two lane halves hold the wave's 64 columns of row m between them
+    };
+    if (rt.rows > BMAX) {   // rows 256..287 by column fragment wm
+        const int wm = le.wave_uniform() >> 2, m = BMAX + le.l31;
+        const int row = rt.row0 + min(m, rt.rows - 1);
+        float dot = fragment(acc.more, m, wm, 4 * wm, row, p.row_w[row]);
+        store(BMAX, 8 * wm, 8 * wm + 8);
+        if (want_dots) {   // the wave column's two fragments are in two waves
             dot += __shfl_xor(dot, 32);
-            if (lane < 32 && m < rt.rows)
-                p.dots[(size_t)(rt.row0 + m) * p.n_dots + ct * 4 + wn] = dot;
+            float* other = (float*)(smem + (4 + wn) * 16384 + 12288) + le.l31;   // the second one's region, past its three pieces
+            if (wm == 1) *other = dot;
+            __syncthreads();
+            if (wm == 0 && lane < 32 && m < rt.rows) p.dots[(size_t)row * p.n_dots + ct * 4 + wn] = dot + *other;
+        }
+    }
+#pragma unroll
+    for (int tf = 0; tf < 4; ++tf) {
+        const int m = acc_row(le, tf);
+        const int row = rt.row0 + min(m, rt.rows - 1);
+        const float gt = p.row_w[row];
+        float d0 = fragment(acc.a[tf][0], m, 0, 0, row, gt), d1 = fragment(acc.a[tf][1], m, 1, 4, row, gt);
+        store(128 * le.wm + 32 * tf, 0, 16);
+        if (want_dots) {
+            // the two lane halves hold a fragment's 32 columns of the row between them
+            d0 += __shfl_xor(d0, 32);
+            d1 += __shfl_xor(d1, 32);
+            if (lane < 32 && m < rt.rows) p.dots[(size_t)row * p.n_dots + ct * 4 + wn] = d0 + d1;
         }
     }
 }
@@ -277,24 +291,17 @@ __device__ __forceinline__ void dxp_task(const BwdParams& p, const RowTile rt, i
     const int n0 = ct * BN;
     const Lane ln;
     FragAddr fa;
-    frag_addresses<false, false>(fa, lds_addr(smem), ln);
-    KcLoader lb;
-    KcSplitLoader la;
-    lb.n = KcLoader::blocks_for(ln, rt.rows);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = rt.row0 + min(KcGeom::row(ln, i), rt.rows - 1);
-        lb.p[i] = p.dgu + ((size_t)row * 2 * I + KcGeom::chunk(ln, i) * 8) * 2;
-        const int c = min(n0 + KcGeom::row(ln, i), d - 1);
-        la.p[i] = p.w_gate + (((size_t)rt.expert * d + c) * I + KcGeom::chunk(ln, i) * 8) * 2;
-    }
+    frag_addresses<kKc, false>(fa, lds_addr(smem), ln);
+    KcLoader la;
+    la.init(ln, p.w_gate + ((size_t)rt.expert * d + n0) * I * 2, d - n0, I * 2);
     la.left = I / BK;
     la.delta = (long long)(p.w_up - p.w_gate) - (long long)I * 2;
-    f32x16_t acc[4][2];
-    mma_tile<false, false>(lb, la, 2 * I / BK, rt.rows, smem, fa, acc);
+    Acc acc;
+    row_tile_gemm<kKc>(ln, la, 2 * I / BK, rt.rows, smem, fa, acc,
+                       [&](int m) { return p.dgu + (size_t)(rt.row0 + m) * 2 * I * 2; });
     after_mainloop();
     char* obase = p.dxp + ((size_t)rt.row0 * d + n0) * 2;
-    store_subtile_bf16(acc, smem, rt.rows, d - n0, [&](int row, int col, u32x4_t v) {
+    store_subtile_bf16<true>(acc, smem, rt.rows, d - n0, [&](int row, int col, u32x4_t v) {
         store_stream16(obase + ((size_t)row * d + col) * 2, v);
     });
 }
@@ -319,7 +326,7 @@ __device__ __forceinline__ void accumulate8(float* q, const f32x16_t& a, int vg)
 // depend on which workgroup adds, nor on the order in which the parts were computed.
 // Returns whether acc now holds the complete sum (the caller then stores the tile).
 __device__ __forceinline__ bool finish_part(const BwdParams& p, int e, int tile, int part, int parts,
-                                            f32x16_t (&acc)[4][2], int* s_flag) {
+                                            Acc& acc, int* s_flag) {
     if (parts <= 1) return true;
     const Lane ln;
     // 8-byte write-through stores: the two halves of a register quad go to separate 512-byte runs,
@@ -333,8 +340,8 @@ __device__ __forceinline__ bool finish_part(const BwdParams& p, int e, int tile,
         for (int af = 0; af < 2; ++af)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const f32x2_t lo = {acc[tf][af][4 * q], acc[tf][af][4 * q + 1]};
-                const f32x2_t hi = {acc[tf][af][4 * q + 2], acc[tf][af][4 * q + 3]};
+                const f32x2_t lo = {acc.a[tf][af][4 * q], acc.a[tf][af][4 * q + 1]};
+                const f32x2_t hi = {acc.a[tf][af][4 * q + 2], acc.a[tf][af][4 * q + 3]};
                 char* dst = mine + ((tf * 2 + af) * 4 + q) * 1024;
                 store_wt8(dst, __builtin_bit_cast(u32x2_t, lo));
                 store_wt8(dst + 512, __builtin_bit_cast(u32x2_t, hi));
@@ -354,7 +361,7 @@ __device__ __forceinline__ bool finish_part(const BwdParams& p, int e, int tile,
 #pragma unroll
         for (int af = 0; af < 2; ++af)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[tf][af][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc.a[tf][af][v] = 0.f;
     for (int j = 0; j < parts; ++j) {
         const char* src = slots + (size_t)j * kPartialTileBytes + lane_off;
 #pragma unroll
@@ -365,10 +372,10 @@ __device__ __forceinline__ bool finish_part(const BwdParams& p, int e, int tile,
                 for (int q = 0; q < 4; ++q) {
                     const char* blk = src + ((tf * 2 + af) * 4 + q) * 1024;
                     const f32x2_t lo = *(const f32x2_t*)blk, hi = *(const f32x2_t*)(blk + 512);
-                    acc[tf][af][4 * q] += lo[0];
-                    acc[tf][af][4 * q + 1] += lo[1];
-                    acc[tf][af][4 * q + 2] += hi[0];
-                    acc[tf][af][4 * q + 3] += hi[1];
+                    acc.a[tf][af][4 * q] += lo[0];
+                    acc.a[tf][af][4 * q + 1] += lo[1];
+                    acc.a[tf][af][4 * q + 2] += hi[0];
+                    acc.a[tf][af][4 * q + 3] += hi[1];
                 }
     }
     return true;
@@ -385,7 +392,7 @@ __device__ __forceinline__ void dwd_task(const BwdParams& p, int e, int idx, int
     const int m0 = mt * BMAX, n0 = nt * BN;
     const Lane ln;
     FragAddr fa;
-    frag_addresses<true, true>(fa, lds_addr(smem), ln);
+    frag_addresses<kKs, true>(fa, lds_addr(smem), ln);
     KsTailLoader lb;
     KsGatherLoader la;
 #pragma unroll
@@ -397,8 +404,8 @@ __device__ __forceinline__ void dwd_task(const BwdParams& p, int e, int idx, int
     lb.ld_bytes = (long long)I * 2;
     lb.K = cnt;
     la.init(ln, p.dy, (long long)d * 2, p.row_tok + r0, cnt);
-    f32x16_t acc[4][2];
-    mma_tile<true, true>(lb, la, (cnt + BK - 1) / BK, min(BMAX, I - m0), smem, fa, acc);
+    Acc acc;
+    weight_tile_gemm(lb, la, (cnt + BK - 1) / BK, min(BMAX, I - m0), smem, fa, acc);
     after_mainloop();
     if (SPLIT && !finish_part(p, e, p.mt_dwgu * p.nt_dwgu + mt * p.nt_dwd + nt, wgrad_part(idx), wgrad_parts(idx), acc, s_flag)) return;
     if (ACC) {
@@ -412,13 +419,13 @@ __device__ __forceinline__ void dwd_task(const BwdParams& p, int e, int idx, int
 #pragma unroll
                     for (int vg = 0; vg < 2; ++vg) {
                         const int col = n0 + acc_col8(le, af, vg);
-                        if (col < d) accumulate8((float*)p.dw_down + ((size_t)e * I + m) * d + col, acc[tf][af], vg);
+                        if (col < d) accumulate8((float*)p.dw_down + ((size_t)e * I + m) * d + col, acc.a[tf][af], vg);
                     }
             }
         }
     } else {
         char* obase = p.dw_down + (((size_t)e * I + m0) * d + n0) * 2;
-        store_subtile_bf16(acc, smem, I - m0, d - n0, [&](int row, int col, u32x4_t v) {
+        store_subtile_bf16<false>(acc, smem, I - m0, d - n0, [&](int row, int col, u32x4_t v) {
             store_stream16(obase + ((size_t)row * d + col) * 2, v);
         });
     }
@@ -436,7 +443,7 @@ __device__ __forceinline__ void dwgu_task(const BwdParams& p, int e, int idx, in
     const int m0 = mt * BMAX, n0i = nt * (BN / 2);
     const Lane ln;
     FragAddr fa;
-    frag_addresses<true, true>(fa, lds_addr(smem), ln);
+    frag_addresses<kKs, true>(fa, lds_addr(smem), ln);
     KsGatherLoader lb;
     KsTailLoader la;
 #pragma unroll
@@ -450,8 +457,8 @@ __device__ __forceinline__ void dwgu_task(const BwdParams& p, int e, int idx, in
     la.ld_bytes = (long long)2 * I * 2;
     la.K = cnt;
     lb.init(ln, p.x, (long long)d * 2, p.row_tok + r0, cnt);
-    f32x16_t acc[4][2];
-    mma_tile<true, true>(lb, la, (cnt + BK - 1) / BK, min(BMAX, d - m0), smem, fa, acc);
+    Acc acc;
+    weight_tile_gemm(lb, la, (cnt + BK - 1) / BK, min(BMAX, d - m0), smem, fa, acc);
     after_mainloop();
     if (SPLIT && !finish_part(p, e, mt * p.nt_dwgu + nt, wgrad_part(idx), wgrad_parts(idx), acc, s_flag)) return;
     if (ACC) {
@@ -466,14 +473,14 @@ __device__ __forceinline__ void dwgu_task(const BwdParams& p, int e, int idx, in
                     for (int vg = 0; vg < 2; ++vg) {
                         const int icol = n0i + 32 * le.wn + 16 * vg + 8 * le.hf;
                         if (icol < I)
-                            accumulate8((float*)(af ? p.dw_up : p.dw_gate) + ((size_t)e * d + m) * I + icol, acc[tf][af], vg);
+                            accumulate8((float*)(af ? p.dw_up : p.dw_gate) + ((size_t)e * d + m) * I + icol, acc.a[tf][af], vg);
                     }
             }
         }
     } else {
         // the wave's 64 columns are 32 columns of dW_gate and the same 32 of dW_up: pieces 0..3 | 4..7
         const size_t ebase = ((size_t)e * d + m0) * I;
-        store_subtile_bf16(acc, smem, d - m0, BN, [&](int row, int col, u32x4_t v) {
+        store_subtile_bf16<false>(acc, smem, d - m0, BN, [&](int row, int col, u32x4_t v) {
             const int pc = (col >> 3) & 7;
             const int icol = n0i + 32 * (col >> 6) + 8 * (pc & 3);
             if (icol < I) store_stream16(((pc & 4) ? p.dw_up : p.dw_gate) + (ebase + (size_t)row * I + icol) * 2, v);
@@ -558,8 +565,9 @@ __device__ __forceinline__ void dtopk_task(const BwdParams& p, int t) {
 
 template <int NW, int KM = kMaxTopK>
 __device__ __forceinline__ void dx_task(const BwdParams& p, int block) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int tt = wave; tt < kDxTokens; tt += NW) {
+    const Lane ln;
+    const int lane = ln.l;
+    for (int tt = ln.w; tt < kDxTokens; tt += NW) {
         const int t = block * kDxTokens + tt;
         if (t >= p.s.T) break;
         int rows[KM];
@@ -637,7 +645,7 @@ __device__ __forceinline__ void bwd_worker_body(const BwdParams& p, int phase, c
                 const int e = task_expert(task);
                 // rows of the whole expert (a part of a split reduction carries only its own share)
                 const int rows_e = SPLIT ? p.offsets[e + 1] - p.offsets[e] : task.rows;
-                const int need = (rows_e + p.bm - 1) / p.bm * p.nct_dh;
+                const int need = row_tiles(rows_e, p.bm) * p.nct_dh;
                 // a worker takes several of an expert's 72 output tiles in a row: the expert it has
                 // already seen complete (and acquired) needs no second look at the flag
                 if (e != seen_e) {

@@ -101,7 +101,7 @@ constexpr int kPersistentPass = kPasses - 1;
 // Control words at the head of a forward/backward workspace.
 enum CtrlWord {
     CTRL_STATUS = 0,   // 0 ok, else MOE_ERR_DEVICE
-    CTRL_NRT = 1,      // number of row tiles
+    CTRL_NRT = 1,      // scoreboard slots of the row tiles
     CTRL_NTAIL = 2,    // number of tail tasks
     CTRL_NWAIT = 3,    // completions the tail tasks wait for
     CTRL_DONE = 4,     // completion counter of the last GEMM phase
@@ -246,8 +246,8 @@ struct QueuePlan {
     int32_t a[kQueues][kListSlots + 1];   // producer tasks in front of slot i of a list, without the other blocks
     int32_t b[kQueues][kListSlots + 1];   // consumer tasks likewise
     int32_t rows[kMaxExperts];
-    int32_t rt0[kMaxExperts];             // first row tile of the expert
-    int32_t sums[kPlanWaves];             // row tiles of each wave's experts
+    int32_t rt0[kMaxExperts];             // first scoreboard slot of the expert
+    int32_t sums[kPlanWaves];             // slots of each wave's experts
     int32_t most[kPlanWaves];
     int32_t counts[kPlanWaves];           // experts with few and with many rows
     int32_t hist[kPlanWaves][64];
@@ -266,11 +266,28 @@ __device__ __forceinline__ int queue_lag(int total_producer_tasks, int ec) {
 }
 
 
-// Row tiles of an expert; tiles have 256 or 128 rows.
-__device__ __forceinline__ int row_tiles(int rows, int bm) { return (rows + bm - 1) >> (bm == 256 ? 8 : 7); }
+// Scoreboard slots of an expert's row tiles: one for every bm = 256 or 128 rows.
+__device__ __forceinline__ int row_slots(int rows, int bm) { return (rows + bm - 1) >> (bm == 256 ? 8 : 7); }
+// Row tiles of an expert.  A tile costs its stream of weights whatever its rows (one of some 20 rows 0.43 of a full one), and
+// batches are powers of two more often than not, so that many experts have just over a multiple of 256 rows: up to
+// three of the others take 32 rows each of a last tile that has no more.  A higher tile costs 0.11 of a tile beyond its
+// share of the work: with eight of them in place of one (4096 rows) the layer took 3 % longer, with three (1875 rows) 1 %
+// less, with one (512 rows and some) the forward pass 6 % less and (256 and some) 17 %.  Past 16 tiles there is nothing
+// to gain.
+constexpr int kMostHigher = 3, kMostTiles = 16;
+__device__ __forceinline__ int higher_tiles(int rows, int bm) {
+    const int n = row_slots(rows, bm), m = (rows - (n - 1) * bm + 31) >> 5;
+    return bm == 256 && n <= kMostTiles && m <= min(kMostHigher, n - 1) ? m : 0;
+}
+__device__ __forceinline__ int row_tiles(int rows, int bm) { return row_slots(rows, bm) - (higher_tiles(rows, bm) > 0 ? 1 : 0); }
+// First row of an expert's tile j, the first `higher` tiles being higher, and the rows of it.
+__device__ __forceinline__ int tile_first(int j, int higher, int bm) { return j * bm + 32 * min(j, higher); }
+__device__ __forceinline__ int tile_rows(int j, int higher, int bm, int rows) {
+    return min(bm + (j < higher ? 32 : 0), rows - tile_first(j, higher, bm));
+}
 // The plan of this workgroup (kPlanThreads threads, all of them call; ends with a barrier).
 // a_of(rows) / b_of(rows): tasks of an expert's producer and consumer block; `per_row_tile` producer tasks for
-// each row tile of bm rows.  limit > 0: experts with up to skip_of(counts) rows have no tasks, where counts is the
+// each bm rows.  limit > 0: experts with up to skip_of(counts) rows have no tasks, where counts is the
 // number of experts with 1..limit rows and, shifted left by 16, of those with more.
 template <class FS, class FA, class FB>
 __device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, int ec, int limit, FS skip_of, int bm,
@@ -300,7 +317,7 @@ __device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, 
     P.hist[w][lane] = 0;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int e = 256 * w + 64 * r + lane, nt = row_tiles(rows[r], bm);
+        const int e = 256 * w + 64 * r + lane, nt = row_slots(rows[r], bm);
         int incl = nt;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -417,7 +434,7 @@ __device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, 
     }
     __syncthreads();
 }
-// First entries of expert e's two blocks in the task array, and its first row tile.
+// First entries of expert e's two blocks in the task array, and its first scoreboard slot.
 __device__ __forceinline__ int plan_a(const QueuePlan& P, int e) {
     const int q = P.slot[e] / kListSlots, i = P.slot[e] % kListSlots;
     return P.base[q] + P.a[q][i] + P.b[q][max(0, i - P.lag)];
@@ -504,7 +521,7 @@ __device__ __forceinline__ void worker_arrived(int* ctrl, int xcd, int workers, 
 struct RowTile {   // one row tile of one local expert
     int32_t expert;  // local expert id
     int32_t row0;    // first row (position in the expert-sorted order)
-    int32_t rows;    // valid rows in this tile (1..BM)
+    int32_t rows;    // valid rows in this tile (1..288)
 };
 
 // One GEMM task, self-contained so that a worker needs a single 16-byte load

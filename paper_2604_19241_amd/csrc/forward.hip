@@ -59,17 +59,17 @@ __device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePl
     for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {
         const int rows_x = P.rows[x], nt_x = row_tiles(rows_x, bm);
         if (nt_x == 0) continue;
-        const int rt0 = plan_rt0(P, x), r0 = p.offsets[x];
+        const int rt0 = plan_rt0(P, x), r0 = p.offsets[x], higher = higher_tiles(rows_x, bm);
         for (int i = lane; i < nt_x; i += 64) p.flag1[rt0 + i] = 0;
         Task* t1 = p.tasks + plan_a(P, x);
         Task* t2 = p.tasks + plan_b(P, x);
         for_each_tile(lane, nt_x, p.nct1, [&](int j, int ct) {
             t1[block_pos<true>(j, ct, nt_x, p.nct1)] =
-                Task{rt0 + j, task_code(TASK_GEMM1, x, ct), r0 + j * bm, min(bm, rows_x - j * bm)};
+                Task{rt0 + j, task_code(TASK_GEMM1, x, ct), r0 + tile_first(j, higher, bm), tile_rows(j, higher, bm, rows_x)};
         });
         for_each_tile(lane, nt_x, p.nct2, [&](int j, int ct) {
             t2[block_pos<true>(j, ct, nt_x, p.nct2)] =
-                Task{rt0 + j, task_code(TASK_GEMM2, x, ct), r0 + j * bm, min(bm, rows_x - j * bm)};
+                Task{rt0 + j, task_code(TASK_GEMM2, x, ct), r0 + tile_first(j, higher, bm), tile_rows(j, higher, bm, rows_x)};
         });
     }
     if (block == 0) write_ctrl(P, p.ctrl, (p.s.T + kCombineTokens - 1) / kCombineTokens, p.workers);
@@ -100,9 +100,8 @@ fwd_second_kernel(FwdParams p) {
 // ------------------------------------------------------------- GEMM1 task
 // h[row0.., ct*128 .. +128) = silu(x_e W_gate) * (x_e W_up) for one row tile.
 // Tile rows = the tile's tokens (their rows of x fetched through the permutation: the dispatch);
-// tile columns = 128 gate columns and the same 128 up columns, arranged so that column fragment
-// 0 of a wave holds gate columns and fragment 1 the same up columns: G and U of one h element
-// sit in the same lane and accumulator element.
+// tile columns = 128 gate columns and the same 128 up columns, a column fragment being 16 gate columns and the same
+// 16 up columns: G and U of one h element sit in the same lane and accumulator, elements v and 8 + v.
 template <class Hook>
 __device__ __forceinline__ void gemm1_task(const FwdParams& p, const RowTile rt, int ct,
                                            char* smem, Hook after_mainloop) {
@@ -110,23 +109,13 @@ __device__ __forceinline__ void gemm1_task(const FwdParams& p, const RowTile rt,
     const int n0h = ct * (BN / 2);
     const Lane ln;
     FragAddr fa;
-    frag_addresses<true, false>(fa, lds_addr(smem), ln);
-    KcLoader lb;
-    KsLoader la;
-    lb.n = KcLoader::blocks_for(ln, rt.rows);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = min(KcGeom::row(ln, i), rt.rows - 1);   // rows past the tile alias its last row
-        const int tok = p.perm[rt.row0 + m] / k;
-        lb.p[i] = p.x + ((size_t)tok * d + KcGeom::chunk(ln, i) * 8) * 2;
-        const int c = KsGeom::chunk(ln, i);                    // tile column chunk: (wave column, gate|up, 8-column piece)
-        const int hc = min(n0h + 32 * (c >> 3) + 8 * (c & 3), I - 8);   // chunks past I alias the last chunk
-        const char* w = ((c >> 2) & 1) ? p.w_up : p.w_gate;
-        la.p[i] = w + (((size_t)rt.expert * d + KsGeom::krow(ln, i)) * I + hc) * 2;
-    }
-    la.step = (long long)BK * I * 2;
-    f32x16_t acc[4][2];
-    mma_tile<true, false>(lb, la, d / BK, rt.rows, smem, fa, acc);
+    frag_addresses<kKsPair, false>(fa, lds_addr(smem), ln);
+    KsPairLoader la;
+    const size_t first = (size_t)rt.expert * d * I * 2;
+    la.init(ln, p.w_gate + first, p.w_up + first, n0h, I, I * 2);
+    Acc acc;
+    row_tile_gemm<kKsPair>(ln, la, d / BK, rt.rows, smem, fa, acc,
+                           [&](int m) { return p.x + (size_t)(p.perm[rt.row0 + m] / k) * d * 2; });
     after_mainloop();
 
     // epilogue.  The wave's sub-tile is 128 rows x (32 gate columns | the same 32 up columns).
@@ -138,6 +127,17 @@ __device__ __forceinline__ void gemm1_task(const FwdParams& p, const RowTile rt,
     const int wm = le.wm, wn = le.wn;
     const int hc0 = n0h + 32 * wn;        // first h column of this wave
     const int rows_w = rt.rows - 128 * wm; // rows of the tile inside this wave's 128
+    const int rows_m = rt.rows - BMAX;     // rows past 256: 16 of the wave's h columns, from 16 wm on
+    auto h8 = [](const f32x16_t& a) {
+        float hv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float g = a[e], u = a[8 + e];
+            hv[e] = g * sigmoid_f(g) * u;
+        }
+        return u32x4_t{pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3]), pack_bf16x2(hv[4], hv[5]),
+                       pack_bf16x2(hv[6], hv[7])};
+    };
     if (p.gu) {
         WaveRepack<8> rp(smem, le);
 #pragma unroll
@@ -145,7 +145,7 @@ __device__ __forceinline__ void gemm1_task(const FwdParams& p, const RowTile rt,
 #pragma unroll
             for (int af = 0; af < 2; ++af)
 #pragma unroll
-                for (int vg = 0; vg < 2; ++vg) rp.put(32 * tf + l31, 4 * af + 2 * vg + hf, pack8(acc[tf][af], vg));
+                for (int vg = 0; vg < 2; ++vg) rp.put(32 * tf + l31, 4 * vg + 2 * af + hf, pack8(acc.a[tf][af], vg));
         const int pc = rp.get_piece();                       // 0..3: G pieces, 4..7: U pieces
         const int col = hc0 + 8 * (pc & 3);
         char* gbase = p.gu + ((size_t)(rt.row0 + 128 * wm) * 2 * I + ((pc & 4) ? I : 0) + col) * 2;
@@ -155,23 +155,26 @@ __device__ __forceinline__ void gemm1_task(const FwdParams& p, const RowTile rt,
             const u32x4_t v = rp.get(j);
             if (row < rows_w && col < I) store_stream16(gbase + (size_t)row * 2 * I * 2, v);
         }
+        if (rows_m > 0) {
+            WaveRepack<4> rm(smem, le);
+#pragma unroll
+            for (int vg = 0; vg < 2; ++vg) rm.put(l31, 2 * vg + hf, pack8(acc.more, vg));
+            const int pm = rm.get_piece(), mcol = hc0 + 16 * wm + 8 * (pm & 1);   // 0, 1: G pieces, 2, 3: U pieces
+            char* mbase = p.gu + ((size_t)(rt.row0 + BMAX) * 2 * I + ((pm & 2) ? I : 0) + mcol) * 2;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int row = rm.get_row(j);
+                const u32x4_t v = rm.get(j);
+                if (row < rows_m && mcol < I) store_stream16(mbase + (size_t)row * 2 * I * 2, v);
+            }
+        }
     }
     {
         WaveRepack<4> rp(smem, le);
 #pragma unroll
         for (int tf = 0; tf < 4; ++tf)
 #pragma unroll
-            for (int vg = 0; vg < 2; ++vg) {
-                float hv[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float g = acc[tf][0][8 * vg + e], u = acc[tf][1][8 * vg + e];
-                    hv[e] = g * sigmoid_f(g) * u;
-                }
-                rp.put(32 * tf + l31, 2 * vg + hf,
-                       u32x4_t{pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3]), pack_bf16x2(hv[4], hv[5]),
-                               pack_bf16x2(hv[6], hv[7])});
-            }
+            for (int af = 0; af < 2; ++af) rp.put(32 * tf + l31, 2 * af + hf, h8(acc.a[tf][af]));
         const int col = hc0 + 4 * rp.get8_piece();   // 8-byte pieces: 4 columns each
         char* hbase = p.h + ((size_t)(rt.row0 + 128 * wm) * I + col) * 2;
 #pragma unroll
@@ -179,6 +182,10 @@ __device__ __forceinline__ void gemm1_task(const FwdParams& p, const RowTile rt,
             const int row = rp.get8_row(j);
             const u32x2_t v = rp.get8(j);
             if (row < rows_w && col < I) store_wt8(hbase + (size_t)row * I * 2, v);
+        }
+        if (rows_m > 0) {   // the lane's 8 columns of row 256 + l31 as they are: a few rows
+            const int mcol = hc0 + 16 * wm + 8 * hf;
+            if (l31 < rows_m && mcol < I) store_wt16(p.h + ((size_t)(rt.row0 + BMAX + l31) * I + mcol) * 2, h8(acc.more));
         }
     }
 }
@@ -192,23 +199,15 @@ __device__ __forceinline__ void gemm2_task(const FwdParams& p, const RowTile rt,
     const int n0 = ct * BN;
     const Lane ln;
     FragAddr fa;
-    frag_addresses<true, false>(fa, lds_addr(smem), ln);
-    KcLoader lb;
+    frag_addresses<kKs, false>(fa, lds_addr(smem), ln);
     KsLoader la;
-    lb.n = KcLoader::blocks_for(ln, rt.rows);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = min(KcGeom::row(ln, i), rt.rows - 1);
-        lb.p[i] = p.h + ((size_t)(rt.row0 + m) * I + KcGeom::chunk(ln, i) * 8) * 2;
-        const int c = min(n0 + KsGeom::chunk(ln, i) * 8, d - 8);
-        la.p[i] = p.w_down + (((size_t)rt.expert * I + KsGeom::krow(ln, i)) * d + c) * 2;
-    }
-    la.step = (long long)BK * d * 2;
-    f32x16_t acc[4][2];
-    mma_tile<true, false>(lb, la, I / BK, rt.rows, smem, fa, acc);
+    la.init(ln, p.w_down + (size_t)rt.expert * I * d * 2, n0, d, d * 2);
+    Acc acc;
+    row_tile_gemm<kKs>(ln, la, I / BK, rt.rows, smem, fa, acc,
+                       [&](int m) { return p.h + (size_t)(rt.row0 + m) * I * 2; });
     after_mainloop();
     char* obase = p.o + ((size_t)rt.row0 * d + n0) * 2;
-    store_subtile_bf16(acc, smem, rt.rows, d - n0, [&](int row, int col, u32x4_t v) {
+    store_subtile_bf16<true>(acc, smem, rt.rows, d - n0, [&](int row, int col, u32x4_t v) {
         store_stream16(obase + ((size_t)row * d + col) * 2, v);
     });
 }

@@ -6,11 +6,13 @@
 // 16 values per lane and accumulator, arranged so that a lane ends with runs of 8 consecutive
 // columns and stores 16 bytes).  Wave w = 4 wm + wn owns rows [128 wm, +128) as 4 fragments
 // of 32 and columns [64 wn, +64) as 2 fragments of 32: 8 accumulators of
-// v_mfma_f32_32x32x16_bf16, 6 fragment reads per 8 matrix instructions.
+// v_mfma_f32_32x32x16_bf16, 6 fragment reads per 8 matrix instructions.  A tile of a row-tile GEMM may have
+// 32 rows more (see higher_tiles): the two waves of a wave column then each multiply them by one of its two
+// column fragments, a ninth accumulator.
 //
-// K advances in stages of 64.  A stage of an operand is a 32 KB LDS image in one of two forms:
+// K advances in stages of 64.  A stage of an operand is a 32 KB LDS image in one of two forms (36 KB for 288 rows):
 //   KC  the operand's k runs along its memory rows (activations [rows, k]; weights read
-//       "transposed"): image [256 rows][128 B], the 16-byte chunk c of row r at chunk position
+//       "transposed"): image [288 rows][128 B], the 16-byte chunk c of row r at chunk position
 //       c ^ ((r >> 1) & 7), fragments by ds_read_b128;
 //   KS  the operand's k is its memory row index (weights [k, n]; both operands of the
 //       weight-gradient GEMMs): image [64 k][512 B], the 16-byte chunk c of k row k at chunk
@@ -22,7 +24,7 @@
 // lane p's 16 bytes to (LDS base) + 16 p, so nothing is staged in registers and no LDS
 // write instruction or register transpose exists.
 //
-// Two stage buffers (128 KB of LDS).  Stage t+2 is requested right behind the barrier that
+// Two stage buffers (136 KB of LDS).  Stage t+2 is requested right behind the barrier that
 // ends the fragment reads of stage t, so it has a whole stage of matrix work to land; one
 // workgroup barrier per stage.  The fragment reads are inline assembly: the compiler would put
 // a full vmcnt(0) in front of every LDS read it knows about while a DMA load is in flight.
@@ -36,9 +38,12 @@ namespace uniep {
 
 constexpr int BK = 64;
 constexpr int BN = 256;                 // tile columns (A role)
-constexpr int BMAX = 256;               // tile rows (B role)
-constexpr int kOperandBytes = 32768;    // one operand, one stage
-constexpr int kStageBytes = 2 * kOperandBytes;   // rows (B role) first, columns (A role) second
+constexpr int BMAX = 256;               // tile rows (B role) of the waves' own fragments
+constexpr int kMoreRows = 32;           // and those that a wave column shares
+enum OperandForm { kKc = 0, kKs = 1, kKsPair = 2 };   // of an LDS image; the last see KsPairLoader
+constexpr int kOperandBytes = 32768;    // 256 rows or columns, one stage
+constexpr int kRowBytes = kOperandBytes + kMoreRows * 128;
+constexpr int kStageBytes = kRowBytes + kOperandBytes;   // rows (B role) first, columns (A role) second
 constexpr int kMmaSmem = 2 * kStageBytes;
 constexpr int kMmaThreads = 512;
 
@@ -87,9 +92,12 @@ __device__ __forceinline__ int acc_col8(const Lane& ln, int af, int vg) {
 struct FragAddr {
     uint32_t b[4];   // B role: KC -> per k-sub-step (+ tf * 4096); KS -> b[0] + ((tf << 6) ^ b[1]) per row fragment (+ kk * 8192 + hr * 2048)
     uint32_t a[4];   // A role: KC -> per k-sub-step (+ af * 4096); KS -> a[0..1] per column fragment (+ kk * 8192 + hr * 2048)
+    uint32_t more;   // B role, KC: from this wave's first row to row 256
 };
 
-template <bool A_KS, bool B_KS>
+// kKsPair: a column fragment is 16 columns of one matrix and the same 16 of another (GEMM1: gate, up), so that it yields
+// h by itself (the images of KsPairLoader).
+template <int A_FORM, bool B_KS>
 __device__ __forceinline__ void frag_addresses(FragAddr& fa, uint32_t lds0, const Lane& ln) {
     const int l = ln.l;
     const int wm = ln.wm, wn = ln.wn;
@@ -107,13 +115,19 @@ __device__ __forceinline__ void frag_addresses(FragAddr& fa, uint32_t lds0, cons
         for (int kk = 0; kk < 4; ++kk)
             fa.b[kk] = lds0 + (128 * wm + l31) * 128 + (((2 * kk + kh) ^ x0) << 4);
     }
-    const uint32_t a0 = lds0 + kOperandBytes;
-    if (A_KS) {
+    const uint32_t a0 = lds0 + kRowBytes;
+    fa.more = (BMAX - 128 * wm) * 128;
+    if (A_FORM != kKc) {
         const int sq = ((q & 1) << 1) | (q >> 1);   // piece -> position of its 4 columns inside the 16
 #pragma unroll
         for (int af = 0; af < 2; ++af) {
-            const int c = 8 * wn + 4 * af + 2 * g + (sq >> 1);
-            fa.a[af] = a0 + (8 * kh + e) * 512 + ((c ^ (e << 2)) << 4) + (sq & 1) * 8;
+            if (A_FORM == kKsPair) {
+                const int c = (4 * wn + 2 * af + (sq >> 1)) ^ (e << 2) ^ (2 * g);
+                fa.a[af] = a0 + g * (kOperandBytes / 2) + (8 * kh + e) * 256 + (c << 4) + (sq & 1) * 8;
+            } else {
+                const int c = 8 * wn + 4 * af + 2 * g + (sq >> 1);
+                fa.a[af] = a0 + (8 * kh + e) * 512 + ((c ^ (e << 2)) << 4) + (sq & 1) * 8;
+            }
         }
         fa.a[2] = fa.a[3] = 0;
     } else {
@@ -129,22 +143,31 @@ __device__ __forceinline__ void frag_addresses(FragAddr& fa, uint32_t lds0, cons
 struct Frags {
     u32x4_t b[4];   // B role, one per row fragment
     u32x4_t a[2];   // A role, one per column fragment
+    u32x4_t more;   // B role, rows 256..287
 };
 
 // The two halves of a transposing read land in the low and high register pair of one
 // 128-bit fragment: the pair is addressed through a 64-bit view of the same registers.
-#define UNIEP_TR2(dst, addr, off)                                                                  \
-    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:" #off "\n ds_read_b64_tr_b16 %1, %2 offset:" #off "+2048" \
+#define UNIEP_TR2(dst, addr, off, next)                                                            \
+    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:" #off "\n ds_read_b64_tr_b16 %1, %2 offset:" #off "+" #next \
                  : "=&v"(lo_), "=&v"(hi_) : "v"(addr) : "memory");                                   \
     dst = u32x4_t{lo_[0], lo_[1], hi_[0], hi_[1]}
 
-template <int KK>
+// FORM: kKs = k rows of 512 bytes, kKsPair = of 256 bytes
+template <int FORM, int KK>
 __device__ __forceinline__ void read_ks(u32x4_t& dst, uint32_t addr) {
     u32x2_t lo_, hi_;
-    if (KK == 0) { UNIEP_TR2(dst, addr, 0); }
-    else if (KK == 1) { UNIEP_TR2(dst, addr, 8192); }
-    else if (KK == 2) { UNIEP_TR2(dst, addr, 16384); }
-    else { UNIEP_TR2(dst, addr, 24576); }
+    if (FORM == kKs) {
+        if (KK == 0) { UNIEP_TR2(dst, addr, 0, 2048); }
+        else if (KK == 1) { UNIEP_TR2(dst, addr, 8192, 2048); }
+        else if (KK == 2) { UNIEP_TR2(dst, addr, 16384, 2048); }
+        else { UNIEP_TR2(dst, addr, 24576, 2048); }
+    } else {
+        if (KK == 0) { UNIEP_TR2(dst, addr, 0, 1024); }
+        else if (KK == 1) { UNIEP_TR2(dst, addr, 4096, 1024); }
+        else if (KK == 2) { UNIEP_TR2(dst, addr, 8192, 1024); }
+        else { UNIEP_TR2(dst, addr, 12288, 1024); }
+    }
 }
 #undef UNIEP_TR2
 
@@ -156,75 +179,72 @@ __device__ __forceinline__ void read_kc(u32x4_t& dst, uint32_t addr) {
     else asm volatile("ds_read_b128 %0, %1 offset:12288" : "=&v"(dst) : "v"(addr) : "memory");
 }
 
-// LDS read instructions of one call of read_frags
-template <int NTF, bool A_KS, bool B_KS>
-constexpr int reads_per_step() { return (B_KS ? 2 : 1) * NTF + (A_KS ? 2 : 1) * 2; }
-
-// Fragments of k-sub-step KK of the stage at byte offset `boff`.
-template <int NTF, bool A_KS, bool B_KS, int KK>
-__device__ __forceinline__ void read_frags(Frags& f, const FragAddr& fa, uint32_t boff) {
-    if (A_KS) {
-        read_ks<KK>(f.a[0], fa.a[0] + boff);
-        read_ks<KK>(f.a[1], fa.a[1] + boff);
+// Fragments of k-sub-step KK of the stage whose images lie `boff` (rows) and `aoff` (columns) bytes behind the first one's.
+template <int NTF, int MORE, int A_FORM, bool B_KS, int KK>
+__device__ __forceinline__ void read_frags(Frags& f, const FragAddr& fa, uint32_t boff, uint32_t aoff) {
+    if (A_FORM != kKc) {
+        read_ks<A_FORM, KK>(f.a[0], fa.a[0] + aoff);
+        read_ks<A_FORM, KK>(f.a[1], fa.a[1] + aoff);
     } else {
-        const uint32_t ad = fa.a[KK] + boff;
+        const uint32_t ad = fa.a[KK] + aoff;
         read_kc<0>(f.a[0], ad);
         read_kc<1>(f.a[1], ad);
     }
     if (B_KS) {
         const uint32_t bd = fa.b[0] + boff;
-        if (NTF > 0) read_ks<KK>(f.b[0], bd + fa.b[1]);
-        if (NTF > 1) read_ks<KK>(f.b[1], bd + (fa.b[1] ^ 64u));
-        if (NTF > 2) read_ks<KK>(f.b[2], bd + (fa.b[1] ^ 128u));
-        if (NTF > 3) read_ks<KK>(f.b[3], bd + (fa.b[1] ^ 192u));
+        if (NTF > 0) read_ks<kKs, KK>(f.b[0], bd + fa.b[1]);
+        if (NTF > 1) read_ks<kKs, KK>(f.b[1], bd + (fa.b[1] ^ 64u));
+        if (NTF > 2) read_ks<kKs, KK>(f.b[2], bd + (fa.b[1] ^ 128u));
+        if (NTF > 3) read_ks<kKs, KK>(f.b[3], bd + (fa.b[1] ^ 192u));
     } else {
         const uint32_t bd = fa.b[KK] + boff;
         if (NTF > 0) read_kc<0>(f.b[0], bd);
         if (NTF > 1) read_kc<1>(f.b[1], bd);
         if (NTF > 2) read_kc<2>(f.b[2], bd);
         if (NTF > 3) read_kc<3>(f.b[3], bd);
+        if (MORE) read_kc<0>(f.more, bd + fa.more);
     }
 }
 
 // Wait until at most N LDS operations are outstanding; ties the fragment registers.
-template <int N>
+template <int N, int MORE>
 __device__ __forceinline__ void wait_frags(Frags& f) {
-    asm volatile("s_waitcnt lgkmcnt(%6)"
-                 : "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]), "+v"(f.a[0]), "+v"(f.a[1])
-                 : "n"(N) : "memory");
+    if (MORE)
+        asm volatile("s_waitcnt lgkmcnt(%7)"
+                     : "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]), "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.more)
+                     : "n"(N) : "memory");
+    else
+        asm volatile("s_waitcnt lgkmcnt(%6)"
+                     : "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]), "+v"(f.a[0]), "+v"(f.a[1])
+                     : "n"(N) : "memory");
 }
 
-template <int NTF>
-__device__ __forceinline__ void mfma_step(const Frags& f, f32x16_t (&acc)[4][2]) {
-#pragma unroll
-    for (int tf = 0; tf < NTF; ++tf)
-#pragma unroll
-        for (int af = 0; af < 2; ++af)
-            acc[tf][af] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, f.a[af]),
-                                                                  __builtin_bit_cast(bf16x8_t, f.b[tf]),
-                                                                  acc[tf][af], 0, 0, 0);
-}
+// Accumulators of a wave: a[row fragment][column fragment], and rows 256..287 by one of the column fragments.
+struct Acc {
+    f32x16_t a[4][2];
+    f32x16_t more;
+};
 
 // The matrix instructions of one k-sub-step (fragments `cur`) with the fragment reads of sub-step KK
 // (into `nxt`) between the first three of them: a wave issues in order, and a matrix instruction
 // keeps its pipe busy for 32 clocks during which the same wave may issue other instructions, so
 // the reads cost no matrix issue slot, and the LDS sees them spread out instead of in bursts of
 // six to twelve from every wave at once.
-template <int NTF, bool A_KS, bool B_KS, int KK>
+// MORE = 1 + the column fragment that this wave multiplies rows 256..287 by; 0 = the tile has none.
+template <int NTF, int MORE, int A_FORM, bool B_KS, int KK>
 __device__ __forceinline__ void mfma_step_reading(const Frags& cur, Frags& nxt, const FragAddr& fa, uint32_t boff,
-                                                  f32x16_t (&acc)[4][2], bool rd = true) {
+                                                  uint32_t aoff, Acc& acc) {
     auto mm = [&](int tf, int af) {
-        acc[tf][af] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, cur.a[af]),
-                                                              __builtin_bit_cast(bf16x8_t, cur.b[tf]), acc[tf][af], 0, 0, 0);
+        acc.a[tf][af] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, cur.a[af]),
+                                                                __builtin_bit_cast(bf16x8_t, cur.b[tf]), acc.a[tf][af], 0, 0, 0);
     };
-    const uint32_t ad = (A_KS ? 0u : fa.a[KK]) + boff, bd = (B_KS ? fa.b[0] : fa.b[KK]) + boff;
+    const uint32_t ad = (A_FORM != kKc ? 0u : fa.a[KK]) + aoff, bd = (B_KS ? fa.b[0] : fa.b[KK]) + boff;
     auto rb = [&](int tf) {
-        if (!rd) return;
         if (B_KS) {
-            if (tf == 0) read_ks<KK>(nxt.b[0], bd + fa.b[1]);
-            if (tf == 1) read_ks<KK>(nxt.b[1], bd + (fa.b[1] ^ 64u));
-            if (tf == 2) read_ks<KK>(nxt.b[2], bd + (fa.b[1] ^ 128u));
-            if (tf == 3) read_ks<KK>(nxt.b[3], bd + (fa.b[1] ^ 192u));
+            if (tf == 0) read_ks<kKs, KK>(nxt.b[0], bd + fa.b[1]);
+            if (tf == 1) read_ks<kKs, KK>(nxt.b[1], bd + (fa.b[1] ^ 64u));
+            if (tf == 2) read_ks<kKs, KK>(nxt.b[2], bd + (fa.b[1] ^ 128u));
+            if (tf == 3) read_ks<kKs, KK>(nxt.b[3], bd + (fa.b[1] ^ 192u));
         } else {
             if (tf == 0) read_kc<0>(nxt.b[0], bd);
             if (tf == 1) read_kc<1>(nxt.b[1], bd);
@@ -233,10 +253,9 @@ __device__ __forceinline__ void mfma_step_reading(const Frags& cur, Frags& nxt, 
         }
     };
     auto ra = [&](int af) {
-        if (!rd) return;
-        if (A_KS) {
-            if (af == 0) read_ks<KK>(nxt.a[0], fa.a[0] + boff);
-            else read_ks<KK>(nxt.a[1], fa.a[1] + boff);
+        if (A_FORM != kKc) {
+            if (af == 0) read_ks<A_FORM, KK>(nxt.a[0], fa.a[0] + aoff);
+            else read_ks<A_FORM, KK>(nxt.a[1], fa.a[1] + aoff);
         } else {
             if (af == 0) read_kc<0>(nxt.a[0], ad);
             else read_kc<1>(nxt.a[1], ad);
@@ -266,18 +285,24 @@ __device__ __forceinline__ void mfma_step_reading(const Frags& cur, Frags& nxt, 
     __builtin_amdgcn_sched_barrier(0);
     if (NTF > 3) rb(3);
     __builtin_amdgcn_sched_barrier(0);
-    if (NTF > 3) {
-        mm(3, 0);
-        mm(3, 1);
+    if (NTF > 3) mm(3, 0);
+    if (MORE) {
+        __builtin_amdgcn_sched_barrier(0);
+        read_kc<0>(nxt.more, bd + fa.more);
+        __builtin_amdgcn_sched_barrier(0);
     }
+    if (NTF > 3) mm(3, 1);
+    if (MORE)
+        acc.more = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, cur.a[MORE == 2]),
+                                                           __builtin_bit_cast(bf16x8_t, cur.more), acc.more, 0, 0, 0);
 }
 
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ------------------------------------------------------------------ DMA sources
-// Every loader moves one operand: issue(dst) requests the next stage into the 32 KB image at
+// Every loader moves one operand: issue(dst) requests the next stage into the image at
 // `dst` (4 DMA instructions per wave, 1 KB each) and advances; DMA instruction i of wave w
-// fills the 1 KB block u = 4 w + i of the image.
+// fills the 1 KB block u = 4 w + i of the image, and a fifth one of waves 0..3 block 32 + w (rows 256..287).
 __device__ __forceinline__ void dma16(const char* src, char* dst) {
     __builtin_amdgcn_global_load_lds((glb_void_t*)src, (lds_void_t*)dst, 16, 0, 0);
 }
@@ -293,70 +318,132 @@ __device__ __forceinline__ int wave_block_off(const Lane& ln) { return ln.wave_u
 struct KcGeom {
     static __device__ __forceinline__ int row(const Lane& ln, int i) { return 8 * (4 * ln.w + i) + (ln.l >> 3); }
     static __device__ __forceinline__ int chunk(const Lane& ln, int i) { return (ln.l & 7) ^ ((row(ln, i) >> 1) & 7); }
+    // of the fifth instruction (waves 0..3)
+    static __device__ __forceinline__ int more_row(const Lane& ln) { return BMAX + 8 * ln.w + (ln.l >> 3); }
+    static __device__ __forceinline__ int more_chunk(const Lane& ln) { return (ln.l & 7) ^ ((more_row(ln) >> 1) & 7); }
 };
-// Rows whose k runs on: every stage is 128 bytes further along each row.  Only the first
-// `n` of the wave's four 8-row blocks are moved: blocks whose rows all lie beyond the tile's
-// rows are skipped (nothing reads them except row fragments whose outputs are never stored).
+// The column operands of the row-tile GEMMs (weights) are addressed by scalar bases and two 32-bit offsets a lane, for the
+// instructions with i even and odd: a 64-bit address a lane and instruction takes 8 registers and 8 vector additions a stage.
+typedef const __attribute__((address_space(1))) char* glb_ptr_t;
+__device__ __forceinline__ void dma16s(glb_ptr_t base, uint32_t off, char* dst) {
+    asm volatile("" : "+s"(base), "+v"(off));   // scalar base + lane offset, not one 64-bit lane address
+    __builtin_amdgcn_global_load_lds((glb_void_t*)(base + off), (lds_void_t*)dst, 16, 0, 0);
+}
+// Rows whose k runs on (weights read transposed): every stage is 128 bytes further along each row, and after `left` more stages
+// in a second matrix of the same layout (W_gate then W_up along k), `delta` bytes on.
 struct KcLoader {
-    const char* p[4];
-    int n = 4;   // wave-uniform
-    __device__ __forceinline__ void sync() {}
-    // blocks of this wave that hold rows of a tile with `rows` rows
-    __device__ __forceinline__ void prepare() {}
-    static __device__ __forceinline__ int blocks_for(const Lane& ln, int rows) {
-        return min(4, max(0, (rows - 32 * ln.wave_uniform() + 7) >> 3));
-    }
-    __device__ __forceinline__ void issue(char* dst) {
-        char* d = dst + wave_block_off();
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i < n) dma16(p[i], d + i * 1024);
-            p[i] += BK * 2;
-        }
-    }
-};
-// The same with the k axis being the concatenation of two matrices of identical layout (W_gate
-// then W_up along k): after `left` more stages every pointer jumps by `delta` bytes.
-struct KcSplitLoader {
-    const char* p[4];
-    long long delta;   // (second matrix) - (first matrix) - (bytes walked in the first)
+    glb_ptr_t p[4];     // first k of the instruction's eight rows in the stage to come (uniform)
+    uint32_t off[2];
+    long long delta;
     int left;
+    // n rows from first_row on, ld_bytes apart (n a multiple of 8; those past the last alias the last eight)
+    __device__ __forceinline__ void init(const Lane& ln, const char* first_row, int n, uint32_t ld_bytes) {
+        const int w = ln.wave_uniform();
+        left = INT_MAX;
+        delta = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = (glb_ptr_t)(first_row + (size_t)min(8 * (4 * w + i), n - 8) * ld_bytes);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) off[i] = (ln.l >> 3) * ld_bytes + KcGeom::chunk(ln, i) * 16;
+    }
     __device__ __forceinline__ void prepare() {}
-    __device__ __forceinline__ void sync() {}
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + wave_block_off();
-        if (left == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) p[i] += delta;
-        }
+        const long long jump = left == 0 ? delta : 0;
         --left;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            dma16(p[i], d + i * 1024);
+            p[i] += jump;
+            dma16s(p[i], off[i & 1], d + i * 1024);
             p[i] += BK * 2;
         }
     }
 };
-
+// The row operand: up to 288 rows, row_of(r) = address of row r's first k (r below `rows`; rows past the last alias it).
+struct RowLoader {
+    const char* p[4];
+    const char* pm;   // the fifth instruction's
+    int n;            // blocks of this wave that hold rows of the tile (wave-uniform); bit 3: the fifth one does too
+    template <class F>
+    __device__ __forceinline__ void init(const Lane& ln, int rows, F row_of) {
+        const int w = ln.wave_uniform();
+        n = min(4, max(0, (rows - 32 * w + 7) >> 3)) | (w < 4 && rows > BMAX + 8 * w ? 8 : 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = row_of(min(KcGeom::row(ln, i), rows - 1)) + KcGeom::chunk(ln, i) * 16;
+        pm = p[0];
+        if (n & 8) pm = row_of(min(KcGeom::more_row(ln), rows - 1)) + KcGeom::more_chunk(ln) * 16;
+    }
+    __device__ __forceinline__ void prepare() {}
+    __device__ __forceinline__ void issue(char* dst) {
+        const int off = wave_block_off();
+        char* d = dst + off;
+        // one branch for a wave whose blocks all hold rows: a branch around every request delays the last of them
+        if ((n & 7) == 4) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dma16(p[i], d + i * 1024);
+        } else if (n & 7) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (i < (n & 7)) dma16(p[i], d + i * 1024);
+        }
+        if (n & 8) dma16(pm, dst + kOperandBytes + (off >> 2));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] += BK * 2;
+        pm += BK * 2;
+    }
+};
 // KS image: block u holds k rows 2u, 2u+1 (512 B = 32 chunks each); lane p moves the chunk of
 // k row 2u + p/32 that belongs at chunk position p%32.
 struct KsGeom {
     static __device__ __forceinline__ int krow(const Lane& ln, int i) { return 2 * (4 * ln.w + i) + ln.hf; }
     static __device__ __forceinline__ int chunk(const Lane& ln, int i) { return ln.l31 ^ ((krow(ln, i) & 3) << 2); }
 };
-// Dense matrix [K, n], K a multiple of 64: p[i] = address of (k row krow(i), this lane's chunk).
+// Dense matrix [K, n], K a multiple of 64.
 struct KsLoader {
-    const char* p[4];
-    long long step;   // 64 memory rows
+    glb_ptr_t p[4];     // first k row of the instruction in the stage to come (uniform)
+    uint32_t off[2];
+    uint32_t step;      // 64 memory rows
+    // columns from `first` (first_row's address, of n) on, ld_bytes a k row; chunks past n alias the last one
+    __device__ __forceinline__ void init(const Lane& ln, const char* first_row, int first, int n, uint32_t ld_bytes) {
+        const int w = ln.wave_uniform();
+        step = BK * ld_bytes;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = (glb_ptr_t)(first_row + (size_t)(2 * (4 * w + i)) * ld_bytes);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) off[i] = ln.hf * ld_bytes + min(first + KsGeom::chunk(ln, i) * 8, n - 8) * 2;
+    }
     __device__ __forceinline__ void prepare() {}
-    __device__ __forceinline__ void sync() {}
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + wave_block_off();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            dma16(p[i], d + i * 1024);
+            dma16s(p[i], off[i & 1], d + i * 1024);
             p[i] += step;
         }
+    }
+};
+// Two such matrices, 128 columns of each (GEMM1: gate, up): two images [64 k][256 B], one behind the other, the chunk c of k row
+// k at c ^ ((k & 3) << 2), in the second with bit 1 turned over as well.  Instructions 0, 1 of a wave move 4 k rows
+// each of the first, 2, 3 of the second.
+struct KsPairLoader {
+    glb_ptr_t p[2];     // this wave's first k row in the stage to come (uniform)
+    uint32_t off[2];
+    uint32_t ld;
+    __device__ __forceinline__ void init(const Lane& ln, const char* row0, const char* row1, int first, int n, uint32_t ld_bytes) {
+        ld = ld_bytes;
+        p[0] = (glb_ptr_t)(row0 + (size_t)(8 * ln.wave_uniform()) * ld);
+        p[1] = (glb_ptr_t)(row1 + (size_t)(8 * ln.wave_uniform()) * ld);
+        const int e = ln.l >> 4, c = (ln.l & 15) ^ (e << 2);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) off[i] = e * ld + min(first + (c ^ (2 * i)) * 8, n - 8) * 2;
+    }
+    __device__ __forceinline__ void prepare() {}
+    __device__ __forceinline__ void issue(char* dst) {
+        char* d = dst + (wave_block_off() >> 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dma16s(p[i >> 1] + (i & 1) * 4 * ld, off[i >> 1], d + (i >> 1) * (kOperandBytes / 2) + (i & 1) * 1024);
+        p[0] += BK * ld;
+        p[1] += BK * ld;
     }
 };
 // Reduction over K memory rows with K not a multiple of 64 (the rows of one expert): k rows at
@@ -376,7 +463,6 @@ struct KsTailLoader {
     int k0;               // reduction index of instruction 0's k row in the stage to come
     int K;
     __device__ __forceinline__ void prepare() {}
-    __device__ __forceinline__ void sync() {}
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + wave_block_off();
 #pragma unroll
@@ -451,14 +537,13 @@ struct KsGatherLoader {
 //                   request the column operand of stage t+2 (a CU takes about 64 DMA requests
 //                   before issue blocks, which is what one stage has: the second half goes out
 //                   behind a burst of matrix work instead of in front of it; 1 % on the step).
-template <int NTF, bool A_KS, bool B_KS, class LB, class LA>
-__device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, const FragAddr& fa,
-                                         f32x16_t (&acc)[4][2]) {
+template <int NTF, int MORE, int A_FORM, bool B_KS, class LB, class LA>
+__device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, const FragAddr& fa, Acc& acc) {
     lb.prepare();
     la.prepare();
     __builtin_amdgcn_sched_barrier(0);
     lb.issue(smem);
-    la.issue(smem + kOperandBytes);
+    la.issue(smem + kRowBytes);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     if (nk > 1) {
@@ -466,27 +551,27 @@ __device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, con
         la.prepare();
         __builtin_amdgcn_sched_barrier(0);
         lb.issue(smem + kStageBytes);
-        la.issue(smem + kStageBytes + kOperandBytes);
+        la.issue(smem + kStageBytes + kRowBytes);
     }
     Frags f0, f1;
-    if (NTF > 0) read_frags<NTF, A_KS, B_KS, 0>(f0, fa, 0);
+    if (NTF > 0) read_frags<NTF, MORE, A_FORM, B_KS, 0>(f0, fa, 0, 0);
     for (int t = 0; t < nk; ++t) {
         const uint32_t boff = (t & 1) * kStageBytes, noff = kStageBytes - boff;
         __builtin_amdgcn_sched_barrier(0);
         if (NTF > 0) {
-            wait_frags<0>(f0);
+            wait_frags<0, MORE>(f0);
             __builtin_amdgcn_sched_barrier(0);
-            mfma_step_reading<NTF, A_KS, B_KS, 1>(f0, f1, fa, boff, acc);
+            mfma_step_reading<NTF, MORE, A_FORM, B_KS, 1>(f0, f1, fa, boff, boff, acc);
             __builtin_amdgcn_sched_barrier(0);
-            wait_frags<0>(f1);
+            wait_frags<0, MORE>(f1);
             __builtin_amdgcn_sched_barrier(0);
-            mfma_step_reading<NTF, A_KS, B_KS, 2>(f1, f0, fa, boff, acc);
+            mfma_step_reading<NTF, MORE, A_FORM, B_KS, 2>(f1, f0, fa, boff, boff, acc);
             __builtin_amdgcn_sched_barrier(0);
-            wait_frags<0>(f0);
+            wait_frags<0, MORE>(f0);
             __builtin_amdgcn_sched_barrier(0);
-            mfma_step_reading<NTF, A_KS, B_KS, 3>(f0, f1, fa, boff, acc);
+            mfma_step_reading<NTF, MORE, A_FORM, B_KS, 3>(f0, f1, fa, boff, boff, acc);
             __builtin_amdgcn_sched_barrier(0);
-            wait_frags<0>(f1);
+            wait_frags<0, MORE>(f1);
         }
         if (t + 1 < nk) {
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -499,12 +584,14 @@ __device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, con
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        // the matrix instructions of sub-step 3, with the first fragment reads of stage t+1 (if there is one) between them
-        if (NTF > 0) mfma_step_reading<NTF, A_KS, B_KS, 0>(f1, f0, fa, noff, acc, t + 1 < nk);
+        // the matrix instructions of sub-step 3, with the first fragment reads of stage t+1 between them (behind the last
+        // stage they read what is there: a branch around each of them costs every stage)
+        if (NTF > 0) mfma_step_reading<NTF, MORE, A_FORM, B_KS, 0>(f1, f0, fa, noff, noff, acc);
         __builtin_amdgcn_sched_barrier(0);
-        if (t + 2 < nk) la.issue(smem + boff + kOperandBytes);   // the second operand's requests behind a burst of matrix work
+        if (t + 2 < nk) la.issue(smem + boff + kRowBytes);   // the second operand's requests behind a burst of matrix work
     }
     __builtin_amdgcn_sched_barrier(0);
+    if (NTF > 0) wait_frags<0, MORE>(f0);
     __builtin_amdgcn_s_barrier();   // every wave has read its last fragments: the buffers may be refilled
 }
 
@@ -514,24 +601,48 @@ __device__ __forceinline__ int active_row_frags(int rows) {
     return __builtin_amdgcn_readfirstlane(mine <= 0 ? 0 : (mine >= 128 ? 4 : (mine + 31) >> 5));
 }
 
-// Runs mma_loop with the wave's NTF (a scalar branch: every wave runs exactly one instance, and all
-// instances execute the same barriers).
-template <bool A_KS, bool B_KS, class LB, class LA>
-__device__ __forceinline__ void mma_tile(LB& lb, LA& la, int nk, int rows, char* smem, const FragAddr& fa,
-                                         f32x16_t (&acc)[4][2]) {
+__device__ __forceinline__ void zero_acc(Acc& acc, bool more) {
 #pragma unroll
     for (int tf = 0; tf < 4; ++tf)
 #pragma unroll
         for (int af = 0; af < 2; ++af)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[tf][af][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc.a[tf][af][v] = 0.f;
+    if (more)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc.more[v] = 0.f;
+}
+
+// A tile of a row-tile GEMM (nk >= 1; row_of as in RowLoader), by the loop for the wave's NTF (scalar branches: every
+// wave runs exactly one instance, and all instances of a loop execute the same barriers).
+template <int A_FORM, class LA, class F>
+__device__ __forceinline__ void row_tile_gemm(const Lane& ln, LA& la, int nk, int rows, char* smem, const FragAddr& fa, Acc& acc,
+                                              F row_of) {
+    const int ntf = active_row_frags(rows);
+    RowLoader lb;
+    lb.init(ln, rows, row_of);
+    zero_acc(acc, true);
+    if (rows > BMAX) {
+        if (ln.wave_uniform() < 4) mma_loop<4, 1, A_FORM, false>(lb, la, nk, smem, fa, acc);
+        else mma_loop<4, 2, A_FORM, false>(lb, la, nk, smem, fa, acc);
+    } else if (ntf == 4) mma_loop<4, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
+    else if (ntf == 3) mma_loop<3, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
+    else if (ntf == 2) mma_loop<2, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
+    else if (ntf == 1) mma_loop<1, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
+    else mma_loop<0, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
+}
+
+// A tile of a weight-gradient GEMM: both operands have k as their memory rows.
+template <class LB, class LA>
+__device__ __forceinline__ void weight_tile_gemm(LB& lb, LA& la, int nk, int rows, char* smem, const FragAddr& fa, Acc& acc) {
+    zero_acc(acc, false);
     if (nk <= 0) return;   // empty reduction (an expert without rows): the tile is all zeros
     const int ntf = active_row_frags(rows);
-    if (ntf == 4) mma_loop<4, A_KS, B_KS>(lb, la, nk, smem, fa, acc);
-    else if (ntf == 3) mma_loop<3, A_KS, B_KS>(lb, la, nk, smem, fa, acc);
-    else if (ntf == 2) mma_loop<2, A_KS, B_KS>(lb, la, nk, smem, fa, acc);
-    else if (ntf == 1) mma_loop<1, A_KS, B_KS>(lb, la, nk, smem, fa, acc);
-    else mma_loop<0, A_KS, B_KS>(lb, la, nk, smem, fa, acc);
+    if (ntf == 4) mma_loop<4, 0, kKs, true>(lb, la, nk, smem, fa, acc);
+    else if (ntf == 3) mma_loop<3, 0, kKs, true>(lb, la, nk, smem, fa, acc);
+    else if (ntf == 2) mma_loop<2, 0, kKs, true>(lb, la, nk, smem, fa, acc);
+    else if (ntf == 1) mma_loop<1, 0, kKs, true>(lb, la, nk, smem, fa, acc);
+    else mma_loop<0, 0, kKs, true>(lb, la, nk, smem, fa, acc);
 }
 
 // ------------------------------------------------------------------ epilogue helpers
@@ -582,10 +693,9 @@ struct WaveRepack {
 
 // The wave's 128 x 64 bf16 sub-tile of the accumulators, handed to store(tile row, tile column,
 // 8 columns as 16 bytes) with 8 neighbouring lanes on one row (128 contiguous bytes); rows at
-// and beyond `rows` and 8-column pieces at and beyond `cols` (tile coordinates) are left out.
-template <class StoreFn>
-__device__ __forceinline__ void store_subtile_bf16(const f32x16_t (&acc)[4][2], char* smem, int rows, int cols,
-                                                   StoreFn store) {
+// and beyond `rows` and 8-column pieces at and beyond `cols` (tile coordinates) are left out.  MORE: the tile may have rows 256..287.
+template <bool MORE, class StoreFn>
+__device__ __forceinline__ void store_subtile_bf16(const Acc& acc, char* smem, int rows, int cols, StoreFn store) {
     const Lane ln;
     WaveRepack<8> rp(smem, ln);
     const int l31 = ln.l31, hf = ln.hf;
@@ -595,13 +705,25 @@ __device__ __forceinline__ void store_subtile_bf16(const f32x16_t (&acc)[4][2], 
 #pragma unroll
         for (int af = 0; af < 2; ++af)
 #pragma unroll
-            for (int vg = 0; vg < 2; ++vg) rp.put(32 * tf + l31, 4 * af + 2 * vg + hf, pack8(acc[tf][af], vg));
+            for (int vg = 0; vg < 2; ++vg) rp.put(32 * tf + l31, 4 * af + 2 * vg + hf, pack8(acc.a[tf][af], vg));
     const int col = 64 * wn + 8 * rp.get_piece();
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         const int row = 128 * wm + rp.get_row(j);
         const u32x4_t v = rp.get(j);
         if (row < rows && col < cols) store(row, col, v);
+    }
+    if (MORE && rows > BMAX) {   // rows 256..287 by column fragment wm
+        WaveRepack<4> rm(smem, ln);
+#pragma unroll
+        for (int vg = 0; vg < 2; ++vg) rm.put(l31, 2 * vg + hf, pack8(acc.more, vg));
+        const int mcol = 64 * wn + 32 * wm + 8 * rm.get_piece();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int row = BMAX + rm.get_row(j);
+            const u32x4_t v = rm.get(j);
+            if (row < rows && mcol < cols) store(row, mcol, v);
+        }
     }
 }
 

@@ -88,7 +88,6 @@ struct ThinParams {
     ThinRule rule;
 };
 
-typedef const __attribute__((address_space(1))) char* glb_ptr_t;
 typedef const __attribute__((address_space(1))) u32x4_t* glb_vec_t;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 typedef __attribute__((address_space(3))) char* lds_ptr_t;
