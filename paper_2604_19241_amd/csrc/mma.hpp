@@ -24,7 +24,7 @@
 // lane p's 16 bytes to (LDS base) + 16 p, so nothing is staged in registers and no LDS
 // write instruction or register transpose exists.
 //
-// Two stage buffers (136 KB of LDS).  Stage t+2 is requested right behind the barrier that
+// Two stage buffers (136 KB of LDS; three, 144 KB, for tiles of up to 128 rows, see mma_low).  Stage t+2 is requested right behind the barrier that
 // ends the fragment reads of stage t, so it has a whole stage of matrix work to land; one
 // workgroup barrier per stage.  The fragment reads are inline assembly: the compiler would put
 // a full vmcnt(0) in front of every LDS read it knows about while a DMA load is in flight.
@@ -44,7 +44,11 @@ enum OperandForm { kKc = 0, kKs = 1, kKsPair = 2 };   // of an LDS image; the la
 constexpr int kOperandBytes = 32768;    // 256 rows or columns, one stage
 constexpr int kRowBytes = kOperandBytes + kMoreRows * 128;
 constexpr int kStageBytes = kRowBytes + kOperandBytes;   // rows (B role) first, columns (A role) second
-constexpr int kMmaSmem = 2 * kStageBytes;
+constexpr int kLowRows = 128;           // tiles with no more rows
+constexpr int kLowRowBytes = kLowRows * 128;
+constexpr int kLowStageBytes = kLowRowBytes + kOperandBytes;
+constexpr int kMmaSmem = 3 * kLowStageBytes;
+static_assert(kMmaSmem >= 2 * kStageBytes, "");
 constexpr int kMmaThreads = 512;
 
 typedef __attribute__((address_space(3))) void lds_void_t;
@@ -392,6 +396,28 @@ struct RowLoader {
         pm += BK * 2;
     }
 };
+// The same for tiles of up to 128 rows: instruction i of wave w fills block 2 w + i.  Both are always issued (rows past the last
+// alias it), so that every wave has as many requests on their way.
+struct LowRowLoader {
+    const char* p[2];
+    template <class F>
+    __device__ __forceinline__ void init(const Lane& ln, int rows, F row_of) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = 8 * (2 * ln.w + i) + (ln.l >> 3);
+            p[i] = row_of(min(r, rows - 1)) + ((ln.l & 7) ^ ((r >> 1) & 7)) * 16;
+        }
+    }
+    __device__ __forceinline__ void issue(char* dst) {
+        char* d = dst + (wave_block_off() >> 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            dma16(p[i], d + i * 1024);
+            p[i] += BK * 2;
+        }
+    }
+};
+
 // KS image: block u holds k rows 2u, 2u+1 (512 B = 32 chunks each); lane p moves the chunk of
 // k row 2u + p/32 that belongs at chunk position p%32.
 struct KsGeom {
@@ -601,6 +627,65 @@ __device__ __forceinline__ int active_row_frags(int rows) {
     return __builtin_amdgcn_readfirstlane(mine <= 0 ? 0 : (mine >= 128 ? 4 : (mine + 31) >> 5));
 }
 
+// The loop for tiles of up to 128 rows (waves 4..7 only move operands): their stages are 48 KB, so that three buffers fit and
+// stages t+1 and t+2 are on their way while stage t is multiplied.  The matrix work of a stage takes a quarter to a
+// half of the time that its requests take to arrive: with two buffers such a tile took a round trip to memory a stage
+// (training step of 256 tokens on 8 experts of 512 x 1024, 64 rows each, 135 -> 123 us; 4099 tokens on 64 experts of
+// 2048 x 1408, tiles of 256 and 128 rows, forward 510 -> 502 us; Zipf(1.2) routing of 8001 tokens 2444 -> 2419 us).
+template <int NTF, int A_FORM, class LA>
+__device__ __forceinline__ void mma_low(LowRowLoader& lb, LA& la, int nk, char* smem, const FragAddr& fa, Acc& acc) {
+    constexpr int kRequests = 6;   // of a wave, a stage
+    constexpr uint32_t kA = kLowRowBytes - kRowBytes;   // fa.a is made for the larger row image
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+        if (t < nk) {
+            lb.issue(smem + t * kLowStageBytes);
+            la.issue(smem + t * kLowStageBytes + kLowRowBytes);
+        }
+    if (nk > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kRequests) : "memory");
+    else if (nk > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kRequests) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    Frags f0, f1;
+    if (NTF > 0) read_frags<NTF, 0, A_FORM, false, 0>(f0, fa, 0, kA);
+    uint32_t boff = 0;
+    for (int t = 0; t < nk; ++t) {
+        const uint32_t noff = boff == 2 * kLowStageBytes ? 0 : boff + kLowStageBytes;
+        __builtin_amdgcn_sched_barrier(0);
+        if (NTF > 0) {
+            wait_frags<0, 0>(f0);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_step_reading<NTF, 0, A_FORM, false, 1>(f0, f1, fa, boff, boff + kA, acc);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_frags<0, 0>(f1);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_step_reading<NTF, 0, A_FORM, false, 2>(f1, f0, fa, boff, boff + kA, acc);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_frags<0, 0>(f0);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_step_reading<NTF, 0, A_FORM, false, 3>(f0, f1, fa, boff, boff + kA, acc);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_frags<0, 0>(f1);
+        }
+        if (t + 1 < nk) {
+            // stage t+1 is here; stage t+2, if there is one, may still be on its way
+            if (t + 2 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kRequests) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            if (t + 3 < nk) {
+                lb.issue(smem + boff);
+                la.issue(smem + boff + kLowRowBytes);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (NTF > 0) mfma_step_reading<NTF, 0, A_FORM, false, 0>(f1, f0, fa, noff, noff + kA, acc);
+        boff = noff;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (NTF > 0) wait_frags<0, 0>(f0);
+    __builtin_amdgcn_s_barrier();
+}
+
 __device__ __forceinline__ void zero_acc(Acc& acc, bool more) {
 #pragma unroll
     for (int tf = 0; tf < 4; ++tf)
@@ -613,12 +698,23 @@ __device__ __forceinline__ void zero_acc(Acc& acc, bool more) {
         for (int v = 0; v < 16; ++v) acc.more[v] = 0.f;
 }
 
-// A tile of a row-tile GEMM (nk >= 1; row_of as in RowLoader), by the loop for the wave's NTF (scalar branches: every
+// A tile of a row-tile GEMM (nk >= 1; row_of as in RowLoader), by the loop for its rows and the wave's NTF (scalar branches: every
 // wave runs exactly one instance, and all instances of a loop execute the same barriers).
 template <int A_FORM, class LA, class F>
 __device__ __forceinline__ void row_tile_gemm(const Lane& ln, LA& la, int nk, int rows, char* smem, const FragAddr& fa, Acc& acc,
                                               F row_of) {
     const int ntf = active_row_frags(rows);
+    if (rows <= kLowRows) {
+        LowRowLoader lb;
+        lb.init(ln, rows, row_of);
+        zero_acc(acc, false);
+        if (ntf == 4) mma_low<4, A_FORM>(lb, la, nk, smem, fa, acc);
+        else if (ntf == 3) mma_low<3, A_FORM>(lb, la, nk, smem, fa, acc);
+        else if (ntf == 2) mma_low<2, A_FORM>(lb, la, nk, smem, fa, acc);
+        else if (ntf == 1) mma_low<1, A_FORM>(lb, la, nk, smem, fa, acc);
+        else mma_low<0, A_FORM>(lb, la, nk, smem, fa, acc);
+        return;
+    }
     RowLoader lb;
     lb.init(ln, rows, row_of);
     zero_acc(acc, true);
@@ -628,8 +724,7 @@ __device__ __forceinline__ void row_tile_gemm(const Lane& ln, LA& la, int nk, in
     } else if (ntf == 4) mma_loop<4, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
     else if (ntf == 3) mma_loop<3, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
     else if (ntf == 2) mma_loop<2, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
-    else if (ntf == 1) mma_loop<1, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
-    else mma_loop<0, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
+    else mma_loop<1, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
 }
 
 // A tile of a weight-gradient GEMM: both operands have k as their memory rows.
