@@ -12,6 +12,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 namespace uniep {
 
@@ -24,8 +25,22 @@ constexpr int kPieces = (kChunk + kMaxTopK - 1 + 63) / 64;   // 64-slot pieces o
 // 44 chunks of 256 experts 13.6 us (with the scan's launch 15.7), 128 chunks 16.8 us (15.9).
 constexpr int kFewChunks = 64;
 
-static int chunk_tokens(int k) { return (kChunk + k - 1) / k; }
-static int chunks_of(const moe_shape_t& s) { return (s.T + chunk_tokens(s.k) - 1) / chunk_tokens(s.k); }
+// From kManyChunks chunks on a chunk has up to 1024 slots, a thread each: a quarter of the workgroups, whose 16 waves rank a
+// piece each instead of 4 of them, and a quarter of the table to scan.  With fewer, CUs would stay idle.
+// Measured, us of the whole routing, chunks of 256 / of 1024 slots (tokens x experts x k): 32768 x 256 x 8 38.2 / 36.8,
+// 65536 x 64 x 8 49.1 / 35.2, 60001 x 256 x 8 65.5 / 52.4, but 16384 x 256 x 8 22.4 / 34.7, 24000 x 128 x 6 27.5 / 29.2.
+constexpr int kLongPieces = kChunkThreads / 64;
+constexpr int kManyChunks = 1024;
+struct Chunks {
+    int tokens, n;   // of a chunk; chunks
+    bool lng;
+};
+static Chunks chunks_of(const moe_shape_t& s) {
+    const int tokens = (kChunk + s.k - 1) / s.k, n = (s.T + tokens - 1) / tokens;
+    if (n < kManyChunks) return Chunks{tokens, n, false};
+    const int more = kChunkThreads / s.k;
+    return Chunks{more, (s.T + more - 1) / more, true};
+}
 // Whether the top-k is a launch of its own, one token a wave over the whole chip, ahead of the ranking
 // (one launch more), instead of part of the chunk's workgroup (up to 16 tokens a wave, one after the other,
 // on as many CUs as there are chunks).  Measured, us of the whole routing, in one launch with the ranking / apart:
@@ -36,8 +51,9 @@ static int chunks_of(const moe_shape_t& s) { return (s.T + chunk_tokens(s.k) - 1
 // 21.1 / 19.8, 65536 x 1024 x 1 141 / 81; more, where the chip is full either way: 65536 x 256 x 2 31.4 / 34.8,
 // 32768 x 256 x 8 39.6 / 40.9.
 constexpr int kTopkGroups = 1 << 16;
-static bool topk_alone(const moe_shape_t& s) {
-    const int n = chunks_of(s), tokens = std::min(s.T, chunk_tokens(s.k));
+static bool topk_alone(const moe_shape_t& s, const Chunks& c) {
+    if (c.lng) return false;
+    const int n = c.n, tokens = std::min(s.T, c.tokens);
     const long long work = (long long)tokens * s.E;
     if (tokens <= kChunkThreads / 64 && (n == 1 || s.E <= 256)) return false;
     if (n == 1) return work * s.k > 13000;
@@ -46,8 +62,11 @@ static bool topk_alone(const moe_shape_t& s) {
 
 // Largest value over the wave, on the data-parallel-primitive path of the vector ALU: six
 // instructions; six shuffles through LDS took ten times as long.
-__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
-#define UNIEP_DPP_MAX(ctrl, rows) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false))
+template <int NT>
+__device__ __forceinline__ void wave_max(uint32_t (&v)[NT]) {
+#define UNIEP_DPP_MAX(ctrl, rows)                                                                                     \
+    _Pragma("unroll") for (int n = 0; n < NT; ++n) v[n] =                                                             \
+        max(v[n], (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[n], ctrl, rows, 0xf, false))
     UNIEP_DPP_MAX(0x111, 0xf);   // row_shr:1
     UNIEP_DPP_MAX(0x112, 0xf);   // row_shr:2
     UNIEP_DPP_MAX(0x114, 0xf);   // row_shr:4
@@ -55,7 +74,8 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
     UNIEP_DPP_MAX(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
     UNIEP_DPP_MAX(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
 #undef UNIEP_DPP_MAX
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+#pragma unroll
+    for (int n = 0; n < NT; ++n) v[n] = (uint32_t)__builtin_amdgcn_readlane((int)v[n], 63);
 }
 // Unsigned integers in the order of the floats.  0 stands for a NaN (which is never selected),
 // an expert already taken and the padding; both zeros get one key, as they compare equal.
@@ -92,42 +112,60 @@ __device__ __forceinline__ int block_exclusive_sum(int v, int32_t* s_wave, int* 
     return before + incl - v;
 }
 
-// Top-k of one token by one wave: lane j < k gets the j-th expert and its gate.
+// One token's logits: lane l has experts l, l + 64, ...  The loads are unconditional (lanes past the last expert load it once
+// more): behind a branch each waited for its data before the next went out, a round trip to memory for every 64 experts
+// (8192 tokens of 512 experts 30.4 -> 28.5 us for the whole routing, 65536 of 256, one selected, 32.3 -> 27.8 us).
 template <int EPL>
-__device__ __forceinline__ void select_experts(const float* __restrict__ row, int E, int k, int lane, int& my_idx, float& gate) {
-    uint32_t key[EPL];
+__device__ __forceinline__ void load_logits(const float* __restrict__ row, int E, int lane, float (&x)[EPL]) {
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-        const int e = lane + 64 * i;
-        key[i] = e < E ? logit_key(row[e]) : 0u;
+    for (int i = 0; i < EPL; ++i) x[i] = row[min(lane + 64 * i, E - 1)];
+}
+// Top-k of NT tokens by one wave: lane j < k gets a token's j-th expert and its gate.  A round is one chain of dependent
+// instructions: the tokens' chains run side by side, without a branch between them (32768 tokens of 256 experts, 8 selected,
+// 36.8 -> 34.4 us for the whole routing).
+template <int EPL, int NT>
+__device__ __forceinline__ void select_experts(const float (&x)[NT][EPL], int E, int k, int lane, int (&my_idx)[NT], float (&gate)[NT]) {
+    uint32_t key[NT][EPL], my_key[NT], best[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) key[n][i] = lane + 64 * i < E ? logit_key(x[n][i]) : 0u;
+        my_idx[n] = 0;
+        my_key[n] = 0;
     }
-    float my_val = 0.f, top1 = 0.f;
-    my_idx = 0;
     for (int j = 0; j < k; ++j) {
-        uint32_t best = key[0];
 #pragma unroll
-        for (int i = 1; i < EPL; ++i) best = max(best, key[i]);
-        best = wave_max(best);
-        float bv = -INFINITY;
-        int be = 0x7fffffff;
-        if (best != 0u) {
-            bv = key_logit(best);
+        for (int n = 0; n < NT; ++n) {
+            best[n] = key[n][0];
+#pragma unroll
+            for (int i = 1; i < EPL; ++i) best[n] = max(best[n], key[n][i]);
+        }
+        wave_max<NT>(best);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            int be = 0;
 #pragma unroll
             for (int i = EPL - 1; i >= 0; --i) {
-                const uint64_t m = __ballot(key[i] == best);
-                if (m) be = 64 * i + (int)__builtin_ctzll(m);
+                const uint64_t m = __ballot(key[n][i] == best[n]);
+                be = m ? 64 * i + (int)__builtin_ctzll(m) : be;
             }
 #pragma unroll
-            for (int i = 0; i < EPL; ++i) key[i] = (lane + 64 * i == be) ? 0u : key[i];
+            for (int i = 0; i < EPL; ++i) key[n][i] = (lane + 64 * i == be) ? 0u : key[n][i];
+            // (nothing but NaN left: no expert, and a key that was 0 already)
+            my_key[n] = lane == j ? best[n] : my_key[n];
+            my_idx[n] = lane == j ? (best[n] ? be : 0x7fffffff) : my_idx[n];
         }
-        if (j == 0) top1 = bv;
-        if (lane == j) { my_val = bv; my_idx = be; }
     }
-    const float p = (lane < k) ? __expf(my_val - top1) : 0.f;
-    float s = p;
 #pragma unroll
-    for (int off = kMaxTopK / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    gate = p / s;
+    for (int n = 0; n < NT; ++n) {
+        const float my_val = my_key[n] ? key_logit(my_key[n]) : -INFINITY;
+        const float top1 = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(my_val)));
+        const float p = (lane < k) ? __expf(my_val - top1) : 0.f;
+        float s = p;
+#pragma unroll
+        for (int off = kMaxTopK / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+        gate[n] = p / s;
+    }
 }
 
 // ------------------------------------------- top-k, gates and ranks inside a chunk
@@ -141,18 +179,19 @@ __device__ __forceinline__ void select_experts(const float* __restrict__ row, in
 // EPL = 0: topk_kernel has selected the experts already.
 // Bound by instruction issue.  With the maximum by shuffles and counts, scan and positions in three
 // launches of their own the whole routing took 101 us for 32768 tokens of 256 experts, 8 selected
-// (now 45 us), and 11-15 us in four launches for up to 16 tokens of 128 experts (now one launch of 3.6-5 us).
+// (now 34 us), and 11-15 us in four launches for up to 16 tokens of 128 experts (now one launch of 3.6-5 us).
 //
 // ONE: the batch is a single chunk (a generation step): the ranks are complete, and the same
 // workgroup scans the counts and writes the rows.
-template <int EPL, bool ONE>
+// PIECES: 64-slot pieces of a chunk (a wave's counts of an expert in a piece are at most 64).
+template <int EPL, bool ONE, int PIECES>
 __global__ void __launch_bounds__(kChunkThreads)
 topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_chunk, int e_start, int e_count,
                  int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ chunk_cnt,
                  int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
                  int32_t* __restrict__ inv_perm) {
-    __shared__ int32_t s_idx[kPieces * 64];
-    __shared__ int32_t s_cnt[kPieces][kMaxExperts];
+    __shared__ int32_t s_idx[PIECES * 64];
+    __shared__ std::conditional_t<(PIECES > kPieces), uint16_t, int32_t> s_cnt[PIECES][kMaxExperts];
     __shared__ int32_t s_off[ONE ? kMaxExperts : 1];
     __shared__ int32_t s_wave[kChunkThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -160,24 +199,35 @@ topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_
     const size_t f0 = (size_t)t0 * k;
     if (tid < e_count)
 #pragma unroll
-        for (int i = 0; i < kPieces; ++i) s_cnt[i][tid] = 0;
+        for (int i = 0; i < PIECES; ++i) s_cnt[i][tid] = 0;
     if constexpr (EPL > 0) {
-        for (int tt = wave; tt < nt; tt += kChunkThreads / 64) {
-            int idx;
-            float gate;
-            select_experts<EPL>(logits + (size_t)(t0 + tt) * E, E, k, lane, idx, gate);
-            if (lane < k) {
-                s_idx[tt * k + lane] = idx;
-                topk_idx[f0 + tt * k + lane] = idx;
-                topk_w[f0 + tt * k + lane] = gate;
-            }
-        }
+        constexpr int kWaves = kChunkThreads / 64;
+        auto tokens = [&](int tt, auto count) {   // tt, tt + kWaves, ...
+            constexpr int NT = decltype(count)::value;
+            float x[NT][EPL], gate[NT];
+            int idx[NT];
+#pragma unroll
+            for (int n = 0; n < NT; ++n) load_logits<EPL>(logits + (size_t)(t0 + tt + n * kWaves) * E, E, lane, x[n]);
+            select_experts<EPL, NT>(x, E, k, lane, idx, gate);
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+                if (lane < k) {
+                    const int f = (tt + n * kWaves) * k + lane;
+                    s_idx[f] = idx[n];
+                    topk_idx[f0 + f] = idx[n];
+                    topk_w[f0 + f] = gate[n];
+                }
+        };
+        int tt = wave;
+        if constexpr (EPL <= 8)   // (16 keys a lane, twice, take too many registers)
+            for (; tt + kWaves < nt; tt += 2 * kWaves) tokens(tt, std::integral_constant<int, 2>{});
+        for (; tt < nt; tt += kWaves) tokens(tt, std::integral_constant<int, 1>{});
     } else if (tid < n) {
         s_idx[tid] = topk_idx[f0 + tid];
     }
     __syncthreads();
     int el = -1, rank = -1;
-    if (wave < kPieces) {
+    if (wave < PIECES) {
         if (tid < n) {
             el = s_idx[tid] - e_start;
             if (el < 0 || el >= e_count) el = -1;
@@ -198,7 +248,7 @@ topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_
     int total = 0;
     if (tid < e_count)
 #pragma unroll
-        for (int i = 0; i < kPieces; ++i) total += s_cnt[i][tid];
+        for (int i = 0; i < PIECES; ++i) total += s_cnt[i][tid];
     if (!ONE) {
         if (tid < n) inv_perm[f0 + tid] = rank;
         if (tid < e_count) chunk_cnt[(size_t)blockIdx.x * e_count + tid] = total;
@@ -227,12 +277,13 @@ __global__ void __launch_bounds__(kRouteThreads)
 topk_kernel(const float* __restrict__ logits, int T, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
     const int lane = threadIdx.x & 63;
     for (int t = blockIdx.x * (kRouteThreads / 64) + (threadIdx.x >> 6); t < T; t += gridDim.x * (kRouteThreads / 64)) {
-        int idx;
-        float gate;
-        select_experts<EPL>(logits + (size_t)t * E, E, k, lane, idx, gate);
+        float x[1][EPL], gate[1];
+        int idx[1];
+        load_logits<EPL>(logits + (size_t)t * E, E, lane, x[0]);
+        select_experts<EPL, 1>(x, E, k, lane, idx, gate);
         if (lane < k) {
-            topk_idx[(size_t)t * k + lane] = idx;
-            topk_w[(size_t)t * k + lane] = gate;
+            topk_idx[(size_t)t * k + lane] = idx[0];
+            topk_w[(size_t)t * k + lane] = gate[0];
         }
     }
 }
@@ -502,52 +553,52 @@ size_t route_workspace_bytes(const moe_shape_t& s) {
 }
 
 template <int EPL>
-static void launch_rank(const moe_shape_t& s, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
+static void launch_rank(const moe_shape_t& s, const Chunks& c, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
                         hipStream_t st) {
-    const int n = chunks_of(s);
-    if (n == 1)
-        hipLaunchKernelGGL((topk_rank_kernel<EPL, true>), dim3(1), dim3(kChunkThreads), 0, st, logits, s.T, s.E, s.k,
-                           chunk_tokens(s.k), s.e_start, s.e_count, (int32_t*)out.topk_idx, (float*)out.topk_w, chunk_cnt,
-                           (int32_t*)out.counts, (int32_t*)out.offsets, (int32_t*)out.perm, (int32_t*)out.inv_perm);
-    else
-        hipLaunchKernelGGL((topk_rank_kernel<EPL, false>), dim3(n), dim3(kChunkThreads), 0, st, logits, s.T, s.E, s.k,
-                           chunk_tokens(s.k), s.e_start, s.e_count, (int32_t*)out.topk_idx, (float*)out.topk_w, chunk_cnt,
-                           (int32_t*)out.counts, (int32_t*)out.offsets, (int32_t*)out.perm, (int32_t*)out.inv_perm);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(c.n), dim3(kChunkThreads), 0, st, logits, s.T, s.E, s.k, c.tokens, s.e_start, s.e_count,
+                           (int32_t*)out.topk_idx, (float*)out.topk_w, chunk_cnt, (int32_t*)out.counts, (int32_t*)out.offsets,
+                           (int32_t*)out.perm, (int32_t*)out.inv_perm);
+    };
+    if constexpr (EPL > 0)
+        if (c.lng) return launch(topk_rank_kernel<EPL, false, kLongPieces>);
+    if (c.n == 1) launch(topk_rank_kernel<EPL, true, kPieces>);
+    else launch(topk_rank_kernel<EPL, false, kPieces>);
 }
 
 template <int EPL>
-static void launch_topk(const moe_shape_t& s, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
+static void launch_topk(const moe_shape_t& s, const Chunks& c, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
                         hipStream_t st) {
-    if (!topk_alone(s)) return launch_rank<EPL>(s, logits, out, chunk_cnt, st);
+    if (!topk_alone(s, c)) return launch_rank<EPL>(s, c, logits, out, chunk_cnt, st);
     const int grid = std::min((s.T + kRouteThreads / 64 - 1) / (kRouteThreads / 64), kTopkGroups);
     hipLaunchKernelGGL(topk_kernel<EPL>, dim3(grid), dim3(kRouteThreads), 0, st, logits, s.T, s.E, s.k,
                        (int32_t*)out.topk_idx, (float*)out.topk_w);
-    launch_rank<0>(s, logits, out, chunk_cnt, st);
+    launch_rank<0>(s, c, logits, out, chunk_cnt, st);
 }
 
 int route_launch(const moe_shape_t& s, const float* logits, const moe_routing_t& out, void* ws,
                  hipStream_t st) {
     int32_t* chunk_cnt = (int32_t*)ws;
-    const int n = chunks_of(s);
     if (s.T == 0) {
         hipLaunchKernelGGL(no_rows_kernel, dim3(1), dim3(kChunkThreads), 0, st, s.e_count, (int32_t*)out.counts,
                            (int32_t*)out.offsets);
         return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
     }
-    const int epl = (s.E + 63) / 64;
-    if (epl <= 1) launch_topk<1>(s, logits, out, chunk_cnt, st);
-    else if (epl <= 2) launch_topk<2>(s, logits, out, chunk_cnt, st);
-    else if (epl <= 4) launch_topk<4>(s, logits, out, chunk_cnt, st);
-    else if (epl <= 8) launch_topk<8>(s, logits, out, chunk_cnt, st);
-    else launch_topk<16>(s, logits, out, chunk_cnt, st);
+    const Chunks c = chunks_of(s);
+    const int n = c.n, epl = (s.E + 63) / 64;
+    if (epl <= 1) launch_topk<1>(s, c, logits, out, chunk_cnt, st);
+    else if (epl <= 2) launch_topk<2>(s, c, logits, out, chunk_cnt, st);
+    else if (epl <= 4) launch_topk<4>(s, c, logits, out, chunk_cnt, st);
+    else if (epl <= 8) launch_topk<8>(s, c, logits, out, chunk_cnt, st);
+    else launch_topk<16>(s, c, logits, out, chunk_cnt, st);
     if (n > 1 && n <= kFewChunks) {
-        hipLaunchKernelGGL((rows_kernel<false>), dim3(n), dim3(kChunkThreads), 0, st, out.topk_idx, s.T, s.k, chunk_tokens(s.k),
+        hipLaunchKernelGGL((rows_kernel<false>), dim3(n), dim3(kChunkThreads), 0, st, out.topk_idx, s.T, s.k, c.tokens,
                            n, s.e_start, s.e_count, chunk_cnt, (int32_t*)out.counts, (int32_t*)out.offsets,
                            (int32_t*)out.perm, (int32_t*)out.inv_perm);
     } else if (n > 1) {
         hipLaunchKernelGGL(chunk_scan_kernel, dim3((s.e_count + kScanExperts - 1) / kScanExperts), dim3(kChunkThreads), 0, st,
                            chunk_cnt, n, s.e_count, (int32_t*)out.counts);
-        hipLaunchKernelGGL((rows_kernel<true>), dim3(n), dim3(kChunkThreads), 0, st, out.topk_idx, s.T, s.k, chunk_tokens(s.k),
+        hipLaunchKernelGGL((rows_kernel<true>), dim3(n), dim3(kChunkThreads), 0, st, out.topk_idx, s.T, s.k, c.tokens,
                            n, s.e_start, s.e_count, chunk_cnt, (int32_t*)out.counts, (int32_t*)out.offsets,
                            (int32_t*)out.perm, (int32_t*)out.inv_perm);
     }

@@ -138,6 +138,20 @@ def test_route_chunk_edges(kw):
     check(cfg, rng.integers(-4, 5, (cfg.T, cfg.E)).astype(np.float32) * np.float32(0.25), "chunk edge")
 
 
+# From 1024 chunks of 256 slots on the chunks are longer: the last one short, the last size and the first, chunks of fewer than
+# 1024 slots (k = 3, 10), one slot a token, experts here and elsewhere, ties in every token.
+@pytest.mark.parametrize("kw", [
+    dict(T=32736, E=40, k=8), dict(T=32768, E=200, k=8, e_start=7, e_count=90), dict(T=100003, E=33, k=3), dict(T=262200, E=65, k=1),
+    dict(T=27001, E=260, k=10, e_start=250, e_count=10), dict(T=16500, E=600, k=16),
+])
+def test_route_long_chunks(kw):
+    cfg = moe_synth.small_config(d=64, I=64, **kw)
+    rng = np.random.default_rng(kw["T"])
+    logits = rng.standard_normal((cfg.T, cfg.E), np.float32)
+    logits[::3] = np.round(logits[::3] * 4)
+    check(cfg, logits, "long chunks")
+
+
 @pytest.mark.parametrize("T", [20, 500])
 def test_route_special_values(T):
     """-inf loses to every number and ties by id, both zeros and equal denormals tie by id, a NaN is
