@@ -76,11 +76,11 @@ __device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePl
 }
 
 __device__ __forceinline__ ThinParams thin_params(const FwdParams& p) {
-    return ThinParams{p.s, p.x, p.w_gate, p.w_up, p.w_down, p.offsets, p.perm, p.gu, p.h, p.o, p.rule};
+    return ThinParams{p.s, p.x, p.w_gate, p.w_up, p.w_down, p.offsets, p.perm, p.gu, p.h, p.o, p.rule, p.workers};
 }
 // The queue (unless every expert is thin) and the thin experts' GEMM1, side by side: neither reads
 // what the other writes.
-__global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
 fwd_first_kernel(FwdParams p) {
     __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared) > sizeof(QueuePlan) ? sizeof(ThinShared) : sizeof(QueuePlan)];
     const int block = (int)blockIdx.x - p.plan_blocks;
@@ -91,7 +91,7 @@ fwd_first_kernel(FwdParams p) {
     if (p.plan_blocks == 0 && block == 0 && threadIdx.x < CTRL_WORDS) p.ctrl[threadIdx.x] = 0;
     thin_run<1>(thin_params(p), block, (int)gridDim.x - p.plan_blocks, *(ThinShared*)smem);
 }
-__global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
 fwd_second_kernel(FwdParams p) {
     __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared)];
     thin_run<2>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
@@ -491,8 +491,8 @@ static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream
     const size_t most = std::min<size_t>(p.s.e_count, (size_t)p.s.T * p.s.k);   // experts with rows
     // A caller's bound on the workers leaves the rest of the chip to somebody else: as many workgroups here.
     const size_t slots = workers < resident ? (size_t)workers : (size_t)kThinGroupsPerCu * resident;
-    const size_t n1 = none_thin ? 0 : std::min(slots, most * (p.s.I / 64));
-    const size_t n2 = std::min(slots, most * ((p.s.d + kThinCols - 1) / kThinCols));
+    const size_t n1 = none_thin ? 0 : std::min(slots, most * (p.s.I / 32));
+    const size_t n2 = std::min(slots, most * (p.s.d / 64));
     hipLaunchKernelGGL(fwd_first_kernel, dim3((unsigned)(n1 + p.plan_blocks)), dim3(kThinThreads), 0, st, p);
     if (!none_thin)
         hipLaunchKernelGGL(fwd_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);

@@ -2,18 +2,21 @@
 // of a skewed batch): the weights are read once and hardly reused, so the time is their stream
 // from HBM and what a task costs before its first and after its last load.
 //
-// A workgroup is 4 waves and owns 128 weight columns (GEMM1: 64 gate columns and the same 64 up
+// A workgroup is 4 waves and owns 256, 128 or 64 weight columns (GEMM1: half of them gate columns, the other half the same up
 // columns) of one expert, with all of its rows.  K advances in stages of 64.  A stage is loaded into
-// registers (a wave: 16 k rows of the weights and 8 rows of activations, five 16-byte loads a lane in
-// whole 128- or 256-byte runs), kThinAhead stages ahead, and passes through one of two LDS images;
-// one barrier a stage.  Loads to registers and not the DMA of the big tiles: the loads of several
-// stages are on their way at any time, more than a CU's DMA path holds.
+// registers (a wave: 16 k rows of the weights and 8 rows of activations, 16 bytes a lane and load), two or four stages
+// ahead, and passes through one of two LDS images; one barrier a stage.  Loads to registers and not the DMA of the big
+// tiles: the loads of several stages are on their way at any time.
+//
+// HBM delivers 256-byte runs of a k row faster than 128-byte ones wherever the rows lie a multiple of 1024 bytes apart (a
+// plain read of 512 experts of 2048 x 512, gate and up, 6.2 and 5.2 TB/s; 32 of 7168 x 2048 6.2 and 5.4), and a longer task has fewer
+// beginnings: 256 columns where they fill the chip (thin_cols).
 //
 // Every output is ONE chain of v_mfma_f32_32x32x16_bf16 in ascending k, weights as the A operand,
 // with the same k in the same lane and element as in the 256-row tiles (mma.hpp): a row's results
 // are bit for bit those of the work queue, so they do not depend on how many rows its expert has, i.e.
-// on what else is in the batch.  That rules out a split of the k axis over waves: wave w multiplies
-// columns [32 w, +32) of the task over the whole k axis.  Measured against a form that dealt the k axis to the
+// on what else is in the batch.  That rules out a split of the k axis over waves: a wave multiplies
+// one fragment of 32 columns (two of 256) of the task over the whole k axis.  Measured against a form that dealt the k axis to the
 // four waves and added four partial sums (no LDS image, no barrier): 32 tokens of width 2048 on 128 experts of
 // inner width 768 185 -> 183 us for the layer, 1021 tokens on 512 experts of 512 728 -> 718 us, one token
 // 33.8 -> 33.6 us; and against 256-row tiles for these experts 258 -> 190, 755 -> 705 and 82 -> 34 us.
@@ -27,11 +30,30 @@ namespace uniep {
 // 252 / 259 / 262 us; 16 of 2048 x 1408 59 / 61 / 106 us, on the queue 88 / 88 / 92 us.
 constexpr int kThinRows = 32;
 constexpr int kThinThreads = 256;
-constexpr int kThinGroupsPerCu = 3;   // as many as the LDS holds (50 KB each); with 2 the same within 0.5 %
-constexpr int kThinCols = 128;      // weight columns of a task
-constexpr int kThinAhead = 4;       // stages in flight (even: stage t is in registers t % 4 and in image t % 2)
-constexpr int kThinWBytes = BK * kThinCols * 2;                       // weights of a stage: image [64 k][256 B]
-constexpr int kThinImage = kThinWBytes + kThinRows * BK * 2;          // and the rows: image [32 rows][128 B]
+constexpr int kThinGroupsPerCu = 2;   // as many as the LDS holds (80 KB each)
+constexpr int kThinXBytes = kThinRows * BK * 2;                       // rows of a stage: image [32 rows][128 B]
+constexpr int kThinMostImage = BK * 256 * 2 + kThinXBytes;
+// Weight columns of a task where `experts` of them have `columns` each, on `cus` CUs.  A CU draws 57 GB/s from HBM
+// at most, whatever it has on its way (its L1 holds 32 KB of lines in flight), so that the time is the tasks of the CU that
+// has most of them; a task of 128 columns takes 0.58 of one of 256, one of 64 (runs of 64 bytes) 0.42.  Measured, us of the
+// layer with 128 columns everywhere / with this rule (tokens, experts of width and inner width): 1021, 512 of 2048 x 512 690 / 624;
+// 256, 32 of 7168 x 2048 506 / 459; 300, 256 of 2304 x 1024 677 / 608; 32, 128 of 2048 x 768 192 / 180; 20, 32 of
+// 7168 x 2048 251 / 225; 1, 128 of 2048 x 768 34.2 / 32.0; 1, 8 of 4096 x 14336 184 / 150.  With 256 columns everywhere: 1 token
+// 46.9 and 229, 3 tokens on 128 experts of 4096 x 1536 189 us for 177; with 64 32 tokens 258 us.
+__device__ __forceinline__ int thin_cols(int experts, int columns, int cus) {
+    auto cost = [&](int width, int weight) { return (experts * ((columns + width - 1) / width) + cus - 1) / cus * weight; };
+    const int wide = cost(256, 100), mid = cost(128, 58), narrow = cost(64, 42);
+    return wide <= min(mid, narrow) ? 256 : mid <= narrow ? 128 : 64;
+}
+template <int NC>
+struct ThinShape {
+    static constexpr int kRow = NC * 2;              // bytes of a k row in the weights' image [64 k][kRow]
+    static constexpr int kW = BK * kRow;
+    static constexpr int kImage = kW + kThinXBytes;
+    static constexpr int kLoads = NC / 32;           // of a wave and stage, 1 KB each
+    static constexpr int kFrags = NC == 256 ? 2 : 1; // column fragments of a wave; of 64 columns waves 2 and 3 have none
+    static constexpr int kAhead = NC == 256 ? 2 : 4; // stages in flight (even: stage t is in registers t % kAhead and in image t % 2)
+};
 
 // Whether the experts with few rows leave the queue.  Both paths give the same bits, so this is a matter of time
 // alone: the two launches of this path stand in front of the queue's, one after the other, and add their latency
@@ -86,6 +108,7 @@ struct ThinParams {
     char* h;
     char* o;
     ThinRule rule;
+    int workers;   // CUs that the launch may fill
 };
 
 typedef const __attribute__((address_space(1))) u32x4_t* glb_vec_t;
@@ -94,24 +117,27 @@ typedef __attribute__((address_space(3))) char* lds_ptr_t;
 typedef __attribute__((address_space(3))) u32x4_t* lds_vec_t;
 typedef __attribute__((address_space(3))) bf16x4_t* lds_tr_t;
 
-// Where a wave's next stage comes from.  GEMM1: weight loads 0, 1 are 8 k rows each of 64 gate columns,
-// 2, 3 the same of the up columns; GEMM2: load i is 4 k rows of 128 columns.
-template <int GEMM>
+// Where a wave's next stage comes from.  GEMM1: the first half of the weight loads are gate columns, the second the same up
+// columns; a load is kRows k rows of kLanes lanes.
+template <int GEMM, int NC>
 struct ThinSource {
+    static constexpr int kLoads = ThinShape<NC>::kLoads;
+    static constexpr int kLanes = GEMM == 1 ? NC / 16 : NC / 8, kRows = 64 / kLanes;
+    static constexpr int kOf = GEMM == 1 ? kLoads / 2 : kLoads;   // loads of a matrix
     glb_ptr_t w[2];      // first k row of this wave in the stage to come (uniform); GEMM2: w[0] only
     uint32_t off;        // this lane's k row and columns behind it
     uint32_t ldw;        // bytes from one k row to the next (uniform)
     glb_ptr_t x;         // this lane's row and chunk
     // advance: 0 = stay on this stage (the last one).  The loads are never left out: behind a branch
     // around them the compiler could not tell how many are in flight and would wait for all.
-    __device__ __forceinline__ void load(u32x4_t (&r)[5], int advance) {
+    __device__ __forceinline__ void load(u32x4_t (&r)[kLoads + 1], int advance) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            glb_ptr_t base = GEMM == 1 ? w[i >> 1] + (size_t)(8 * (i & 1)) * ldw : w[0] + (size_t)(4 * i) * ldw;
+        for (int i = 0; i < kLoads; ++i) {
+            glb_ptr_t base = w[i / kOf] + (size_t)(kRows * (i % kOf)) * ldw;
             asm volatile("" : "+s"(base));   // scalar base + 32-bit lane offset, not one 64-bit lane address per load
             r[i] = __builtin_nontemporal_load((glb_vec_t)(base + off));
         }
-        r[4] = *(glb_vec_t)x;
+        r[kLoads] = *(glb_vec_t)x;
         const size_t step = (size_t)(BK * advance) * ldw;
         w[0] += step;
         if (GEMM == 1) w[1] += step;
@@ -119,51 +145,59 @@ struct ThinSource {
     }
 };
 
-// The LDS images, with the swizzles of mma.hpp: weights, 16-byte chunk c of k row k at c ^ ((k & 3) << 2);
-// rows, chunk c of row r at c ^ ((r >> 1) & 7).  Chunks 4 w .. 4 w + 3 of a k row are wave w's 32 columns
-// (GEMM1: 16 gate columns, then the same 16 up columns).
-template <int GEMM>
+// The LDS images: weights, 16-byte chunk c of k row k at c ^ swz(k) (the bank bits that the chunks and, of 64 columns, the k rows
+// of a fragment read leave free); rows, chunk c of row r at c ^ ((r >> 1) & 7).  Chunks 4 f .. 4 f + 3 of a k row are fragment f's
+// 32 columns (GEMM1: 16 gate columns, then the same 16 up columns).
+template <int GEMM, int NC>
 struct ThinLds {
-    lds_ptr_t wput, xput, wget, xget[4];
+    using S = ThinShape<NC>;
+    using Src = ThinSource<GEMM, NC>;
+    lds_ptr_t wput[2], xput, wget[S::kFrags], xget[4];
+    static __device__ __forceinline__ int swz(int k) { return NC == 64 ? (k & 2) << 1 : (k & 3) << 2; }
     __device__ __forceinline__ ThinLds(lds_ptr_t base, const Lane& ln) {
         const int l = ln.l, w = ln.w, kh = ln.hf, g = (l >> 4) & 1, e = (l & 15) >> 2, q = l & 3;
-        if (GEMM == 1) {
-            const int kr = l >> 3, p = l & 7;
-            wput = base + (16 * w + kr) * 256 + (((4 * (p >> 1) + (p & 1)) ^ ((kr & 3) << 2)) << 4);
-        } else {
-            const int kr = l >> 4, p = l & 15;
-            wput = base + (16 * w + kr) * 256 + ((p ^ (kr << 2)) << 4);
-        }
+        const int kr = l / Src::kLanes, p = l % Src::kLanes, c = GEMM == 1 ? 4 * (p >> 1) + (p & 1) : p;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)   // loads with i even and odd: only two k rows a load make a difference
+            wput[i] = base + (16 * w + kr) * S::kRow + ((c ^ swz(kr + (Src::kRows == 2 ? 2 * i : 0))) << 4);
         const int row = 8 * w + (l >> 3);
-        xput = base + kThinWBytes + row * 128 + (((l & 7) ^ ((row >> 1) & 7)) << 4);
+        xput = base + S::kW + row * 128 + (((l & 7) ^ ((row >> 1) & 7)) << 4);
         const int sq = ((q & 1) << 1) | (q >> 1);   // piece -> position of its 4 columns inside the 16
-        wget = base + (8 * kh + e) * 256 + (((4 * w + 2 * g + (sq >> 1)) ^ (e << 2)) << 4) + (sq & 1) * 8;
+#pragma unroll
+        for (int f = 0; f < S::kFrags; ++f)
+            wget[f] = base + (8 * kh + e) * S::kRow + (((4 * (S::kFrags * (NC == 64 ? w & 1 : w) + f) + 2 * g + (sq >> 1)) ^ swz(e)) << 4) +
+                      (sq & 1) * 8;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
-            xget[kk] = base + kThinWBytes + ln.l31 * 128 + (((2 * kk + kh) ^ ((ln.l31 >> 1) & 7)) << 4);
+            xget[kk] = base + S::kW + ln.l31 * 128 + (((2 * kk + kh) ^ ((ln.l31 >> 1) & 7)) << 4);
     }
-    __device__ __forceinline__ void put(int image, const u32x4_t (&r)[5]) const {
+    __device__ __forceinline__ void put(int image, const u32x4_t (&r)[S::kLoads + 1]) const {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            *(lds_vec_t)(wput + image * kThinImage + (GEMM == 1 ? (i & 1) * 2048 + (i >> 1) * 32 : i * 1024)) = r[i];
-        *(lds_vec_t)(xput + image * kThinImage) = r[4];
+        for (int i = 0; i < S::kLoads; ++i)
+            *(lds_vec_t)(wput[i & 1] + image * S::kImage + (i % Src::kOf) * Src::kRows * S::kRow + (i / Src::kOf) * 32) = r[i];
+        *(lds_vec_t)(xput + image * S::kImage) = r[S::kLoads];
     }
-    // acc[v]: row l % 32, column position 16 (v / 8) + 8 (l / 32) + v % 8 of the wave's 32
-    __device__ __forceinline__ void multiply(int image, f32x16_t& acc) const {
-        bf16x4_t lo[4], hi[4];
+    // acc[f][v]: row l % 32, column position 16 (v / 8) + 8 (l / 32) + v % 8 of the wave's f-th 32
+    __device__ __forceinline__ void multiply(int image, f32x16_t (&acc)[S::kFrags]) const {
+        bf16x4_t lo[S::kFrags][4], hi[S::kFrags][4];
         u32x4_t b[4];
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            const lds_ptr_t a = wget + image * kThinImage + kk * 4096;
-            b[kk] = *(lds_vec_t)(xget[kk] + image * kThinImage);
-            lo[kk] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)a);
-            hi[kk] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(a + 1024));
+            b[kk] = *(lds_vec_t)(xget[kk] + image * S::kImage);
+#pragma unroll
+            for (int f = 0; f < S::kFrags; ++f) {
+                const lds_ptr_t a = wget[f] + image * S::kImage + kk * 16 * S::kRow;
+                lo[f][kk] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)a);
+                hi[f][kk] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(a + 4 * S::kRow));
+            }
         }
         __builtin_amdgcn_sched_barrier(0);   // all reads on their way before the first product: one latency a stage, not four
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_shufflevector(lo[kk], hi[kk], 0, 1, 2, 3, 4, 5, 6, 7),
-                                                          __builtin_bit_cast(bf16x8_t, b[kk]), acc, 0, 0, 0);
+#pragma unroll
+            for (int f = 0; f < S::kFrags; ++f)
+                acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_shufflevector(lo[f][kk], hi[f][kk], 0, 1, 2, 3, 4, 5, 6, 7),
+                                                                 __builtin_bit_cast(bf16x8_t, b[kk]), acc[f], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     }
 };
@@ -176,12 +210,12 @@ __device__ __forceinline__ void thin_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// One stage: registers -> image, the loads of the stage kThinAhead further on into the same registers,
+// One stage: registers -> image, the loads of the stage kAhead further on into the same registers,
 // barrier, matrix work.  An image is written again two stages later, behind the barrier that every wave
 // reaches with its reads of it done.
-template <int GEMM, bool LOAD>
-__device__ __forceinline__ void thin_stage(ThinSource<GEMM>& src, const ThinLds<GEMM>& lds, int image, u32x4_t (&r)[5],
-                                           f32x16_t& acc, int advance) {
+template <int GEMM, int NC, bool LOAD>
+__device__ __forceinline__ void thin_stage(ThinSource<GEMM, NC>& src, const ThinLds<GEMM, NC>& lds, int image,
+                                           u32x4_t (&r)[ThinShape<NC>::kLoads + 1], f32x16_t (&acc)[ThinShape<NC>::kFrags], int advance) {
     lds.put(image, r);
     __builtin_amdgcn_sched_barrier(0);
     if (LOAD) src.load(r, advance);
@@ -189,82 +223,110 @@ __device__ __forceinline__ void thin_stage(ThinSource<GEMM>& src, const ThinLds<
     lds.multiply(image, acc);
 }
 
-// n >= 1 stages: t is in registers t % kThinAhead and in image t % 2.
-template <int GEMM>
-__device__ __forceinline__ void thin_loop(ThinSource<GEMM>& src, const ThinLds<GEMM>& lds, int n, f32x16_t& acc) {
+// n >= 1 stages: t is in registers t % kAhead and in image t % 2.
+template <int GEMM, int NC>
+__device__ __forceinline__ void thin_loop(ThinSource<GEMM, NC>& src, const ThinLds<GEMM, NC>& lds, int n, f32x16_t (&acc)[ThinShape<NC>::kFrags]) {
+    constexpr int kAhead = ThinShape<NC>::kAhead;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    u32x4_t r[kThinAhead][5];
+    for (int f = 0; f < ThinShape<NC>::kFrags; ++f)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[f][v] = 0.f;
+    u32x4_t r[kAhead][ThinShape<NC>::kLoads + 1];
     thin_barrier();   // the task before has read its last image
 #pragma unroll
-    for (int j = 0; j < kThinAhead; ++j) src.load(r[j], j + 1 < n ? 1 : 0);
+    for (int j = 0; j < kAhead; ++j) src.load(r[j], j + 1 < n ? 1 : 0);
     int t = 0;
-    for (; t + kThinAhead < n; t += kThinAhead)
+    for (; t + kAhead < n; t += kAhead)
 #pragma unroll
-        for (int j = 0; j < kThinAhead; ++j)
-            thin_stage<GEMM, true>(src, lds, j & 1, r[j], acc, t + j + 1 + kThinAhead < n ? 1 : 0);
+        for (int j = 0; j < kAhead; ++j)
+            thin_stage<GEMM, NC, true>(src, lds, j & 1, r[j], acc, t + j + 1 + kAhead < n ? 1 : 0);
 #pragma unroll
-    for (int j = 0; j < kThinAhead; ++j)
-        if (t + j < n) thin_stage<GEMM, false>(src, lds, j & 1, r[j], acc, 0);
+    for (int j = 0; j < kAhead; ++j)
+        if (t + j < n) thin_stage<GEMM, NC, false>(src, lds, j & 1, r[j], acc, 0);
 }
 
 // One block of up to 32 rows (row0 .., `rows` valid) by the task's columns.
-// GEMM 1: h = silu(x W_gate) * (x W_up), columns [64 ct, +64); GEMM 2: o = h W_down, columns [128 ct, +128).
-template <int GEMM>
+// GEMM 1: h = silu(x W_gate) * (x W_up), columns [NC/2 ct, +NC/2); GEMM 2: o = h W_down, columns [NC ct, +NC).
+template <int GEMM, int NC>
 __device__ __forceinline__ void thin_block(const ThinParams& p, int e, int ct, int row0, int rows, lds_ptr_t images) {
+    constexpr int kFrags = ThinShape<NC>::kFrags;
     const int d = p.s.d, I = p.s.I;
-    f32x16_t acc;
+    f32x16_t acc[kFrags];
     {
         const Lane in;
-        const int K = GEMM == 1 ? d : I;
-        ThinSource<GEMM> src;
-        src.ldw = (uint32_t)(GEMM == 1 ? I : d) * 2;
+        const int K = GEMM == 1 ? d : I, n = GEMM == 1 ? I : d;
+        ThinSource<GEMM, NC> src;
+        src.ldw = (uint32_t)n * 2;
         const size_t first = ((size_t)e * K + 16 * in.wave_uniform()) * src.ldw;
-        if (GEMM == 1) {
-            src.w[0] = (glb_ptr_t)(p.w_gate + first + (size_t)ct * 128);
-            src.w[1] = (glb_ptr_t)(p.w_up + first + (size_t)ct * 128);
-            src.off = (in.l >> 3) * src.ldw + (in.l & 7) * 16;
-        } else {   // pieces past d alias the last one
-            src.w[0] = src.w[1] = (glb_ptr_t)(p.w_down + first);
-            src.off = (in.l >> 4) * src.ldw + (uint32_t)min(kThinCols * ct + 8 * (in.l & 15), d - 8) * 2;
-        }
+        src.w[0] = (glb_ptr_t)((GEMM == 1 ? p.w_gate : p.w_down) + first);
+        src.w[1] = (glb_ptr_t)((GEMM == 1 ? p.w_up : p.w_down) + first);
+        // pieces past the last column alias it
+        src.off = (in.l / src.kLanes) * src.ldw + (uint32_t)min((GEMM == 1 ? NC / 2 : NC) * ct + 8 * (in.l % src.kLanes), n - 8) * 2;
         const int r = row0 + min(8 * in.w + (in.l >> 3), rows - 1);   // rows past the last alias it
         const char* row = GEMM == 1 ? p.x + (size_t)(p.perm[r] / p.s.k) * d * 2 : p.h + (size_t)r * I * 2;
         src.x = (glb_ptr_t)(row + (in.l & 7) * 16);
-        thin_loop<GEMM>(src, ThinLds<GEMM>(images, in), K / BK, acc);
+        thin_loop<GEMM, NC>(src, ThinLds<GEMM, NC>(images, in), K / BK, acc);
     }
     const Lane out;
-    if (out.l31 >= rows) return;
+    if (out.l31 >= rows || (NC == 64 && out.w >= 2)) return;
     const size_t row = (size_t)(row0 + out.l31);
-    if (GEMM == 1) {
-        const int col = 64 * ct + 16 * out.w + 8 * out.hf;
-        if (p.gu) {
-            *(u32x4_t*)(p.gu + (row * 2 * I + col) * 2) = pack8(acc, 0);
-            *(u32x4_t*)(p.gu + (row * 2 * I + I + col) * 2) = pack8(acc, 1);
-        }
-        float hv[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float g = acc[j], u = acc[8 + j];
-            hv[j] = g * sigmoid_f(g) * u;
-        }
-        *(u32x4_t*)(p.h + (row * I + col) * 2) = u32x4_t{pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3]),
-                                                         pack_bf16x2(hv[4], hv[5]), pack_bf16x2(hv[6], hv[7])};
-    } else {
-        const int col = kThinCols * ct + 32 * out.w + 8 * out.hf;
+    for (int f = 0; f < kFrags; ++f) {
+        if (GEMM == 1) {
+            const int col = NC / 2 * ct + 16 * (kFrags * out.w + f) + 8 * out.hf;
+            if (NC == 256 && col >= I) continue;
+            if (p.gu) {
+                *(u32x4_t*)(p.gu + (row * 2 * I + col) * 2) = pack8(acc[f], 0);
+                *(u32x4_t*)(p.gu + (row * 2 * I + I + col) * 2) = pack8(acc[f], 1);
+            }
+            float hv[8];
 #pragma unroll
-        for (int vg = 0; vg < 2; ++vg)
-            if (col + 16 * vg < d) *(u32x4_t*)(p.o + (row * d + col + 16 * vg) * 2) = pack8(acc, vg);
+            for (int j = 0; j < 8; ++j) {
+                const float g = acc[f][j], u = acc[f][8 + j];
+                hv[j] = g * sigmoid_f(g) * u;
+            }
+            *(u32x4_t*)(p.h + (row * I + col) * 2) = u32x4_t{pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3]),
+                                                             pack_bf16x2(hv[4], hv[5]), pack_bf16x2(hv[6], hv[7])};
+        } else {
+            const int col = NC * ct + 32 * (kFrags * out.w + f) + 8 * out.hf;
+#pragma unroll
+            for (int vg = 0; vg < 2; ++vg)
+                if (col + 16 * vg < d) *(u32x4_t*)(p.o + (row * d + col + 16 * vg) * 2) = pack8(acc[f], vg);
+        }
     }
 }
 
 struct ThinShared {
-    __attribute__((aligned(16))) char images[2 * kThinImage];
+    union {
+        __attribute__((aligned(512))) char images[2 * kThinMostImage];
+        int32_t wave[4];           // of the search, before the first image
+    };
     int32_t row0[kMaxExperts];
-    int32_t rows[kMaxExperts];
+    uint16_t rows[kMaxExperts];    // (up to 32 tokens of 16 slots each, were they all of one expert)
     uint16_t expert[kMaxExperts];
-    int32_t wave[4];
 };
+static_assert(kThinGroupsPerCu * sizeof(ThinShared) <= 160 * 1024, "");
+
+// The tasks of `count` listed experts, every `blocks`-th from `block` on.
+template <int GEMM, int NC>
+__device__ __forceinline__ void thin_tasks(const ThinParams& p, int count, int block, int blocks, ThinShared& S) {
+    const int nct = GEMM == 1 ? (2 * p.s.I + NC - 1) / NC : (p.s.d + NC - 1) / NC;
+    const int even = (count & ~7) * nct;
+    for (int id = block; id < count * nct; id += blocks) {
+        int x, ct;
+        if (id < even) {
+            const int slot = id >> 3;
+            x = (slot / nct) * 8 + (id & 7);
+            ct = slot % nct;
+        } else {
+            x = (count & ~7) + (id - even) / nct;
+            ct = (id - even) % nct;
+        }
+        const int e = rfl(S.expert[x]), row0 = rfl(S.row0[x]), rows = rfl(S.rows[x]);
+        for (int r = 0; r < rows; r += kThinRows)   // more than one round only where max_rows is larger
+            thin_block<GEMM, NC>(p, e, ct, row0 + r, min(rows - r, kThinRows), (lds_ptr_t)S.images);
+    }
+}
 
 // Workgroup `block` of `blocks` (a multiple of 8, unless there are fewer tasks or the caller bounds the
 // workers): it finds the experts of this path by itself (their row counts come from the offsets) and takes
@@ -306,26 +368,14 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
         if (off[j + 1] > off[j] && off[j + 1] - off[j] <= p.rule.max_rows) {
             S.expert[at] = (uint16_t)(4 * tid + j);
             S.row0[at] = off[j];
-            S.rows[at] = off[j + 1] - off[j];
+            S.rows[at] = (uint16_t)(off[j + 1] - off[j]);
             ++at;
         }
     __syncthreads();
-    const int nct = GEMM == 1 ? p.s.I / 64 : (p.s.d + kThinCols - 1) / kThinCols;
-    const int even = (count & ~7) * nct;
-    for (int id = block; id < count * nct; id += blocks) {
-        int x, ct;
-        if (id < even) {
-            const int slot = id >> 3;
-            x = (slot / nct) * 8 + (id & 7);
-            ct = slot % nct;
-        } else {
-            x = (count & ~7) + (id - even) / nct;
-            ct = (id - even) % nct;
-        }
-        const int e = rfl(S.expert[x]), row0 = rfl(S.row0[x]), rows = rfl(S.rows[x]);
-        for (int r = 0; r < rows; r += kThinRows)   // more than one round only where max_rows is larger
-            thin_block<GEMM>(p, e, ct, row0 + r, min(rows - r, kThinRows), (lds_ptr_t)S.images);
-    }
+    const int cols = thin_cols(count, GEMM == 1 ? 2 * p.s.I : p.s.d, p.workers);
+    if (cols == 256) thin_tasks<GEMM, 256>(p, count, block, blocks, S);
+    else if (cols == 128) thin_tasks<GEMM, 128>(p, count, block, blocks, S);
+    else thin_tasks<GEMM, 64>(p, count, block, blocks, S);
 }
 
 }  // namespace uniep

@@ -62,10 +62,19 @@ def test_generation_step_without_a_stash(T, kw):
         assert torch.equal(y, gpu_forward(cfg, inp, schedule, 0)[0])
 
 
-# More tasks than workgroups (768 of them): a workgroup's images are used for one task after the other
+# More tasks than workgroups: a workgroup's images are used for one task after the other
 @pytest.mark.parametrize("rows,I", [([2] * 16, 4096), ([1, 0, 3] * 5, 8256)])
 def test_workgroups_with_several_tasks(rows, I):
     test_forward_at_row_counts(rows, 64, I)
+
+
+# Tasks of 256, 128 and 64 weight columns (as many experts as make each the choice on 256 CUs), the last one of an expert cut off
+# and not, in both GEMMs; k axes shorter than the stages on their way
+@pytest.mark.parametrize("E,d,I", [(128, 448, 256), (85, 512, 320), (86, 64, 384), (200, 576, 320), (230, 128, 64), (20, 320, 192)])
+def test_widths_of_a_task(E, d, I):
+    rows = np.random.default_rng(E).integers(0, 4, E)
+    rows[:4] = (32, 31, 17, 0)
+    test_forward_at_row_counts(rows.tolist(), d, I)
 
 
 # A caller may bring a routing in which a token's slots share an expert: more than 32 rows of an expert in a batch
