@@ -18,13 +18,13 @@ size_t fwd_workspace_bytes(const moe_shape_t& s);
 size_t fwd_ctrl_bytes(const moe_shape_t& s);
 int fwd_launch(const moe_shape_t& s, const void* x, const void* w_gate, const void* w_up,
                const void* w_down, const moe_routing_t& r, void* y, char* gu, char* h, char* o,
-               char* ws, const moe_opts_t& opts, int nw, hipStream_t st);
+               char* ws, const moe_opts_t& opts, hipStream_t st);
 size_t bwd_workspace_bytes(const moe_shape_t& s, int split_rows);
 bool bwd_split_ok(const moe_shape_t& s, int split_rows);
 int bwd_launch(const moe_shape_t& s, const void* dy, const void* x, const void* w_gate,
                const void* w_up, const void* w_down, const moe_routing_t& r, const char* gu,
                const char* h, const char* o, void* dx, void* dw_gate, void* dw_up, void* dw_down,
-               float* dtopk_w, char* ws, const moe_opts_t& opts, int nw, hipStream_t st);
+               float* dtopk_w, char* ws, const moe_opts_t& opts, hipStream_t st);
 }  // namespace uniep
 
 using namespace uniep;
@@ -66,12 +66,6 @@ int check_opts(const moe_opts_t* o, moe_opts_t* out) {
     *out = d;
     return MOE_OK;
 }
-
-// Waves per workgroup = row-tile height / 32.  256-row tiles (8 waves, two per
-// SIMD) by default at every size: waves whose rows lie outside a tile skip the
-// matrix work, and measured from 20 to 6000 rows per expert the 8-wave tiles
-// are 1.3-2x faster than the 4-wave ones.
-int pick_nw(const moe_shape_t&, const moe_opts_t& o) { return o.tile_rows == 128 ? 4 : 8; }
 
 struct SavedLayout {
     size_t gu, h, o, total;
@@ -247,7 +241,7 @@ int moe_fused_forward(const moe_shape_t* shape, const void* x, const void* w_gat
         ob = h + align_up(A_cap * shape->I * 2, 256);
     }
     return fwd_launch(*shape, x, w_gate, w_up, w_down, *routing, y, gu, h, ob, wsb, o,
-                      pick_nw(*shape, o), (hipStream_t)stream);
+                      (hipStream_t)stream);
 }
 
 int moe_fused_backward(const moe_shape_t* shape, const void* dy, const void* x, const void* w_gate,
@@ -275,7 +269,7 @@ int moe_fused_backward(const moe_shape_t* shape, const void* dy, const void* x, 
     const SavedLayout L = saved_layout(*shape);
     const char* sv = (const char*)saved;
     return bwd_launch(*shape, dy, x, w_gate, w_up, w_down, *routing, sv + L.gu, sv + L.h, sv + L.o,
-                      dx, dw_gate, dw_up, dw_down, dtopk_w, (char*)ws, o, pick_nw(*shape, o),
+                      dx, dw_gate, dw_up, dw_down, dtopk_w, (char*)ws, o,
                       (hipStream_t)stream);
 }
 

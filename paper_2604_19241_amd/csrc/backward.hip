@@ -65,7 +65,7 @@ struct BwdParams {
     int32_t* split_tile0;       // [e_count]  first entry of expert e in split_cnt
     char* split_buf;            // [slots][256 KB]  fp32 partial tiles in accumulator layout
     int n_dots;                 // partial sums per routed row: 4 * nct_dh
-    int bm;                     // rows per row tile (256, or 128)
+    TileRule tile;              // rows of the row tiles
     int workers;                // workgroups of the worker launch (the tail waits for all of them)
     long long spin_ticks;
 };
@@ -87,7 +87,8 @@ constexpr size_t kPartialTileBytes = (size_t)BMAX * BN * sizeof(float);
 // expert row r, row_w[r] = its gate (the backward "dispatch" of dY is a gather through these).
 __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
     __shared__ QueuePlan P;
-    const int ec = p.s.e_count, bm = p.bm;
+    const int ec = p.s.e_count;
+    const TileRule tile = p.tile;
     if (blockIdx.x >= kPlanBlocks) {
         const int r = ((int)blockIdx.x - kPlanBlocks) * kPlanThreads + threadIdx.x;
         if (r < p.offsets[ec]) {
@@ -107,12 +108,12 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
         return (p.split_rows > 0 && rows > p.split_rows) ? (rows + p.split_rows - 1) / p.split_rows : 1;
     };
     // (an expert without rows still has its weight gradients written)
-    make_plan(P, p.offsets, ec, 0, [](int) { return 0; }, bm, p.nct_dh, [&](int rows) { return row_tiles(rows, bm) * p.nct_dh; },
-              [&](int rows) { return row_tiles(rows, bm) * p.nct_dxp + (per_dwgu + per_dwd) * parts_of(rows); });
+    make_plan(P, p.offsets, ec, 0, [](int) { return 0; }, tile, p.nct_dh, [&](int rows) { return tile.tiles(rows) * p.nct_dh; },
+              [&](int rows) { return tile.tiles(rows) * p.nct_dxp + (per_dwgu + per_dwd) * parts_of(rows); });
     const int lane = threadIdx.x & 63;
     for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {   // one wave, one expert
-        const int rows_x = P.rows[x], nt_x = row_tiles(rows_x, bm), parts_x = parts_of(rows_x);
-        const int rt0 = plan_rt0(P, x), r0 = p.offsets[x], higher = higher_tiles(rows_x, bm);
+        const int rows_x = P.rows[x], nt_x = tile.tiles(rows_x), parts_x = parts_of(rows_x);
+        const int rt0 = tile.flags(plan_rt0(P, x)), r0 = p.offsets[x], higher = tile.higher(rows_x);
         const int n_dxp = nt_x * p.nct_dxp;
         for (int i = lane; i < nt_x; i += 64) p.flag_rt[rt0 + i] = 0;
         if (lane == 0) p.flag_e[x] = 0;
@@ -142,11 +143,11 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
         // tile), weight-gradient GEMMs over (output row tile, output column tile)
         for_each_tile(lane, nt_x, p.nct_dh, [&](int j, int ct) {
             ta[block_pos<true>(j, ct, nt_x, p.nct_dh)] =
-                Task{rt0 + j, task_code(B_DH, x, ct), r0 + tile_first(j, higher, bm), tile_rows(j, higher, bm, rows_x)};
+                Task{rt0 + j, task_code(B_DH, x, ct), r0 + tile.first(j, higher), tile.rows_of(j, higher, rows_x)};
         });
         for_each_tile(lane, nt_x, p.nct_dxp, [&](int j, int ct) {
             tb[block_pos<true>(j, ct, nt_x, p.nct_dxp)] =
-                Task{rt0 + j, task_code(B_DXP, x, ct), r0 + tile_first(j, higher, bm), tile_rows(j, higher, bm, rows_x)};
+                Task{rt0 + j, task_code(B_DXP, x, ct), r0 + tile.first(j, higher), tile.rows_of(j, higher, rows_x)};
         });
         // weight-gradient tasks: idx = output row tile | part << 8 | parts << 20; row0 / rows = the part's rows
         for_each_tile(lane, p.mt_dwgu, p.nt_dwgu, [&](int mt, int nt) {
@@ -645,7 +646,7 @@ __device__ __forceinline__ void bwd_worker_body(const BwdParams& p, int phase, c
                 const int e = task_expert(task);
                 // rows of the whole expert (a part of a split reduction carries only its own share)
                 const int rows_e = SPLIT ? p.offsets[e + 1] - p.offsets[e] : task.rows;
-                const int need = row_tiles(rows_e, p.bm) * p.nct_dh;
+                const int need = p.tile.tiles(rows_e) * p.nct_dh;
                 // a worker takes several of an expert's 72 output tiles in a row: the expert it has
                 // already seen complete (and acquired) needs no second look at the flag
                 if (e != seen_e) {
@@ -757,7 +758,7 @@ static BwdLayout bwd_layout(const moe_shape_t& s, int split_rows) {
                              (s.T + kDxTokens - 1) / kDxTokens;
     size_t off = 0;
     L.ctrl = off;    off = align_up(off + CTRL_WORDS * sizeof(int), 256);
-    L.flag_rt = off; off = align_up(off + (size_t)L.max_rt * sizeof(int), 256);
+    L.flag_rt = off; off = align_up(off + ((size_t)L.max_rt + s.e_count) * sizeof(int), 256);   // (two an expert more than whole slots)
     L.flag_e = off;  off = align_up(off + (size_t)s.e_count * sizeof(int), 256);
     L.tasks = off;   off = align_up(off + max_tasks * sizeof(Task), 256);
     L.row_tok = off; off = align_up(off + A_cap * sizeof(int32_t), 256);
@@ -810,14 +811,14 @@ static void launch_worker(bool acc, bool split, const BwdParams& p, int workers,
     hipLaunchKernelGGL(bwd_worker_fn(acc, split), dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, phase);
 }
 
-static int bwd_launch_bm(BwdParams& p, const moe_opts_t& opts, int bm, hipStream_t st) {
+static int bwd_launch_tiles(BwdParams& p, const moe_opts_t& opts, hipStream_t st) {
     const bool acc = opts.dw_accumulate != 0, split = opts.dw_split_rows > 0;
     int resident = 0;
     int rc = bwd_resident_workers(acc, split, &resident);
     if (rc != MOE_OK) return rc;
     const int workers = opts.workers > 0 ? min(opts.workers, resident) : resident;
     p.workers = workers;
-    p.bm = bm;
+    p.tile = tile_rule(p.s, opts.tile_rows, p.nct_dh + p.nct_dxp, workers, 3);
     const int A_cap = p.s.T * p.s.k;
     hipLaunchKernelGGL(bwd_first_kernel, dim3(kPlanBlocks + (A_cap + kPlanThreads - 1) / kPlanThreads), dim3(kPlanThreads),
                        0, st, p);
@@ -843,7 +844,7 @@ static int bwd_launch_bm(BwdParams& p, const moe_opts_t& opts, int bm, hipStream
 int bwd_launch(const moe_shape_t& s, const void* dy, const void* x, const void* w_gate,
                const void* w_up, const void* w_down, const moe_routing_t& r, const char* gu,
                const char* h, const char* o, void* dx, void* dw_gate, void* dw_up, void* dw_down,
-               float* dtopk_w, char* ws, const moe_opts_t& opts, int nw, hipStream_t st) {
+               float* dtopk_w, char* ws, const moe_opts_t& opts, hipStream_t st) {
     const BwdLayout L = bwd_layout(s, opts.dw_split_rows);
     BwdParams p;
     p.s = s;
@@ -888,7 +889,7 @@ int bwd_launch(const moe_shape_t& s, const void* dy, const void* x, const void* 
     p.nt_dwgu = L.nt_dwgu;
     const int ms = opts.spin_limit_ms > 0 ? opts.spin_limit_ms : 2000;
     p.spin_ticks = (long long)ms * 100000ll;
-    return bwd_launch_bm(p, opts, nw == 4 ? 128 : 256, st);
+    return bwd_launch_tiles(p, opts, st);
 }
 
 }  // namespace uniep

@@ -266,31 +266,49 @@ __device__ __forceinline__ int queue_lag(int total_producer_tasks, int ec) {
 }
 
 
-// Scoreboard slots of an expert's row tiles: one for every bm = 256 or 128 rows.
-__device__ __forceinline__ int row_slots(int rows, int bm) { return (rows + bm - 1) >> (bm == 256 ? 8 : 7); }
-// Row tiles of an expert.  A tile costs its stream of weights whatever its rows (one of some 20 rows 0.43 of a full one), and
-// batches are powers of two more often than not, so that many experts have just over a multiple of 256 rows: up to
-// three of the others take 32 rows each of a last tile that has no more.  A higher tile costs 0.11 of a tile beyond its
-// share of the work: with eight of them in place of one (4096 rows) the layer took 3 % longer, with three (1875 rows) 1 %
-// less, with one (512 rows and some) the forward pass 6 % less and (256 and some) 17 %.  Past 16 tiles there is nothing
-// to gain.
-constexpr int kMostHigher = 3, kMostTiles = 16;
-__device__ __forceinline__ int higher_tiles(int rows, int bm) {
-    const int n = row_slots(rows, bm), m = (rows - (n - 1) * bm + 31) >> 5;
-    return bm == 256 && n <= kMostTiles && m <= min(kMostHigher, n - 1) ? m : 0;
-}
-__device__ __forceinline__ int row_tiles(int rows, int bm) { return row_slots(rows, bm) - (higher_tiles(rows, bm) > 0 ? 1 : 0); }
-// First row of an expert's tile j, the first `higher` tiles being higher, and the rows of it.
-__device__ __forceinline__ int tile_first(int j, int higher, int bm) { return j * bm + 32 * min(j, higher); }
-__device__ __forceinline__ int tile_rows(int j, int higher, int bm, int rows) {
-    return min(bm + (j < higher ? 32 : 0), rows - tile_first(j, higher, bm));
+// How a pass cuts an expert's rows into tiles of bm = 256 or 128 rows.  A tile costs its stream of weights whatever its rows (one of
+// some 20 rows 0.43 of a full one), and batches are powers of two more often than not, so that many experts have just over a
+// multiple of 256 rows: up to most_higher of the others take 32 rows each of a last tile that has no more.  A higher tile
+// costs 0.11 of a tile beyond its share of the work: with eight of them in place of one (4096 rows) the layer took 3 %
+// longer, with three (1875 rows) 1 % less, with one (512 rows and some) the forward pass 6 % less and (256 and some) 17 %.
+// Past 16 tiles there is nothing to gain.
+struct TileRule {
+    int bm;
+    int most_higher;   // kMostHigher or 0
+    // scoreboard slots of an expert: one for every 256 rows; tiles of 128 rows have two flags a slot
+    static __device__ __forceinline__ int slots(int rows) { return (rows + 255) >> 8; }
+    __device__ __forceinline__ int flags(int slot) const { return bm == 256 ? slot : 2 * slot; }
+    // how many of the tiles are 32 rows higher
+    __device__ __forceinline__ int higher(int rows) const {
+        const int n = slots(rows), m = (rows - (n - 1) * 256 + 31) >> 5;
+        return n <= kMostTiles && m <= min(most_higher, n - 1) ? m : 0;
+    }
+    __device__ __forceinline__ int tiles(int rows) const {
+        return bm == 256 ? slots(rows) - (higher(rows) > 0 ? 1 : 0) : (rows + 127) >> 7;
+    }
+    // first row of tile j, the first `h` tiles being higher, and the rows of it
+    __device__ __forceinline__ int first(int j, int h) const { return j * bm + 32 * min(j, h); }
+    __device__ __forceinline__ int rows_of(int j, int h, int rows) const { return min(bm + (j < h ? 32 : 0), rows - first(j, h)); }
+    static constexpr int kMostHigher = 3, kMostTiles = 16;
+};
+// col_tiles: column tiles an expert of the pass's row-tile GEMMs; halves / 2: tasks of 256 rows a CU (on average) below which tiles
+// have 128 rows.  Where CUs are idle, two tiles side by side take less than one, and low tiles keep two stages on their way
+// (mma_low; not worth it for GEMMs of a few stages).  Measured, us with tiles of 256 / of 128 rows (tasks a CU): training
+// steps of 1000 tokens on 8 experts of 512 x 1024 (0.3) 176 / 133, 1500 on 2 of 8 of 4096 x 14336 (0.8) 1660 / 1407, 4096 on 16 of 128 of 4096 x 1536
+// (1.4) 806 / 762, 8000 on 8 of 512 x 1024 (1.5) 320 / 318, 20000 on 32 of 128 of 1024 x 384 (2.8) 413 / 441; forward passes of 4099 tokens on
+// 16 of 64 of 2048 x 1408 (1.8) 180 / 173, 10000 on 8 of 512 x 1024 (3.0) 111 / 125.  Higher tiles from 3 tasks a CU on:
+// training steps without / with, 3000 tokens on 16 of 64 of 1280 x 896 (0.8) 265 / 276, 8192 on 32 of 256 of 7168 x 2048 (5.5) 3169 / 2960.
+inline TileRule tile_rule(const moe_shape_t& s, int tile_rows, int col_tiles, int workers, int halves) {
+    const long long tasks = (long long)s.T * s.k * s.e_count / s.E * col_tiles / 256;
+    const bool low = tile_rows == 128 || (tile_rows == 0 && 2 * tasks < (long long)halves * workers && s.d + s.I >= 8 * 64);
+    return low ? TileRule{128, 0} : TileRule{256, tasks >= 3ll * workers ? TileRule::kMostHigher : 0};
 }
 // The plan of this workgroup (kPlanThreads threads, all of them call; ends with a barrier).
 // a_of(rows) / b_of(rows): tasks of an expert's producer and consumer block; `per_row_tile` producer tasks for
-// each bm rows.  limit > 0: experts with up to skip_of(counts) rows have no tasks, where counts is the
+// each scoreboard slot.  limit > 0: experts with up to skip_of(counts) rows have no tasks, where counts is the
 // number of experts with 1..limit rows and, shifted left by 16, of those with more.
 template <class FS, class FA, class FB>
-__device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, int ec, int limit, FS skip_of, int bm,
+__device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, int ec, int limit, FS skip_of, const TileRule& tile,
                                           int per_row_tile, FA a_of, FB b_of) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
@@ -317,7 +335,7 @@ __device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, 
     P.hist[w][lane] = 0;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int e = 256 * w + 64 * r + lane, nt = row_slots(rows[r], bm);
+        const int e = 256 * w + 64 * r + lane, nt = tile.slots(rows[r]);
         int incl = nt;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -430,7 +448,7 @@ __device__ __forceinline__ void make_plan(QueuePlan& P, const int32_t* offsets, 
         P.base[kQueues] = base;
         for (int i = 0; i < kPlanWaves; ++i) n += P.sums[i];
         P.n_row_tiles = n;
-        P.lag = queue_lag(n * per_row_tile, ec);
+        P.lag = queue_lag(tile.flags(n) * per_row_tile, ec);
     }
     __syncthreads();
 }

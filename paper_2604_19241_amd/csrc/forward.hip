@@ -40,7 +40,7 @@ struct FwdParams {
     Task* tasks;
     int nct1, nct2;   // column tiles of GEMM1 (128 h-columns each) and GEMM2 (256 each)
     int workers;   // workgroups of the worker launch (the tail waits for all of them)
-    int bm;            // rows per row tile (256, or 128)
+    TileRule tile;     // rows of the row tiles
     ThinRule rule;     // which experts are run outside the work queue; max_rows = 0: none
     int plan_blocks;   // workgroups of the first launch that make the queue: kPlanBlocks, or 0 if there is none
     long long spin_ticks;
@@ -51,25 +51,26 @@ struct FwdParams {
 // row-tile table from the expert offsets, the per-XCD task lists (GEMM1 block of expert i+1 ahead of the
 // GEMM2 block of expert i) and a cleared scoreboard.
 __device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePlan& P) {
-    const int ec = p.s.e_count, bm = p.bm;
-    make_plan(P, p.offsets, ec, p.rule.max_rows, [&](int counts) { return p.rule.limit(counts); }, bm, p.nct1,
-              [&](int rows) { return row_tiles(rows, bm) * p.nct1; },
-              [&](int rows) { return row_tiles(rows, bm) * p.nct2; });
+    const int ec = p.s.e_count;
+    const TileRule tile = p.tile;
+    make_plan(P, p.offsets, ec, p.rule.max_rows, [&](int counts) { return p.rule.limit(counts); }, tile, p.nct1,
+              [&](int rows) { return tile.tiles(rows) * p.nct1; },
+              [&](int rows) { return tile.tiles(rows) * p.nct2; });
     const int lane = threadIdx.x & 63;
     for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {
-        const int rows_x = P.rows[x], nt_x = row_tiles(rows_x, bm);
+        const int rows_x = P.rows[x], nt_x = tile.tiles(rows_x);
         if (nt_x == 0) continue;
-        const int rt0 = plan_rt0(P, x), r0 = p.offsets[x], higher = higher_tiles(rows_x, bm);
+        const int rt0 = tile.flags(plan_rt0(P, x)), r0 = p.offsets[x], higher = tile.higher(rows_x);
         for (int i = lane; i < nt_x; i += 64) p.flag1[rt0 + i] = 0;
         Task* t1 = p.tasks + plan_a(P, x);
         Task* t2 = p.tasks + plan_b(P, x);
         for_each_tile(lane, nt_x, p.nct1, [&](int j, int ct) {
             t1[block_pos<true>(j, ct, nt_x, p.nct1)] =
-                Task{rt0 + j, task_code(TASK_GEMM1, x, ct), r0 + tile_first(j, higher, bm), tile_rows(j, higher, bm, rows_x)};
+                Task{rt0 + j, task_code(TASK_GEMM1, x, ct), r0 + tile.first(j, higher), tile.rows_of(j, higher, rows_x)};
         });
         for_each_tile(lane, nt_x, p.nct2, [&](int j, int ct) {
             t2[block_pos<true>(j, ct, nt_x, p.nct2)] =
-                Task{rt0 + j, task_code(TASK_GEMM2, x, ct), r0 + tile_first(j, higher, bm), tile_rows(j, higher, bm, rows_x)};
+                Task{rt0 + j, task_code(TASK_GEMM2, x, ct), r0 + tile.first(j, higher), tile.rows_of(j, higher, rows_x)};
         });
     }
     if (block == 0) write_ctrl(P, p.ctrl, (p.s.T + kCombineTokens - 1) / kCombineTokens, p.workers);
@@ -408,7 +409,7 @@ __global__ void __launch_bounds__(64 * kTailWaves) fwd_tail_kernel(FwdParams p, 
 
 struct FwdLayout {
     size_t ctrl, flag1, tasks, h, o, total;
-    int max_rt, nct1, nct2;
+    int max_rt, nct1, nct2;   // (tiles of 128 rows)
     size_t max_tasks;
 };
 
@@ -421,7 +422,7 @@ FwdLayout fwd_layout(const moe_shape_t& s, bool with_ho) {
     L.max_tasks = (size_t)L.max_rt * (L.nct1 + L.nct2) + (s.T + kCombineTokens - 1) / kCombineTokens;
     size_t off = 0;
     L.ctrl = off;  off = align_up(off + CTRL_WORDS * sizeof(int), 256);
-    L.flag1 = off; off = align_up(off + (size_t)L.max_rt * sizeof(int), 256);
+    L.flag1 = off; off = align_up(off + ((size_t)L.max_rt + s.e_count) * sizeof(int), 256);   // (two an expert more than whole slots)
     L.tasks = off; off = align_up(off + L.max_tasks * sizeof(Task), 256);
     L.h = off;     if (with_ho) off = align_up(off + A_cap * s.I * 2, 256);
     L.o = off;     if (with_ho) off = align_up(off + A_cap * s.d * 2, 256);
@@ -468,15 +469,13 @@ static void launch_tail(const FwdParams& p, hipStream_t st) {
     });
 }
 
-// BM = rows per row tile: 256, or 128 (every tile then leaves the upper half of the workgroup's
-// rows empty; kept as an option because results must not depend on it).
-static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream_t st) {
+static int fwd_launch_tiles(FwdParams& p, const moe_opts_t& opts, hipStream_t st) {
     int resident = 0;
     int rc = resident_workers(&resident);
     if (rc != MOE_OK) return rc;
     int workers = opts.workers > 0 ? min(opts.workers, resident) : resident;
     p.workers = workers;
-    p.bm = bm;
+    p.tile = tile_rule(p.s, opts.tile_rows, p.nct1 + p.nct2, workers, 4);
     // A token selects an expert at most once, so up to kThinRows tokens no expert has more rows than
     // that: every expert is thin and no work queue is set up.
     const bool all_thin = p.s.T <= kThinRows;
@@ -514,7 +513,7 @@ static int fwd_launch_bm(FwdParams& p, const moe_opts_t& opts, int bm, hipStream
 
 int fwd_launch(const moe_shape_t& s, const void* x, const void* w_gate, const void* w_up,
                const void* w_down, const moe_routing_t& r, void* y, char* gu, char* h, char* o,
-               char* ws, const moe_opts_t& opts, int nw, hipStream_t st) {
+               char* ws, const moe_opts_t& opts, hipStream_t st) {
     const FwdLayout L = fwd_layout(s, false);
     FwdParams p;
     p.s = s;
@@ -537,7 +536,7 @@ int fwd_launch(const moe_shape_t& s, const void* x, const void* w_gate, const vo
     p.nct2 = L.nct2;
     const int ms = opts.spin_limit_ms > 0 ? opts.spin_limit_ms : 2000;
     p.spin_ticks = (long long)ms * 100000ll;   // wall_clock64 ticks at 100 MHz
-    return fwd_launch_bm(p, opts, nw == 4 ? 128 : 256, st);
+    return fwd_launch_tiles(p, opts, st);
 }
 
 

@@ -7,7 +7,7 @@
 // columns and stores 16 bytes).  Wave w = 4 wm + wn owns rows [128 wm, +128) as 4 fragments
 // of 32 and columns [64 wn, +64) as 2 fragments of 32: 8 accumulators of
 // v_mfma_f32_32x32x16_bf16, 6 fragment reads per 8 matrix instructions.  A tile of a row-tile GEMM may have
-// 32 rows more (see higher_tiles): the two waves of a wave column then each multiply them by one of its two
+// 32 rows more (see TileRule): the two waves of a wave column then each multiply them by one of its two
 // column fragments, a ninth accumulator.
 //
 // K advances in stages of 64.  A stage of an operand is a 32 KB LDS image in one of two forms (36 KB for 288 rows):

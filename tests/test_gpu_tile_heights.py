@@ -26,7 +26,7 @@ def run(cfg, inp, tile_rows):
     routing, saved = moe.moe_route(shape, dev["logits"]), moe.alloc_saved(shape, "cuda")
     size = moe.moe_workspace_bytes(shape)
     ws = {key: torch.empty(size[key], dtype=torch.uint8, device="cuda") for key in ("fwd", "bwd")}
-    opts = moe.make_opts(tile_rows=tile_rows, spin_limit_ms=500)
+    opts = moe.make_opts(tile_rows=tile_rows, workers=2, spin_limit_ms=500)   # (few workers: enough tasks for each)
     w = [dev[key] for key in ("w_gate", "w_up", "w_down")]
     out = {"y": moe.moe_fused_forward(shape, dev["x"], *w, routing, saved=saved, ws=ws["fwd"], opts=opts)}
     out.update(moe.moe_fused_backward(shape, dev["dy"], dev["x"], *w, routing, saved, ws=ws["bwd"], opts=opts))
@@ -46,7 +46,7 @@ def test_higher_tiles(counts, d, I):
     own = np.random.default_rng(T).permutation(np.repeat(np.arange(E), counts))
     inp["logits"] = torch.from_numpy(np.eye(E, dtype=np.float32)[own])
     say(f"[heights] rows {counts} d={d} I={I}")
-    got, tasks = run(cfg, inp, 0)
+    got, tasks = run(cfg, inp, 256)
     n, of = sum(tiles(c) for c in counts), lambda v, size: -(-v // size)
     wgrad = E * (of(I, 256) * of(d, 256) + of(d, 256) * of(I, 128))
     assert tasks == [n * (of(I, 128) + of(d, 256)), n * (of(I, 256) + of(d, 256)) + wgrad]
@@ -60,3 +60,41 @@ def test_higher_tiles(counts, d, I):
     for key in ("y", "dx", "dw_gate", "dw_up", "dw_down"):
         check_elementwise(key, to_f64(got[key]), ref[key])
     check_elementwise("dtopk_w", to_f64(got["dtopk_w"]), ref["dtopk_w"], whole_array_rms=True)
+
+
+# Tiles of 128 rows by the sizes: below two tasks a worker forward and one and a half backward, none where the GEMMs have
+# a few stages; two flags a scoreboard slot, at row counts around a slot's edges
+@pytest.mark.parametrize("d,I,workers,low", [(320, 448, 0, (True, True)), (320, 448, 30, (False, False)), (320, 448, 40, (False, True)),
+                                             (64, 64, 0, (False, False))])
+def test_low_tiles_by_the_sizes(d, I, workers, low):
+    counts = [127, 128, 129, 255, 256, 257, 384, 385, 512, 513, 1, 0, 700]
+    E, T = len(counts), sum(counts)
+    cfg = moe_synth.small_config(T=T, d=d, E=E, k=1, I=I)
+    inp = scaled_inputs(cfg, 3, 4.0)
+    own = np.random.default_rng(T).permutation(np.repeat(np.arange(E), counts))
+    inp["logits"] = torch.from_numpy(np.eye(E, dtype=np.float32)[own])
+    say(f"[heights] d={d} I={I} workers={workers}")
+    shape = moe.make_shape(**cfg.shape_dict())
+    dev = {key: v.cuda() for key, v in inp.items()}
+    routing = moe.moe_route(shape, dev["logits"])
+    size = moe.moe_workspace_bytes(shape)
+    w = [dev[key] for key in ("w_gate", "w_up", "w_down")]
+    of = lambda v, size: -(-v // size)
+    wgrad = E * (of(I, 256) * of(d, 256) + of(d, 256) * of(I, 128))
+    got = {}
+    for tile_rows in (0, 256, 128):
+        saved = moe.alloc_saved(shape, "cuda")
+        ws = {key: torch.empty(size[key], dtype=torch.uint8, device="cuda") for key in ("fwd", "bwd")}
+        opts = moe.make_opts(tile_rows=tile_rows, workers=workers, spin_limit_ms=500)
+        got[tile_rows] = {"y": moe.moe_fused_forward(shape, dev["x"], *w, routing, saved=saved, ws=ws["fwd"], opts=opts)}
+        got[tile_rows].update(moe.moe_fused_backward(shape, dev["dy"], dev["x"], *w, routing, saved, ws=ws["bwd"], opts=opts))
+        assert moe.moe_device_status(ws["fwd"]) == 0 and moe.moe_device_status(ws["bwd"]) == 0
+        if tile_rows == 0:
+            tasks = [int(ws[key].view(torch.int32)[LENGTHS:LENGTHS + 8].sum()) for key in ("fwd", "bwd")]
+    n = [sum(of(c, 128) if l else of(c, 256) for c in counts) for l in low]
+    few = sum(1 for c in counts if 0 < c <= 32)   # ahead of the queue or on it: as the plan's own rule says
+    assert tasks[0] in (n[0] * (of(I, 128) + of(d, 256)), (n[0] - few) * (of(I, 128) + of(d, 256)))
+    assert tasks[1] == n[1] * (of(I, 256) + of(d, 256)) + wgrad
+    for tile_rows in (256, 128):
+        for key, v in got[tile_rows].items():
+            assert torch.equal(v, got[0][key]), (tile_rows, key)
