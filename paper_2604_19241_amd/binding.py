@@ -50,6 +50,20 @@ class MoEError(RuntimeError):
         super().__init__(f"{where}: {status_string(code)} ({code})")
 
 
+# Every function that takes a pointer from _ptr or _stream: with the types declared once, pointers and sizes go over as plain integers (an object made for each
+# argument of each call took as long as two launches).
+_P, _N, _I = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int32
+_ARGTYPES = {
+    "moe_route": [_P, _P, _P, _P, _N, _P],
+    "moe_route_static": [_P, _P, _P, _P],
+    "moe_fused_forward": [_P] * 9 + [_N, _P, _P],
+    "moe_fused_backward": [_P] * 14 + [_N, _P, _P],
+    "moe_route_backward": [_P] * 6,
+    "moe_global_map": [_P, _I, _I, _P, _P, _P, _P, _N, _P],
+    "moe_device_status": [_P, _P],
+    "moe_calibration_copy": [_P, _P, _N, _P],
+    "moe_calibration_mfma": [_I, _I, _I, _P, _P, _P, _P],
+}
 _lib = None
 
 
@@ -66,6 +80,8 @@ def load_library():
         lib.moe_status_string.argtypes = [ctypes.c_int]
         for name in EXPORTS:
             getattr(lib, name)   # AttributeError if a declared symbol is not exported
+        for name, types in _ARGTYPES.items():
+            getattr(lib, name).argtypes = types
         _lib = lib
     return _lib
 
@@ -95,11 +111,11 @@ def make_opts(schedule=0, workers=0, spin_limit_ms=0, tile_rows=0, skip_tail=0,
 
 
 def _ptr(t):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device):
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def moe_workspace_bytes(shape: MoEShape) -> dict:
@@ -134,8 +150,8 @@ class Routing:
     inv_perm: torch.Tensor   # [T,k] i32
 
     def c_struct(self) -> MoERoutingC:
-        return MoERoutingC(*(t.data_ptr() for t in (self.topk_idx, self.topk_w, self.counts,
-                                                    self.offsets, self.perm, self.inv_perm)))
+        return MoERoutingC(self.topk_idx.data_ptr(), self.topk_w.data_ptr(), self.counts.data_ptr(),
+                           self.offsets.data_ptr(), self.perm.data_ptr(), self.inv_perm.data_ptr())
 
 
 def _ws(nbytes: int, device) -> torch.Tensor:
@@ -146,18 +162,12 @@ def moe_route(shape: MoEShape, logits: torch.Tensor, ws: torch.Tensor | None = N
     assert logits.is_cuda and logits.dtype == torch.float32 and logits.is_contiguous()
     assert tuple(logits.shape) == (shape.T, shape.E)
     dev = logits.device
-    T, k, ec = shape.T, shape.k, shape.e_count
-    r = Routing(torch.empty((T, k), dtype=torch.int32, device=dev),
-                torch.empty((T, k), dtype=torch.float32, device=dev),
-                torch.empty(ec, dtype=torch.int32, device=dev),
-                torch.empty(ec + 1, dtype=torch.int32, device=dev),
-                torch.empty(T * k, dtype=torch.int32, device=dev),
-                torch.empty((T, k), dtype=torch.int32, device=dev))
+    r = alloc_routing(shape, dev)
     if ws is None:
         ws = _ws(moe_workspace_bytes(shape)["route"], dev)
     cs = r.c_struct()
     _check(load_library().moe_route(ctypes.byref(shape), _ptr(logits), ctypes.byref(cs), _ptr(ws),
-                                    ctypes.c_size_t(ws.numel()), _stream(dev)), "moe_route")
+                                    ws.numel(), _stream(dev)), "moe_route")
     return r
 
 
@@ -174,12 +184,11 @@ def moe_route_static(shape: MoEShape, logits: torch.Tensor, out: Routing) -> Rou
 
 def alloc_routing(shape: MoEShape, device) -> Routing:
     T, k, ec = shape.T, shape.k, shape.e_count
-    return Routing(torch.empty((T, k), dtype=torch.int32, device=device),
-                   torch.empty((T, k), dtype=torch.float32, device=device),
-                   torch.empty(ec, dtype=torch.int32, device=device),
-                   torch.empty(ec + 1, dtype=torch.int32, device=device),
-                   torch.empty(T * k, dtype=torch.int32, device=device),
-                   torch.empty((T, k), dtype=torch.int32, device=device))
+    topk_idx = torch.empty((T, k), dtype=torch.int32, device=device)
+    counts = torch.empty(ec, dtype=torch.int32, device=device)
+    # (empty_like and new_empty: half the time of a call that names type and device)
+    return Routing(topk_idx, torch.empty((T, k), dtype=torch.float32, device=device), counts,
+                   counts.new_empty(ec + 1), counts.new_empty(T * k), torch.empty_like(topk_idx))
 
 
 def moe_calibration_mfma(workgroups: int, waves: int, iters: int, device="cuda") -> dict:
@@ -217,7 +226,7 @@ def moe_fused_forward(shape: MoEShape, x, w_gate, w_up, w_down, routing: Routing
     cs = routing.c_struct()
     _check(load_library().moe_fused_forward(
         ctypes.byref(shape), _ptr(x), _ptr(w_gate), _ptr(w_up), _ptr(w_down), ctypes.byref(cs),
-        _ptr(y), _ptr(saved), _ptr(ws), ctypes.c_size_t(ws.numel()),
+        _ptr(y), _ptr(saved), _ptr(ws), ws.numel(),
         ctypes.byref(opts) if opts is not None else None, _stream(dev)), "moe_fused_forward")
     return y
 
@@ -251,7 +260,7 @@ def moe_fused_backward(shape: MoEShape, dy, x, w_gate, w_up, w_down, routing: Ro
     _check(load_library().moe_fused_backward(
         ctypes.byref(shape), _ptr(dy), _ptr(x), _ptr(w_gate), _ptr(w_up), _ptr(w_down),
         ctypes.byref(cs), _ptr(saved), _ptr(out["dx"]), _ptr(out["dw_gate"]), _ptr(out["dw_up"]),
-        _ptr(out["dw_down"]), _ptr(out.get("dtopk_w")), _ptr(ws), ctypes.c_size_t(ws.numel()),
+        _ptr(out["dw_down"]), _ptr(out.get("dtopk_w")), _ptr(ws), ws.numel(),
         ctypes.byref(opts) if opts is not None else None, _stream(dev)), "moe_fused_backward")
     return out
 
@@ -263,10 +272,8 @@ def moe_route_backward(shape: MoEShape, routing: "Routing", dtopk_w: torch.Tenso
     assert dtopk_w.dtype == torch.float32 and dtopk_w.is_contiguous()
     if out is None:
         out = torch.empty((shape.T, shape.E), dtype=torch.float32, device=dev)
-    lib = load_library()
-    lib.moe_route_backward.argtypes = [ctypes.c_void_p] * 6
-    _check(lib.moe_route_backward(ctypes.byref(shape), _ptr(routing.topk_idx), _ptr(routing.topk_w),
-                                  _ptr(dtopk_w), _ptr(out), _stream(dev)), "moe_route_backward")
+    _check(load_library().moe_route_backward(ctypes.byref(shape), _ptr(routing.topk_idx), _ptr(routing.topk_w),
+                                             _ptr(dtopk_w), _ptr(out), _stream(dev)), "moe_route_backward")
     return out
 
 
@@ -296,23 +303,17 @@ def moe_global_map(shape: MoEShape, W: int, rank: int, routing: "Routing", c_all
     assert tuple(c_all.shape) == (W, shape.E)
     T, k = shape.T, shape.k
 
-    def i32(*size):
-        return torch.empty(size, dtype=torch.int32, device=dev)
-
-    g = GlobalMap(i32(T, k), i32(T, k), i32(T, k), i32(T, k), i32(T, k), i32(T),
-                  i32(shape.E // max(W, 1) + 1))
+    like = torch.empty_like
+    dst_rank = c_all.new_empty((T, k))
+    g = GlobalMap(dst_rank, like(dst_rank), like(dst_rank), like(dst_rank), like(dst_rank), c_all.new_empty(T),
+                  c_all.new_empty(shape.E // max(W, 1) + 1))
     if ws is None:
         ws = _ws(8 * shape.E, dev)
     cs = routing.c_struct()
-    gs = MoEGlobalMapC(*(t.data_ptr() for t in (g.dst_rank, g.dst_expert, g.dst_off, g.dst_row,
-                                                g.send, g.n_dst_ranks, g.recv_offsets)))
-    lib = load_library()
-    lib.moe_global_map.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p,
-                                   ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
-                                   ctypes.c_size_t, ctypes.c_void_p]
-    _check(lib.moe_global_map(ctypes.byref(shape), int(W), int(rank), ctypes.byref(cs), _ptr(c_all),
-                              ctypes.byref(gs), _ptr(ws), ctypes.c_size_t(ws.numel()),
-                              _stream(dev)), "moe_global_map")
+    gs = MoEGlobalMapC(g.dst_rank.data_ptr(), g.dst_expert.data_ptr(), g.dst_off.data_ptr(), g.dst_row.data_ptr(),
+                       g.send.data_ptr(), g.n_dst_ranks.data_ptr(), g.recv_offsets.data_ptr())
+    _check(load_library().moe_global_map(ctypes.byref(shape), int(W), int(rank), ctypes.byref(cs), _ptr(c_all),
+                                         ctypes.byref(gs), _ptr(ws), ws.numel(), _stream(dev)), "moe_global_map")
     return g
 
 
@@ -325,9 +326,7 @@ def moe_calibration_copy(dst: torch.Tensor, src: torch.Tensor) -> None:
     assert dst.is_cuda and src.is_cuda and dst.is_contiguous() and src.is_contiguous()
     nbytes = src.numel() * src.element_size()
     assert dst.numel() * dst.element_size() == nbytes
-    lib = load_library()
-    lib.moe_calibration_copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
-    _check(lib.moe_calibration_copy(_ptr(dst), _ptr(src), nbytes, _stream(src.device)),
+    _check(load_library().moe_calibration_copy(_ptr(dst), _ptr(src), nbytes, _stream(src.device)),
            "moe_calibration_copy")
 
 
