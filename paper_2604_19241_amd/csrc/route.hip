@@ -115,10 +115,13 @@ __device__ __forceinline__ int block_exclusive_sum(int v, int32_t* s_wave, int* 
 // One token's logits: lane l has experts l, l + 64, ...  The loads are unconditional (lanes past the last expert load it once
 // more): behind a branch each waited for its data before the next went out, a round trip to memory for every 64 experts
 // (8192 tokens of 512 experts 30.4 -> 28.5 us for the whole routing, 65536 of 256, one selected, 32.3 -> 27.8 us).
+// `row` the same for the whole wave, and EPL the least power of two that holds E, so that the first half of the loads
+// needs no bound: a scalar base and a few offsets.  An address a lane and load took 77 registers for 16 loads, with which one
+// ranking workgroup fits a CU instead of two (28800 tokens of 513 experts, 8 selected, 85 -> 68 us).
 template <int EPL>
 __device__ __forceinline__ void load_logits(const float* __restrict__ row, int E, int lane, float (&x)[EPL]) {
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) x[i] = row[min(lane + 64 * i, E - 1)];
+    for (int i = 0; i < EPL; ++i) x[i] = row[i < EPL / 2 ? lane + 64 * i : min(lane + 64 * i, E - 1)];
 }
 // Top-k of NT tokens by one wave: lane j < k gets a token's j-th expert and its gate.  A round is one chain of dependent
 // instructions: the tokens' chains run side by side, without a branch between them (32768 tokens of 256 experts, 8 selected,
@@ -184,8 +187,9 @@ __device__ __forceinline__ void select_experts(const float (&x)[NT][EPL], int E,
 // ONE: the batch is a single chunk (a generation step): the ranks are complete, and the same
 // workgroup scans the counts and writes the rows.
 // PIECES: 64-slot pieces of a chunk (a wave's counts of an expert in a piece are at most 64).
+// Two workgroups of 16 waves share a CU: 8 waves a SIMD, up to 64 registers a lane.
 template <int EPL, bool ONE, int PIECES>
-__global__ void __launch_bounds__(kChunkThreads)
+__global__ void __launch_bounds__(kChunkThreads) __attribute__((amdgpu_waves_per_eu(8)))
 topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_chunk, int e_start, int e_count,
                  int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ chunk_cnt,
                  int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
@@ -218,7 +222,7 @@ topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_
                     topk_w[f0 + f] = gate[n];
                 }
         };
-        int tt = wave;
+        int tt = __builtin_amdgcn_readfirstlane(wave);
         if constexpr (EPL <= 8)   // (16 keys a lane, twice, take too many registers)
             for (; tt + kWaves < nt; tt += 2 * kWaves) tokens(tt, std::integral_constant<int, 2>{});
         for (; tt < nt; tt += kWaves) tokens(tt, std::integral_constant<int, 1>{});
@@ -276,7 +280,7 @@ template <int EPL>
 __global__ void __launch_bounds__(kRouteThreads)
 topk_kernel(const float* __restrict__ logits, int T, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
     const int lane = threadIdx.x & 63;
-    for (int t = blockIdx.x * (kRouteThreads / 64) + (threadIdx.x >> 6); t < T; t += gridDim.x * (kRouteThreads / 64)) {
+    for (int t = blockIdx.x * (kRouteThreads / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); t < T; t += gridDim.x * (kRouteThreads / 64)) {
         float x[1][EPL], gate[1];
         int idx[1];
         load_logits<EPL>(logits + (size_t)t * E, E, lane, x[0]);

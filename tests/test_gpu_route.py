@@ -1,5 +1,7 @@
 """GPU parity of moe_route: indices, counts and offsets bit-exact against the
 oracle; gates to fp32 rounding."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -229,3 +231,29 @@ def test_route_backward_of_few_slots_takes_less_than_of_eight():
         us[k] = min(times)
     say(f"[route-bwd] 32768 tokens of 1024 experts: {us}")
     assert us[1] <= 0.92 * us[8], us
+
+
+def routing_us(T, E, k):
+    import paper_2604_19241_amd as moe
+    shape = moe.make_shape(T=T, d=64, E=E, k=k, I=64)
+    logits = torch.randn((T, E), generator=torch.Generator(device="cuda").manual_seed(T), device="cuda")
+    routing = moe.moe_route(shape, logits)
+    ws = torch.empty(moe.moe_workspace_bytes(shape)["route"], dtype=torch.uint8, device="cuda")
+    args = [ctypes.byref(shape), logits.data_ptr(), ctypes.byref(routing.c_struct()), ws.data_ptr(), ws.numel(),
+            torch.cuda.current_stream().cuda_stream]
+    start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    times = []
+    for _ in range(8):
+        start.record()
+        for _ in range(20):
+            assert moe.load_library().moe_route(*args) == 0
+        stop.record()
+        torch.cuda.synchronize()
+        times.append(start.elapsed_time(stop) * 50.0)
+    say(f"[route] {T} tokens, {E} experts, {k} selected: {min(times):.1f} us")
+    return min(times)
+
+
+def test_route_of_many_experts_fills_a_cu():
+    """A ninth row of 64 experts is more work (measured 1.45 times the time), but not one workgroup a CU instead of two (1.83)."""
+    assert routing_us(28800, 513, 8) <= 1.65 * routing_us(28800, 512, 8)
