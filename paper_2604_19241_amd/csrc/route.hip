@@ -25,12 +25,16 @@ constexpr int kPieces = (kChunk + kMaxTopK - 1 + 63) / 64;   // 64-slot pieces o
 // 44 chunks of 256 experts 13.6 us (with the scan's launch 15.7), 128 chunks 16.8 us (15.9).
 constexpr int kFewChunks = 64;
 
-// From kManyChunks chunks on a chunk has up to 1024 slots, a thread each: a quarter of the workgroups, whose 16 waves rank a
-// piece each instead of 4 of them, and a quarter of the table to scan.  With fewer, CUs would stay idle.
-// Measured, us of the whole routing, chunks of 256 / of 1024 slots (tokens x experts x k): 32768 x 256 x 8 38.2 / 36.8,
-// 65536 x 64 x 8 49.1 / 35.2, 60001 x 256 x 8 65.5 / 52.4, but 16384 x 256 x 8 22.4 / 34.7, 24000 x 128 x 6 27.5 / 29.2.
+// From kManyChunks chunks on a chunk has up to 1024 slots, a thread each: a quarter of the workgroups or half of them, whose 16 waves
+// rank a piece each instead of 4 of them, and as much less of the table to scan.  With fewer, CUs would stay idle.
+// The chunks are as many as make whole rounds of kChunkCus, of equal length: 1100 short ones made 275 of 1024 slots, and the
+// last 19 took as long as the 256 before.
+// Measured, us of the whole routing, chunks of 256 slots / of 1024 / as they are (tokens x experts x k): 32768 x 256 x 8 38.2 / 36.8,
+// 65536 x 64 x 8 49.1 / 35.2, 35200 x 256 x 8 48.6 / 47.3 / 33.2, 35200 x 513 x 8 89.4 / 133 / 68.9, 281600 x 8 x 1 51.3 / 64.0 / 38.7,
+// 64000 x 256 x 8 70.9 / 50.2 / 49.2; but 16384 x 256 x 8 22.4 / 34.7, 24000 x 128 x 6 27.5 / 29.2.
 constexpr int kLongPieces = kChunkThreads / 64;
 constexpr int kManyChunks = 1024;
+constexpr int kChunkCus = 256;   // CUs of the chip
 struct Chunks {
     int tokens, n;   // of a chunk; chunks
     bool lng;
@@ -38,7 +42,8 @@ struct Chunks {
 static Chunks chunks_of(const moe_shape_t& s) {
     const int tokens = (kChunk + s.k - 1) / s.k, n = (s.T + tokens - 1) / tokens;
     if (n < kManyChunks) return Chunks{tokens, n, false};
-    const int more = kChunkThreads / s.k;
+    const int round = kChunkCus * (kChunkThreads / s.k), rounds = (s.T + round - 1) / round;
+    const int more = (s.T + kChunkCus * rounds - 1) / (kChunkCus * rounds);
     return Chunks{more, (s.T + more - 1) / more, true};
 }
 // Whether the top-k is a launch of its own, one token a wave over the whole chip, ahead of the ranking

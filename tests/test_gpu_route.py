@@ -141,10 +141,12 @@ def test_route_chunk_edges(kw):
 
 
 # From 1024 chunks of 256 slots on the chunks are longer: the last one short, the last size and the first, chunks of fewer than
-# 1024 slots (k = 3, 10), one slot a token, experts here and elsewhere, ties in every token.
+# 1024 slots (k = 3, 10), one slot a token, experts here and elsewhere, ties in every token; one token more than one, two and
+# three rounds of 256 chunks hold.
 @pytest.mark.parametrize("kw", [
     dict(T=32736, E=40, k=8), dict(T=32768, E=200, k=8, e_start=7, e_count=90), dict(T=100003, E=33, k=3), dict(T=262200, E=65, k=1),
     dict(T=27001, E=260, k=10, e_start=250, e_count=10), dict(T=16500, E=600, k=16),
+    dict(T=32769, E=40, k=8), dict(T=26113, E=40, k=10), dict(T=65537, E=90, k=8), dict(T=78337, E=40, k=10, e_start=3, e_count=30),
 ])
 def test_route_long_chunks(kw):
     cfg = moe_synth.small_config(d=64, I=64, **kw)
@@ -257,3 +259,9 @@ def routing_us(T, E, k):
 def test_route_of_many_experts_fills_a_cu():
     """A ninth row of 64 experts is more work (measured 1.45 times the time), but not one workgroup a CU instead of two (1.83)."""
     assert routing_us(28800, 513, 8) <= 1.65 * routing_us(28800, 512, 8)
+
+
+# 1100 chunks of 256 slots, 7 % more than 1024: not a second round of long chunks (1.2 to 1.9 times the time)
+@pytest.mark.parametrize("T,E,k", [(32768, 256, 8), (16384, 600, 16), (262144, 8, 1)])
+def test_routing_just_past_a_round_of_long_chunks(T, E, k):
+    assert routing_us(T * 1100 // 1024, E, k) <= 1.15 * routing_us(T, E, k)
