@@ -77,6 +77,38 @@ def test_widths_of_a_task(E, d, I):
     test_forward_at_row_counts(rows.tolist(), d, I)
 
 
+def us_of_one_row_each(experts, d, I, E=16):
+    """The layer for one token on each of so many experts, other ones from call to call."""
+    import paper_2604_19241_amd as moe
+    g = torch.Generator(device="cuda").manual_seed(1)
+    w = [torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16) for s in ((E, d, I), (E, d, I), (E, I, d))]
+    shape = moe.make_shape(T=experts, d=d, E=E, k=1, I=I)
+    x = torch.randn((experts, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    y, ws = torch.empty_like(x), torch.empty(moe.moe_workspace_bytes(shape)["fwd"], dtype=torch.uint8, device="cuda")
+    routings = []
+    for first in range(E):
+        logits = torch.zeros((experts, E), device="cuda")
+        logits[torch.arange(experts), (first + torch.arange(experts)) % E] = 1.0
+        routings.append(moe.moe_route(shape, logits))
+    start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    times = []
+    for _ in range(8):
+        start.record()
+        for r in routings:
+            moe.moe_fused_forward(shape, x, *w, r, y=y, ws=ws)
+        stop.record()
+        torch.cuda.synchronize()
+        times.append(start.elapsed_time(stop) * 1e3 / E)
+    return min(times)
+
+
+def test_fewer_experts_take_no_longer():
+    """4 experts have tasks of 64 gate and up columns, 5 of 128: halves of a memory line are not fetched twice for that."""
+    us = {n: us_of_one_row_each(n, 7168, 2048) for n in (4, 5)}
+    say(f"[few rows] {us}")
+    assert us[4] <= us[5], us
+
+
 # A caller may bring a routing in which a token's slots share an expert: more than 32 rows of an expert in a batch
 # of up to 32 tokens are run in blocks of 32.  Against the same slots as tokens of their own, whose experts are on
 # the work queue: the rows have the same bits.
