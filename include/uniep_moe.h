@@ -105,7 +105,7 @@ typedef struct {
                          bounded: the tail kernels and the 32 workgroups that write the queue */
     int32_t spin_limit_ms; /* bound on every scoreboard wait; 0 = 2000 ms.  A wait that
                               exceeds it sets MOE_ERR_DEVICE in the workspace and drains */
-    int32_t tile_rows;     /* rows per GEMM row tile of the queue: 0 = by the sizes, or 128 / 256
+    int32_t tile_rows;     /* rows per GEMM row tile of the queue: 0 = by the rows, or 128 / 256
                               (256: up to 288 where that saves an expert a tile).  The row-tile
                               GEMMs give the same bits either way */
     int32_t skip_tail;     /* measurement aid, 0 or 1: with the default schedule, 1 leaves out the

@@ -48,7 +48,7 @@ struct BwdParams {
     float* dtopk_w;
     int* ctrl;
     int* flag_rt;   // per row tile: dH column tiles finished
-    int* flag_e;    // per expert: dH tiles finished
+    int* flag_e;    // per expert: dH tiles finished, less those it has
     Task* tasks;
     int32_t* row_tok;
     float* row_w;
@@ -65,7 +65,7 @@ struct BwdParams {
     int32_t* split_tile0;       // [e_count]  first entry of expert e in split_cnt
     char* split_buf;            // [slots][256 KB]  fp32 partial tiles in accumulator layout
     int n_dots;                 // partial sums per routed row: 4 * nct_dh
-    TileRule tile;              // rows of the row tiles
+    TileChoice tile;            // rows of the row tiles
     int workers;                // workgroups of the worker launch (the tail waits for all of them)
     long long spin_ticks;
 };
@@ -88,7 +88,6 @@ constexpr size_t kPartialTileBytes = (size_t)BMAX * BN * sizeof(float);
 __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
     __shared__ QueuePlan P;
     const int ec = p.s.e_count;
-    const TileRule tile = p.tile;
     if (blockIdx.x >= kPlanBlocks) {
         const int r = ((int)blockIdx.x - kPlanBlocks) * kPlanThreads + threadIdx.x;
         if (r < p.offsets[ec]) {
@@ -108,15 +107,16 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
         return (p.split_rows > 0 && rows > p.split_rows) ? (rows + p.split_rows - 1) / p.split_rows : 1;
     };
     // (an expert without rows still has its weight gradients written)
-    make_plan(P, p.offsets, ec, 0, [](int) { return 0; }, tile, p.nct_dh, [&](int rows) { return tile.tiles(rows) * p.nct_dh; },
-              [&](int rows) { return tile.tiles(rows) * p.nct_dxp + (per_dwgu + per_dwd) * parts_of(rows); });
+    const TileRule tile = make_plan(
+        P, p.offsets, ec, 0, [](int) { return 0; }, p.tile, p.nct_dh, [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct_dh; },
+        [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct_dxp + (per_dwgu + per_dwd) * parts_of(rows); });
     const int lane = threadIdx.x & 63;
     for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {   // one wave, one expert
         const int rows_x = P.rows[x], nt_x = tile.tiles(rows_x), parts_x = parts_of(rows_x);
         const int rt0 = tile.flags(plan_rt0(P, x)), r0 = p.offsets[x], higher = tile.higher(rows_x);
         const int n_dxp = nt_x * p.nct_dxp;
         for (int i = lane; i < nt_x; i += 64) p.flag_rt[rt0 + i] = 0;
-        if (lane == 0) p.flag_e[x] = 0;
+        if (lane == 0) p.flag_e[x] = -nt_x * p.nct_dh;
         if (p.split_rows > 0) {   // slots of the split experts in front of this one: output tiles, and partial tiles
             int st = 0, sp = 0;
             for (int e = lane; e < x; e += 64) {
@@ -641,16 +641,14 @@ __device__ __forceinline__ void bwd_worker_body(const BwdParams& p, int phase, c
                     dxp_task(p, rt, ct, smem, issue);
                 }
             } else {
-                // weight-gradient tiles read what ALL dH tiles of the expert wrote (dG|dU, gate * h):
-                // its row tiles times the dH column tiles
+                // weight-gradient tiles read what ALL dH tiles of the expert wrote (dG|dU, gate * h)
                 const int e = task_expert(task);
-                // rows of the whole expert (a part of a split reduction carries only its own share)
+                // rows of the whole expert (a part of a split reduction carries only its own share): without any there is nothing to wait for
                 const int rows_e = SPLIT ? p.offsets[e + 1] - p.offsets[e] : task.rows;
-                const int need = p.tile.tiles(rows_e) * p.nct_dh;
                 // a worker takes several of an expert's 72 output tiles in a row: the expert it has
                 // already seen complete (and acquired) needs no second look at the flag
                 if (e != seen_e) {
-                    if (threadIdx.x == 0) s_ok = wait_ge(p.flag_e + e, need, ctrl, p.spin_ticks);
+                    if (threadIdx.x == 0) s_ok = rows_e <= 0 || wait_ge(p.flag_e + e, 0, ctrl, p.spin_ticks);
                     __syncthreads();
                     if (s_ok) seen_e = e;
                 }
@@ -818,7 +816,7 @@ static int bwd_launch_tiles(BwdParams& p, const moe_opts_t& opts, hipStream_t st
     if (rc != MOE_OK) return rc;
     const int workers = opts.workers > 0 ? min(opts.workers, resident) : resident;
     p.workers = workers;
-    p.tile = tile_rule(p.s, opts.tile_rows, p.nct_dh + p.nct_dxp, workers, 3);
+    p.tile = TileChoice{TileChoice::rows_of(p.s, opts.tile_rows), {p.nct_dh, p.nct_dxp}, {p.s.d / BK, 2 * p.s.I / BK}, workers, 0.5f, 0.3f, 1.f};
     const int A_cap = p.s.T * p.s.k;
     hipLaunchKernelGGL(bwd_first_kernel, dim3(kPlanBlocks + (A_cap + kPlanThreads - 1) / kPlanThreads), dim3(kPlanThreads),
                        0, st, p);

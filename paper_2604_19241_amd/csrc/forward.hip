@@ -40,7 +40,7 @@ struct FwdParams {
     Task* tasks;
     int nct1, nct2;   // column tiles of GEMM1 (128 h-columns each) and GEMM2 (256 each)
     int workers;   // workgroups of the worker launch (the tail waits for all of them)
-    TileRule tile;     // rows of the row tiles
+    TileChoice tile;   // rows of the row tiles
     ThinRule rule;     // which experts are run outside the work queue; max_rows = 0: none
     int plan_blocks;   // workgroups of the first launch that make the queue: kPlanBlocks, or 0 if there is none
     long long spin_ticks;
@@ -52,10 +52,9 @@ struct FwdParams {
 // GEMM2 block of expert i) and a cleared scoreboard.
 __device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePlan& P) {
     const int ec = p.s.e_count;
-    const TileRule tile = p.tile;
-    make_plan(P, p.offsets, ec, p.rule.max_rows, [&](int counts) { return p.rule.limit(counts); }, tile, p.nct1,
-              [&](int rows) { return tile.tiles(rows) * p.nct1; },
-              [&](int rows) { return tile.tiles(rows) * p.nct2; });
+    const TileRule tile = make_plan(P, p.offsets, ec, p.rule.max_rows, [&](int counts) { return p.rule.limit(counts); }, p.tile, p.nct1,
+                                    [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct1; },
+                                    [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct2; });
     const int lane = threadIdx.x & 63;
     for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {
         const int rows_x = P.rows[x], nt_x = tile.tiles(rows_x);
@@ -475,7 +474,7 @@ static int fwd_launch_tiles(FwdParams& p, const moe_opts_t& opts, hipStream_t st
     if (rc != MOE_OK) return rc;
     int workers = opts.workers > 0 ? min(opts.workers, resident) : resident;
     p.workers = workers;
-    p.tile = tile_rule(p.s, opts.tile_rows, p.nct1 + p.nct2, workers, 4);
+    p.tile = TileChoice{TileChoice::rows_of(p.s, opts.tile_rows), {p.nct1, p.nct2}, {p.s.d / BK, p.s.I / BK}, workers, 0.55f, 0.6f, 0.3f};
     // A token selects an expert at most once, so up to kThinRows tokens no expert has more rows than
     // that: every expert is thin and no work queue is set up.
     const bool all_thin = p.s.T <= kThinRows;

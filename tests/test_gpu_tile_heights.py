@@ -62,9 +62,9 @@ def test_higher_tiles(counts, d, I):
     check_elementwise("dtopk_w", to_f64(got["dtopk_w"]), ref["dtopk_w"], whole_array_rms=True)
 
 
-# Tiles of 128 rows by the sizes: below two tasks a worker forward and one and a half backward, none where the GEMMs have
-# a few stages; two flags a scoreboard slot, at row counts around a slot's edges
-@pytest.mark.parametrize("d,I,workers,low", [(320, 448, 0, (True, True)), (320, 448, 30, (False, False)), (320, 448, 40, (False, True)),
+# Tiles of 128 rows where they take less: on many workers in both passes, on some in the backward pass, on few and where the GEMMs
+# have a few stages in none; two flags a scoreboard slot, at row counts around a slot's edges
+@pytest.mark.parametrize("d,I,workers,low", [(320, 448, 0, (True, True)), (320, 448, 30, (False, False)), (320, 448, 60, (False, True)),
                                              (64, 64, 0, (False, False))])
 def test_low_tiles_by_the_sizes(d, I, workers, low):
     counts = [127, 128, 129, 255, 256, 257, 384, 385, 512, 513, 1, 0, 700]
@@ -98,3 +98,37 @@ def test_low_tiles_by_the_sizes(d, I, workers, low):
     for tile_rows in (256, 128):
         for key, v in got[tile_rows].items():
             assert torch.equal(v, got[0][key]), (tile_rows, key)
+
+
+# A share of the experts: the rows that it has choose the tiles, not those that even routing would give it.  Even routing of 4000
+# tokens over 64 experts would make low tiles right for 4 of them, of 20000 over 8 tall ones.
+@pytest.mark.parametrize("T,E,rows,workers,height", [(4000, 64, 900, 16, 256), (20000, 8, 150, 64, 128)])
+def test_tiles_follow_the_rows_of_a_share(T, E, rows, workers, height):
+    n, d, I = 4, 320, 448
+    cfg = moe_synth.small_config(T=T, d=d, E=E, k=1, I=I, e_start=2, e_count=n)
+    inp = scaled_inputs(cfg, 5, 4.0)
+    there = [e for e in range(E) if not 2 <= e < 2 + n]
+    own = np.concatenate([np.repeat(np.arange(2, 2 + n), rows), np.resize(there, T - n * rows)])
+    inp["logits"] = torch.from_numpy(np.eye(E, dtype=np.float32)[np.random.default_rng(T).permutation(own)])
+    say(f"[heights] share of {n} of {E}, {rows} rows each, {T} tokens")
+    shape = moe.make_shape(**cfg.shape_dict())
+    dev = {key: v.cuda() for key, v in inp.items()}
+    routing = moe.moe_route(shape, dev["logits"])
+    assert routing.counts.tolist() == [rows] * n
+    size = moe.moe_workspace_bytes(shape)
+    w = [dev[key] for key in ("w_gate", "w_up", "w_down")]
+    of = lambda v, size: -(-v // size)
+    wgrad = n * (of(I, 256) * of(d, 256) + of(d, 256) * of(I, 128))
+    got = {}
+    for tile_rows in (0, 384 - height):
+        saved = moe.alloc_saved(shape, "cuda")
+        ws = {key: torch.empty(size[key], dtype=torch.uint8, device="cuda") for key in ("fwd", "bwd")}
+        opts = moe.make_opts(tile_rows=tile_rows, workers=workers, spin_limit_ms=500)
+        got[tile_rows] = {"y": moe.moe_fused_forward(shape, dev["x"], *w, routing, saved=saved, ws=ws["fwd"], opts=opts)}
+        got[tile_rows].update(moe.moe_fused_backward(shape, dev["dy"], dev["x"], *w, routing, saved, ws=ws["bwd"], opts=opts))
+        assert moe.moe_device_status(ws["fwd"]) == 0 and moe.moe_device_status(ws["bwd"]) == 0
+        tasks = [int(ws[key].view(torch.int32)[LENGTHS:LENGTHS + 8].sum()) for key in ("fwd", "bwd")]
+        tiles_of = n * of(rows, tile_rows or height)
+        assert tasks == [tiles_of * (of(I, 128) + of(d, 256)), tiles_of * (of(I, 256) + of(d, 256)) + wgrad], tile_rows
+    for key, v in got[0].items():
+        assert torch.equal(v, got[384 - height][key]), key
