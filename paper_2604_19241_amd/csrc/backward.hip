@@ -70,7 +70,7 @@ struct BwdParams {
     long long spin_ticks;
 };
 
-// Weight-gradient tasks carry (output row tile, part, parts) in Task.idx.
+// Weight-gradient tasks carry the output row tile in Task.idx; where reductions may be split, (output row tile, part, parts).
 __host__ __device__ __forceinline__ int wgrad_idx(int mt, int part, int parts) { return mt | (part << 8) | (parts << 20); }
 __device__ __forceinline__ int wgrad_mt(int idx) { return idx & 0xff; }
 __device__ __forceinline__ int wgrad_part(int idx) { return (idx >> 8) & 0xfff; }
@@ -149,13 +149,14 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
             tb[block_pos<true>(j, ct, nt_x, p.nct_dxp)] =
                 Task{rt0 + j, task_code(B_DXP, x, ct), r0 + tile.first(j, higher), tile.rows_of(j, higher, rows_x)};
         });
-        // weight-gradient tasks: idx = output row tile | part << 8 | parts << 20; row0 / rows = the part's rows
+        // weight-gradient tasks: row0 / rows = the part's rows
+        auto idx_of = [&](int mt, int part) { return p.split_rows > 0 ? wgrad_idx(mt, part, parts_x) : mt; };
         for_each_tile(lane, p.mt_dwgu, p.nt_dwgu, [&](int mt, int nt) {
             for (int j = 0; j < parts_x; ++j) {
                 const int first = (parts_x > 1) ? j * p.split_rows : 0;
                 const int len = (parts_x > 1) ? min(p.split_rows, rows_x - first) : rows_x;
                 tb[n_dxp + block_pos<false>(mt, nt, p.mt_dwgu, p.nt_dwgu) * parts_x + j] =
-                    Task{wgrad_idx(mt, j, parts_x), task_code(B_DWGU, x, nt), r0 + first, len};
+                    Task{idx_of(mt, j), task_code(B_DWGU, x, nt), r0 + first, len};
             }
         });
         for_each_tile(lane, p.mt_dwd, p.nt_dwd, [&](int mt, int nt) {
@@ -163,7 +164,7 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
                 const int first = (parts_x > 1) ? j * p.split_rows : 0;
                 const int len = (parts_x > 1) ? min(p.split_rows, rows_x - first) : rows_x;
                 tb[n_dxp + per_dwgu * parts_x + block_pos<false>(mt, nt, p.mt_dwd, p.nt_dwd) * parts_x + j] =
-                    Task{wgrad_idx(mt, j, parts_x), task_code(B_DWD, x, nt), r0 + first, len};
+                    Task{idx_of(mt, j), task_code(B_DWD, x, nt), r0 + first, len};
             }
         });
     }
@@ -388,7 +389,7 @@ __device__ __forceinline__ bool finish_part(const BwdParams& p, int e, int tile,
 template <bool ACC, bool SPLIT, class Hook>
 __device__ __forceinline__ void dwd_task(const BwdParams& p, int e, int idx, int nt, int r0, int cnt,
                                          char* smem, int* s_flag, Hook after_mainloop) {
-    const int mt = wgrad_mt(idx);
+    const int mt = SPLIT ? wgrad_mt(idx) : idx;
     const int d = p.s.d, I = p.s.I;
     const int m0 = mt * BMAX, n0 = nt * BN;
     const Lane ln;
@@ -439,7 +440,7 @@ __device__ __forceinline__ void dwd_task(const BwdParams& p, int e, int idx, int
 template <bool ACC, bool SPLIT, class Hook>
 __device__ __forceinline__ void dwgu_task(const BwdParams& p, int e, int idx, int nt, int r0, int cnt,
                                           char* smem, int* s_flag, Hook after_mainloop) {
-    const int mt = wgrad_mt(idx);
+    const int mt = SPLIT ? wgrad_mt(idx) : idx;
     const int d = p.s.d, I = p.s.I;
     const int m0 = mt * BMAX, n0i = nt * (BN / 2);
     const Lane ln;

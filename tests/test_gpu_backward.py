@@ -281,3 +281,19 @@ def test_backward_split_weight_gradient_reduction(split):
                                  routing, saved, opts=opts, out=out, want_dtopk_w=False)
     for key in ("dw_gate", "dw_up", "dw_down"):
         assert torch.equal(acc[key].to(torch.bfloat16), ref[key]), key
+
+
+@pytest.mark.parametrize("d,I", [(65600, 64), (64, 65600)])
+def test_weight_gradients_of_more_than_256_row_tiles(d, I):
+    """Every 256 rows of a weight gradient are a task's tile, 257 of them here."""
+    cfg = moe_synth.small_config(T=70, d=d, E=2, k=1, I=I)
+    inp = scaled_inputs(cfg, 61, 1.0)
+    say(f"[bwd wide] {cfg.shape_dict()}")
+    got, _ = gpu_fwd_bwd(cfg, inp, 0, 0)
+    b = bits(inp, ("x", "dy", "w_gate", "w_up", "w_down"))
+    r = oracle.route(cfg.shape_dict(), inp["logits"].numpy())
+    want = oracle.backward(cfg.shape_dict(), b["x"], b["dy"], b["w_gate"], b["w_up"], b["w_down"], r, round_bf16=True, acc="f32")
+    for key in KEYS:
+        err = rel_l2(to_f64(got[key]), want[key])
+        assert err <= GRAD_REL_L2, (key, err)
+        check_elementwise(key, to_f64(got[key]), want[key])
