@@ -72,7 +72,8 @@ typedef struct {
  * A = offsets[e_count] is the number of (token, slot) assignments that land on
  * local experts; "row" r in [0, A) is a position in the expert-sorted order. */
 typedef struct {
-    const int32_t* topk_idx; /* [T,k]  expert id of slot j (descending logit; ties: lower id) */
+    const int32_t* topk_idx; /* [T,k]  expert id of slot j (descending logit; ties: lower id); INT32_MAX
+                                where fewer logits of the token are numbers: the slot has no expert */
     const float* topk_w;     /* [T,k]  gate: softmax renormalised over the k selected */
     const int32_t* counts;   /* [e_count]    C_exp: rows per local expert */
     const int32_t* offsets;  /* [e_count+1]  O_exp: exclusive prefix sum of counts */
@@ -232,7 +233,8 @@ int moe_fused_backward(const moe_shape_t* shape, const void* dy, const void* x,
 int moe_route_backward(const moe_shape_t* shape, const int32_t* topk_idx, const float* topk_w,
                        const float* dtopk_w, float* dlogits, void* stream);
 
-/* Outputs of moe_global_map (device pointers, all written by the call). */
+/* Outputs of moe_global_map (device pointers, all written by the call).  A slot without an
+ * expert has -1 in the four dst_ arrays and 0 in `send`, and counts for no rank. */
 typedef struct {
     int32_t* dst_rank;     /* [T,k]  r_tgt = e / N_epr */
     int32_t* dst_expert;   /* [T,k]  e_loc = e % N_epr */

@@ -489,7 +489,7 @@ global_offsets_kernel(const int32_t* __restrict__ c_all, const int32_t* __restri
 // thread per token read and wrote with a stride: 8.3 us for 32768 tokens with 8 slots, now 4.7 us.
 __global__ void __launch_bounds__(kRouteThreads)
 global_map_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ m_loc, int T,
-                  int k, int per_group, int n_epr, const int32_t* __restrict__ off_base,
+                  int k, int per_group, int E, int n_epr, const int32_t* __restrict__ off_base,
                   const int32_t* __restrict__ row_base, int32_t* __restrict__ dst_rank,
                   int32_t* __restrict__ dst_expert, int32_t* __restrict__ dst_off,
                   int32_t* __restrict__ dst_row, int32_t* __restrict__ send,
@@ -501,22 +501,26 @@ global_map_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restric
     const bool live = tid < nt * k;
     if (live) {
         const int e = topk_idx[f], loc = m_loc[f];
-        const int r_tgt = e / n_epr;
+        const bool any = (uint32_t)e < (uint32_t)E;   // a token with fewer than k logits that are numbers has slots without an expert
+        const int r_tgt = any ? e / n_epr : -1;
         s_rank[tid] = r_tgt;
         dst_rank[f] = r_tgt;
-        dst_expert[f] = e - r_tgt * n_epr;
-        dst_off[f] = loc + off_base[e];
-        dst_row[f] = loc + row_base[e];
+        dst_expert[f] = any ? e - r_tgt * n_epr : -1;
+        dst_off[f] = any ? loc + off_base[e] : -1;
+        dst_row[f] = any ? loc + row_base[e] : -1;
     }
     __syncthreads();
     if (live) {
-        bool first = true;
+        bool first = s_rank[tid] >= 0;
         for (int i = tid - tid % k; i < tid; ++i) first = first && s_rank[i] != s_rank[tid];
         send[f] = first ? 1 : 0;
     }
     if (tid < nt) {
         unsigned long long seen = 0ull;
-        for (int j = 0; j < k; ++j) seen |= 1ull << s_rank[tid * k + j];
+        for (int j = 0; j < k; ++j) {
+            const int r = s_rank[tid * k + j];
+            if (r >= 0) seen |= 1ull << r;
+        }
         n_dst_ranks[t0 + tid] = __popcll(seen);
     }
 }
@@ -533,7 +537,7 @@ int global_map_launch(const moe_shape_t& s, int W, int rank, const moe_routing_t
     const int per_group = kRouteThreads / s.k;   // whole tokens whose slots fill a workgroup
     if (s.T > 0)
         hipLaunchKernelGGL(global_map_kernel, dim3((s.T + per_group - 1) / per_group), dim3(kRouteThreads), 0, st, r.topk_idx,
-                           r.inv_perm, s.T, s.k, per_group, n_epr, off_base, row_base, out.dst_rank, out.dst_expert,
+                           r.inv_perm, s.T, s.k, per_group, s.E, n_epr, off_base, row_base, out.dst_rank, out.dst_expert,
                            out.dst_off, out.dst_row, out.send, out.n_dst_ranks);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }

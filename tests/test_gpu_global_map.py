@@ -77,3 +77,34 @@ def test_global_map_is_bitwise_repeatable():
         again = moe.moe_global_map(shape, 8, 5, r, c_all)
         for key in KEYS + ("recv_offsets",):
             assert torch.equal(getattr(first, key), getattr(again, key)), key
+
+
+@pytest.mark.parametrize("W,E,k", [(2, 16, 4), (8, 128, 8), (64, 64, 1)])
+def test_global_map_of_tokens_without_enough_numbers(W, E, k):
+    """A NaN is never selected: the slots that are left over go nowhere, the others where they do without them."""
+    import paper_2604_19241_amd as moe
+    T, rank = 300, W - 1
+    rng = np.random.default_rng(E)
+    logits = rng.standard_normal((T, E)).astype(np.float32)
+    few = np.arange(0, T, 3)
+    for t in few:
+        logits[t, rng.permutation(E)[:E - t % k]] = np.nan   # t % k numbers left, none in some
+    cfg = moe_synth.small_config(T=T, d=64, E=E, k=k, I=64)
+    shape = moe.make_shape(**cfg.shape_dict())
+    say(f"[global map] NaN logits {cfg.shape_dict()} W={W}")
+    r = moe.moe_route(shape, torch.from_numpy(logits).cuda())
+    c_all = torch.stack([r.counts] * W).contiguous()
+    got = moe.moe_global_map(shape, W, rank, r, c_all)
+    idx, n_epr, counts = r.topk_idx.cpu().numpy(), E // W, r.counts.cpu().numpy().astype(np.int64)
+    there = idx < E
+    assert there.sum() == counts.sum() and (~there).sum() == sum(k - t % k for t in few)
+    e = np.where(there, idx, 0)
+    off = r.inv_perm.cpu().numpy() - (np.cumsum(counts) - counts)[e] + rank * counts[e]
+    total = (W * counts).reshape(W, n_epr)
+    start = (np.cumsum(total, axis=1) - total).reshape(E)
+    dst = np.where(there, e // n_epr, -1)
+    first = there & ~np.array([[(dst[t, :j] == dst[t, j]).any() for j in range(k)] for t in range(T)])
+    want = {"dst_rank": dst, "dst_expert": np.where(there, e % n_epr, -1), "dst_off": np.where(there, off, -1),
+            "dst_row": np.where(there, start[e] + off, -1), "send": first, "n_dst_ranks": first.sum(axis=1)}
+    for key in KEYS:
+        assert np.array_equal(getattr(got, key).cpu().numpy(), want[key]), key
