@@ -36,7 +36,7 @@
  * Shape limits (MOE_ERR_SHAPE otherwise): 1 <= k <= 16, k <= E <= 1024,
  * 0 <= e_start, 1 <= e_count, e_start + e_count <= E, d and I multiples of 64,
  * T >= 0 (T == 0 is a no-op apart from zeroed counts/offsets), T*k < 2^30
- * (byte offsets inside the kernels are 64-bit).
+ * (byte offsets inside the kernels are 64-bit).  Forward and backward: d <= 2^24, I <= 2^23.
  */
 #ifndef UNIEP_MOE_H
 #define UNIEP_MOE_H

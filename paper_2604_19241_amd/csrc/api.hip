@@ -41,6 +41,13 @@ int check_shape(const moe_shape_t* s) {
     return MOE_OK;
 }
 
+// A GEMM task has 16 bits for its column tile, of 256 columns (d) or 128 (I, gate and up side by side).
+int check_layer_shape(const moe_shape_t* s) {
+    const int rc = check_shape(s);
+    if (rc != MOE_OK) return rc;
+    return s->d > 65536 * 256 || s->I > 65536 * 128 ? MOE_ERR_SHAPE : MOE_OK;
+}
+
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 int check_routing(const moe_routing_t* r, int T) {
@@ -210,7 +217,7 @@ int moe_route_static(const moe_shape_t* shape, const float* logits, const moe_ro
 int moe_fused_forward(const moe_shape_t* shape, const void* x, const void* w_gate, const void* w_up,
                       const void* w_down, const moe_routing_t* routing, void* y, void* saved,
                       void* ws, size_t ws_bytes, const moe_opts_t* opts, void* stream) {
-    int rc = check_shape(shape);
+    int rc = check_layer_shape(shape);
     if (rc != MOE_OK) return rc;
     rc = check_routing(routing, shape->T);
     if (rc != MOE_OK) return rc;
@@ -249,7 +256,7 @@ int moe_fused_backward(const moe_shape_t* shape, const void* dy, const void* x, 
                        const void* saved, void* dx, void* dw_gate, void* dw_up, void* dw_down,
                        float* dtopk_w, void* ws, size_t ws_bytes, const moe_opts_t* opts,
                        void* stream) {
-    int rc = check_shape(shape);
+    int rc = check_layer_shape(shape);
     if (rc != MOE_OK) return rc;
     rc = check_routing(routing, shape->T);
     if (rc != MOE_OK) return rc;

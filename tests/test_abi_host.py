@@ -63,6 +63,16 @@ def test_bad_shapes_are_rejected(lib, kw):
     assert rc == b.MOE_ERR_SHAPE
 
 
+@pytest.mark.parametrize("d,I,ok", [(1 << 24, 64, True), ((1 << 24) + 64, 64, False), (64, 1 << 23, True), (64, (1 << 23) + 64, False)])
+def test_more_column_tiles_than_a_task_can_name_are_rejected(lib, d, I, ok):
+    from paper_2604_19241_amd import binding as b
+    s = ctypes.byref(b.make_shape(T=0, d=d, E=2, k=1, I=I))
+    want = b.MOE_ERR_ARG if ok else b.MOE_ERR_SHAPE   # (the null routing is the next thing looked at)
+    assert lib.moe_fused_forward(s, *[None] * 8, 0, None, None) == want
+    assert lib.moe_fused_backward(s, *[None] * 13, 0, None, None) == want
+    assert lib.moe_route(s, None, None, None, 0, None) == b.MOE_ERR_ARG
+
+
 def test_workspace_sizes_and_layout(lib):
     from paper_2604_19241_amd import binding as b
     s = b.make_shape(T=256, d=512, E=8, k=2, I=1024)
