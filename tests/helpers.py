@@ -126,3 +126,15 @@ def scaled_inputs(cfg, seed, wscale=1.0):
         for key in ("w_gate", "w_up", "w_down"):
             inp[key] = (inp[key].float() * wscale).to(torch.bfloat16)
     return inp
+
+
+def queue_length(ws):
+    """Tasks of the last pass's work queue: the eight list lengths at the workspace's head."""
+    return int(ws.view(torch.int32)[8:16].sum())
+
+
+def tiles(rows):
+    """Row tiles of an expert where tiles of 256 rows may take up to 32 rows more."""
+    n = -(-rows // 256)
+    short = -(-(rows - 256 * (n - 1)) // 32)
+    return n - 1 if n <= 16 and short <= min(3, n - 1) else n

@@ -8,11 +8,11 @@ import torch
 
 import moe_synth
 import oracle
-from helpers import bits, check_elementwise, rel_l2, say, scaled_inputs, to_f64
+from helpers import bits, check_elementwise, queue_length, rel_l2, say, scaled_inputs, tiles, to_f64
 
 pytestmark = pytest.mark.gpu
 
-GRAD_REL_L2 = 1e-2   # the benchmark spec tolerance for gradients
+GRAD_REL_L2 = 1e-2   # tolerance for gradients
 KEYS = ("dx", "dw_gate", "dw_up", "dw_down")
 
 
@@ -176,8 +176,9 @@ def test_forward_backward_empty_batch():
         assert (g[key] == 0).all(), key
 
 
-@pytest.mark.parametrize("schedule,tile_rows", [(0, 0), (1, 0), (2, 0), (0, 128)])
-def test_backward_accumulates_weight_gradients_in_fp32(schedule, tile_rows):
+# (few workers: tiles of up to 288 rows)
+@pytest.mark.parametrize("schedule,tile_rows,workers", [(0, 0, 0), (1, 0, 0), (2, 0, 0), (0, 128, 0), (0, 256, 0), (1, 256, 0), (0, 256, 4)])
+def test_backward_accumulates_weight_gradients_in_fp32(schedule, tile_rows, workers):
     """opts.dw_accumulate: the fp32 accumulators are added to the caller's fp32 buffers.  Onto
     zeros the result rounds to exactly the bf16 gradients of the plain call; a second call
     doubles it exactly; onto a non-zero buffer it is the fp32 sum, element for element; experts
@@ -186,25 +187,32 @@ def test_backward_accumulates_weight_gradients_in_fp32(schedule, tile_rows):
     cfg = moe_synth.small_config(T=1100, d=320, E=12, k=3, I=448, e_start=2, e_count=9)
     inp = scaled_inputs(cfg, 31, 4.0)
     inp["logits"][:, 5] = -30.0   # a local expert that no token selects
-    say(f"[bwd accumulate] {cfg.shape_dict()} schedule={schedule} tile_rows={tile_rows}")
-    plain, routing = gpu_fwd_bwd(cfg, inp, schedule, tile_rows)
+    say(f"[bwd accumulate] {cfg.shape_dict()} schedule={schedule} tile_rows={tile_rows} workers={workers}")
+    plain, routing = gpu_fwd_bwd(cfg, inp, schedule, tile_rows, workers=workers)
     counts = routing.counts.cpu().numpy()
     assert (counts == 0).any() and (counts > 256).any()
     shape = moe.make_shape(**cfg.shape_dict())
     dev = {key: v.cuda() for key, v in inp.items()}
     saved = moe.alloc_saved(shape, "cuda")
     moe.moe_fused_forward(shape, dev["x"], dev["w_gate"], dev["w_up"], dev["w_down"], routing, saved=saved)
-    opts = moe.make_opts(schedule=schedule, tile_rows=tile_rows, spin_limit_ms=500, dw_accumulate=1)
+    opts = moe.make_opts(schedule=schedule, tile_rows=tile_rows, workers=workers, spin_limit_ms=500, dw_accumulate=1)
     wkeys = ("dw_gate", "dw_up", "dw_down")
+    ws = torch.empty(moe.moe_backward_workspace_bytes(shape, opts), dtype=torch.uint8, device="cuda")
 
     def run(main):
         out = {"dx": torch.empty_like(dev["x"]), "dtopk_w": torch.empty((shape.T, shape.k), dtype=torch.float32, device="cuda")}
         out.update(main)
         return moe.moe_fused_backward(shape, dev["dy"], dev["x"], dev["w_gate"], dev["w_up"], dev["w_down"],
-                                      routing, saved, opts=opts, out=out)
+                                      routing, saved, ws=ws, opts=opts, out=out)
 
     zeros = {key: torch.zeros_like(dev["w_" + key[3:]], dtype=torch.float32) for key in wkeys}
     once = run(zeros)
+    assert moe.moe_device_status(ws) == 0
+    if tile_rows:   # the tiles are as tall as the parameters say
+        tall = {(128, 0): sum(-(-c // 128) for c in counts), (256, 0): sum(-(-c // 256) for c in counts),
+                (256, 4): sum(tiles(int(c)) for c in counts)}
+        n = tall[tile_rows, workers]
+        assert len(set(tall.values())) == 3 and queue_length(ws) == n * (2 + 2) + cfg.e_count * (2 * 2 + 2 * 4)
     first = {key: once[key].clone() for key in wkeys}
     for key in wkeys:
         assert torch.equal(first[key].to(torch.bfloat16), plain[key]), key

@@ -1,5 +1,8 @@
 """Forward of experts with few rows (their own kernels, or the work queue beside experts with more), at the
 row counts where fragments and paths change, against the oracle."""
+import re
+from pathlib import Path
+
 import numpy as np
 import pytest
 import torch
@@ -62,18 +65,30 @@ def test_generation_step_without_a_stash(T, kw):
         assert torch.equal(y, gpu_forward(cfg, inp, schedule, 0)[0])
 
 
-# More tasks than workgroups: a workgroup's images are used for one task after the other
-@pytest.mark.parametrize("rows,I", [([2] * 16, 4096), ([1, 0, 3] * 5, 8256)])
+def widths(rows, d, I):
+    """Weight columns of a task of GEMM1 and GEMM2 on 256 CUs, by the weights that the source gives the rounds."""
+    text = (Path(__file__).resolve().parents[1] / "paper_2604_19241_amd" / "csrc" / "thin.hpp").read_text()
+    cost = {int(c): int(w) for c, w in re.findall(r"= cost\((\d+), (\d+)\)", text)}
+    assert sorted(cost) == [64, 128, 256]
+    n = sum(1 for r in rows if r)
+    return tuple(min((-(-n * -(-columns // c) // 256) * cost[c], -c) for c in cost)[1] * -1 for columns in (2 * I, d))
+
+
+# More tasks than the 512 workgroups: a workgroup's images are used for one task after the other
+@pytest.mark.parametrize("rows,I", [([2] * 16, 8256), ([1, 0, 3] * 5, 8256)])
 def test_workgroups_with_several_tasks(rows, I):
+    assert sum(1 for r in rows if r) * -(-2 * I // widths(rows, 64, I)[0]) > 600
     test_forward_at_row_counts(rows, 64, I)
 
 
 # Tasks of 256, 128 and 64 weight columns (as many experts as make each the choice on 256 CUs), the last one of an expert cut off
 # and not, in both GEMMs; k axes shorter than the stages on their way
-@pytest.mark.parametrize("E,d,I", [(128, 448, 256), (85, 512, 320), (86, 64, 384), (200, 576, 320), (230, 128, 64), (20, 320, 192)])
-def test_widths_of_a_task(E, d, I):
+@pytest.mark.parametrize("E,d,I,of", [(128, 448, 256, (256, 256)), (85, 512, 320, (256, 128)), (86, 64, 384, (256, 64)), (200, 576, 320, (128, 128)),
+                                      (230, 128, 64, (128, 128)), (20, 320, 192, (64, 64)), (23, 128, 448, (64, 64))])
+def test_widths_of_a_task(E, d, I, of):
     rows = np.random.default_rng(E).integers(0, 4, E)
     rows[:4] = (32, 31, 17, 0)
+    assert widths(rows, d, I) == of
     test_forward_at_row_counts(rows.tolist(), d, I)
 
 

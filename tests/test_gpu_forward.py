@@ -12,7 +12,7 @@ from helpers import (bits, check_elementwise, gpu_routing_as_np, max_abs, max_ab
 
 pytestmark = pytest.mark.gpu
 
-# the benchmark spec tolerances (bf16 forward)
+# tolerances of the bf16 forward pass
 MAX_ABS = 2e-2
 REL_L2 = 5e-3
 

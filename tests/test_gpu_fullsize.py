@@ -43,7 +43,7 @@ def run_gpu(cfg, inp, backward):
 def test_fullsize_whole_output_parity(cid):
     """Every element of y, and for the configurations with a backward pass every element of dX,
     dtopk_w and of the three weight gradients of every local expert, against the oracle run whole
-    with fp32 accumulation (the benchmark spec's wording; seconds to tens of seconds of host time)."""
+    with fp32 accumulation (seconds to tens of seconds of host time)."""
     cfg = moe_synth.CONFIGS[cid]
     sh = cfg.shape_dict()
     say(f"[full] config {cid} {cfg.name}: generating inputs")

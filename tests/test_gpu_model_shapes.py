@@ -10,25 +10,26 @@ import torch
 
 import moe_synth
 import oracle
-from helpers import bits, check_elementwise, gpu_routing_as_np, max_abs_beyond_ulp, rel_l2, say, to_f64
+from helpers import bits, check_elementwise, gpu_routing_as_np, max_abs_beyond_ulp, queue_length, rel_l2, say, to_f64
 from test_gpu_backward import GRAD_REL_L2, KEYS, gpu_fwd_bwd
 from test_gpu_forward import MAX_ABS, REL_L2
 
 pytestmark = pytest.mark.gpu
 
-# (model id, tokens, e_start, e_count, tile_rows); tile_rows 0 = the default 256-row tiles
+# (model id, tokens, e_start, e_count, tile_rows); tile_rows 0 = by the rows
 CASES = [
-    (1, 2048, 8, 8, 0),      # I = 1408: 5.5 column tiles of 256
-    (2, 2048, 8, 16, 0),     # d = 1280, I = 896, k = 6
-    (4, 8192, 40, 4, 0),     # d = 5120, 160 experts
-    (7, 4096, 0, 4, 0),      # d = 4096, I = 1536
-    (8, 1024, 158, 2, 0),    # d = 6144, I = 2560, the last two experts, ~50 rows each
-    (8, 1024, 158, 2, 128),  # the same on 128-row tiles (4 waves)
-    (9, 8192, 100, 16, 0),   # 512 experts, k = 10, I = 512
-    (10, 4096, 96, 32, 0),   # I = 384
-    (10, 1024, 0, 128, 0),   # every expert local, ~50 rows each
+    (1, 2048, 8, 8, 256),     # I = 1408: 5.5 column tiles of 256
+    (1, 2048, 8, 8, 0),
+    (2, 2048, 8, 16, 256),    # d = 1280, I = 896, k = 6
+    (4, 8192, 40, 4, 256),    # d = 5120, 160 experts
+    (7, 4096, 0, 4, 256),     # d = 4096, I = 1536
+    (8, 1024, 158, 2, 256),   # d = 6144, I = 2560, the last two experts, ~50 rows each
+    (8, 1024, 158, 2, 128),   # the same on 128-row tiles
+    (9, 8192, 100, 16, 256),  # 512 experts, k = 10, I = 512
+    (10, 4096, 96, 32, 256),  # I = 384
+    (10, 1024, 0, 128, 0),    # every expert local, ~50 rows each
     (10, 1024, 0, 128, 128),
-    (12, 8192, 32, 8, 0),    # d = 2304
+    (12, 8192, 32, 8, 256),   # d = 2304
 ]
 
 
@@ -48,8 +49,12 @@ def test_model_shape_forward_backward(mid, tokens, e_start, e_count, tile_rows):
 
     import paper_2604_19241_amd as moe
     shape = moe.make_shape(**sh)
+    ws = torch.empty(moe.moe_workspace_bytes(shape)["fwd"], dtype=torch.uint8, device="cuda")
     y = moe.moe_fused_forward(shape, inp["x"].cuda(), inp["w_gate"].cuda(), inp["w_up"].cuda(),
-                              inp["w_down"].cuda(), routing, opts=moe.make_opts(tile_rows=tile_rows))
+                              inp["w_down"].cuda(), routing, ws=ws, opts=moe.make_opts(tile_rows=tile_rows))
+    if tile_rows:   # tiles of that height (experts with few rows may be ahead of the queue)
+        n = [sum(-(-int(c) // tile_rows) for c in r["counts"] if c > least) for least in (0, 32)]
+        assert queue_length(ws) in [m * (-(-cfg.I // 128) + -(-cfg.d // 256)) for m in n]
     want = oracle.forward(sh, b["x"], b["w_gate"], b["w_up"], b["w_down"], r, round_bf16=True,
                           acc="f32")
     yg = to_f64(y)

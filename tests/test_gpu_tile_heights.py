@@ -8,16 +8,9 @@ import torch
 import moe_synth
 import oracle
 import paper_2604_19241_amd as moe
-from helpers import bits, check_elementwise, say, scaled_inputs, to_f64
+from helpers import bits, check_elementwise, queue_length, say, scaled_inputs, tiles, to_f64
 
 pytestmark = pytest.mark.gpu
-LENGTHS = 8   # word of the workspace's head that the eight list lengths start at
-
-
-def tiles(rows):
-    n = -(-rows // 256)
-    short = -(-(rows - 256 * (n - 1)) // 32)
-    return n - 1 if n <= 16 and short <= min(3, n - 1) else n
 
 
 def run(cfg, inp, tile_rows):
@@ -32,7 +25,7 @@ def run(cfg, inp, tile_rows):
     out.update(moe.moe_fused_backward(shape, dev["dy"], dev["x"], *w, routing, saved, ws=ws["bwd"], opts=opts))
     out.update({key: v[:cfg.T] for key, v in moe.saved_views(shape, saved).items()})
     assert moe.moe_device_status(ws["fwd"]) == 0 and moe.moe_device_status(ws["bwd"]) == 0
-    return out, [int(ws[key].view(torch.int32)[LENGTHS:LENGTHS + 8].sum()) for key in ("fwd", "bwd")]
+    return out, [queue_length(ws[key]) for key in ("fwd", "bwd")]
 
 
 # one fragment more and one row past it, one tile and several; two and three fragments more; the most tiles that take rows;
@@ -90,7 +83,7 @@ def test_low_tiles_by_the_sizes(d, I, workers, low):
         got[tile_rows].update(moe.moe_fused_backward(shape, dev["dy"], dev["x"], *w, routing, saved, ws=ws["bwd"], opts=opts))
         assert moe.moe_device_status(ws["fwd"]) == 0 and moe.moe_device_status(ws["bwd"]) == 0
         if tile_rows == 0:
-            tasks = [int(ws[key].view(torch.int32)[LENGTHS:LENGTHS + 8].sum()) for key in ("fwd", "bwd")]
+            tasks = [queue_length(ws[key]) for key in ("fwd", "bwd")]
     n = [sum(of(c, 128) if l else of(c, 256) for c in counts) for l in low]
     few = sum(1 for c in counts if 0 < c <= 32)   # ahead of the queue or on it: as the plan's own rule says
     assert tasks[0] in (n[0] * (of(I, 128) + of(d, 256)), (n[0] - few) * (of(I, 128) + of(d, 256)))
@@ -127,7 +120,7 @@ def test_tiles_follow_the_rows_of_a_share(T, E, rows, workers, height):
         got[tile_rows] = {"y": moe.moe_fused_forward(shape, dev["x"], *w, routing, saved=saved, ws=ws["fwd"], opts=opts)}
         got[tile_rows].update(moe.moe_fused_backward(shape, dev["dy"], dev["x"], *w, routing, saved, ws=ws["bwd"], opts=opts))
         assert moe.moe_device_status(ws["fwd"]) == 0 and moe.moe_device_status(ws["bwd"]) == 0
-        tasks = [int(ws[key].view(torch.int32)[LENGTHS:LENGTHS + 8].sum()) for key in ("fwd", "bwd")]
+        tasks = [queue_length(ws[key]) for key in ("fwd", "bwd")]
         tiles_of = n * of(rows, tile_rows or height)
         assert tasks == [tiles_of * (of(I, 128) + of(d, 256)), tiles_of * (of(I, 256) + of(d, 256)) + wgrad], tile_rows
     for key, v in got[0].items():
