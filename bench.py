@@ -87,12 +87,16 @@ def event_ms(fn, n, before=None):
 def measured_traffic(cfg_name, kernels):
     """HBM bytes that one call's launches of `kernels` move, from the committed counter summary
     (profiles/hbm_traffic_<workload>.txt, written by profile_summary.py
-    from a FETCH_SIZE and a WRITE_SIZE run scaled by the calibration copy), or None."""
+    from a FETCH_SIZE and a WRITE_SIZE run scaled by the calibration copy), or None where there
+    is none of the present kernels."""
+    import profile_summary
     path = ROOT / "profiles" / f"hbm_traffic_{cfg_name.replace('-', '_')}.txt"
     if not path.exists():
         return None
-    found = {}
-    for line in path.read_text().splitlines():
+    found, lines = {}, path.read_text().splitlines()
+    if f"sources: {profile_summary.sources()}" not in lines:
+        return None
+    for line in lines:
         if "traffic_bytes_per_launch=" in line:
             found[line.split()[0]] = float(line.split("traffic_bytes_per_launch=")[1].split()[0])
     return sum(found.get(k, 0.0) for k in kernels) if kernels[-1] in found else None

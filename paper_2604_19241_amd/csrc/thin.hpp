@@ -33,7 +33,7 @@ constexpr int kThinThreads = 256;
 constexpr int kThinGroupsPerCu = 2;   // as many as the LDS holds (80 KB each)
 constexpr int kThinXBytes = kThinRows * BK * 2;                       // rows of a stage: image [32 rows][128 B]
 constexpr int kThinMostImage = BK * 256 * 2 + kThinXBytes;
-// Weight columns of a task where `experts` of them have `columns` each, on `cus` CUs.  A CU draws 57 GB/s from HBM
+// Weight columns of a task where `experts` of them have `columns` each, on `cus` CUs.  A CU draws some 57 GB/s from HBM
 // at most, whatever it has on its way (its L1 holds 32 KB of lines in flight), so that the time is the tasks of the CU that
 // has most of them; a task of 128 columns takes 0.58 of one of 256, one of 64 (runs of 64 bytes) 0.42.  Measured, us of the
 // layer with 128 columns everywhere / with this rule (tokens, experts of width and inner width): 1021, 512 of 2048 x 512 690 / 624;

@@ -10,16 +10,25 @@
 `traffic` turns one FETCH_SIZE run and one WRITE_SIZE run into HBM bytes per launch,
 scaled by what the same counters read for `calibration_copy_kernel`, whose traffic is
 known (N bytes read, N bytes written).  bench.py reads the "traffic_bytes_per_launch"
-lines of the file written by `traffic`.
+lines of the file written by `traffic`, if its sources are the present ones.
 """
 from __future__ import annotations
 
 import argparse
 import collections
+import hashlib
+import re
 import sqlite3
 from pathlib import Path
 
 COPY_KERNEL = "calibration_copy_kernel"
+CSRC = Path(__file__).resolve().parent / "paper_2604_19241_amd" / "csrc"
+
+
+def sources() -> str:
+    """A hash of the kernels' sources without comments and white space."""
+    text = "".join(re.sub(r"//.*|\s+", "", f.read_text()) for f in sorted(CSRC.glob("*.h*")))
+    return hashlib.sha256(text.encode()).hexdigest()[:16]
 
 
 def _db(path: str) -> sqlite3.Connection:
@@ -130,7 +139,8 @@ def main():
             f.write(f"{COPY_KERNEL}: {a.copy_bytes} bytes read and written per launch; counters read "
                     f"FETCH_SIZE={copy_f[0]:.6g} WRITE_SIZE={copy_w[0]:.6g} per dispatch\n")
             f.write(f"scale: bytes per FETCH_SIZE unit = {fs:.2f}, per WRITE_SIZE unit = {wsc:.2f} "
-                    "(1024 would be exact KiB)\n\n")
+                    "(1024 would be exact KiB)\n")
+            f.write(f"sources: {sources()}\n\n")
             for k in sorted(fetch):
                 if k not in write or COPY_KERNEL in k:
                     continue
