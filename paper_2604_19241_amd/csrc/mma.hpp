@@ -700,6 +700,11 @@ __device__ __forceinline__ void zero_acc(Acc& acc, bool more) {
 
 // A tile of a row-tile GEMM (nk >= 1; row_of as in RowLoader), by the loop for its rows and the wave's NTF (scalar branches: every
 // wave runs exactly one instance, and all instances of a loop execute the same barriers).
+// Instances for odd numbers of row fragments are 16 % of the library's code.  Without them (one and three fragments by the loops
+// for two and four), us with / without: 128 experts of 2048 x 768 with 144, 208, 340 and 460 rows each, forward 340 / 344, 393 / 402,
+// 562 / 577 and 727 / 736, backward 802 / 812, 933 / 942, 1252 / 1263 and 1548 / 1570; 24 of 4096 x 1536 with 460 467 / 479 and 1065 / 1074.  Fewer
+// instances are faster only on small layers (8 experts of 512 x 1024 with 112 and 176 rows each 49.8 / 49.0 and 57.9 / 56.0,
+// with 80 and 208 47.4 / 48.2 and 60.1 / 60.9).
 template <int A_FORM, class LA, class F>
 __device__ __forceinline__ void row_tile_gemm(const Lane& ln, LA& la, int nk, int rows, char* smem, const FragAddr& fa, Acc& acc,
                                               F row_of) {
