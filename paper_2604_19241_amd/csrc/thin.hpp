@@ -26,8 +26,9 @@
 namespace uniep {
 
 // Rows up to which an expert takes this path: one fragment of the matrix instruction.  More would be blocks of 32, each
-// with the weights again: 128 experts of 2048 x 768 with 16 / 32 / 40 rows each 207 / 223 / 419 us, on the queue
-// 252 / 259 / 262 us; 16 of 2048 x 1408 59 / 61 / 106 us, on the queue 88 / 88 / 92 us.
+// with the weights again.  128 experts of 2048 x 768 with 16 / 32 rows each 206 / 213 us, on the queue 239 / 244 us, with
+// 40 on the queue 245 us (in two blocks 419 us, with tasks of 128 columns); 16 of 2048 x 1408 55 / 56 us, on the queue
+// 81 / 81 us, with 40 82 us (106 us).
 constexpr int kThinRows = 32;
 constexpr int kThinThreads = 256;
 constexpr int kThinGroupsPerCu = 2;   // as many as the LDS holds (80 KB each)
@@ -59,14 +60,19 @@ struct ThinShape {
 // alone: the two launches of this path stand in front of the queue's, one after the other, and add their latency
 // where the queue would have had CUs to spare for the same experts.  In whole numbers and from the counts alone,
 // so that every workgroup of a pass comes to the same answer by itself.  It pays
-//  - where no expert has more rows: nothing is left for the queue (8 experts of 2048 x 1408 with 10 rows each 39 us,
-//    on the queue 69 us; 128 of 2048 x 768 with 4 rows each 201 and 247 us);
+//  - where no expert has more rows: nothing is left for the queue (8 experts of 2048 x 1408 with 10 rows each 36 us,
+//    on the queue 70 us; 128 of 2048 x 768 with 4 rows each 191 and 223 us; 512 of 2048 x 512 with 2 521 and 560 us);
 //  - where nearly all have few or the others are bound by matrix work, and the queue is spared more time than this path
 //    takes.  The queue takes no less than a chain of GEMM1 and GEMM2 stages of 1 us each, else 30 us and the weights
-//    at 5.2 TB/s; this path 20 us and 6.4 TB/s (117 experts of 2048 x 768 with few rows beside 8 with 1900 each 346 us,
-//    on the queue 362 us; 63 beside 38 with 800 each 434 and 451 us).
-// It does not pay for 13 experts of 2048 x 1408 beside 3 with more rows (124 and 93 us), 14 beside 2 of 2048 x 768
-// (83 and 65 us), 43 beside 19 of 5120 x 1536 (749 and 687 us), 3 beside 5 of 4096 x 14336 (835 and 746 us).
+//    at 5.2 TB/s; this path 20 us and 6.4 TB/s (117 experts of 2048 x 768 with few rows beside 8 with 1900 each 350 us,
+//    on the queue 364 us; 112 beside 16 with 2000 each 510 and 525 us).
+// It did not pay for 13 experts of 2048 x 1408 beside 3 with more rows (124 and 93 us, now 81 us on the queue), 14 beside 2 of
+// 2048 x 768 (83 and 65 us), 43 beside 19 of 5120 x 1536 (749 and 687 us, now 527), 3 beside 5 of 4096 x 14336 (835 and 746 us, now 565).
+// The second line is from before the queue's low tiles kept two stages on their way (mma_low), and the queue would now be
+// the faster of the two in most of what lies on this side of it: 58 beside 4 with 2000 rows of 5120 x 1536 960 us, on the queue 790 us,
+// 28 beside 4 with 800 of 7168 x 2048 822 and 678 us, 95 beside one with 33 of 2048 x 768 192 and 179 us, 63 beside 38 with
+// 800 each 435 and 428 us.  Of 402 combinations of eight layers that the rule sends ahead of it the queue takes more
+// than 1 % less in 335 (half of all 4 % less or better, at best 22 %) and more than 1 % more in 20 (at most 4 %).
 struct ThinRule {
     int max_rows;              // an expert has few rows up to here
     int many_most;             // up to so many experts with more rows have so many that matrix work bounds them
