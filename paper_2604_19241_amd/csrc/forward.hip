@@ -51,8 +51,8 @@ struct FwdParams {
 // row-tile table from the expert offsets, the per-XCD task lists (GEMM1 block of expert i+1 ahead of the
 // GEMM2 block of expert i) and a cleared scoreboard.
 __device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePlan& P) {
-    const int ec = p.s.e_count;
-    const TileRule tile = make_plan(P, p.offsets, ec, p.rule.max_rows, [&](int counts) { return p.rule.limit(counts); }, p.tile, p.nct1,
+    const int ec = p.s.e_count, rows_here = p.offsets[ec];
+    const TileRule tile = make_plan(P, p.offsets, ec, p.rule.max_rows, [&](int counts) { return p.rule.limit(counts, rows_here); }, p.tile, p.nct1,
                                     [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct1; },
                                     [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct2; });
     const int lane = threadIdx.x & 63;

@@ -75,23 +75,27 @@ struct ThinShape {
 // than 1 % less in 335 (half of all 4 % less or better, at best 22 %) and more than 1 % more in 20 (at most 4 %).
 struct ThinRule {
     int max_rows;              // an expert has few rows up to here
-    int many_most;             // up to so many experts with more rows have so many that matrix work bounds them
+    // Up to so many experts with more rows have so many that matrix work bounds them: 512 rows each, of those that even routing
+    // gives the experts here, but no more than there are.  (A share with few of the tokens' rows was taken for one with many: 19
+    // experts of 5120 x 1536 with 60 rows beside 43 with 10, 40000 tokens elsewhere, 579 us, now on the queue 517 us; 8 of 7168 x
+    // 2048 with 50 beside 24 with 20, 64000 elsewhere, 547 -> 490 us.)
+    int many_most;
     long long chain_ns;
     int queue_ns, thin_ns;     // an expert's weights
     __host__ __device__ __forceinline__ long long queue(int experts) const {
         const long long stream = 30000 + (long long)experts * queue_ns;
         return stream > chain_ns ? stream : chain_ns;
     }
-    __host__ __device__ __forceinline__ bool pays(int few, int many) const {
+    __device__ __forceinline__ bool pays(int few, int many, int rows) const {
         if (many == 0) return true;
-        if (few < 8 * many && many > many_most) return false;
+        if (few < 8 * many && many > min(many_most, rows / 512)) return false;
         return queue(few + many) - queue(many) > 20000 + (long long)few * thin_ns;
     }
     // Rows up to which an expert of this batch takes this path (0 = none does); counts: experts with few rows and,
-    // shifted left by 16, with more.
-    __device__ __forceinline__ int limit(int counts) const {
+    // shifted left by 16, with more; rows: of all of them.
+    __device__ __forceinline__ int limit(int counts, int rows) const {
         const int c = rfl(counts);
-        return pays(c & 0xffff, c >> 16) ? max_rows : 0;
+        return pays(c & 0xffff, c >> 16, rfl(rows)) ? max_rows : 0;
     }
 };
 inline ThinRule thin_rule(const moe_shape_t& s, int max_rows) {
@@ -347,6 +351,7 @@ template <int GEMM>
 __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blocks, ThinShared& S) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ec = p.s.e_count;
+    const int rows_here = p.offsets[ec];
     int off[5], mine = 0;
 #pragma unroll
     for (int j = 0; j < 5; ++j) off[j] = p.offsets[min(4 * tid + j, ec)];
@@ -369,7 +374,7 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
         if (w < wave) at += S.wave[w];
         count += S.wave[w];
     }
-    if (p.rule.limit(count) == 0) return;
+    if (p.rule.limit(count, rows_here) == 0) return;
     at &= 0xffff;
     count &= 0xffff;
     if (count == 0) return;

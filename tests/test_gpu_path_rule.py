@@ -67,6 +67,33 @@ def test_the_same_bits_on_both_paths(few, many, rows, ahead):
         assert torch.equal(v, want[name][:n]), name
 
 
+# 128 of 136 experts, `many` of them with so many rows and the others with 10: the rows that are here decide, not the tokens (24000
+# of them, of which even routing would send 22588 here).
+@pytest.mark.parametrize("many,rows,ahead", [(38, 50, False), (20, 200, False), (30, 560, True)])
+def test_a_share_is_judged_by_its_rows(many, rows, ahead):
+    T, E, ec, d, I = 24000, 136, 128, 2048, 768
+    counts = np.full(ec, 10)
+    counts[:many] = rows
+    own = np.concatenate([np.repeat(np.arange(ec), counts), np.resize(np.arange(ec, E), T - counts.sum())])
+    own = torch.from_numpy(np.random.default_rng(many).permutation(own)).cuda()
+    shape = moe.make_shape(T=T, d=d, E=E, k=1, I=I, e_count=ec)
+    logits = torch.zeros((T, E), device="cuda")
+    logits[torch.arange(T), own] = 1.0
+    g = torch.Generator(device="cuda").manual_seed(many)
+    x, *w = [torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16) * 0.05 for s in ((T, d), (ec, d, I), (ec, d, I), (ec, I, d))]
+    say(f"[path] share: {many} with {rows}")
+    ws = torch.empty(moe.moe_workspace_bytes(shape)["fwd"], dtype=torch.uint8, device="cuda")
+    y = moe.moe_fused_forward(shape, x, *w, moe.moe_route(shape, logits), ws=ws)
+    assert moe.moe_device_status(ws) == 0
+    queued = counts[counts > (32 if ahead else 0)]
+    assert int(ws.view(torch.int32)[ROW_TILES]) == int((-(-queued // 256)).sum())
+    # the same rows as a layer of their own
+    here = own < ec
+    whole = moe.make_shape(T=int(here.sum()), d=d, E=ec, k=1, I=I)
+    want = moe.moe_fused_forward(whole, x[here].contiguous(), *w, moe.moe_route(whole, logits[here][:, :ec].contiguous()))
+    assert torch.equal(y[here], want) and (y[~here] == 0).all()
+
+
 def test_no_launch_for_few_rows_where_the_sizes_rule_it_out():
     first_call()
     # more rows than 32 for each of all experts, or than 128 where only some are here
