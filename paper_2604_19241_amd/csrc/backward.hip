@@ -817,7 +817,7 @@ static int bwd_launch_tiles(BwdParams& p, const moe_opts_t& opts, hipStream_t st
     if (rc != MOE_OK) return rc;
     const int workers = opts.workers > 0 ? min(opts.workers, resident) : resident;
     p.workers = workers;
-    p.tile = TileChoice{TileChoice::rows_of(p.s, opts.tile_rows), {p.nct_dh, p.nct_dxp}, {p.s.d / BK, 2 * p.s.I / BK}, workers, 0.5f, 0.3f, 1.f};
+    p.tile = TileChoice{TileChoice::rows_of(p.s, opts.tile_rows), p.nct_dh + p.nct_dxp, workers, 3};
     const int A_cap = p.s.T * p.s.k;
     hipLaunchKernelGGL(bwd_first_kernel, dim3(kPlanBlocks + (A_cap + kPlanThreads - 1) / kPlanThreads), dim3(kPlanThreads),
                        0, st, p);

@@ -248,7 +248,7 @@ struct QueuePlan {
     int32_t rows[kMaxExperts];
     int32_t rt0[kMaxExperts];             // first scoreboard slot of the expert
     int32_t sums[kPlanWaves];             // slots of each wave's experts
-    int32_t most[kPlanWaves], low[kPlanWaves], total[kPlanWaves];
+    int32_t most[kPlanWaves], total[kPlanWaves];   // rows: of the expert that has most, together
     int32_t counts[kPlanWaves];           // experts with few and with many rows
     int32_t hist[kPlanWaves][64];
     int32_t first[kPlanWaves][64];
@@ -291,49 +291,27 @@ struct TileRule {
     __device__ __forceinline__ int rows_of(int j, int h, int rows) const { return min(bm + (j < h ? 32 : 0), rows - first(j, h)); }
     static constexpr int kMostHigher = 3, kMostTiles = 16;
 };
-// What the plan adds up over the experts on the queue.
-struct QueueRows {
-    int rows, most;        // together, and of the expert that has most
-    int slots, low;        // tiles of 256 and of 128 rows
-};
 // Chooses the rule from the rows that the queue has, which only the device knows (a share of the experts may hold several times
 // the rows that even routing would give it, or a fraction), the same in every planning workgroup.
-// Tiles of 128 rows: where CUs are idle, two tiles side by side take less than one, and low tiles keep two stages on their way
-// (mma_low; not worth it for GEMMs of a few stages).  Where the CUs are full they cost more, as each streams the weights
-// for itself.  What a pass takes with either is the larger of three for each of its two row-tile GEMMs, in stages of a full tile:
-// one tile; the work a CU, and `tail` of a tile as the CUs do not end together; `xcd` of the work a CU if the expert
-// with most rows stayed on its XCD.  A tile of r rows takes 0.45 + 0.55 r / 256, a low one low0 + 0.1 r / 128.
-// The numbers are those that chose best where both were measured.  Over 7306 forward and backward passes (11 layers, shares, even, skewed and
-// uneven routing) 142 take more than 3 % longer than with 256 rows everywhere, all together 5.6 % less; by a bound on the tasks a CU,
-// from the tokens alone, 584 did and all together took 4.9 % less.  Measured, us with 256 / 128 rows: forward of 3932 rows on 8
-// experts of 2048 x 1408 111 / 125, of 9828 on 64 of 1280 x 896 143 / 161, of 46158 on 32 of 1024 x 384 163 / 194, but of 378 on
-// 2 of 4096 x 14336 435 / 332, of 4024 on 16 of 2048 x 1408 151 / 121; backward of 1966 on 8 of 512 x 1024 96 / 71.
+// halves / 2: tasks of 256 rows a CU (on average) below which tiles have 128 rows.  Where CUs are idle, two tiles side by side
+// take less than one, and low tiles keep two stages on their way (mma_low; not worth it for GEMMs of a few stages); where
+// the CUs are full they cost more, as each streams the weights for itself.  Measured, us with tiles of 256 / of 128 rows (tasks a CU):
+// training steps of 1000 tokens on 8 experts of 512 x 1024 (0.3) 176 / 133, 1500 on 2 of 8 of 4096 x 14336 (0.8) 1660 / 1407,
+// 4096 on 16 of 128 of 4096 x 1536 (1.4) 806 / 762, 8000 on 8 of 512 x 1024 (1.5) 320 / 318, 20000 on 32 of 128 of 1024 x 384
+// (2.8) 413 / 441; forward passes of 4099 tokens on 16 of 64 of 2048 x 1408 (1.8) 180 / 173, 10000 on 8 of 512 x 1024 (3.0)
+// 111 / 125, 46158 rows on 32 of 1024 x 384 163 / 194.  Of 400 batches of eleven layers (shares, even and skewed routing) the bound is on
+// average 0.8 % forward and 0.2 % backward from the better height; an estimate of both times from the tiles, the rows and
+// the largest expert was 0.7 % and 0.4 %, but up to 21 % from it.
 // Higher tiles from 3 tasks a CU on: training steps without / with, 3000 tokens on 16 of 64 experts of 1280 x 896 (0.8)
 // 265 / 276, 8192 on 32 of 256 of 7168 x 2048 (5.5) 3169 / 2960.
 struct TileChoice {
     static int rows_of(const moe_shape_t& s, int caller) { return caller == 0 && s.d + s.I < 8 * 64 ? 256 : caller; }
-    int tile_rows;            // 128, 256, or 0 = by the rows
-    int cols[2], stages[2];   // column tiles and stages of the pass's row-tile GEMMs
-    int workers;
-    float low0, tail, xcd;
-    // times the workers
-    __device__ __forceinline__ float cost(const QueueRows& q, float c0, float c1, int bm, int tiles) const {
-        const float tile = c0 + c1 * (float)min(q.most, bm) / (float)bm;
-        const float all = c0 * (float)tiles + c1 * (float)q.rows / (float)bm;
-        const float most = c0 * (float)((q.most + bm - 1) / bm) + c1 * (float)q.most / (float)bm;
-        const float w = (float)workers;
-        float sum = 0.f;
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            const float n = (float)cols[g], ends = tail * tile * fminf(w, n * (float)tiles);
-            sum += (float)stages[g] * fmaxf(fmaxf(tile * w, n * all + ends), xcd * (float)kQueues * n * most);
-        }
-        return sum;
-    }
-    __device__ __forceinline__ TileRule rule(const QueueRows& q) const {
-        if (tile_rows == 128 || (tile_rows == 0 && cost(q, low0, 0.1f, 128, q.low) < cost(q, 0.45f, 0.55f, 256, q.slots)))
-            return TileRule{128, 0};
-        const long long tasks = (long long)q.rows * (cols[0] + cols[1]) / 256;
+    int tile_rows;   // 128, 256, or 0 = by the rows
+    int col_tiles;   // column tiles an expert of the pass's row-tile GEMMs
+    int workers, halves;
+    __device__ __forceinline__ TileRule rule(int rows) const {
+        const long long tasks = (long long)rows * col_tiles / 256;
+        if (tile_rows == 128 || (tile_rows == 0 && 2 * tasks < (long long)halves * workers)) return TileRule{128, 0};
         return TileRule{256, tasks >= 3ll * workers ? TileRule::kMostHigher : 0};
     }
 };
@@ -347,7 +325,7 @@ __device__ __forceinline__ TileRule make_plan(QueuePlan& P, const int32_t* offse
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
     constexpr int kRounds = kMaxExperts / kPlanThreads;
-    int rows[kRounds], run = 0, most = 0, low = 0, sum = 0, counts = 0;
+    int rows[kRounds], run = 0, most = 0, sum = 0, counts = 0;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {   // wave w looks at experts 256 w + 64 r + lane
         const int e = 256 * w + 64 * r + lane;
@@ -380,32 +358,27 @@ __device__ __forceinline__ TileRule make_plan(QueuePlan& P, const int32_t* offse
         P.rt0[e] = run + incl - nt;   // inside the wave; the waves before are added by the reader (plan_rt0)
         run += __shfl(incl, 63);
         most = max(most, rows[r]);
-        low += (rows[r] + 127) >> 7;
         sum += rows[r];
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         most = max(most, __shfl_xor(most, o));
-        low += __shfl_xor(low, o);
         sum += __shfl_xor(sum, o);
     }
     if (lane == 0) {
         P.sums[w] = run;
         P.most[w] = most;
-        P.low[w] = low;
         P.total[w] = sum;
     }
     __syncthreads();
-    QueueRows all = {0, 0, 0, 0};
+    int total = 0, n_slots = 0;
 #pragma unroll
     for (int i = 0; i < kPlanWaves; ++i) {
-        all.rows += P.total[i];
-        all.most = max(all.most, P.most[i]);
-        all.slots += P.sums[i];
-        all.low += P.low[i];
+        total += P.total[i];
+        most = max(most, P.most[i]);
+        n_slots += P.sums[i];
     }
-    most = all.most;
-    const TileRule tile = choice.rule(all);
+    const TileRule tile = choice.rule(total);
     // rank inside the class: the wave's experts of the class so far + the lanes below
     const float scale = most > 0 ? 62.f / (float)most : 0.f;
     int cls[kRounds], rank[kRounds];
@@ -496,8 +469,8 @@ __device__ __forceinline__ TileRule make_plan(QueuePlan& P, const int32_t* offse
             base += P.a[q][kListSlots] + P.b[q][kListSlots];
         }
         P.base[kQueues] = base;
-        P.n_row_tiles = all.slots;
-        P.lag = queue_lag(tile.flags(all.slots) * per_row_tile, ec);
+        P.n_row_tiles = n_slots;
+        P.lag = queue_lag(tile.flags(n_slots) * per_row_tile, ec);
     }
     __syncthreads();
     return tile;

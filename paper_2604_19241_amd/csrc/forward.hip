@@ -474,7 +474,7 @@ static int fwd_launch_tiles(FwdParams& p, const moe_opts_t& opts, hipStream_t st
     if (rc != MOE_OK) return rc;
     int workers = opts.workers > 0 ? min(opts.workers, resident) : resident;
     p.workers = workers;
-    p.tile = TileChoice{TileChoice::rows_of(p.s, opts.tile_rows), {p.nct1, p.nct2}, {p.s.d / BK, p.s.I / BK}, workers, 0.55f, 0.6f, 0.3f};
+    p.tile = TileChoice{TileChoice::rows_of(p.s, opts.tile_rows), p.nct1 + p.nct2, workers, 4};
     // A token selects an expert at most once, so up to kThinRows tokens no expert has more rows than
     // that: every expert is thin and no work queue is set up.
     const bool all_thin = p.s.T <= kThinRows;

@@ -55,9 +55,9 @@ def test_higher_tiles(counts, d, I):
     check_elementwise("dtopk_w", to_f64(got["dtopk_w"]), ref["dtopk_w"], whole_array_rms=True)
 
 
-# Tiles of 128 rows where they take less: on many workers in both passes, on some in the backward pass, on few and where the GEMMs
-# have a few stages in none; two flags a scoreboard slot, at row counts around a slot's edges
-@pytest.mark.parametrize("d,I,workers,low", [(320, 448, 0, (True, True)), (320, 448, 30, (False, False)), (320, 448, 60, (False, True)),
+# Tiles of 128 rows by the sizes: below two tasks a worker forward and one and a half backward, none where the GEMMs have
+# a few stages; two flags a scoreboard slot, at row counts around a slot's edges
+@pytest.mark.parametrize("d,I,workers,low", [(320, 448, 0, (True, True)), (320, 448, 30, (False, False)), (320, 448, 40, (False, True)),
                                              (64, 64, 0, (False, False))])
 def test_low_tiles_by_the_sizes(d, I, workers, low):
     counts = [127, 128, 129, 255, 256, 257, 384, 385, 512, 513, 1, 0, 700]
