@@ -128,9 +128,8 @@ __device__ __forceinline__ void load_logits(const float* __restrict__ row, int E
 #pragma unroll
     for (int i = 0; i < EPL; ++i) x[i] = row[i < EPL / 2 ? lane + 64 * i : min(lane + 64 * i, E - 1)];
 }
-// Top-k of NT tokens by one wave: lane j < k gets a token's j-th expert and its gate.  A round is one chain of dependent
-// instructions: the tokens' chains run side by side, without a branch between them (32768 tokens of 256 experts, 8 selected,
-// 36.8 -> 34.4 us for the whole routing).
+// Top-k where RowSelect is not taken, NT tokens by one wave: lane j < k gets a token's j-th expert and its gate.  A round is one
+// chain of dependent instructions: the tokens' chains run side by side, without a branch between them.
 template <int EPL, int NT>
 __device__ __forceinline__ void select_experts(const float (&x)[NT][EPL], int E, int k, int lane, int (&my_idx)[NT], float (&gate)[NT]) {
     uint32_t key[NT][EPL], my_key[NT], best[NT];
@@ -176,24 +175,207 @@ __device__ __forceinline__ void select_experts(const float (&x)[NT][EPL], int E,
     }
 }
 
+template <int EPL>
+struct WaveSelect {
+    // tokens t, t + BY, ... of the wave, two at a time where the registers allow it (16 keys a lane, twice, take too many)
+    template <int BY, class Put>
+    static __device__ __forceinline__ void run(const float* __restrict__ logits, int wave, int n, int E, int k, Put put) {
+        const int lane = threadIdx.x & 63;
+        auto tokens = [&](int t, auto count) {
+            constexpr int NT = decltype(count)::value;
+            float x[NT][EPL], gate[NT];
+            int idx[NT];
+#pragma unroll
+            for (int i = 0; i < NT; ++i) load_logits<EPL>(logits + (size_t)(t + i * BY) * E, E, lane, x[i]);
+            select_experts<EPL, NT>(x, E, k, lane, idx, gate);
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+                if (lane < k) put(t + i * BY, lane, idx[i], gate[i]);
+        };
+        int t = wave;
+        if constexpr (EPL <= 8)
+            for (; t + BY < n; t += 2 * BY) tokens(t, std::integral_constant<int, 2>{});
+        for (; t < n; t += BY) tokens(t, std::integral_constant<int, 1>{});
+    }
+    static constexpr int kTokens = 1;
+    template <class Put>
+    static __device__ __forceinline__ void one(const float* __restrict__ logits, int t, int, int E, int k, Put put) {
+        run<1>(logits + (size_t)t * E, 0, 1, E, k, [&](int, int slot, int expert, float gate) { put(t, slot, expert, gate); });
+    }
+};
+
+// ------------------------------------------- top-k of up to 256 experts
+// Four tokens a wave, one in each row of 16 lanes: lane q of a row has the experts q, q + 16, ... of its token, as doubles that are
+// ordered as (value, then lower expert id): the logit's key in the high bits, 1023 - id below.  No two experts
+// have the same one, so a lane's list needs no ids beside it, and a compare-and-exchange is two instructions.  Every lane sorts its
+// EPL keys; a round takes the largest head of the row (four rotations, for the four tokens at once) and the
+// lane that had it moves its list up by one.  Bound by instruction issue: some 150 instructions a token with 256 experts and 8
+// selected, where a token on all 64 lanes (six steps a maximum, a ballot for every key) took 480.  The whole routing, us, so / now (tokens x
+// experts x k): 32768 x 256 x 8 33.3 / 23.2, 60001 x 256 x 8 47.0 / 33.9, 65536 x 128 x 8 38.4 / 27.1, 24000 x 128 x 6 25.5 / 21.6, 8192 x 128 x 8
+// 13.8 / 12.3, 65536 x 8 x 2 18.3 / 13.7, 32 x 128 x 8 6.0 / 6.0.  With one workgroup of the ranking a CU instead of two, the registers
+// of which hold the next tokens' logits, 60001 x 256 x 8 took 39.6.  More than 8 of 129 to 256 experts stay with WaveSelect: 16 sorted keys a
+// lane and 16 rounds that move them were slower.
+// The keys are positive, normal and finite: those of -inf and +inf have the exponents 0x003 and 0x7fc.
+// 0.0 stands for a NaN (never selected) and for the padding.
+__device__ __forceinline__ double expert_key(float x, int id) {
+    const uint32_t key = logit_key(x);
+    const uint32_t lo = (key << 31) | (uint32_t)(kMaxExperts - 1 - id);
+    return __builtin_bit_cast(double, (uint64_t)(key >> 1) << 32 | (key ? lo : 0u));
+}
+__device__ __forceinline__ uint32_t double_key(double v) { return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 31); }
+__device__ __forceinline__ int double_expert(double v) {
+    return kMaxExperts - 1 - (int)((uint32_t)__builtin_bit_cast(uint64_t, v) & (kMaxExperts - 1));
+}
+// The value of the lane BY further on in the row of 16 (in a circle).
+template <int BY>
+__device__ __forceinline__ uint32_t row_ror(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + BY, 0xf, 0xf, true);
+}
+template <int BY>
+__device__ __forceinline__ double row_ror(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)row_ror<BY>((uint32_t)(u >> 32)) << 32 | row_ror<BY>((uint32_t)u));
+}
+template <int BY>
+__device__ __forceinline__ float row_ror(float v) {
+    return __uint_as_float(row_ror<BY>(__float_as_uint(v)));
+}
+// Larger one to a, smaller one to b.
+__device__ __forceinline__ void exchange(double& a, double& b) {
+    const double m = fmin(a, b);
+    a = fmax(a, b);
+    b = m;
+}
+// Descending (Batcher's odd-even merge sort).  The scheduler would otherwise run the passes into one another and need twice the registers.
+template <int N>
+__device__ __forceinline__ void sort_descending(double* v) {
+#pragma unroll
+    for (int p = 1; p < N; p *= 2)
+#pragma unroll
+        for (int q = p; q >= 1; q /= 2) {
+#pragma unroll
+            for (int j = q % p; j + q < N; j += 2 * q)
+#pragma unroll
+                for (int i = 0; i < q; ++i)
+                    if (i + j + q < N && (i + j) / (2 * p) == (i + j + q) / (2 * p)) exchange(v[i + j], v[i + j + q]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+}
+
+// How a wave selects the experts of its tokens.  KM: compile-time bound on k.
+template <int EPL_, int KM>
+struct RowSelect {
+    static constexpr int kTokens = 4;   // of a wave, at a time
+    static constexpr int EPL = EPL_, D = EPL < KM ? EPL : KM;
+    // (a scalar base and 32-bit byte offsets; rows past the n-th alias it)
+    static __device__ __forceinline__ void load(const float* __restrict__ logits, int t, int n, int E, float (&x)[EPL]) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));   // nothing is kept over the loop: every lane offset would take a register
+        const int q = tid & 15;
+        const char* base = (const char*)(logits + (size_t)t * E);
+        const uint32_t row = (uint32_t)(min((tid >> 4) & 3, n - 1 - t) * E);
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+            const uint32_t e = (uint32_t)(EPL > 2 && i < EPL / 2 ? q + 16 * i : min(q + 16 * i, E - 1));
+            x[i] = *(const float*)(base + (row + e) * 4u);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // tokens t .. t + 3, the wave's t = 4 wave, 4 (wave + BY), ...: put(token, slot, expert, gate) for every slot below k
+    template <int BY, class Put>
+    static __device__ __forceinline__ void run(const float* __restrict__ logits, int wave, int n, int E, int k, Put put) {
+        for (int t = 4 * wave; t < n; t += 4 * BY) one(logits, t, n, E, k, put);
+    }
+    template <class Put>
+    static __device__ __forceinline__ void one(const float* __restrict__ logits, int t, int n, int E, int k, Put put) {
+        float x[EPL];
+        load(logits, t, n, E, x);
+        select(x, t, n, E, k, put);
+    }
+    template <class Put>
+    static __device__ __forceinline__ void select(const float (&x)[EPL], int t, int n, int E, int k, Put put) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int q = tid & 15, mine = t + ((tid >> 4) & 3);
+        double v[EPL];
+        // the D largest of the lane's, descending
+#pragma unroll
+        for (int h = 0; h < EPL; h += D) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = h; i < h + D; ++i) {
+                const bool any = (EPL > 2 && i < EPL / 2) || q + 16 * i < E;
+                v[i] = expert_key(any ? x[i] : __builtin_nanf(""), q + 16 * i);
+            }
+            sort_descending<D>(v + h);
+        }
+        if constexpr (EPL > D) {   // of two such lists the larger ones in turn are the D largest, and rise and fall at most once
+            static_assert(EPL == 2 * D, "");
+#pragma unroll
+            for (int i = 0; i < D; ++i) v[i] = fmax(v[i], v[EPL - 1 - i]);
+#pragma unroll
+            for (int o = D / 2; o >= 1; o /= 2) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < D; ++i)
+                    if ((i & o) == 0) exchange(v[i], v[i + o]);
+            }
+        }
+        double taken = 0.0, top = 0.0;
+        auto round = [&](int j, int depth) {   // depth: entries of the lists that a later round may still take
+            double best = fmax(v[0], row_ror<8>(v[0]));
+            best = fmax(best, row_ror<4>(best));
+            best = fmax(best, row_ror<2>(best));
+            best = fmax(best, row_ror<1>(best));
+            if (j == 0) top = best;
+            taken = q == j ? best : taken;
+            const bool won = __builtin_bit_cast(uint64_t, v[0]) == __builtin_bit_cast(uint64_t, best);
+#pragma unroll
+            for (int i = 0; i < D && i < depth; ++i) v[i] = won ? (i + 1 < D ? v[i + 1] : 0.0) : v[i];
+        };
+        if constexpr (KM <= 8) {
+#pragma unroll
+            for (int j = 0; j < KM; ++j) {
+                if (j >= k) break;
+                round(j, KM - 1 - j);
+            }
+        } else {
+            for (int j = 0; j < k; ++j) round(j, D);
+        }
+        // nothing but NaN left: no expert
+        const uint32_t key = double_key(taken), top_key = double_key(top);
+        const float val = key ? key_logit(key) : -INFINITY, top1 = top_key ? key_logit(top_key) : -INFINITY;
+        const float p = q < k ? __expf(val - top1) : 0.f;
+        float s = p + row_ror<8>(p);
+        s += row_ror<4>(s);
+        s += row_ror<2>(s);
+        s += row_ror<1>(s);
+        if (q < k && mine < n) put(mine, q, key ? double_expert(taken) : 0x7fffffff, p / s);
+    }
+};
+
+struct NoSelect {
+    static constexpr int kTokens = 0;
+};
+
 // ------------------------------------------- top-k, gates and ranks inside a chunk
-// One workgroup per chunk, one wave per token at a time.  Lane l holds experts l, l+64, ... as
-// sortable keys; a round of arg-max under the order (value desc, expert id asc) is one wave
-// maximum and one ballot per key, whose first set bit is the lowest expert id.  Gates come from
+// One workgroup per chunk, whose waves select the experts of four tokens (RowSelect) or one or two (WaveSelect: lane l holds experts l,
+// l+64, ... as sortable keys; a round of arg-max under the order (value desc, expert id asc) is one wave
+// maximum and one ballot per key, whose first set bit is the lowest expert id) at a time.  Gates come from
 // the k selected logits (the softmax denominator over all E cancels in the renormalisation).
 // Then wave i ranks the chunk's slots [64 i, 64 i + 64): lanes that share an expert are the
 // intersection of the ballots of the expert id's bits.  chunk_cnt[c][e] = slots of chunk c
 // routed to local expert e; inv_perm[f] = rank of slot f among its chunk's slots of that expert.
-// EPL = 0: topk_kernel has selected the experts already.
+// SEL: RowSelect, WaveSelect, or NoSelect where topk_kernel has selected the experts already.
 // Bound by instruction issue.  With the maximum by shuffles and counts, scan and positions in three
 // launches of their own the whole routing took 101 us for 32768 tokens of 256 experts, 8 selected
-// (now 34 us), and 11-15 us in four launches for up to 16 tokens of 128 experts (now one launch of 3.6-5 us).
+// (now 23 us), and 11-15 us in four launches for up to 16 tokens of 128 experts (now one launch of 3.6-5 us).
 //
 // ONE: the batch is a single chunk (a generation step): the ranks are complete, and the same
 // workgroup scans the counts and writes the rows.
 // PIECES: 64-slot pieces of a chunk (a wave's counts of an expert in a piece are at most 64).
 // Two workgroups of 16 waves share a CU: 8 waves a SIMD, up to 64 registers a lane.
-template <int EPL, bool ONE, int PIECES>
+template <class SEL, bool ONE, int PIECES>
 __global__ void __launch_bounds__(kChunkThreads) __attribute__((amdgpu_waves_per_eu(8)))
 topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_chunk, int e_start, int e_count,
                  int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ chunk_cnt,
@@ -209,28 +391,14 @@ topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_
     if (tid < e_count)
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) s_cnt[i][tid] = 0;
-    if constexpr (EPL > 0) {
-        constexpr int kWaves = kChunkThreads / 64;
-        auto tokens = [&](int tt, auto count) {   // tt, tt + kWaves, ...
-            constexpr int NT = decltype(count)::value;
-            float x[NT][EPL], gate[NT];
-            int idx[NT];
-#pragma unroll
-            for (int n = 0; n < NT; ++n) load_logits<EPL>(logits + (size_t)(t0 + tt + n * kWaves) * E, E, lane, x[n]);
-            select_experts<EPL, NT>(x, E, k, lane, idx, gate);
-#pragma unroll
-            for (int n = 0; n < NT; ++n)
-                if (lane < k) {
-                    const int f = (tt + n * kWaves) * k + lane;
-                    s_idx[f] = idx[n];
-                    topk_idx[f0 + f] = idx[n];
-                    topk_w[f0 + f] = gate[n];
-                }
-        };
-        int tt = __builtin_amdgcn_readfirstlane(wave);
-        if constexpr (EPL <= 8)   // (16 keys a lane, twice, take too many registers)
-            for (; tt + kWaves < nt; tt += 2 * kWaves) tokens(tt, std::integral_constant<int, 2>{});
-        for (; tt < nt; tt += kWaves) tokens(tt, std::integral_constant<int, 1>{});
+    if constexpr (SEL::kTokens > 0) {
+        SEL::template run<kChunkThreads / 64>(
+            logits + (size_t)t0 * E, __builtin_amdgcn_readfirstlane(wave), nt, E, k, [&](int token, int slot, int expert, float gate) {
+                const int f = token * k + slot;
+                s_idx[f] = expert;
+                topk_idx[f0 + f] = expert;
+                topk_w[f0 + f] = gate;
+            });
     } else if (tid < n) {
         s_idx[tid] = topk_idx[f0 + tid];
     }
@@ -280,21 +448,16 @@ topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_
 }
 
 // ------------------------------------------- top-k alone
-// One token a wave, over the whole chip; topk_rank_kernel<0, ..> then ranks what this wrote.
-template <int EPL>
+// Over the whole chip, four tokens or one a wave; topk_rank_kernel<NoSelect, ..> then ranks what this wrote.
+template <class SEL>
 __global__ void __launch_bounds__(kRouteThreads)
 topk_kernel(const float* __restrict__ logits, int T, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    const int lane = threadIdx.x & 63;
-    for (int t = blockIdx.x * (kRouteThreads / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); t < T; t += gridDim.x * (kRouteThreads / 64)) {
-        float x[1][EPL], gate[1];
-        int idx[1];
-        load_logits<EPL>(logits + (size_t)t * E, E, lane, x[0]);
-        select_experts<EPL, 1>(x, E, k, lane, idx, gate);
-        if (lane < k) {
-            topk_idx[(size_t)t * k + lane] = idx[0];
-            topk_w[(size_t)t * k + lane] = gate[0];
-        }
-    }
+    constexpr int kPer = kRouteThreads / 64 * SEL::kTokens;
+    for (int t = blockIdx.x * kPer + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * SEL::kTokens; t < T; t += gridDim.x * kPer)
+        SEL::one(logits, t, T, E, k, [&](int token, int slot, int expert, float gate) {
+            topk_idx[(size_t)token * k + slot] = expert;
+            topk_w[(size_t)token * k + slot] = gate;
+        });
 }
 
 // ------------------------------------------------------------- scan over chunks
@@ -565,7 +728,7 @@ size_t route_workspace_bytes(const moe_shape_t& s) {
     return align_up(n_chunks * (size_t)s.e_count * sizeof(int32_t) + 256, 256);
 }
 
-template <int EPL>
+template <class SEL>
 static void launch_rank(const moe_shape_t& s, const Chunks& c, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
                         hipStream_t st) {
     auto launch = [&](auto kernel) {
@@ -573,20 +736,20 @@ static void launch_rank(const moe_shape_t& s, const Chunks& c, const float* logi
                            (int32_t*)out.topk_idx, (float*)out.topk_w, chunk_cnt, (int32_t*)out.counts, (int32_t*)out.offsets,
                            (int32_t*)out.perm, (int32_t*)out.inv_perm);
     };
-    if constexpr (EPL > 0)
-        if (c.lng) return launch(topk_rank_kernel<EPL, false, kLongPieces>);
-    if (c.n == 1) launch(topk_rank_kernel<EPL, true, kPieces>);
-    else launch(topk_rank_kernel<EPL, false, kPieces>);
+    if constexpr (SEL::kTokens > 0)
+        if (c.lng) return launch(topk_rank_kernel<SEL, false, kLongPieces>);
+    if (c.n == 1) launch(topk_rank_kernel<SEL, true, kPieces>);
+    else launch(topk_rank_kernel<SEL, false, kPieces>);
 }
 
-template <int EPL>
+template <class SEL>
 static void launch_topk(const moe_shape_t& s, const Chunks& c, const float* logits, const moe_routing_t& out, int32_t* chunk_cnt,
                         hipStream_t st) {
-    if (!topk_alone(s, c)) return launch_rank<EPL>(s, c, logits, out, chunk_cnt, st);
-    const int grid = std::min((s.T + kRouteThreads / 64 - 1) / (kRouteThreads / 64), kTopkGroups);
-    hipLaunchKernelGGL(topk_kernel<EPL>, dim3(grid), dim3(kRouteThreads), 0, st, logits, s.T, s.E, s.k,
+    if (!topk_alone(s, c)) return launch_rank<SEL>(s, c, logits, out, chunk_cnt, st);
+    const int per = kRouteThreads / 64 * SEL::kTokens, grid = std::min((s.T + per - 1) / per, kTopkGroups);
+    hipLaunchKernelGGL(topk_kernel<SEL>, dim3(grid), dim3(kRouteThreads), 0, st, logits, s.T, s.E, s.k,
                        (int32_t*)out.topk_idx, (float*)out.topk_w);
-    launch_rank<0>(s, c, logits, out, chunk_cnt, st);
+    launch_rank<NoSelect>(s, c, logits, out, chunk_cnt, st);
 }
 
 int route_launch(const moe_shape_t& s, const float* logits, const moe_routing_t& out, void* ws,
@@ -598,12 +761,19 @@ int route_launch(const moe_shape_t& s, const float* logits, const moe_routing_t&
         return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
     }
     const Chunks c = chunks_of(s);
-    const int n = c.n, epl = (s.E + 63) / 64;
-    if (epl <= 1) launch_topk<1>(s, c, logits, out, chunk_cnt, st);
-    else if (epl <= 2) launch_topk<2>(s, c, logits, out, chunk_cnt, st);
-    else if (epl <= 4) launch_topk<4>(s, c, logits, out, chunk_cnt, st);
-    else if (epl <= 8) launch_topk<8>(s, c, logits, out, chunk_cnt, st);
-    else launch_topk<16>(s, c, logits, out, chunk_cnt, st);
+    const int n = c.n;
+    auto rows_of = [&](auto most) {   // up to 256 experts: keys a lane of 16
+        constexpr int KM = decltype(most)::value;
+        if (s.E <= 32) launch_topk<RowSelect<2, KM>>(s, c, logits, out, chunk_cnt, st);
+        else if (s.E <= 64) launch_topk<RowSelect<4, KM>>(s, c, logits, out, chunk_cnt, st);
+        else if (s.E <= 128) launch_topk<RowSelect<8, KM>>(s, c, logits, out, chunk_cnt, st);
+        else if constexpr (KM == 8) launch_topk<RowSelect<16, KM>>(s, c, logits, out, chunk_cnt, st);
+    };
+    if (s.E <= 256 && s.k <= 8) rows_of(std::integral_constant<int, 8>{});
+    else if (s.E <= 128) rows_of(std::integral_constant<int, kMaxTopK>{});
+    else if (s.E <= 256) launch_topk<WaveSelect<4>>(s, c, logits, out, chunk_cnt, st);
+    else if (s.E <= 512) launch_topk<WaveSelect<8>>(s, c, logits, out, chunk_cnt, st);
+    else launch_topk<WaveSelect<16>>(s, c, logits, out, chunk_cnt, st);
     if (n > 1 && n <= kFewChunks) {
         hipLaunchKernelGGL((rows_kernel<false>), dim3(n), dim3(kChunkThreads), 0, st, out.topk_idx, s.T, s.k, c.tokens,
                            n, s.e_start, s.e_count, chunk_cnt, (int32_t*)out.counts, (int32_t*)out.offsets,

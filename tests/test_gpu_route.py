@@ -173,6 +173,32 @@ def test_route_special_values(T):
     assert np.array_equal(got["topk_idx"], order[:, :cfg.k])
 
 
+# Up to 256 experts four tokens share a wave, 16 lanes each with 2, 4, 8 or 16 keys: the first and last number of experts of each,
+# one, eight, nine and sixteen selected, tokens that are no multiple of four, logits that are not aligned to 16 bytes.
+@pytest.mark.parametrize("E,k", [(1, 1), (3, 2), (16, 4), (17, 16), (32, 8), (33, 8), (64, 9), (65, 16), (128, 8), (128, 1), (129, 8), (129, 9),
+                                 (255, 7), (256, 8), (256, 16), (257, 8)])
+@pytest.mark.parametrize("T", [3, 67, 301])
+def test_route_order_of_special_values(T, E, k):
+    import paper_2604_19241_amd as moe
+    say(f"[route] special values, {T} tokens, {E} experts, {k} selected")
+    rng = np.random.default_rng(1000 * E + k)
+    pool = np.array([0.0, -0.0, -np.inf, np.inf, 1e-30, -1e-30, 3e38, -3e38, 1.5, 1.5000001, -1.5, np.nan], np.float32)
+    logits = pool[rng.integers(0, len(pool), (T, E))]
+    logits[1::3] = rng.standard_normal((len(logits[1::3]), E))
+    buffer = torch.empty(T * E + 1, dtype=torch.float32, device="cuda")
+    buffer[1:] = torch.from_numpy(logits).cuda().flatten()
+    r = moe.moe_route(moe.make_shape(T=T, d=64, E=E, k=k, I=64), buffer[1:].view(T, E))
+    value = np.where(np.isnan(logits), -np.inf, logits).astype(np.float64) + 0.0
+    order = np.lexsort((np.broadcast_to(np.arange(E), value.shape), -value, np.isnan(logits)), axis=1)[:, :k]
+    picked = np.take_along_axis(logits, order, 1)
+    assert np.array_equal(r.topk_idx.cpu().numpy(), np.where(np.isnan(picked), 0x7fffffff, order))
+    plain = np.isfinite(picked).all(1)
+    with np.errstate(over="ignore"):
+        p = np.exp((picked[plain] - picked[plain, :1]).astype(np.float64))
+    # exp and the quotient in fp32: a few units in the last place
+    assert np.allclose(r.topk_w.cpu().numpy()[plain], p / p.sum(1, keepdims=True), rtol=2e-6, atol=1e-7)
+
+
 # Where the top-k is a launch of its own and where it is not: tokens of one chunk (a wave each, little work,
 # more work), fewer than 128, 256 and 512 chunks with little and with more work a chunk
 @pytest.mark.parametrize("kw", [
