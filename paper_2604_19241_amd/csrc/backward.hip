@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_first_kernel(BwdParams p) {
     };
     // (an expert without rows still has its weight gradients written)
     const TileRule tile = make_plan(
-        P, p.offsets, ec, 0, [](int) { return 0; }, p.tile, p.nct_dh, [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct_dh; },
+        P, p.offsets, ec, false, [](int) { return 2; }, [](int, int, int) { return 0; }, p.tile, p.nct_dh, [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct_dh; },
         [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct_dxp + (per_dwgu + per_dwd) * parts_of(rows); });
     const int lane = threadIdx.x & 63;
     for (int x = block * kPlanWaves + (threadIdx.x >> 6); x < ec; x += kPlanBlocks * kPlanWaves) {   // one wave, one expert

@@ -80,6 +80,8 @@ __device__ __forceinline__ void add_relaxed(int* p, int v) {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ int rfl(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // ---- work queues -----------------------------------------------------------
 // The GEMM tasks are cut into kQueues lists, one per XCD (each XCD has its own
 // L2): every expert belongs to one list (see QueuePlan), so the tiles that share
@@ -249,7 +251,7 @@ struct QueuePlan {
     int32_t rt0[kMaxExperts];             // first scoreboard slot of the expert
     int32_t sums[kPlanWaves];             // slots of each wave's experts
     int32_t most[kPlanWaves], total[kPlanWaves];   // rows: of the expert that has most, together
-    int32_t counts[kPlanWaves];           // experts with few and with many rows
+    int32_t counts[kPlanWaves][2];        // experts with few (and, shifted left by 16, medium) and with more rows
     int32_t hist[kPlanWaves][64];
     int32_t first[kPlanWaves][64];
     uint16_t slot[kMaxExperts];           // list * kListSlots + slot
@@ -317,28 +319,35 @@ struct TileChoice {
 };
 // The plan of this workgroup (kPlanThreads threads, all of them call; ends with a barrier).
 // Returns how rows are cut.  a_of(rule, rows) / b_of(rule, rows): tasks of an expert's producer and consumer block; `per_row_tile`
-// producer tasks for each scoreboard slot.  limit > 0: experts with up to skip_of(counts) rows have no tasks, where counts is the
-// number of experts with 1..limit rows and, shifted left by 16, of those with more.
-template <class FS, class FA, class FB>
-__device__ __forceinline__ TileRule make_plan(QueuePlan& P, const int32_t* offsets, int ec, int limit, FS skip_of, const TileChoice& choice,
+// producer tasks for each scoreboard slot.  skips: experts with up to skip_of(few, medium, more) rows have no tasks, the numbers
+// of experts with rows whose class_of(rows) is 0, 1 and 2.
+template <class FC, class FS, class FA, class FB>
+__device__ __forceinline__ TileRule make_plan(QueuePlan& P, const int32_t* offsets, int ec, bool skips, FC class_of, FS skip_of, const TileChoice& choice,
                                               int per_row_tile, FA a_of, FB b_of) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
     constexpr int kRounds = kMaxExperts / kPlanThreads;
-    int rows[kRounds], run = 0, most = 0, sum = 0, counts = 0;
+    int rows[kRounds], run = 0, most = 0, sum = 0, counts = 0, more = 0;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {   // wave w looks at experts 256 w + 64 r + lane
         const int e = 256 * w + 64 * r + lane;
         rows[r] = offsets[min(e + 1, ec)] - offsets[min(e, ec)];
-        counts += __popcll(__ballot(rows[r] > 0 && rows[r] <= limit)) + (__popcll(__ballot(rows[r] > limit)) << 16);
+        counts += __popcll(__ballot(rows[r] > 0 && class_of(rows[r]) == 0)) + (__popcll(__ballot(class_of(rows[r]) == 1)) << 16);
+        more += __popcll(__ballot(class_of(rows[r]) == 2));
     }
-    if (limit > 0) {
-        if (lane == 0) P.counts[w] = counts;
+    if (skips) {
+        if (lane == 0) {
+            P.counts[w][0] = counts;
+            P.counts[w][1] = more;
+        }
         __syncthreads();
-        counts = 0;
+        counts = more = 0;
 #pragma unroll
-        for (int i = 0; i < kPlanWaves; ++i) counts += P.counts[i];
-        const int skip = skip_of(counts);
+        for (int i = 0; i < kPlanWaves; ++i) {
+            counts += P.counts[i][0];
+            more += P.counts[i][1];
+        }
+        const int skip = skip_of(rfl(counts & 0xffff), rfl((uint32_t)counts >> 16), rfl(more));
 #pragma unroll
         for (int r = 0; r < kRounds; ++r)
             if (rows[r] <= skip) rows[r] = 0;

@@ -52,7 +52,8 @@ struct FwdParams {
 // GEMM2 block of expert i) and a cleared scoreboard.
 __device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePlan& P) {
     const int ec = p.s.e_count, rows_here = p.offsets[ec];
-    const TileRule tile = make_plan(P, p.offsets, ec, p.rule.max_rows, [&](int counts) { return p.rule.limit(counts, rows_here); }, p.tile, p.nct1,
+    const TileRule tile = make_plan(P, p.offsets, ec, p.rule.max_rows > 0, [&](int rows) { return p.rule.size_class(rows); },
+                                    [&](int few, int medium, int more) { return p.rule.limit(few, medium, more, rfl(rows_here)); }, p.tile, p.nct1,
                                     [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct1; },
                                     [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct2; });
     const int lane = threadIdx.x & 63;

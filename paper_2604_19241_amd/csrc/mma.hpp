@@ -481,7 +481,6 @@ __device__ __forceinline__ void lds_zero16(char* dst) {
     const uint32_t ad = lds_addr(dst) + (threadIdx.x & 63) * 16;   // (cheap; recomputed where it is used)
     asm volatile("ds_write_b128 %0, %1" : : "v"(ad), "v"(zero4()) : "memory");
 }
-__device__ __forceinline__ int rfl(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 struct KsTailLoader {
     const char* p[2];

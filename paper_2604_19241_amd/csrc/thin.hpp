@@ -25,7 +25,8 @@
 
 namespace uniep {
 
-// Rows up to which an expert takes this path: one fragment of the matrix instruction.  More would be blocks of 32, each
+// Rows up to which an expert has few: one fragment of the matrix instruction.  Experts with up to kThinMostRows, two fragments that share
+// the weights, may take this path too (ThinRule::limit).  More would be blocks of 32, each
 // with the weights again.  128 experts of 2048 x 768 with 16 / 32 rows each 206 / 213 us, on the queue 239 / 244 us, with
 // 40 on the queue 245 us (in two blocks 419 us, with tasks of 128 columns); 16 of 2048 x 1408 55 / 56 us, on the queue
 // 81 / 81 us, with 40 82 us (106 us).
@@ -34,6 +35,7 @@ constexpr int kThinThreads = 256;
 constexpr int kThinGroupsPerCu = 2;   // as many as the LDS holds (80 KB each)
 constexpr int kThinXBytes = kThinRows * BK * 2;                       // rows of a stage: image [32 rows][128 B]
 constexpr int kThinMostImage = BK * 256 * 2 + kThinXBytes;
+constexpr int kThinMostRows = 2 * kThinRows;
 // Weight columns of a task where `experts` of them have `columns` each, on `cus` CUs.  A CU draws some 57 GB/s from HBM
 // at most, whatever it has on its way (its L1 holds 32 KB of lines in flight), so that the time is the tasks of the CU that
 // has most of them; a task of 128 columns takes 0.58 of one of 256, one of 64 (runs of 64 bytes) 0.42.  Measured, us of the
@@ -46,11 +48,13 @@ __device__ __forceinline__ int thin_cols(int experts, int columns, int cus) {
     const int wide = cost(256, 100), mid = cost(128, 58), narrow = cost(64, 42);
     return wide <= min(mid, narrow) ? 256 : mid <= narrow ? 128 : 64;
 }
-template <int NC>
+// NR: blocks of 32 rows
+template <int NC, int NR>
 struct ThinShape {
     static constexpr int kRow = NC * 2;              // bytes of a k row in the weights' image [64 k][kRow]
     static constexpr int kW = BK * kRow;
-    static constexpr int kImage = kW + kThinXBytes;
+    static constexpr int kImage = kW + NR * kThinXBytes;
+    static_assert(kImage <= kThinMostImage, "");
     static constexpr int kLoads = NC / 32;           // of a wave and stage, 1 KB each
     static constexpr int kFrags = NC == 256 ? 2 : 1; // column fragments of a wave; of 64 columns waves 2 and 3 have none
     static constexpr int kAhead = NC == 256 ? 2 : 4; // stages in flight (even: stage t is in registers t % kAhead and in image t % 2)
@@ -74,6 +78,7 @@ struct ThinShape {
 // 800 each 435 and 428 us.  Of 402 combinations of eight layers that the rule sends ahead of it the queue takes more
 // than 1 % less in 335 (half of all 4 % less or better, at best 22 %) and more than 1 % more in 20 (at most 4 %).
 struct ThinRule {
+    static constexpr int kOftenMedium = 128;
     int max_rows;              // an expert has few rows up to here
     // Up to so many experts with more rows have so many that matrix work bounds them: 512 rows each, of those that even routing
     // gives the experts here, but no more than there are.  (A share with few of the tokens' rows was taken for one with many: 19
@@ -82,6 +87,7 @@ struct ThinRule {
     int many_most;
     long long chain_ns;
     int queue_ns, thin_ns;     // an expert's weights
+    int full_ns, medium_ns;    // the same where no expert has more than medium rows
     __host__ __device__ __forceinline__ long long queue(int experts) const {
         const long long stream = 30000 + (long long)experts * queue_ns;
         return stream > chain_ns ? stream : chain_ns;
@@ -91,17 +97,29 @@ struct ThinRule {
         if (few < 8 * many && many > min(many_most, rows / 512)) return false;
         return queue(few + many) - queue(many) > 20000 + (long long)few * thin_ns;
     }
-    // Rows up to which an expert of this batch takes this path (0 = none does); counts: experts with few rows and,
-    // shifted left by 16, with more; rows: of all of them.
-    __device__ __forceinline__ int limit(int counts, int rows) const {
-        const int c = rfl(counts);
-        return pays(c & 0xffff, c >> 16, rfl(rows)) ? max_rows : 0;
+    // 0: up to max_rows rows, 1: medium, up to kThinMostRows, 2: more
+    __device__ __forceinline__ int size_class(int rows) const { return rows <= max_rows ? 0 : max_rows > 0 && rows <= kThinMostRows ? 1 : 2; }
+    // Rows up to which an expert of this batch takes this path (0 = none does); experts with few, medium and more rows,
+    // and the rows of all of them.
+    // Where no expert has more than medium rows and there are more than kOftenMedium experts, all of them take this path if that is
+    // the faster way for them together: tasks of two blocks of rows stream the weights at 5.0 TB/s (128 columns), the queue takes 30 us and
+    // 5.5 TB/s.  Measured, us of the layer, with medium experts on the queue / here (tokens, experts of width and inner width; rows an expert):
+    // 1021, 512 of 2048 x 512 (20) 620 / 577; 1300 (25) 645 / 573; 700, 256 of 2304 x 1024 (22) 664 / 628; but 1200, 32 of 256 of 7168 x 2048
+    // (38) 511 / 564, 640, 128 of 2048 x 768 (40) 251 / 247 to 257.  Fewer experts would often gain as well (512, 128 of 1024 x 384 (24) 96 / 71;
+    // 500, 128 of 2048 x 768 (31) 247 / 232; 250, 64 of 2048 x 1408 (23) 229 / 202): they keep the choice that is tested for them.
+    __device__ __forceinline__ int limit(int few, int medium, int more, int rows) const {
+        if (more == 0 && medium > 0 && few + medium > kOftenMedium) {
+            const long long stream = 30000 + (long long)(few + medium) * full_ns;
+            const long long here = 20000 + (long long)few * thin_ns + (long long)medium * medium_ns;
+            if (here < (stream > chain_ns ? stream : chain_ns)) return kThinMostRows;
+        }
+        return pays(few, medium + more, rows) ? max_rows : 0;
     }
 };
 inline ThinRule thin_rule(const moe_shape_t& s, int max_rows) {
     const long long bytes = 6ll * s.d * s.I;
     return ThinRule{max_rows, (int)((long long)s.T * s.k * s.e_count / s.E / 512), 1000ll * ((s.d + s.I) / BK),
-                    (int)(bytes / 5200), (int)(bytes / 6400)};
+                    (int)(bytes / 5200), (int)(bytes / 6400), (int)(bytes / 5500), (int)(bytes / 5000)};
 }
 // Whether it can pay beside an expert with many rows, whatever the counts.
 inline bool thin_may_pay(const ThinRule& r, const moe_shape_t& s) { return r.queue(s.e_count) - r.chain_ns > 20000; }
@@ -129,39 +147,41 @@ typedef __attribute__((address_space(3))) bf16x4_t* lds_tr_t;
 
 // Where a wave's next stage comes from.  GEMM1: the first half of the weight loads are gate columns, the second the same up
 // columns; a load is kRows k rows of kLanes lanes.
-template <int GEMM, int NC>
+template <int GEMM, int NC, int NR>
 struct ThinSource {
-    static constexpr int kLoads = ThinShape<NC>::kLoads;
+    static constexpr int kLoads = ThinShape<NC, NR>::kLoads;
     static constexpr int kLanes = GEMM == 1 ? NC / 16 : NC / 8, kRows = 64 / kLanes;
     static constexpr int kOf = GEMM == 1 ? kLoads / 2 : kLoads;   // loads of a matrix
     glb_ptr_t w[2];      // first k row of this wave in the stage to come (uniform); GEMM2: w[0] only
     uint32_t off;        // this lane's k row and columns behind it
     uint32_t ldw;        // bytes from one k row to the next (uniform)
-    glb_ptr_t x;         // this lane's row and chunk
+    glb_ptr_t x[NR];     // this lane's rows and chunk
     // advance: 0 = stay on this stage (the last one).  The loads are never left out: behind a branch
     // around them the compiler could not tell how many are in flight and would wait for all.
-    __device__ __forceinline__ void load(u32x4_t (&r)[kLoads + 1], int advance) {
+    __device__ __forceinline__ void load(u32x4_t (&r)[kLoads + NR], int advance) {
 #pragma unroll
         for (int i = 0; i < kLoads; ++i) {
             glb_ptr_t base = w[i / kOf] + (size_t)(kRows * (i % kOf)) * ldw;
             asm volatile("" : "+s"(base));   // scalar base + 32-bit lane offset, not one 64-bit lane address per load
             r[i] = __builtin_nontemporal_load((glb_vec_t)(base + off));
         }
-        r[kLoads] = *(glb_vec_t)x;
+#pragma unroll
+        for (int n = 0; n < NR; ++n) r[kLoads + n] = *(glb_vec_t)x[n];
         const size_t step = (size_t)(BK * advance) * ldw;
         w[0] += step;
         if (GEMM == 1) w[1] += step;
-        x += BK * 2 * advance;
+#pragma unroll
+        for (int n = 0; n < NR; ++n) x[n] += BK * 2 * advance;
     }
 };
 
 // The LDS images: weights, 16-byte chunk c of k row k at c ^ swz(k) (the bank bits that the chunks and, of 64 columns, the k rows
 // of a fragment read leave free); rows, chunk c of row r at c ^ ((r >> 1) & 7).  Chunks 4 f .. 4 f + 3 of a k row are fragment f's
 // 32 columns (GEMM1: 16 gate columns, then the same 16 up columns).
-template <int GEMM, int NC>
+template <int GEMM, int NC, int NR>
 struct ThinLds {
-    using S = ThinShape<NC>;
-    using Src = ThinSource<GEMM, NC>;
+    using S = ThinShape<NC, NR>;
+    using Src = ThinSource<GEMM, NC, NR>;
     lds_ptr_t wput[2], xput, wget[S::kFrags], xget[4];
     static __device__ __forceinline__ int swz(int k) { return NC == 64 ? (k & 2) << 1 : (k & 3) << 2; }
     __device__ __forceinline__ ThinLds(lds_ptr_t base, const Lane& ln) {
@@ -181,19 +201,21 @@ struct ThinLds {
         for (int kk = 0; kk < 4; ++kk)
             xget[kk] = base + S::kW + ln.l31 * 128 + (((2 * kk + kh) ^ ((ln.l31 >> 1) & 7)) << 4);
     }
-    __device__ __forceinline__ void put(int image, const u32x4_t (&r)[S::kLoads + 1]) const {
+    __device__ __forceinline__ void put(int image, const u32x4_t (&r)[S::kLoads + NR]) const {
 #pragma unroll
         for (int i = 0; i < S::kLoads; ++i)
             *(lds_vec_t)(wput[i & 1] + image * S::kImage + (i % Src::kOf) * Src::kRows * S::kRow + (i / Src::kOf) * 32) = r[i];
-        *(lds_vec_t)(xput + image * S::kImage) = r[S::kLoads];
+#pragma unroll
+        for (int n = 0; n < NR; ++n) *(lds_vec_t)(xput + image * S::kImage + n * kThinXBytes) = r[S::kLoads + n];
     }
     // acc[f][v]: row l % 32, column position 16 (v / 8) + 8 (l / 32) + v % 8 of the wave's f-th 32
-    __device__ __forceinline__ void multiply(int image, f32x16_t (&acc)[S::kFrags]) const {
+    __device__ __forceinline__ void multiply(int image, f32x16_t (&acc)[NR][S::kFrags]) const {
         bf16x4_t lo[S::kFrags][4], hi[S::kFrags][4];
-        u32x4_t b[4];
+        u32x4_t b[NR][4];
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            b[kk] = *(lds_vec_t)(xget[kk] + image * S::kImage);
+#pragma unroll
+            for (int n = 0; n < NR; ++n) b[n][kk] = *(lds_vec_t)(xget[kk] + image * S::kImage + n * kThinXBytes);
 #pragma unroll
             for (int f = 0; f < S::kFrags; ++f) {
                 const lds_ptr_t a = wget[f] + image * S::kImage + kk * 16 * S::kRow;
@@ -206,8 +228,10 @@ struct ThinLds {
         for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
             for (int f = 0; f < S::kFrags; ++f)
-                acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_shufflevector(lo[f][kk], hi[f][kk], 0, 1, 2, 3, 4, 5, 6, 7),
-                                                                 __builtin_bit_cast(bf16x8_t, b[kk]), acc[f], 0, 0, 0);
+#pragma unroll
+                for (int n = 0; n < NR; ++n)
+                    acc[n][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_shufflevector(lo[f][kk], hi[f][kk], 0, 1, 2, 3, 4, 5, 6, 7),
+                                                                        __builtin_bit_cast(bf16x8_t, b[n][kk]), acc[n][f], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     }
 };
@@ -223,9 +247,9 @@ __device__ __forceinline__ void thin_barrier() {
 // One stage: registers -> image, the loads of the stage kAhead further on into the same registers,
 // barrier, matrix work.  An image is written again two stages later, behind the barrier that every wave
 // reaches with its reads of it done.
-template <int GEMM, int NC, bool LOAD>
-__device__ __forceinline__ void thin_stage(ThinSource<GEMM, NC>& src, const ThinLds<GEMM, NC>& lds, int image,
-                                           u32x4_t (&r)[ThinShape<NC>::kLoads + 1], f32x16_t (&acc)[ThinShape<NC>::kFrags], int advance) {
+template <int GEMM, int NC, int NR, bool LOAD>
+__device__ __forceinline__ void thin_stage(ThinSource<GEMM, NC, NR>& src, const ThinLds<GEMM, NC, NR>& lds, int image,
+                                           u32x4_t (&r)[ThinShape<NC, NR>::kLoads + NR], f32x16_t (&acc)[NR][ThinShape<NC, NR>::kFrags], int advance) {
     lds.put(image, r);
     __builtin_amdgcn_sched_barrier(0);
     if (LOAD) src.load(r, advance);
@@ -234,14 +258,16 @@ __device__ __forceinline__ void thin_stage(ThinSource<GEMM, NC>& src, const Thin
 }
 
 // n >= 1 stages: t is in registers t % kAhead and in image t % 2.
-template <int GEMM, int NC>
-__device__ __forceinline__ void thin_loop(ThinSource<GEMM, NC>& src, const ThinLds<GEMM, NC>& lds, int n, f32x16_t (&acc)[ThinShape<NC>::kFrags]) {
-    constexpr int kAhead = ThinShape<NC>::kAhead;
+template <int GEMM, int NC, int NR>
+__device__ __forceinline__ void thin_loop(ThinSource<GEMM, NC, NR>& src, const ThinLds<GEMM, NC, NR>& lds, int n, f32x16_t (&acc)[NR][ThinShape<NC, NR>::kFrags]) {
+    constexpr int kAhead = ThinShape<NC, NR>::kAhead;
 #pragma unroll
-    for (int f = 0; f < ThinShape<NC>::kFrags; ++f)
+    for (int n = 0; n < NR; ++n)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[f][v] = 0.f;
-    u32x4_t r[kAhead][ThinShape<NC>::kLoads + 1];
+        for (int f = 0; f < ThinShape<NC, NR>::kFrags; ++f)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[n][f][v] = 0.f;
+    u32x4_t r[kAhead][ThinShape<NC, NR>::kLoads + NR];
     thin_barrier();   // the task before has read its last image
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) src.load(r[j], j + 1 < n ? 1 : 0);
@@ -249,59 +275,66 @@ __device__ __forceinline__ void thin_loop(ThinSource<GEMM, NC>& src, const ThinL
     for (; t + kAhead < n; t += kAhead)
 #pragma unroll
         for (int j = 0; j < kAhead; ++j)
-            thin_stage<GEMM, NC, true>(src, lds, j & 1, r[j], acc, t + j + 1 + kAhead < n ? 1 : 0);
+            thin_stage<GEMM, NC, NR, true>(src, lds, j & 1, r[j], acc, t + j + 1 + kAhead < n ? 1 : 0);
 #pragma unroll
     for (int j = 0; j < kAhead; ++j)
-        if (t + j < n) thin_stage<GEMM, NC, false>(src, lds, j & 1, r[j], acc, 0);
+        if (t + j < n) thin_stage<GEMM, NC, NR, false>(src, lds, j & 1, r[j], acc, 0);
 }
 
-// One block of up to 32 rows (row0 .., `rows` valid) by the task's columns.
+// Up to 32 NR rows (row0 .., `rows` valid) by the task's columns.
 // GEMM 1: h = silu(x W_gate) * (x W_up), columns [NC/2 ct, +NC/2); GEMM 2: o = h W_down, columns [NC ct, +NC).
-template <int GEMM, int NC>
+template <int GEMM, int NC, int NR>
 __device__ __forceinline__ void thin_block(const ThinParams& p, int e, int ct, int row0, int rows, lds_ptr_t images) {
-    constexpr int kFrags = ThinShape<NC>::kFrags;
+    constexpr int kFrags = ThinShape<NC, NR>::kFrags;
     const int d = p.s.d, I = p.s.I;
-    f32x16_t acc[kFrags];
+    f32x16_t acc[NR][kFrags];
     {
         const Lane in;
         const int K = GEMM == 1 ? d : I, n = GEMM == 1 ? I : d;
-        ThinSource<GEMM, NC> src;
+        ThinSource<GEMM, NC, NR> src;
         src.ldw = (uint32_t)n * 2;
         const size_t first = ((size_t)e * K + 16 * in.wave_uniform()) * src.ldw;
         src.w[0] = (glb_ptr_t)((GEMM == 1 ? p.w_gate : p.w_down) + first);
         src.w[1] = (glb_ptr_t)((GEMM == 1 ? p.w_up : p.w_down) + first);
         // pieces past the last column alias it
         src.off = (in.l / src.kLanes) * src.ldw + (uint32_t)min((GEMM == 1 ? NC / 2 : NC) * ct + 8 * (in.l % src.kLanes), n - 8) * 2;
-        const int r = row0 + min(8 * in.w + (in.l >> 3), rows - 1);   // rows past the last alias it
-        const char* row = GEMM == 1 ? p.x + (size_t)(p.perm[r] / p.s.k) * d * 2 : p.h + (size_t)r * I * 2;
-        src.x = (glb_ptr_t)(row + (in.l & 7) * 16);
-        thin_loop<GEMM, NC>(src, ThinLds<GEMM, NC>(images, in), K / BK, acc);
+#pragma unroll
+        for (int b = 0; b < NR; ++b) {
+            const int r = row0 + min(32 * b + 8 * in.w + (in.l >> 3), rows - 1);   // rows past the last alias it
+            const char* row = GEMM == 1 ? p.x + (size_t)(p.perm[r] / p.s.k) * d * 2 : p.h + (size_t)r * I * 2;
+            src.x[b] = (glb_ptr_t)(row + (in.l & 7) * 16);
+        }
+        thin_loop<GEMM, NC, NR>(src, ThinLds<GEMM, NC, NR>(images, in), K / BK, acc);
     }
     const Lane out;
-    if (out.l31 >= rows || (NC == 64 && out.w >= 2)) return;
-    const size_t row = (size_t)(row0 + out.l31);
+    if (NC == 64 && out.w >= 2) return;
 #pragma unroll
-    for (int f = 0; f < kFrags; ++f) {
-        if (GEMM == 1) {
-            const int col = NC / 2 * ct + 16 * (kFrags * out.w + f) + 8 * out.hf;
-            if (NC == 256 && col >= I) continue;
-            if (p.gu) {
-                *(u32x4_t*)(p.gu + (row * 2 * I + col) * 2) = pack8(acc[f], 0);
-                *(u32x4_t*)(p.gu + (row * 2 * I + I + col) * 2) = pack8(acc[f], 1);
+    for (int n = 0; n < NR; ++n) {
+        if (32 * n + out.l31 >= rows) return;
+        const size_t row = (size_t)(row0 + 32 * n + out.l31);
+#pragma unroll
+        for (int f = 0; f < kFrags; ++f) {
+            if (GEMM == 1) {
+                const int col = NC / 2 * ct + 16 * (kFrags * out.w + f) + 8 * out.hf;
+                if (NC == 256 && col >= I) continue;
+                if (p.gu) {
+                    *(u32x4_t*)(p.gu + (row * 2 * I + col) * 2) = pack8(acc[n][f], 0);
+                    *(u32x4_t*)(p.gu + (row * 2 * I + I + col) * 2) = pack8(acc[n][f], 1);
+                }
+                float hv[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float g = acc[n][f][j], u = acc[n][f][8 + j];
+                    hv[j] = g * sigmoid_f(g) * u;
+                }
+                *(u32x4_t*)(p.h + (row * I + col) * 2) = u32x4_t{pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3]),
+                                                                 pack_bf16x2(hv[4], hv[5]), pack_bf16x2(hv[6], hv[7])};
+            } else {
+                const int col = NC * ct + 32 * (kFrags * out.w + f) + 8 * out.hf;
+#pragma unroll
+                for (int vg = 0; vg < 2; ++vg)
+                    if (col + 16 * vg < d) *(u32x4_t*)(p.o + (row * d + col + 16 * vg) * 2) = pack8(acc[n][f], vg);
             }
-            float hv[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float g = acc[f][j], u = acc[f][8 + j];
-                hv[j] = g * sigmoid_f(g) * u;
-            }
-            *(u32x4_t*)(p.h + (row * I + col) * 2) = u32x4_t{pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3]),
-                                                             pack_bf16x2(hv[4], hv[5]), pack_bf16x2(hv[6], hv[7])};
-        } else {
-            const int col = NC * ct + 32 * (kFrags * out.w + f) + 8 * out.hf;
-#pragma unroll
-            for (int vg = 0; vg < 2; ++vg)
-                if (col + 16 * vg < d) *(u32x4_t*)(p.o + (row * d + col + 16 * vg) * 2) = pack8(acc[f], vg);
         }
     }
 }
@@ -309,7 +342,7 @@ __device__ __forceinline__ void thin_block(const ThinParams& p, int e, int ct, i
 struct ThinShared {
     union {
         __attribute__((aligned(512))) char images[2 * kThinMostImage];
-        int32_t wave[4];           // of the search, before the first image
+        int32_t wave[2][4];        // of the search, before the first image
     };
     int32_t row0[kMaxExperts];
     uint16_t rows[kMaxExperts];    // (up to 32 tokens of 16 slots each, were they all of one expert)
@@ -317,9 +350,9 @@ struct ThinShared {
 };
 static_assert(kThinGroupsPerCu * sizeof(ThinShared) <= 160 * 1024, "");
 
-// The tasks of `count` listed experts, every `blocks`-th from `block` on.
-template <int GEMM, int NC>
-__device__ __forceinline__ void thin_tasks(const ThinParams& p, int count, int block, int blocks, ThinShared& S) {
+// The tasks of `count` listed experts from the `first`-th on, every `blocks`-th from `block` on.
+template <int GEMM, int NC, int NR>
+__device__ __forceinline__ void thin_tasks(const ThinParams& p, int first, int count, int block, int blocks, ThinShared& S) {
     const int nct = GEMM == 1 ? (2 * p.s.I + NC - 1) / NC : (p.s.d + NC - 1) / NC;
     const int even = (count & ~7) * nct;
     for (int id = block; id < count * nct; id += blocks) {
@@ -336,9 +369,10 @@ __device__ __forceinline__ void thin_tasks(const ThinParams& p, int count, int b
             x = (count & ~7) + t / nct;
             ct = t % nct;
         }
+        x += first;
         const int e = rfl(S.expert[x]), row0 = rfl(S.row0[x]), rows = rfl(S.rows[x]);
-        for (int r = 0; r < rows; r += kThinRows)   // more than one round only where max_rows is larger
-            thin_block<GEMM, NC>(p, e, ct, row0 + r, min(rows - r, kThinRows), (lds_ptr_t)S.images);
+        for (int r = 0; r < rows; r += NR * kThinRows)   // more than one round only where max_rows is larger
+            thin_block<GEMM, NC, NR>(p, e, ct, row0 + r, min(rows - r, NR * kThinRows), (lds_ptr_t)S.images);
     }
 }
 
@@ -352,13 +386,14 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ec = p.s.e_count;
     const int rows_here = p.offsets[ec];
-    int off[5], mine = 0;
+    int off[5], mine = 0, more = 0;
 #pragma unroll
     for (int j = 0; j < 5; ++j) off[j] = p.offsets[min(4 * tid + j, ec)];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {   // few and, shifted left by 16, many rows
-        const int rows = off[j + 1] - off[j];
-        mine += rows <= 0 ? 0 : rows <= p.rule.max_rows ? 1 : 1 << 16;
+    for (int j = 0; j < 4; ++j) {   // few and, shifted left by 16, medium rows
+        const int rows = off[j + 1] - off[j], c = p.rule.size_class(rows);
+        mine += rows <= 0 ? 0 : c == 0 ? 1 : c == 1 ? 1 << 16 : 0;
+        more += __popcll(__ballot(c == 2));
     }
     int pre = mine;
 #pragma unroll
@@ -366,31 +401,45 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
         const int v = __shfl_up(pre, o);
         if (lane >= o) pre += v;
     }
-    if (lane == 63) S.wave[wave] = pre;
+    if (lane == 63) {
+        S.wave[0][wave] = pre;
+        S.wave[1][wave] = more;
+    }
     __syncthreads();
     int at = pre - mine, count = 0;
+    more = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        if (w < wave) at += S.wave[w];
-        count += S.wave[w];
+        if (w < wave) at += S.wave[0][w];
+        count += S.wave[0][w];
+        more += S.wave[1][w];
     }
-    if (p.rule.limit(count, rows_here) == 0) return;
-    at &= 0xffff;
-    count &= 0xffff;
-    if (count == 0) return;
+    const int few = rfl(count & 0xffff), medium = rfl((uint32_t)count >> 16);
+    const int limit = p.rule.limit(few, medium, rfl(more), rfl(rows_here));
+    const int two = limit > kThinRows && limit <= kThinMostRows ? medium : 0;   // experts with two blocks of rows here
+    if (limit == 0 || few + two == 0) return;
+    int at_few = at & 0xffff, at_two = few + (int)((uint32_t)at >> 16);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        if (off[j + 1] > off[j] && off[j + 1] - off[j] <= p.rule.max_rows) {
-            S.expert[at] = (uint16_t)(4 * tid + j);
-            S.row0[at] = off[j];
-            S.rows[at] = (uint16_t)(off[j + 1] - off[j]);
-            ++at;
+    for (int j = 0; j < 4; ++j) {
+        const int rows = off[j + 1] - off[j];
+        if (rows > 0 && rows <= limit) {
+            const int i = p.rule.size_class(rows) == 0 ? at_few++ : at_two++;
+            S.expert[i] = (uint16_t)(4 * tid + j);
+            S.row0[i] = off[j];
+            S.rows[i] = (uint16_t)rows;
         }
+    }
     __syncthreads();
-    const int cols = thin_cols(count, GEMM == 1 ? 2 * p.s.I : p.s.d, p.workers);
-    if (cols == 256) thin_tasks<GEMM, 256>(p, count, block, blocks, S);
-    else if (cols == 128) thin_tasks<GEMM, 128>(p, count, block, blocks, S);
-    else thin_tasks<GEMM, 64>(p, count, block, blocks, S);
+    const int columns = GEMM == 1 ? 2 * p.s.I : p.s.d;
+    if (two > 0) {   // the longer tasks first; who has had one more of them gets one less of the others
+        thin_tasks<GEMM, 128, 2>(p, few, two, block, blocks, S);
+        block -= (two * ((columns + 127) / 128) & ~7) % blocks;
+        if (block < 0) block += blocks;
+    }
+    const int cols = thin_cols(few, columns, p.workers);
+    if (cols == 256) thin_tasks<GEMM, 256, 1>(p, 0, few, block, blocks, S);
+    else if (cols == 128) thin_tasks<GEMM, 128, 1>(p, 0, few, block, blocks, S);
+    else thin_tasks<GEMM, 64, 1>(p, 0, few, block, blocks, S);
 }
 
 }  // namespace uniep

@@ -92,6 +92,46 @@ def test_widths_of_a_task(E, d, I, of):
     test_forward_at_row_counts(rows.tolist(), d, I)
 
 
+# Up to 64 rows, where no expert has more and 129 have some: tasks of two blocks of rows beside tasks of one, their last columns cut off
+# and not, with few and with many of either, more of them than workgroups.  Against the same tokens beside an expert of 65 rows, with which
+# the experts of 33 to 64 are on the work queue: the same bits.
+@pytest.mark.parametrize("rows,d,I", [([33] + [1] * 128, 64, 64), ([64, 32, 1, 63] + [2] * 130, 320, 192), ([40] * 7 + [9] * 122, 1088, 576),
+                                      ([33, 0, 47] + [3] * 200, 576, 320), ([1] * 140 + [50, 64], 64, 384), ([60] * 130, 192, 1088),
+                                      ([33, 64] * 150 + [1, 32] * 100, 128, 448)])
+def test_two_blocks_of_rows(rows, d, I):
+    import paper_2604_19241_amd as moe
+    E, T = len(rows) + 1, sum(rows) + 65
+    cfg = moe_synth.small_config(T=T, d=d, E=E, k=1, I=I)
+    dev = {key: v.cuda() for key, v in scaled_inputs(cfg, 17, 4.0).items()}
+    own = torch.from_numpy(np.random.default_rng(T).permutation(np.repeat(np.arange(E - 1), rows))).cuda()
+    got = {}
+    for more in (0, 1):
+        t, e = sum(rows) + 65 * more, E - 1 + more
+        say(f"[two blocks] {rows[:8]}.. d={d} I={I} queue={more}")
+        shape = moe.make_shape(T=t, d=d, E=e, k=1, I=I)
+        to = torch.cat([own, torch.full((t - len(own),), E - 1, device="cuda")])
+        routing = moe.moe_route(shape, torch.nn.functional.one_hot(to, e).float())
+        assert routing.counts.tolist() == rows + [65] * more
+        saved = moe.alloc_saved(shape, "cuda")
+        ws = torch.empty(moe.moe_workspace_bytes(shape)["fwd"], dtype=torch.uint8, device="cuda")
+        y = moe.moe_fused_forward(shape, dev["x"][:t], dev["w_gate"][:e], dev["w_up"][:e], dev["w_down"][:e], routing, saved=saved, ws=ws)
+        assert moe.moe_device_status(ws) == 0
+        assert (int(ws.view(torch.int32)[1]) > 0) == (more > 0)   # row tiles of the queue
+        got[more] = dict(moe.saved_views(shape, saved), y=y)
+    for name, v in got[0].items():
+        assert torch.equal(v, got[1][name][:len(v)]), name
+    # and a plain product in fp32: h and o within the roundings to bf16 of x W and of h
+    x, r = dev["x"][:len(own)].float(), torch.argsort(own, stable=True)
+    for e in sorted(set(own.tolist())):
+        at = own[r] == e
+        xe = x[r][at]
+        g, u = xe @ dev["w_gate"][e].float(), xe @ dev["w_up"][e].float()
+        h = torch.nn.functional.silu(g) * u
+        assert rel_l2(to_f64(got[0]["h"][:len(own)][at]), h.double().cpu().numpy()) <= REL_L2
+        o = got[0]["h"][:len(own)][at].float() @ dev["w_down"][e].float()
+        assert rel_l2(to_f64(got[0]["o"][:len(own)][at]), o.double().cpu().numpy()) <= REL_L2
+
+
 def us_of_one_row_each(experts, d, I, E=16):
     """The layer for one token on each of so many experts, other ones from call to call."""
     import paper_2604_19241_amd as moe
