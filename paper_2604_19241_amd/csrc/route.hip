@@ -41,14 +41,21 @@ struct Chunks {
 };
 static Chunks chunks_of(const moe_shape_t& s) {
     const int tokens = (kChunk + s.k - 1) / s.k, n = (s.T + tokens - 1) / tokens;
+    // Up to a slot a thread make one chunk, whose workgroup writes the rows as well: without the launch behind it 256 tokens of 8 experts, 2 selected,
+    // take 5.6 us for 6.9, 512 slots of 64 tokens of 128 6.5 for 7.8, 1000 of 100 tokens of 512 9.1 for 10.9, 1024 of 64 of 1024 14.4 for 15.8.
+    if ((long long)s.T * s.k <= kChunkThreads) return Chunks{s.T, 1, s.T * s.k > kPieces * 64};
     if (n < kManyChunks) return Chunks{tokens, n, false};
     const int round = kChunkCus * (kChunkThreads / s.k), rounds = (s.T + round - 1) / round;
     const int more = (s.T + kChunkCus * rounds - 1) / (kChunkCus * rounds);
     return Chunks{more, (s.T + more - 1) / more, true};
 }
-// Whether the top-k is a launch of its own, one token a wave over the whole chip, ahead of the ranking
-// (one launch more), instead of part of the chunk's workgroup (up to 16 tokens a wave, one after the other,
-// on as many CUs as there are chunks).  Measured, us of the whole routing, in one launch with the ranking / apart:
+// Whether the top-k is a launch of its own, over the whole chip, ahead of the ranking
+// (one launch more), instead of part of the chunk's workgroup (on as many CUs as there are chunks).
+// RowSelect: a workgroup's 16 waves have 64 tokens at a time, so that a chunk of no more, or as many chunks as CUs, need no launch
+// ahead.  Measured, us of the whole routing, in one launch with the ranking / apart (tokens x experts x k): 64 x 128 x 8 6.5 / 7.8, 512 x 256 x 8
+// 8.5 / 9.3, 1000 x 256 x 8 9.3 / 10.0, 4099 x 64 x 6 11.7 / 12.6, 16384 x 64 x 2 12.2 / 12.6, 32768 x 256 x 2 18.0 / 19.0; but 128 x 128 x 8 9.9 / 6.8,
+// 1024 x 64 x 1 18.8 / 6.1, 1024 x 256 x 2 11.6 / 8.4, 2048 x 256 x 4 10.2 / 9.7, 8192 x 64 x 1 10.0 / 8.5.
+// WaveSelect: up to 16 tokens a wave, one after the other.  Measured when it selected among any number of experts:
 // up to 16 tokens a chunk have a wave each: 1 x 64 experts, 16 tokens 3.4 / 4.8 (tokens x experts x k below);
 // one chunk: 24 x 64 x 8 5.5 / 5.8, 32 x 256 x 1 5.1 / 5.4, but 32 x 256 x 8 8.9 / 6.9, 256 x 1024 x 1 51 / 8;
 // fewer chunks than CUs: 1024 x 128 x 8 10.4 / 9.6, 8192 x 1024 x 1 100 / 17, 4096 x 64 x 8 13.1 / 13.4,
@@ -56,10 +63,13 @@ static Chunks chunks_of(const moe_shape_t& s) {
 // 21.1 / 19.8, 65536 x 1024 x 1 141 / 81; more, where the chip is full either way: 65536 x 256 x 2 31.4 / 34.8,
 // 32768 x 256 x 8 39.6 / 40.9.
 constexpr int kTopkGroups = 1 << 16;
+// RowSelect or WaveSelect
+static bool rows_select(const moe_shape_t& s) { return s.E <= 128 || (s.E <= 256 && s.k <= 8); }
 static bool topk_alone(const moe_shape_t& s, const Chunks& c) {
-    if (c.lng) return false;
+    if (c.lng && c.n > 1) return false;
     const int n = c.n, tokens = std::min(s.T, c.tokens);
     const long long work = (long long)tokens * s.E;
+    if (rows_select(s)) return n < (s.E <= 64 ? 128 : 256) && (tokens > kChunkThreads / 16 || work > 8192);
     if (tokens <= kChunkThreads / 64 && (n == 1 || s.E <= 256)) return false;
     if (n == 1) return work * s.k > 13000;
     return n < 128 || (n < 256 && work >= 4096) || (n < 512 && work >= 16384);
@@ -737,8 +747,9 @@ static void launch_rank(const moe_shape_t& s, const Chunks& c, const float* logi
                            (int32_t*)out.perm, (int32_t*)out.inv_perm);
     };
     if constexpr (SEL::kTokens > 0)
-        if (c.lng) return launch(topk_rank_kernel<SEL, false, kLongPieces>);
-    if (c.n == 1) launch(topk_rank_kernel<SEL, true, kPieces>);
+        if (c.lng && c.n > 1) return launch(topk_rank_kernel<SEL, false, kLongPieces>);
+    if (c.lng) launch(topk_rank_kernel<SEL, true, kLongPieces>);
+    else if (c.n == 1) launch(topk_rank_kernel<SEL, true, kPieces>);
     else launch(topk_rank_kernel<SEL, false, kPieces>);
 }
 

@@ -261,6 +261,20 @@ def test_route_backward_of_few_slots_takes_less_than_of_eight():
     assert us[1] <= 0.92 * us[8], us
 
 
+# One chunk of up to 1024 slots, with up to 320 and more, and the first batch of several; the top-k in its workgroup (64 tokens and 8192 logits)
+# and apart, with 16 lanes a token and with 64.
+@pytest.mark.parametrize("kw", [
+    dict(T=40, E=40, k=8), dict(T=41, E=40, k=8), dict(T=128, E=40, k=8), dict(T=129, E=40, k=8), dict(T=1024, E=7, k=1), dict(T=1025, E=7, k=1),
+    dict(T=64, E=128, k=8, e_start=9, e_count=100), dict(T=65, E=128, k=8), dict(T=64, E=129, k=8), dict(T=32, E=256, k=8), dict(T=33, E=256, k=8),
+    dict(T=64, E=200, k=16), dict(T=64, E=1024, k=16, e_start=1, e_count=1023), dict(T=102, E=512, k=10), dict(T=103, E=512, k=10),
+    dict(T=127 * 128, E=64, k=2), dict(T=127 * 128 + 1, E=64, k=2), dict(T=255 * 128, E=65, k=2), dict(T=255 * 128 + 1, E=65, k=2),
+])
+def test_route_of_one_chunk(kw):
+    cfg = moe_synth.small_config(d=64, I=64, **kw)
+    rng = np.random.default_rng(kw["T"] * kw["k"])
+    check(cfg, rng.integers(-40, 41, (cfg.T, cfg.E)).astype(np.float32) * np.float32(0.25), "one chunk or several")
+
+
 def routing_us(T, E, k):
     import paper_2604_19241_amd as moe
     shape = moe.make_shape(T=T, d=64, E=E, k=k, I=64)
