@@ -614,18 +614,18 @@ route_backward_kernel(const int32_t* __restrict__ topk_idx, const float* __restr
 // Algorithm 1 for one rank of W (Section 3.1).  The AllGather of the per-rank
 // histograms is the caller's; c_all [W, E] is its result.
 
-// One workgroup of 1024 threads, thread e per expert.  Eq. 1 along the rank axis,
+// By a workgroup of kMapThreads, thread e per expert: Eq. 1 along the rank axis,
 // the total rows every expert receives, and the start of every expert's segment
 // in its destination rank's buffer (exclusive scan inside each group of n_epr
-// experts).  Writes off_base[e] = O_all[rank, e] - O_exp[e] and row_base[e] =
-// segment start + off_base[e], so that the mapping kernel only adds M_loc, and
-// this rank's own segment table recv_offsets [n_epr + 1].
-__global__ void __launch_bounds__(1024)
-global_offsets_kernel(const int32_t* __restrict__ c_all, const int32_t* __restrict__ o_exp, int E,
-                      int W, int rank, int n_epr, int32_t* __restrict__ off_base,
-                      int32_t* __restrict__ row_base, int32_t* __restrict__ recv_offsets) {
-    __shared__ int32_t s_first[1024];
-    __shared__ int32_t s_wave[1024 / 64];
+// experts).  off_base = O_all[rank, e] - O_exp[e] and row_base = segment start + off_base, so that the mapping only
+// adds M_loc; `recv` writes this rank's own segment table recv_offsets [n_epr + 1].  Ends with a barrier.
+constexpr int kMapThreads = 1024;
+struct MapScan {
+    int32_t first[kMapThreads];
+    int32_t wave[kMapThreads / 64];
+};
+__device__ __forceinline__ void global_bases(MapScan& S, const int32_t* __restrict__ c_all, const int32_t* __restrict__ o_exp, int E, int W, int rank,
+                                             int n_epr, int32_t* off_base, int32_t* row_base, bool recv, int32_t* __restrict__ recv_offsets) {
     const int e = threadIdx.x;
     int total = 0, before = 0;
     if (e < E) {
@@ -637,20 +637,28 @@ global_offsets_kernel(const int32_t* __restrict__ c_all, const int32_t* __restri
         }
     }
     int all;
-    const int first = block_exclusive_sum<1024 / 64>(total, s_wave, &all);
-    s_first[e] = first;
+    const int first = block_exclusive_sum<kMapThreads / 64>(total, S.wave, &all);
+    S.first[e] = first;
     __syncthreads();
     if (e < E) {
         const int g0 = (e / n_epr) * n_epr;              // first expert of e's rank
-        const int start = first - s_first[g0];
+        const int start = first - S.first[g0];
         const int ob = before - o_exp[e];
         off_base[e] = ob;
         row_base[e] = start + ob;
-        if (e / n_epr == rank) {
+        if (recv && e / n_epr == rank) {
             recv_offsets[e - g0] = start;
             if (e - g0 == n_epr - 1) recv_offsets[n_epr] = start + total;
         }
     }
+    __syncthreads();
+}
+__global__ void __launch_bounds__(kMapThreads)
+global_offsets_kernel(const int32_t* __restrict__ c_all, const int32_t* __restrict__ o_exp, int E,
+                      int W, int rank, int n_epr, int32_t* __restrict__ off_base,
+                      int32_t* __restrict__ row_base, int32_t* __restrict__ recv_offsets) {
+    __shared__ MapScan S;
+    global_bases(S, c_all, o_exp, E, W, rank, n_epr, off_base, row_base, true, recv_offsets);
 }
 
 // One thread per slot: destination (rank, local expert, offset inside the expert's
@@ -659,21 +667,35 @@ global_offsets_kernel(const int32_t* __restrict__ c_all, const int32_t* __restri
 // worker of Section 3.2 replicates it for the token's other experts on that rank).
 // A workgroup has per_group whole tokens and their slots' ranks in LDS, where a slot finds the
 // earlier slots of its token.  Bound by its seven arrays, which a
-// thread per token read and wrote with a stride: 8.3 us for 32768 tokens with 8 slots, now 4.7 us.
-__global__ void __launch_bounds__(kRouteThreads)
+// thread per token read and wrote with a stride: 8.3 us for 32768 tokens with 8 slots, then 4.7 us.
+// BASES: every workgroup makes the experts' bases for itself, one launch less, and reads the W histograms for that.  Us, with the other launch / without:
+// 32768 tokens, 256 experts, 8 selected, 8 ranks 7.0 / 5.5; 20000, 512, 10, 8 7.2 / 5.6; 60001, 256, 8, 2 8.2 / 7.3; 100, 8, 2, 8 4.5 / 3.5.
+template <bool BASES>
+__global__ void __launch_bounds__(kMapThreads)
 global_map_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ m_loc, int T,
-                  int k, int per_group, int E, int n_epr, const int32_t* __restrict__ off_base,
-                  const int32_t* __restrict__ row_base, int32_t* __restrict__ dst_rank,
+                  int k, int per_group, int E, int n_epr, const int32_t* __restrict__ c_all, const int32_t* __restrict__ o_exp, int W, int rank,
+                  const int32_t* __restrict__ off_base, const int32_t* __restrict__ row_base, int32_t* __restrict__ dst_rank,
                   int32_t* __restrict__ dst_expert, int32_t* __restrict__ dst_off,
                   int32_t* __restrict__ dst_row, int32_t* __restrict__ send,
-                  int32_t* __restrict__ n_dst_ranks) {
-    __shared__ int32_t s_rank[kRouteThreads];
+                  int32_t* __restrict__ n_dst_ranks, int32_t* __restrict__ recv_offsets) {
+    __shared__ int32_t s_rank[kMapThreads];
     const int tid = threadIdx.x;
     const int t0 = blockIdx.x * per_group, nt = min(per_group, T - t0);
     const size_t f = (size_t)t0 * k + tid;
     const bool live = tid < nt * k;
+    int e = 0, loc = 0;
     if (live) {
-        const int e = topk_idx[f], loc = m_loc[f];
+        e = topk_idx[f];
+        loc = m_loc[f];
+    }
+    if constexpr (BASES) {
+        __shared__ MapScan S;
+        __shared__ int32_t s_off[kMapThreads], s_row[kMapThreads];
+        global_bases(S, c_all, o_exp, E, W, rank, n_epr, s_off, s_row, blockIdx.x == 0, recv_offsets);
+        off_base = s_off;
+        row_base = s_row;
+    }
+    if (live) {
         const bool any = (uint32_t)e < (uint32_t)E;   // a token with fewer than k logits that are numbers has slots without an expert
         const int r_tgt = any ? e / n_epr : -1;
         s_rank[tid] = r_tgt;
@@ -700,18 +722,28 @@ global_map_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restric
 
 // ------------------------------------------------------------------ host side
 
+// Up to so many counts every workgroup reads the histograms for itself: 16 KB from L2 are a fraction of what it writes.
+constexpr int kMapTable = 4096;
+
 int global_map_launch(const moe_shape_t& s, int W, int rank, const moe_routing_t& r,
                       const int32_t* c_all, const moe_global_map_t& out, void* ws, hipStream_t st) {
     int32_t* off_base = (int32_t*)ws;
     int32_t* row_base = off_base + s.E;
     const int n_epr = s.E / W;
-    hipLaunchKernelGGL(global_offsets_kernel, dim3(1), dim3(1024), 0, st, c_all, r.offsets, s.E, W,
-                       rank, n_epr, off_base, row_base, out.recv_offsets);
-    const int per_group = kRouteThreads / s.k;   // whole tokens whose slots fill a workgroup
-    if (s.T > 0)
-        hipLaunchKernelGGL(global_map_kernel, dim3((s.T + per_group - 1) / per_group), dim3(kRouteThreads), 0, st, r.topk_idx,
-                           r.inv_perm, s.T, s.k, per_group, s.E, n_epr, off_base, row_base, out.dst_rank, out.dst_expert,
-                           out.dst_off, out.dst_row, out.send, out.n_dst_ranks);
+    const int per_group = kMapThreads / s.k;   // whole tokens whose slots fill a workgroup
+    const int groups = (s.T + per_group - 1) / per_group;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(groups), dim3(kMapThreads), 0, st, r.topk_idx, r.inv_perm, s.T, s.k, per_group, s.E, n_epr, c_all, r.offsets,
+                           W, rank, off_base, row_base, out.dst_rank, out.dst_expert, out.dst_off, out.dst_row, out.send, out.n_dst_ranks,
+                           out.recv_offsets);
+    };
+    if (groups > 0 && W * s.E <= kMapTable) {
+        launch(global_map_kernel<true>);
+    } else {
+        hipLaunchKernelGGL(global_offsets_kernel, dim3(1), dim3(kMapThreads), 0, st, c_all, r.offsets, s.E, W, rank, n_epr, off_base, row_base,
+                           out.recv_offsets);
+        if (groups > 0) launch(global_map_kernel<false>);
+    }
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 

@@ -54,6 +54,13 @@ def test_global_map_matches_oracle(W, E, k, toks):
     run_case(W, E, k, toks, seed=7 * W + E)
 
 
+# 4096 counts of all ranks, which every workgroup reads for itself, and more, which one does for all; tokens that fill workgroups of 1024
+# slots, one more and one less, and a rank without any.
+@pytest.mark.parametrize("W,E,k,toks", [(4, 1024, 4, [256, 257, 255, 0]), (8, 1024, 4, [512, 1, 0, 513, 511, 2, 3, 4]), (16, 272, 16, [64, 65, 63, 0] * 4)])
+def test_global_map_with_and_without_a_launch_for_the_bases(W, E, k, toks):
+    run_case(W, E, k, toks, seed=W + E)
+
+
 def test_global_map_skewed_routing_and_statistics():
     """Zipf-biased routing; also the distinct-destination count of uniform top-8 over 8 ranks,
     which for distinct experts (16 per rank) averages 8 (1 - C(112,8)/C(128,8)) = 5.34."""
