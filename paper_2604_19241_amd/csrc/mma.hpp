@@ -24,7 +24,7 @@
 // lane p's 16 bytes to (LDS base) + 16 p, so nothing is staged in registers and no LDS
 // write instruction or register transpose exists.
 //
-// Two stage buffers (136 KB of LDS; three, 144 KB, for tiles of up to 128 rows, see mma_low).  Stage t+2 is requested right behind the barrier that
+// Two stage buffers (136 KB of LDS; three, 144 KB, for tiles of up to 128 rows, see mma_low).  The first two stages are requested together, stage t+2 right behind the barrier that
 // ends the fragment reads of stage t, so it has a whole stage of matrix work to land; one
 // workgroup barrier per stage.  The fragment reads are inline assembly: the compiler would put
 // a full vmcnt(0) in front of every LDS read it knows about while a DMA load is in flight.
@@ -351,6 +351,10 @@ struct KcLoader {
         for (int i = 0; i < 2; ++i) off[i] = (ln.l >> 3) * ld_bytes + KcGeom::chunk(ln, i) * 16;
     }
     __device__ __forceinline__ void prepare() {}
+    __device__ __forceinline__ void prepare_two() {}
+    __device__ __forceinline__ void fetch() {}
+    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
+    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + wave_block_off();
         const long long jump = left == 0 ? delta : 0;
@@ -368,6 +372,7 @@ struct RowLoader {
     const char* p[4];
     const char* pm;   // the fifth instruction's
     int n;            // blocks of this wave that hold rows of the tile (wave-uniform); bit 3: the fifth one does too
+    __device__ __forceinline__ bool full() const { return (n & 7) == 4; }   // at least 4 requests a stage
     template <class F>
     __device__ __forceinline__ void init(const Lane& ln, int rows, F row_of) {
         const int w = ln.wave_uniform();
@@ -378,6 +383,10 @@ struct RowLoader {
         if (n & 8) pm = row_of(min(KcGeom::more_row(ln), rows - 1)) + KcGeom::more_chunk(ln) * 16;
     }
     __device__ __forceinline__ void prepare() {}
+    __device__ __forceinline__ void prepare_two() {}
+    __device__ __forceinline__ void fetch() {}
+    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
+    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         const int off = wave_block_off();
         char* d = dst + off;
@@ -439,6 +448,10 @@ struct KsLoader {
         for (int i = 0; i < 2; ++i) off[i] = ln.hf * ld_bytes + min(first + KsGeom::chunk(ln, i) * 8, n - 8) * 2;
     }
     __device__ __forceinline__ void prepare() {}
+    __device__ __forceinline__ void prepare_two() {}
+    __device__ __forceinline__ void fetch() {}
+    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
+    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + wave_block_off();
 #pragma unroll
@@ -464,6 +477,10 @@ struct KsPairLoader {
         for (int i = 0; i < 2; ++i) off[i] = e * ld + min(first + (c ^ (2 * i)) * 8, n - 8) * 2;
     }
     __device__ __forceinline__ void prepare() {}
+    __device__ __forceinline__ void prepare_two() {}
+    __device__ __forceinline__ void fetch() {}
+    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
+    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + (wave_block_off() >> 1);
 #pragma unroll
@@ -483,11 +500,16 @@ __device__ __forceinline__ void lds_zero16(char* dst) {
 }
 
 struct KsTailLoader {
+    __device__ __forceinline__ bool full() const { return true; }   // 4 requests a stage, but the last
     const char* p[2];
     long long ld_bytes;   // one memory row (wave-uniform)
     int k0;               // reduction index of instruction 0's k row in the stage to come
     int K;
     __device__ __forceinline__ void prepare() {}
+    __device__ __forceinline__ void prepare_two() {}
+    __device__ __forceinline__ void fetch() {}
+    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
+    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + wave_block_off();
 #pragma unroll
@@ -501,9 +523,11 @@ struct KsTailLoader {
     }
 };
 // The same with a gather: reduction index k is memory row rows[k] of a [T, ld] matrix.  The
-// row indices of a stage are fetched (plain loads) right behind the DMA of the stage before
-// it and are complete by the barrier in between.  init() is called once per tile, after
+// row indices of the first two stages are fetched at once, those of every later one by a plain load right behind the DMA of the stage before
+// it, complete by the barrier in between.  init() is called once per tile, after
 // coloff[] is filled.
+// A wave moves 8 rows a stage, and each half of it 4 of them: lane l loads the index for instruction l % 4, and prepare()
+// hands it to the four lanes of its quad (a load for each instruction was four times as many).
 // prepare() turns the fetched indices into the four source addresses, and the main loop calls
 // it for both loaders before either requests anything: while a DMA is pending the compiler puts
 // a full vmcnt(0) in front of every use of a register that an ordinary load filled (it cannot
@@ -514,30 +538,42 @@ struct KsGatherLoader {
     uint32_t coloff[2];       // byte offset, inside a memory row, of the chunk instructions i, i % 2 = j move
     long long ld_bytes;       // wave-uniform
     const int32_t* rows;      // row_tok + first row of the expert (wave-uniform)
-    int32_t tok[4];           // memory rows of the stage whose DMA goes out next
-    const char* a[4];         // their addresses (prepare)
+    int32_t tok;              // memory row of instruction l % 4 in the stage whose DMA goes out next
+    int32_t tok1;             // the same of stage 1, until that is requested
+    const char* a[4];         // the instructions' addresses (prepare)
     int k0;                   // reduction index of instruction 0's k row in that stage
+    int mine;                 // from there to the one that this lane fetches the index of
     int K;
-    __device__ __forceinline__ void fetch() {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) tok[i] = rows[min(k0 + 2 * i, K - 1)];
-    }
+    __device__ __forceinline__ bool full() const { return true; }
+    __device__ __forceinline__ void fetch() { tok = rows[min(k0 + mine, K - 1)]; }
     __device__ __forceinline__ void init(const Lane& ln, const char* src_, long long ld_bytes_, const int32_t* rows_, int K_) {
         src = src_;
         ld_bytes = ld_bytes_;
         rows = rows_;
         K = K_;
         k0 = KsGeom::krow(ln, 0);
+        mine = 2 * (ln.l & 3);
         fetch();
+        tok1 = rows[min(k0 + BK + mine, K - 1)];
+    }
+    template <int I>
+    __device__ __forceinline__ const char* address(int32_t from) const {   // quad_perm [I, I, I, I]
+        const int32_t t = __builtin_amdgcn_update_dpp(0, from, I * 0x55, 0xf, 0xf, true);
+        const char* p = src + (long long)t * ld_bytes + coloff[I & 1];
+        asm volatile("" : "+v"(p));   // the address exists before the first request
+        return p;
     }
     __device__ __forceinline__ void prepare() {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            a[i] = src + (long long)tok[i] * ld_bytes + coloff[i & 1];
-            asm volatile("" : "+v"(a[i]));   // the address exists before the first request
-        }
+        a[0] = address<0>(tok);
+        a[1] = address<1>(tok);
+        a[2] = address<2>(tok);
+        a[3] = address<3>(tok);
     }
-    __device__ __forceinline__ void issue(char* dst) {
+    __device__ __forceinline__ void prepare_two() {
+        prepare();
+        asm volatile("" : "+v"(tok1));   // here before the first request, so that issue_second() does not wait for it behind that
+    }
+    __device__ __forceinline__ void issue_first(char* dst) {
         char* d = dst + wave_block_off();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -545,6 +581,14 @@ struct KsGatherLoader {
             else lds_zero16(d + i * 1024);
         }
         k0 += BK;
+    }
+    __device__ __forceinline__ void issue_second(char* dst) {
+        tok = tok1;
+        prepare();
+        issue_first(dst);
+    }
+    __device__ __forceinline__ void issue(char* dst) {
+        issue_first(dst);
         fetch();
     }
 };
@@ -562,25 +606,34 @@ struct KsGatherLoader {
 //                   request the column operand of stage t+2 (a CU takes about 64 DMA requests
 //                   before issue blocks, which is what one stage has: the second half goes out
 //                   behind a burst of matrix work instead of in front of it; 1 % on the step).
+// Stages 0 and 1 are requested together: stage 1 used to wait for stage 0 to land, and had then only that stage's matrix work to arrive
+// in, once a tile (backward pass of 8192 tokens on 128 experts of 2048 x 768 1617 -> 1591 us).  A reduction over an expert's rows has
+// `last` sub-steps in its last stage: those that hold only zeros were an eighth of the matrix work at 256 rows an expert.  Both together, training
+// steps: 8192 tokens on 128 experts of 2048 x 768 2347 -> 2298 us, Zipf(1.2) 2435 -> 2389, 32 of 256 of 7168 x 2048 2960 -> 2853.
 template <int NTF, int MORE, int A_FORM, bool B_KS, class LB, class LA>
-__device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, const FragAddr& fa, Acc& acc) {
-    lb.prepare();
-    la.prepare();
+__device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, const FragAddr& fa, Acc& acc, int last = 4) {
+    int full = rfl(nk > (B_KS ? 2 : 1) && lb.full());
+    asm volatile("" : "+s"(full));   // (otherwise the branches of issue() and of the wait are threaded, with scalar addresses in vector registers)
+    lb.prepare_two();
+    la.prepare_two();
     __builtin_amdgcn_sched_barrier(0);
-    lb.issue(smem);
-    la.issue(smem + kRowBytes);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
+    lb.issue_first(smem);
+    la.issue_first(smem + kRowBytes);
+    // stage 1 right behind stage 0: its requests wait for nothing but their turn
     if (nk > 1) {
-        lb.prepare();
-        la.prepare();
-        __builtin_amdgcn_sched_barrier(0);
-        lb.issue(smem + kStageBytes);
-        la.issue(smem + kStageBytes + kRowBytes);
+        lb.issue_second(smem + kStageBytes);
+        la.issue_second(smem + kStageBytes + kRowBytes);
     }
+    // (a wave's requests of stage 1 are 8 or 9, or fewer where it has few rows or the reduction ends in it)
+    if (full) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    lb.fetch();
+    la.fetch();
     Frags f0, f1;
     if (NTF > 0) read_frags<NTF, MORE, A_FORM, B_KS, 0>(f0, fa, 0, 0);
-    for (int t = 0; t < nk; ++t) {
+    const int whole = B_KS ? nk - 1 : nk;   // the last stage of a reduction over rows may have fewer than 64
+    for (int t = 0; t < whole; ++t) {
         const uint32_t boff = (t & 1) * kStageBytes, noff = kStageBytes - boff;
         __builtin_amdgcn_sched_barrier(0);
         if (NTF > 0) {
@@ -617,6 +670,30 @@ __device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, con
     }
     __builtin_amdgcn_sched_barrier(0);
     if (NTF > 0) wait_frags<0, MORE>(f0);
+    if constexpr (B_KS && NTF > 0) {
+        // sub-steps without a row are left out: they would add zeros
+        const uint32_t boff = ((nk - 1) & 1) * kStageBytes;
+        mfma_step_reading<NTF, MORE, A_FORM, B_KS, 1>(f0, f1, fa, boff, boff, acc);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_frags<0, MORE>(f1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (last > 1) {
+            mfma_step_reading<NTF, MORE, A_FORM, B_KS, 2>(f1, f0, fa, boff, boff, acc);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_frags<0, MORE>(f0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (last > 2) {
+                mfma_step_reading<NTF, MORE, A_FORM, B_KS, 3>(f0, f1, fa, boff, boff, acc);
+                __builtin_amdgcn_sched_barrier(0);
+                wait_frags<0, MORE>(f1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (last > 3) mfma_step_reading<NTF, MORE, A_FORM, B_KS, 3>(f1, f0, fa, boff, boff, acc);
+                __builtin_amdgcn_sched_barrier(0);
+                wait_frags<0, MORE>(f0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
     __builtin_amdgcn_s_barrier();   // every wave has read its last fragments: the buffers may be refilled
 }
 
@@ -737,11 +814,12 @@ __device__ __forceinline__ void weight_tile_gemm(LB& lb, LA& la, int nk, int row
     zero_acc(acc, false);
     if (nk <= 0) return;   // empty reduction (an expert without rows): the tile is all zeros
     const int ntf = active_row_frags(rows);
-    if (ntf == 4) mma_loop<4, 0, kKs, true>(lb, la, nk, smem, fa, acc);
-    else if (ntf == 3) mma_loop<3, 0, kKs, true>(lb, la, nk, smem, fa, acc);
-    else if (ntf == 2) mma_loop<2, 0, kKs, true>(lb, la, nk, smem, fa, acc);
-    else if (ntf == 1) mma_loop<1, 0, kKs, true>(lb, la, nk, smem, fa, acc);
-    else mma_loop<0, 0, kKs, true>(lb, la, nk, smem, fa, acc);
+    const int last = rfl(((lb.K - 1) % BK) / 16 + 1);   // sub-steps of the last stage: the rest are zeros
+    if (ntf == 4) mma_loop<4, 0, kKs, true>(lb, la, nk, smem, fa, acc, last);
+    else if (ntf == 3) mma_loop<3, 0, kKs, true>(lb, la, nk, smem, fa, acc, last);
+    else if (ntf == 2) mma_loop<2, 0, kKs, true>(lb, la, nk, smem, fa, acc, last);
+    else if (ntf == 1) mma_loop<1, 0, kKs, true>(lb, la, nk, smem, fa, acc, last);
+    else mma_loop<0, 0, kKs, true>(lb, la, nk, smem, fa, acc, last);
 }
 
 // ------------------------------------------------------------------ epilogue helpers

@@ -112,6 +112,28 @@ def test_backward_long_reduction(tile_rows):
         check_elementwise(key, to_f64(g[key]), want[key])
 
 
+# Weight-gradient reductions that end in each of a stage's four steps of 16 rows, on both sides of it, in the first stage, the second, the
+# third and a later one (the first two are requested together), with outputs that fill a tile, part of it and several.
+@pytest.mark.parametrize("d,I", [(320, 192), (64, 64), (512, 576)])
+@pytest.mark.parametrize("first", [0, 64, 128, 320])
+def test_backward_reductions_end_anywhere_in_a_stage(first, d, I):
+    rows = [first + n for n in (1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64)]
+    T, E = sum(rows), len(rows)
+    cfg = moe_synth.small_config(T=T, d=d, E=E, k=1, I=I)
+    inp = scaled_inputs(cfg, first + d, 4.0)
+    own = np.random.default_rng(T).permutation(np.repeat(np.arange(E), rows))
+    inp["logits"] = torch.from_numpy(np.eye(E, dtype=np.float32)[own])
+    b = bits(inp, ("x", "dy", "w_gate", "w_up", "w_down"))
+    r = oracle.route(cfg.shape_dict(), inp["logits"].numpy())
+    assert r["counts"].tolist() == rows
+    say(f"[bwd] reductions of {rows} rows, d={d} I={I}")
+    g, _ = gpu_fwd_bwd(cfg, inp, 0, 0)
+    want = oracle.backward(cfg.shape_dict(), b["x"], b["dy"], b["w_gate"], b["w_up"], b["w_down"], r, round_bf16=True, acc="f32")
+    for key in KEYS:
+        assert rel_l2(to_f64(g[key]), want[key]) <= GRAD_REL_L2, key
+        check_elementwise(key, to_f64(g[key]), want[key])
+
+
 def test_backward_is_bitwise_repeatable_and_schedule_independent():
     cfg = moe_synth.small_config(T=900, d=256, E=16, k=4, I=256, zipf_s=1.2)
     inp = scaled_inputs(cfg, 22, 4.0)
