@@ -42,7 +42,6 @@ struct FwdParams {
     int workers;   // workgroups of the worker launch (the tail waits for all of them)
     TileChoice tile;   // rows of the row tiles
     ThinRule rule;     // which experts are run outside the work queue; max_rows = 0: none
-    int plan_blocks;   // workgroups of the first launch that make the queue: kPlanBlocks, or 0 if there is none
     long long spin_ticks;
 };
 
@@ -84,18 +83,26 @@ __device__ __forceinline__ ThinParams thin_params(const FwdParams& p) {
 __global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
 fwd_first_kernel(FwdParams p) {
     __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared) > sizeof(QueuePlan) ? sizeof(ThinShared) : sizeof(QueuePlan)];
-    const int block = (int)blockIdx.x - p.plan_blocks;
-    if (block < 0) {
-        fwd_setup(p, (int)blockIdx.x, *(QueuePlan*)smem);
-        return;
-    }
-    if (p.plan_blocks == 0 && block == 0 && threadIdx.x < CTRL_WORDS) p.ctrl[threadIdx.x] = 0;
-    thin_run<1>(thin_params(p), block, (int)gridDim.x - p.plan_blocks, *(ThinShared*)smem);
+    const int block = (int)blockIdx.x - kPlanBlocks;
+    if (block < 0) fwd_setup(p, (int)blockIdx.x, *(QueuePlan*)smem);
+    else thin_run<1, false>(thin_params(p), block, (int)gridDim.x - kPlanBlocks, *(ThinShared*)smem);
 }
 __global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
 fwd_second_kernel(FwdParams p) {
     __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared)];
-    thin_run<2>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
+    thin_run<2, false>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
+}
+// The same where there is no queue.
+__global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
+thin_first_kernel(FwdParams p) {
+    __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared)];
+    if (blockIdx.x == 0 && threadIdx.x < CTRL_WORDS) p.ctrl[threadIdx.x] = 0;
+    thin_run<1, true>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
+}
+__global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
+thin_second_kernel(FwdParams p) {
+    __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared)];
+    thin_run<2, true>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
 }
 
 // ------------------------------------------------------------- GEMM1 task
@@ -486,19 +493,19 @@ static int fwd_launch_tiles(FwdParams& p, const moe_opts_t& opts, hipStream_t st
     const long long enough = (long long)kThinRows * p.s.E * (p.s.e_count == p.s.E ? 1 : 4);
     const bool none_thin = !all_thin && (long long)p.s.T * p.s.k > enough && !thin_may_pay(thin_rule(p.s, kThinRows), p.s);
     p.rule = thin_rule(p.s, all_thin ? INT_MAX : none_thin ? 0 : kThinRows);
-    p.plan_blocks = all_thin ? 0 : kPlanBlocks;
     const size_t most = std::min<size_t>(p.s.e_count, (size_t)p.s.T * p.s.k);   // experts with rows
     // A caller's bound on the workers leaves the rest of the chip to somebody else: as many workgroups here.
     const size_t slots = workers < resident ? (size_t)workers : (size_t)kThinGroupsPerCu * resident;
     const size_t n1 = none_thin ? 0 : std::min(slots, most * (p.s.I / 32));
     const size_t n2 = std::min(slots, most * (p.s.d / 64));
-    hipLaunchKernelGGL(fwd_first_kernel, dim3((unsigned)(n1 + p.plan_blocks)), dim3(kThinThreads), 0, st, p);
-    if (!none_thin)
-        hipLaunchKernelGGL(fwd_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);
     if (all_thin) {
+        hipLaunchKernelGGL(thin_first_kernel, dim3((unsigned)n1), dim3(kThinThreads), 0, st, p);
+        hipLaunchKernelGGL(thin_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);
         if (!opts.skip_tail || opts.schedule == 1 || opts.schedule == 2) launch_tail(p, st);
         return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
     }
+    hipLaunchKernelGGL(fwd_first_kernel, dim3((unsigned)(n1 + kPlanBlocks)), dim3(kThinThreads), 0, st, p);
+    if (!none_thin) hipLaunchKernelGGL(fwd_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);
     if (opts.schedule == 2) {
         for (int phase = 0; phase < 3; ++phase)
             hipLaunchKernelGGL(fwd_worker_kernel, dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, phase);
