@@ -47,7 +47,7 @@ def _short(name: str) -> str:
         if key in name:
             return key
     name = name.split("(")[0]
-    return name.split("::")[-1][:60]
+    return re.sub(r"\w+::", "", name).removeprefix("void ")[:60]
 
 
 def kernel_rows(con):
