@@ -102,11 +102,14 @@ struct ThinRule {
     // Rows up to which an expert of this batch takes this path (0 = none does); experts with few, medium and more rows,
     // and the rows of all of them.
     // Where no expert has more than medium rows and there are more than kOftenMedium experts, all of them take this path if that is
-    // the faster way for them together: tasks of two blocks of rows stream the weights at 5.0 TB/s (128 columns), the queue takes 30 us and
-    // 5.5 TB/s.  Measured, us of the layer, with medium experts on the queue / here (tokens, experts of width and inner width; rows an expert):
-    // 1021, 512 of 2048 x 512 (20) 620 / 577; 1300 (25) 645 / 573; 700, 256 of 2304 x 1024 (22) 664 / 628; but 1200, 32 of 256 of 7168 x 2048
-    // (38) 511 / 564, 640, 128 of 2048 x 768 (40) 251 / 247 to 257.  Fewer experts would often gain as well (512, 128 of 1024 x 384 (24) 96 / 71;
-    // 500, 128 of 2048 x 768 (31) 247 / 232; 250, 64 of 2048 x 1408 (23) 229 / 202): they keep the choice that is tested for them.
+    // the faster way for them together: tasks of two blocks of rows (128 columns) stream the weights at 4.5 TB/s, the queue takes 30 us and
+    // 5.4 TB/s and 50 ns an expert.  Measured, us of the layer, with medium experts on the queue / here (experts of width and inner width, with few + medium
+    // rows): 512 of 2048 x 512, 477 + 35 624 / 590, 280 + 232 633 / 599, 93 + 419 637 / 662; 256 of 2304 x 1024, 250 + 6 665 / 648, 192 + 64 675 / 645,
+    // 76 + 128 557 / 596, 0 + 256 707 / 770; 160 of 5120 x 1536, 144 + 16 1348 / 1300, 46 + 80 1067 / 1150; 256 of 7168 x 2048, 192 + 64 3834 / 3665, 18 + 230
+    // 3876 / 4308.  Of 462 batches of 18 layers the estimate sends 322 here, half of them 4 % faster or more, 6 more than 1 % slower (at most 4 %); of the others 17
+    // would be more than 1 % faster (at most 7 %).  (At 5.0 and 5.5 TB/s and no time an expert it sent 18 here that were slower, by up to 7 %.)
+    // Fewer experts would often gain as well (512 tokens on 128 of 1024 x 384, 24 rows each, 96 / 71; 500 on 128 of 2048 x 768, 31 rows,
+    // 247 / 232; 250 on 64 of 2048 x 1408, 23 rows, 229 / 202): they keep the choice that is tested for them.
     __device__ __forceinline__ int limit(int few, int medium, int more, int rows) const {
         if (more == 0 && medium > 0 && few + medium > kOftenMedium) {
             const long long stream = 30000 + (long long)(few + medium) * full_ns;
@@ -119,7 +122,7 @@ struct ThinRule {
 inline ThinRule thin_rule(const moe_shape_t& s, int max_rows) {
     const long long bytes = 6ll * s.d * s.I;
     return ThinRule{max_rows, (int)((long long)s.T * s.k * s.e_count / s.E / 512), 1000ll * ((s.d + s.I) / BK),
-                    (int)(bytes / 5200), (int)(bytes / 6400), (int)(bytes / 5500), (int)(bytes / 5000)};
+                    (int)(bytes / 5200), (int)(bytes / 6400), (int)(bytes / 5400) + 50, (int)(bytes / 4500)};
 }
 // Whether it can pay beside an expert with many rows, whatever the counts.
 inline bool thin_may_pay(const ThinRule& r, const moe_shape_t& s) { return r.queue(s.e_count) - r.chain_ns > 20000; }

@@ -67,6 +67,26 @@ def test_the_same_bits_on_both_paths(few, many, rows, ahead):
         assert torch.equal(v, want[name][:n]), name
 
 
+# 256 experts of 2304 x 1024, none with more than 64 rows: all of them ahead of the queue where the estimate says that it is faster (192 with up to 32
+# rows and 64 with more 645 us, on the queue 675 us), all on it where it is not (76 and 128 557 us, ahead of it 596 us), and the last and first numbers on its two sides.
+@pytest.mark.parametrize("few,medium,ahead", [(192, 64, True), (120, 136, True), (119, 137, False), (76, 128, False)])
+def test_up_to_64_rows_leave_the_queue_where_that_is_faster(few, medium, ahead):
+    E, d, I = 256, 2304, 1024
+    rng = np.random.default_rng(medium)
+    counts = np.zeros(E, np.int64)
+    at = rng.permutation(E)
+    counts[at[:few]] = rng.integers(1, 33, few)
+    counts[at[few:few + medium]] = rng.integers(33, 65, medium)
+    n = int(counts.sum())
+    say(f"[path] few={few} medium={medium}")
+    got, tiles = forward(*batch(counts, d, I))
+    assert tiles == (0 if ahead else few + medium), tiles
+    want, tiles = forward(*batch(counts, d, I, extra=33))   # on the queue, by their own rows
+    assert tiles == E
+    for name, v in got.items():
+        assert torch.equal(v, want[name][:n]), name
+
+
 # 128 of 136 experts, `many` of them with so many rows and the others with 10: the rows that are here decide, not the tokens (24000
 # of them, of which even routing would send 22588 here).
 @pytest.mark.parametrize("many,rows,ahead", [(38, 50, False), (20, 200, False), (30, 560, True)])
