@@ -49,9 +49,10 @@ struct FwdParams {
 // The work queue of the experts that thin_run leaves to it, made by the first kPlanBlocks workgroups:
 // row-tile table from the expert offsets, the per-XCD task lists (GEMM1 block of expert i+1 ahead of the
 // GEMM2 block of expert i) and a cleared scoreboard.
+template <bool TWO>
 __device__ __forceinline__ void fwd_setup(const FwdParams& p, int block, QueuePlan& P) {
     const int ec = p.s.e_count, rows_here = p.offsets[ec];
-    const TileRule tile = make_plan(P, p.offsets, ec, p.rule.max_rows > 0, [&](int rows) { return p.rule.size_class(rows); },
+    const TileRule tile = make_plan(P, p.offsets, ec, p.rule.max_rows > 0, [&](int rows) { return p.rule.size_class<TWO>(rows); },
                                     [&](int few, int medium, int more) { return p.rule.limit(few, medium, more, rfl(rows_here)); }, p.tile, p.nct1,
                                     [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct1; },
                                     [&](const TileRule& t, int rows) { return t.tiles(rows) * p.nct2; });
@@ -80,29 +81,32 @@ __device__ __forceinline__ ThinParams thin_params(const FwdParams& p) {
 }
 // The queue (unless every expert is thin) and the thin experts' GEMM1, side by side: neither reads
 // what the other writes.
+// TWO: thin_may_be_two.
+template <bool TWO>
 __global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
 fwd_first_kernel(FwdParams p) {
     __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared) > sizeof(QueuePlan) ? sizeof(ThinShared) : sizeof(QueuePlan)];
     const int block = (int)blockIdx.x - kPlanBlocks;
-    if (block < 0) fwd_setup(p, (int)blockIdx.x, *(QueuePlan*)smem);
-    else thin_run<1, false>(thin_params(p), block, (int)gridDim.x - kPlanBlocks, *(ThinShared*)smem);
+    if (block < 0) fwd_setup<TWO>(p, (int)blockIdx.x, *(QueuePlan*)smem);
+    else thin_run<1, TWO ? kThinTwo : kThinFew>(thin_params(p), block, (int)gridDim.x - kPlanBlocks, *(ThinShared*)smem);
 }
+template <bool TWO>
 __global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
 fwd_second_kernel(FwdParams p) {
     __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared)];
-    thin_run<2, false>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
+    thin_run<2, TWO ? kThinTwo : kThinFew>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
 }
 // The same where there is no queue.
 __global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
 thin_first_kernel(FwdParams p) {
     __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared)];
     if (blockIdx.x == 0 && threadIdx.x < CTRL_WORDS) p.ctrl[threadIdx.x] = 0;
-    thin_run<1, true>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
+    thin_run<1, kThinAll>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
 }
 __global__ void __launch_bounds__(kThinThreads) __attribute__((amdgpu_waves_per_eu(2)))
 thin_second_kernel(FwdParams p) {
     __shared__ __attribute__((aligned(16))) char smem[sizeof(ThinShared)];
-    thin_run<2, true>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
+    thin_run<2, kThinAll>(thin_params(p), (int)blockIdx.x, (int)gridDim.x, *(ThinShared*)smem);
 }
 
 // ------------------------------------------------------------- GEMM1 task
@@ -504,8 +508,10 @@ static int fwd_launch_tiles(FwdParams& p, const moe_opts_t& opts, hipStream_t st
         if (!opts.skip_tail || opts.schedule == 1 || opts.schedule == 2) launch_tail(p, st);
         return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
     }
-    hipLaunchKernelGGL(fwd_first_kernel, dim3((unsigned)(n1 + kPlanBlocks)), dim3(kThinThreads), 0, st, p);
-    if (!none_thin) hipLaunchKernelGGL(fwd_second_kernel, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);
+    const bool two = thin_may_be_two(p.s);
+    hipLaunchKernelGGL(two ? fwd_first_kernel<true> : fwd_first_kernel<false>, dim3((unsigned)(n1 + kPlanBlocks)), dim3(kThinThreads), 0, st, p);
+    if (!none_thin)
+        hipLaunchKernelGGL(two ? fwd_second_kernel<true> : fwd_second_kernel<false>, dim3((unsigned)n2), dim3(kThinThreads), 0, st, p);
     if (opts.schedule == 2) {
         for (int phase = 0; phase < 3; ++phase)
             hipLaunchKernelGGL(fwd_worker_kernel, dim3(workers), dim3(kMmaThreads), kMmaSmem, st, p, phase);

@@ -97,8 +97,9 @@ struct ThinRule {
         if (few < 8 * many && many > min(many_most, rows / 512)) return false;
         return queue(few + many) - queue(many) > 20000 + (long long)few * thin_ns;
     }
-    // 0: up to max_rows rows, 1: medium, up to kThinMostRows, 2: more
-    __device__ __forceinline__ int size_class(int rows) const { return rows <= max_rows ? 0 : max_rows > 0 && rows <= kThinMostRows ? 1 : 2; }
+    // 0: up to max_rows rows, 1 (TWO): medium, up to kThinMostRows, 2: more
+    template <bool TWO>
+    __device__ __forceinline__ int size_class(int rows) const { return rows <= max_rows ? 0 : TWO && max_rows > 0 && rows <= kThinMostRows ? 1 : 2; }
     // Rows up to which an expert of this batch takes this path (0 = none does); experts with few, medium and more rows,
     // and the rows of all of them.
     // Where no expert has more than medium rows and there are more than kOftenMedium experts, all of them take this path if that is
@@ -124,6 +125,8 @@ inline ThinRule thin_rule(const moe_shape_t& s, int max_rows) {
     return ThinRule{max_rows, (int)((long long)s.T * s.k * s.e_count / s.E / 512), 1000ll * ((s.d + s.I) / BK),
                     (int)(bytes / 5200), (int)(bytes / 6400), (int)(bytes / 5400) + 50, (int)(bytes / 4500)};
 }
+// Whether the rule may send experts with medium rows here, whatever the counts.
+inline bool thin_may_be_two(const moe_shape_t& s) { return s.e_count > ThinRule::kOftenMedium; }
 // Whether it can pay beside an expert with many rows, whatever the counts.
 inline bool thin_may_pay(const ThinRule& r, const moe_shape_t& s) { return r.queue(s.e_count) - r.chain_ns > 20000; }
 
@@ -384,10 +387,14 @@ __device__ __forceinline__ void thin_tasks(const ThinParams& p, int first, int c
 // every `blocks`-th task.  Workgroups go to the XCDs in turn, so for as many experts as fill all eight
 // the tasks of one expert share an XCD (its rows are then fetched by one L2); what is left over
 // is spread task by task.
-// ALL: every expert is of this path, whatever its rows, and the choices above are left out (one token on 128 experts of 2048 x 768, 8 selected,
-// 31.8 -> 31.2 us, 32 tokens 177.4 -> 176.8).
-template <int GEMM, bool ALL>
+// kThinAll: every expert is of this path, whatever its rows, and the choices above are left out (one token on 128 experts of 2048 x 768, 8 selected,
+// 31.8 -> 31.2 us).  kThinTwo: experts may have two blocks of rows here.  The code for these costs 0.2 to 0.7 us a launch, 2 % of a
+// small share's layer, where the rule never sends them here (300 tokens on 16 of 128 of 1024 x 384 20.3 us, with it 21.1; 128 on 16 of 128 of 2048 x 768
+// 36.8 and 37.9; 300 on 8 of 64 of 1280 x 896 52.9 and 53.6).
+enum ThinForm { kThinAll, kThinFew, kThinTwo };
+template <int GEMM, ThinForm FORM>
 __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blocks, ThinShared& S) {
+    constexpr bool ALL = FORM == kThinAll, TWO = FORM == kThinTwo;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ec = p.s.e_count;
     const int rows_here = ALL ? 0 : p.offsets[ec];
@@ -395,10 +402,10 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
 #pragma unroll
     for (int j = 0; j < 5; ++j) off[j] = p.offsets[min(4 * tid + j, ec)];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {   // few and, shifted left by 16, medium rows
-        const int rows = off[j + 1] - off[j], c = ALL ? 0 : p.rule.size_class(rows);
-        mine += rows <= 0 ? 0 : c == 0 ? 1 : c == 1 ? 1 << 16 : 0;
-        if (!ALL) more += __popcll(__ballot(c == 2));
+    for (int j = 0; j < 4; ++j) {   // few and, shifted left by 16, medium (without those: more) rows
+        const int rows = off[j + 1] - off[j], c = ALL ? 0 : p.rule.size_class<TWO>(rows);
+        mine += rows <= 0 ? 0 : c == 0 ? 1 : c == 1 || !TWO ? 1 << 16 : 0;
+        if (TWO) more += __popcll(__ballot(c == 2));
     }
     int pre = mine;
 #pragma unroll
@@ -408,7 +415,7 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
     }
     if (lane == 63) {
         S.wave[0][wave] = pre;
-        if (!ALL) S.wave[1][wave] = more;
+        if (TWO) S.wave[1][wave] = more;
     }
     __syncthreads();
     int at = pre - mine, count = 0;
@@ -417,18 +424,18 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
     for (int w = 0; w < 4; ++w) {
         if (w < wave) at += S.wave[0][w];
         count += S.wave[0][w];
-        if (!ALL) more += S.wave[1][w];
+        if (TWO) more += S.wave[1][w];
     }
-    const int few = rfl(count & 0xffff), medium = rfl((uint32_t)count >> 16);
-    const int limit = ALL ? INT_MAX : p.rule.limit(few, medium, rfl(more), rfl(rows_here));
-    const int two = limit > kThinRows && limit <= kThinMostRows ? medium : 0;   // experts with two blocks of rows here
+    const int few = rfl(count & 0xffff), rest = rfl((uint32_t)count >> 16);
+    const int limit = ALL ? INT_MAX : TWO ? p.rule.limit(few, rest, rfl(more), rfl(rows_here)) : p.rule.limit(few, 0, rest, rfl(rows_here));
+    const int two = TWO && limit == kThinMostRows ? rest : 0;   // experts with two blocks of rows here
     if (limit == 0 || few + two == 0) return;
     int at_few = at & 0xffff, at_two = few + (int)((uint32_t)at >> 16);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int rows = off[j + 1] - off[j];
         if (rows > 0 && rows <= limit) {
-            const int i = ALL || p.rule.size_class(rows) == 0 ? at_few++ : at_two++;
+            const int i = !TWO || p.rule.size_class<TWO>(rows) == 0 ? at_few++ : at_two++;
             S.expert[i] = (uint16_t)(4 * tid + j);
             S.row0[i] = off[j];
             S.rows[i] = (uint16_t)rows;
@@ -436,10 +443,12 @@ __device__ __forceinline__ void thin_run(const ThinParams& p, int block, int blo
     }
     __syncthreads();
     const int columns = GEMM == 1 ? 2 * p.s.I : p.s.d;
-    if (!ALL && two > 0) {   // the longer tasks first; who has had one more of them gets one less of the others
-        thin_tasks<GEMM, 128, 2>(p, few, two, block, blocks, S);
-        block -= (two * ((columns + 127) / 128) & ~7) % blocks;
-        if (block < 0) block += blocks;
+    if constexpr (TWO) {
+        if (two > 0) {   // the longer tasks first; who has had one more of them gets one less of the others
+            thin_tasks<GEMM, 128, 2>(p, few, two, block, blocks, S);
+            block -= (two * ((columns + 127) / 128) & ~7) % blocks;
+            if (block < 0) block += blocks;
+        }
     }
     const int cols = thin_cols(few, columns, p.workers);
     if (cols == 256) thin_tasks<GEMM, 256, 1>(p, 0, few, block, blocks, S);

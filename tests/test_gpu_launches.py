@@ -90,6 +90,16 @@ def test_workers_bounds_every_launch_of_the_forward_gemms(T, workers):
         assert min(groups) >= 128, gemms
 
 
+# Experts of 33 to 64 rows leave the queue in layers of more than 128 experts alone: elsewhere the launches have no code for them.
+@pytest.mark.parametrize("experts,two", [(128, False), (129, True)])
+def test_launches_for_few_rows_have_no_more_code_than_they_may_run(experts, two):
+    first_call()
+    got = forward_launches(moe.make_shape(T=300, d=256, E=160, k=4, I=128, e_count=experts), moe.make_opts())
+    say(f"[launches] {experts} experts: {got}")
+    names = [name for name, _, _ in got if "first" in name or "second" in name]
+    assert len(names) == 2 and all(("ILb1E" in name or "<true>" in name) == two for name in names), names
+
+
 def every_launch_fits(got):
     say(f"[launches] {got}")
     assert all(0 < groups and groups * threads < 2 ** 32 for _, groups, threads in got), got
