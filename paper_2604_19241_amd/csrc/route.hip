@@ -688,12 +688,13 @@ global_map_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restric
         e = topk_idx[f];
         loc = m_loc[f];
     }
+    const int32_t *off = off_base, *row = row_base;
     if constexpr (BASES) {
         __shared__ MapScan S;
         __shared__ int32_t s_off[kMapThreads], s_row[kMapThreads];
         global_bases(S, c_all, o_exp, E, W, rank, n_epr, s_off, s_row, blockIdx.x == 0, recv_offsets);
-        off_base = s_off;
-        row_base = s_row;
+        off = s_off;
+        row = s_row;
     }
     if (live) {
         const bool any = (uint32_t)e < (uint32_t)E;   // a token with fewer than k logits that are numbers has slots without an expert
@@ -701,8 +702,8 @@ global_map_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restric
         s_rank[tid] = r_tgt;
         dst_rank[f] = r_tgt;
         dst_expert[f] = any ? e - r_tgt * n_epr : -1;
-        dst_off[f] = any ? loc + off_base[e] : -1;
-        dst_row[f] = any ? loc + row_base[e] : -1;
+        dst_off[f] = any ? loc + off[e] : -1;
+        dst_row[f] = any ? loc + row[e] : -1;
     }
     __syncthreads();
     if (live) {
