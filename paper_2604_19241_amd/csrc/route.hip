@@ -668,17 +668,17 @@ global_offsets_kernel(const int32_t* __restrict__ c_all, const int32_t* __restri
 // A workgroup has per_group whole tokens and their slots' ranks in LDS, where a slot finds the
 // earlier slots of its token.  Bound by its seven arrays, which a
 // thread per token read and wrote with a stride: 8.3 us for 32768 tokens with 8 slots, then 4.7 us.
-// BASES: every workgroup makes the experts' bases for itself, one launch less, and reads the W histograms for that.  Us, with the other launch / without:
-// 32768 tokens, 256 experts, 8 selected, 8 ranks 7.0 / 5.5; 20000, 512, 10, 8 7.2 / 5.6; 60001, 256, 8, 2 8.2 / 7.3; 100, 8, 2, 8 4.5 / 3.5.
+// BASES: every workgroup makes the experts' bases for itself, one launch less, and reads the W histograms for that (see global_map_launch); such a
+// workgroup has kMapThreads threads, one without kRouteThreads.
 template <bool BASES>
-__global__ void __launch_bounds__(kMapThreads)
+__global__ void __launch_bounds__(BASES ? kMapThreads : kRouteThreads)
 global_map_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ m_loc, int T,
                   int k, int per_group, int E, int n_epr, const int32_t* __restrict__ c_all, const int32_t* __restrict__ o_exp, int W, int rank,
                   const int32_t* __restrict__ off_base, const int32_t* __restrict__ row_base, int32_t* __restrict__ dst_rank,
                   int32_t* __restrict__ dst_expert, int32_t* __restrict__ dst_off,
                   int32_t* __restrict__ dst_row, int32_t* __restrict__ send,
                   int32_t* __restrict__ n_dst_ranks, int32_t* __restrict__ recv_offsets) {
-    __shared__ int32_t s_rank[kMapThreads];
+    __shared__ int32_t s_rank[BASES ? kMapThreads : kRouteThreads];
     const int tid = threadIdx.x;
     const int t0 = blockIdx.x * per_group, nt = min(per_group, T - t0);
     const size_t f = (size_t)t0 * k + tid;
@@ -723,27 +723,31 @@ global_map_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restric
 
 // ------------------------------------------------------------------ host side
 
-// Up to so many counts every workgroup reads the histograms for itself: 16 KB from L2 are a fraction of what it writes.
+// Up to so many counts, and no more workgroups than run at a time (two a CU), every workgroup of the mapping makes the bases for itself.  Us, by a launch
+// of their own / so (tokens x experts x k, ranks): 100 x 256 x 8, 8 6.0 / 4.9, 32768 7.4 / 6.0, 65536 (512 workgroups) 9.1 / 8.2, but 80000 (625)
+// 10.1 / 10.7, 131072 (1024) 12.0 / 12.9, 300001 19.2 / 24.8; 52000 x 512 x 10, 8 (510) 10.3 / 8.8, 65536 (643) 11.2 / 11.5; 32768 x 128 x 16, 32 (512)
+// 11.1 / 10.1, 45000 (704) 13.3 / 14.2.  By the counts: 16384 x 1024 x 8 with 4 ranks 7.1 / 5.9, with 8 7.0 / 5.8, with 64 8.7 / 7.7, but 45000 with 16 8.7 / 8.6, with
+// 64 10.2 / 12.2.  Where the bases have their launch, 1024 threads a workgroup are the slower: 300001 x 256 x 8 21.9 for 19.2, 1000 x 1024 x 8 7.0 for 6.5.
 constexpr int kMapTable = 4096;
+constexpr int kMapGroups = 2 * kChunkCus;
 
 int global_map_launch(const moe_shape_t& s, int W, int rank, const moe_routing_t& r,
                       const int32_t* c_all, const moe_global_map_t& out, void* ws, hipStream_t st) {
     int32_t* off_base = (int32_t*)ws;
     int32_t* row_base = off_base + s.E;
     const int n_epr = s.E / W;
-    const int per_group = kMapThreads / s.k;   // whole tokens whose slots fill a workgroup
-    const int groups = (s.T + per_group - 1) / per_group;
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(groups), dim3(kMapThreads), 0, st, r.topk_idx, r.inv_perm, s.T, s.k, per_group, s.E, n_epr, c_all, r.offsets,
-                           W, rank, off_base, row_base, out.dst_rank, out.dst_expert, out.dst_off, out.dst_row, out.send, out.n_dst_ranks,
-                           out.recv_offsets);
+    auto launch = [&](auto kernel, int threads) {
+        const int per_group = threads / s.k;   // whole tokens whose slots fill a workgroup
+        hipLaunchKernelGGL(kernel, dim3((s.T + per_group - 1) / per_group), dim3(threads), 0, st, r.topk_idx, r.inv_perm, s.T, s.k, per_group, s.E, n_epr,
+                           c_all, r.offsets, W, rank, off_base, row_base, out.dst_rank, out.dst_expert, out.dst_off, out.dst_row, out.send,
+                           out.n_dst_ranks, out.recv_offsets);
     };
-    if (groups > 0 && W * s.E <= kMapTable) {
-        launch(global_map_kernel<true>);
+    if (s.T > 0 && W * s.E <= kMapTable && s.T <= kMapGroups * (kMapThreads / s.k)) {
+        launch(global_map_kernel<true>, kMapThreads);
     } else {
         hipLaunchKernelGGL(global_offsets_kernel, dim3(1), dim3(kMapThreads), 0, st, c_all, r.offsets, s.E, W, rank, n_epr, off_base, row_base,
                            out.recv_offsets);
-        if (groups > 0) launch(global_map_kernel<false>);
+        if (s.T > 0) launch(global_map_kernel<false>, kRouteThreads);
     }
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }

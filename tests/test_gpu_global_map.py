@@ -61,6 +61,22 @@ def test_global_map_with_and_without_a_launch_for_the_bases(W, E, k, toks):
     run_case(W, E, k, toks, seed=W + E)
 
 
+# 512 workgroups of 1024 slots run at a time: with one token more the bases have a launch of their own, and the workgroups 256 slots.
+@pytest.mark.parametrize("E,k,T,one", [(8, 8, 65536, True), (8, 8, 65537, False), (16, 10, 52224, True), (16, 10, 52225, False), (8, 2, 0, False)])
+def test_global_map_of_more_workgroups_than_run_at_a_time(E, k, T, one):
+    import ctypes
+    import paper_2604_19241_amd as moe
+    from test_gpu_launches import launches
+    shape = moe.make_shape(T=T, d=64, E=E, k=k, I=64)
+    routing, mapping, p = moe.binding.MoERoutingC(*[4096] * 6), moe.binding.MoEGlobalMapC(*[4096] * 7), ctypes.c_void_p(4096)
+    got = launches(lambda st: moe.load_library().moe_global_map(ctypes.byref(shape), 2, 1, ctypes.byref(routing), p, ctypes.byref(mapping), p,
+                                                                ctypes.c_size_t(8 * E), st))
+    say(f"[global map] {T} tokens: {got}")
+    assert [threads for _, _, threads in got] == ([1024] if one else [1024, 256] if T else [1024])
+    if T:
+        run_case(2, E, k, [300, T], seed=T)
+
+
 def test_global_map_skewed_routing_and_statistics():
     """Zipf-biased routing; also the distinct-destination count of uniform top-8 over 8 ranks,
     which for distinct experts (16 per rank) averages 8 (1 - C(112,8)/C(128,8)) = 5.34."""
