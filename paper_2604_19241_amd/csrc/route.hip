@@ -54,24 +54,37 @@ static Chunks chunks_of(const moe_shape_t& s) {
 // RowSelect: a workgroup's 16 waves have 64 tokens at a time, so that a chunk of no more, or as many chunks as CUs, need no launch
 // ahead.  Measured, us of the whole routing, in one launch with the ranking / apart (tokens x experts x k): 64 x 128 x 8 6.5 / 7.8, 512 x 256 x 8
 // 8.5 / 9.3, 1000 x 256 x 8 9.3 / 10.0, 4099 x 64 x 6 11.7 / 12.6, 16384 x 64 x 2 12.2 / 12.6, 32768 x 256 x 2 18.0 / 19.0; but 128 x 128 x 8 9.9 / 6.8,
-// 1024 x 64 x 1 18.8 / 6.1, 1024 x 256 x 2 11.6 / 8.4, 2048 x 256 x 4 10.2 / 9.7, 8192 x 64 x 1 10.0 / 8.5.
+// 1024 x 64 x 1 18.8 / 6.1, 1024 x 256 x 2 11.6 / 8.4, 2048 x 256 x 4 10.2 / 9.7, 8192 x 64 x 1 10.0 / 8.5.  With 16 keys a lane a launch of its own
+// pays from 33 tokens a chunk on, up to 96 chunks: 256 x 129 x 5 9.95 / 9.55, 512 x 129 x 5 9.97 / 9.12, 4096 x 144 x 5 13.9 / 13.2, 256 x 160 x 7 10.4 / 9.8, but 32 tokens a
+// chunk 256 x 129 x 8 8.0 / 8.7, and 5000 x 129 x 6 13.6 / 14.3, 8192 x 144 x 7 14.1 / 14.8.
 // WaveSelect: up to 16 tokens a wave, one after the other.  Measured when it selected among any number of experts:
 // up to 16 tokens a chunk have a wave each: 1 x 64 experts, 16 tokens 3.4 / 4.8 (tokens x experts x k below);
-// one chunk: 24 x 64 x 8 5.5 / 5.8, 32 x 256 x 1 5.1 / 5.4, but 32 x 256 x 8 8.9 / 6.9, 256 x 1024 x 1 51 / 8;
+// one chunk: 24 x 64 x 8 5.5 / 5.8, 32 x 256 x 1 5.1 / 5.4, 32 x 129 x 1 4.6 / 4.8, but 32 x 256 x 8 8.9 / 6.9, 256 x 1024 x 1 51 / 8, 64 x 129 x 1 6.0 / 5.5,
+// 100 x 129 x 1 7.6 / 5.6;
 // fewer chunks than CUs: 1024 x 128 x 8 10.4 / 9.6, 8192 x 1024 x 1 100 / 17, 4096 x 64 x 8 13.1 / 13.4,
 // 4096 x 256 x 8 16.0 / 15.2; as many: 8192 x 128 x 8 14.7 / 15.7, 8192 x 512 x 8 23.7 / 20.3, 65536 x 64 x 1
 // 21.1 / 19.8, 65536 x 1024 x 1 141 / 81; more, where the chip is full either way: 65536 x 256 x 2 31.4 / 34.8,
 // 32768 x 256 x 8 39.6 / 40.9.
 constexpr int kTopkGroups = 1 << 16;
-// RowSelect or WaveSelect
-static bool rows_select(const moe_shape_t& s) { return s.E <= 128 || (s.E <= 256 && s.k <= 8); }
+// RowSelect or WaveSelect.  Of 129 to 256 experts RowSelect sorts 16 keys a lane, whatever k; WaveSelect's time is its k rounds.  One or two selected, in batches that
+// are bound by latency, are the faster by WaveSelect, as are the first few tokens with up to 7.  Us of the whole routing, RowSelect / WaveSelect: 1 x 256 x 1
+// 4.08 / 3.56, 24 x 256 x 1 4.77 / 4.20, 256 x 256 x 1 5.90 / 5.47, 128 x 129 x 2 5.85 / 5.60, 700 x 160 x 2 9.08 / 8.89, 5000 x 256 x 2 10.5 / 10.0,
+// 1 x 256 x 4 4.30 / 4.08, 2 x 129 x 3 4.24 / 3.93; but 32 x 256 x 2 4.89 / 5.38, 24 x 256 x 3 5.1 / 5.5, 6 x 256 x 8 4.7 / 5.0, 8192 x 129 x 2 11.4 / 11.7,
+// 60001 x 256 x 1 23.2 / 24.6, x 2 25.2 / 28.0.
+static bool rows_select(const moe_shape_t& s) {
+    if (s.E <= 128) return true;
+    return s.E <= 256 && s.k <= 8 && !(s.T < 8192 && s.T * (s.k - 2) < 6);
+}
 static bool topk_alone(const moe_shape_t& s, const Chunks& c) {
     if (c.lng && c.n > 1) return false;
     const int n = c.n, tokens = std::min(s.T, c.tokens);
     const long long work = (long long)tokens * s.E;
-    if (rows_select(s)) return n < (s.E <= 64 ? 128 : 256) && (tokens > kChunkThreads / 16 || work > 8192);
+    if (rows_select(s)) {
+        if (s.E > 128 && tokens > kChunkThreads / 32 && n < 96) return true;
+        return n < (s.E <= 64 ? 128 : 256) && (tokens > kChunkThreads / 16 || work > 8192);
+    }
     if (tokens <= kChunkThreads / 64 && (n == 1 || s.E <= 256)) return false;
-    if (n == 1) return work * s.k > 13000;
+    if (n == 1) return work * s.k > 13000 || (s.E <= 256 && tokens > 48);
     return n < 128 || (n < 256 && work >= 4096) || (n < 512 && work >= 16384);
 }
 
@@ -817,7 +830,7 @@ int route_launch(const moe_shape_t& s, const float* logits, const moe_routing_t&
         else if (s.E <= 128) launch_topk<RowSelect<8, KM>>(s, c, logits, out, chunk_cnt, st);
         else if constexpr (KM == 8) launch_topk<RowSelect<16, KM>>(s, c, logits, out, chunk_cnt, st);
     };
-    if (s.E <= 256 && s.k <= 8) rows_of(std::integral_constant<int, 8>{});
+    if (rows_select(s) && s.k <= 8) rows_of(std::integral_constant<int, 8>{});
     else if (s.E <= 128) rows_of(std::integral_constant<int, kMaxTopK>{});
     else if (s.E <= 256) launch_topk<WaveSelect<4>>(s, c, logits, out, chunk_cnt, st);
     else if (s.E <= 512) launch_topk<WaveSelect<8>>(s, c, logits, out, chunk_cnt, st);

@@ -275,6 +275,25 @@ def test_route_of_one_chunk(kw):
     check(cfg, rng.integers(-40, 41, (cfg.T, cfg.E)).astype(np.float32) * np.float32(0.25), "one chunk or several")
 
 
+# Of 129 to 256 experts a token has 16 lanes or, in batches bound by latency with few selected, a wave: on both sides of the line, by the kernels that are launched.
+@pytest.mark.parametrize("T,E,k,select", [
+    (1, 256, 1, "Wave"), (8191, 129, 2, "Wave"), (8192, 129, 2, "Row"), (5, 200, 3, "Wave"), (6, 200, 3, "Row"), (2, 256, 4, "Wave"), (3, 256, 4, "Row"),
+    (1, 129, 7, "Wave"), (2, 129, 7, "Row"), (1, 256, 8, "Row"), (1, 256, 9, "Wave"), (64, 129, 1, "Wave"), (100, 129, 1, "Wave"), (256, 129, 5, "Row"),
+    (4993, 144, 5, "Row"), (4992, 144, 5, "Row"), (1, 128, 1, "Row"), (1, 257, 1, "Wave"),
+])
+def test_route_by_lanes_of_a_token(T, E, k, select):
+    import paper_2604_19241_amd as moe
+    from test_gpu_launches import launches
+    shape, p = moe.make_shape(T=T, d=64, E=E, k=k, I=64), ctypes.c_void_p(4096)
+    r = moe.binding.MoERoutingC(*[4096] * 6)
+    got = launches(lambda st: moe.load_library().moe_route(ctypes.byref(shape), p, ctypes.byref(r), p,
+                                                           ctypes.c_size_t(moe.moe_workspace_bytes(shape)["route"]), st))
+    assert [n for n in ("Row", "Wave") if any(n + "Select" in name for name, _, _ in got)] == [select], got
+    cfg = moe_synth.small_config(T=T, d=64, E=E, k=k, I=64)
+    rng = np.random.default_rng(T + E)
+    check(cfg, rng.integers(-40, 41, (T, E)).astype(np.float32) * np.float32(0.25), f"{select}Select")
+
+
 def routing_us(T, E, k):
     import paper_2604_19241_amd as moe
     shape = moe.make_shape(T=T, d=64, E=E, k=k, I=64)
