@@ -553,6 +553,8 @@ struct KsGatherLoader {
         K = K_;
         k0 = KsGeom::krow(ln, 0);
         mine = 2 * (ln.l & 3);
+        tok = tok1 = 0;
+        if (K <= 0) return;   // an expert without rows has no index to read: its first one may lie past the last row
         fetch();
         tok1 = rows[min(k0 + BK + mine, K - 1)];
     }

@@ -90,6 +90,27 @@ def test_backward_idle_experts_and_skew():
     check_backward(cfg, seed=5, schedule=1, tile_rows=0, wscale=4.0)
 
 
+# The first and the last expert without rows, and all of the row table's entries taken: no index lies in front of it or behind it.
+@pytest.mark.parametrize("split", [0, 256])
+def test_backward_of_experts_without_rows_at_both_ends(split):
+    rows = [0, 0, 70, 0, 300, 1, 0]
+    cfg = moe_synth.small_config(T=sum(rows), d=320, E=len(rows), k=1, I=192)
+    inp = scaled_inputs(cfg, 5, 4.0)
+    own = np.random.default_rng(5).permutation(np.repeat(np.arange(cfg.E), rows))
+    inp["logits"] = torch.from_numpy(np.eye(cfg.E, dtype=np.float32)[own])
+    b = bits(inp, ("x", "dy", "w_gate", "w_up", "w_down"))
+    r = oracle.route(cfg.shape_dict(), inp["logits"].numpy())
+    assert r["counts"].tolist() == rows
+    say(f"[bwd] rows {rows}, split {split}")
+    g, _ = gpu_fwd_bwd(cfg, inp, 0, 0, split=split)
+    want = oracle.backward(cfg.shape_dict(), b["x"], b["dy"], b["w_gate"], b["w_up"], b["w_down"], r, round_bf16=True, acc="f32")
+    for key in KEYS:
+        assert rel_l2(to_f64(g[key]), want[key]) <= GRAD_REL_L2, key
+        check_elementwise(key, to_f64(g[key]), want[key])
+    for key in KEYS[1:]:
+        assert all((g[key][e] == 0).all() for e, n in enumerate(rows) if n == 0), key
+
+
 @pytest.mark.parametrize("tile_rows", [128, 256])
 def test_backward_long_reduction(tile_rows):
     """One expert with well over a thousand rows: the weight-gradient tiles reduce over many more
