@@ -610,8 +610,7 @@ struct KsGatherLoader {
 //                   behind a burst of matrix work instead of in front of it; 1 % on the step).
 // Stages 0 and 1 are requested together: stage 1 used to wait for stage 0 to land, and had then only that stage's matrix work to arrive
 // in, once a tile (backward pass of 8192 tokens on 128 experts of 2048 x 768 1617 -> 1591 us).  A reduction over an expert's rows has
-// `last` sub-steps in its last stage, and fewer than 4 are run behind the loop: those that hold only zeros were an eighth of the matrix work
-// at 256 rows an expert.  Both together, training
+// `last` sub-steps in its last stage: those that hold only zeros were an eighth of the matrix work at 256 rows an expert.  Both together, training
 // steps: 8192 tokens on 128 experts of 2048 x 768 2347 -> 2298 us, Zipf(1.2) 2435 -> 2389, 32 of 256 of 7168 x 2048 2960 -> 2853.
 template <int NTF, int MORE, int A_FORM, bool B_KS, class LB, class LA>
 __device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, const FragAddr& fa, Acc& acc, int last = 4) {
@@ -635,7 +634,7 @@ __device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, con
     la.fetch();
     Frags f0, f1;
     if (NTF > 0) read_frags<NTF, MORE, A_FORM, B_KS, 0>(f0, fa, 0, 0);
-    const int whole = B_KS && last < 4 ? nk - 1 : nk;
+    const int whole = B_KS ? nk - 1 : nk;   // the last stage of a reduction over rows may have fewer than 64
     for (int t = 0; t < whole; ++t) {
         const uint32_t boff = (t & 1) * kStageBytes, noff = kStageBytes - boff;
         __builtin_amdgcn_sched_barrier(0);
@@ -674,24 +673,64 @@ __device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, con
     __builtin_amdgcn_sched_barrier(0);
     if (NTF > 0) wait_frags<0, MORE>(f0);
     if constexpr (B_KS && NTF > 0) {
-        if (last < 4) {   // sub-steps without a row are left out: they would add zeros
-            const uint32_t boff = ((nk - 1) & 1) * kStageBytes;
-            mfma_step_reading<NTF, MORE, A_FORM, B_KS, 1>(f0, f1, fa, boff, boff, acc);
+        // sub-steps without a row are left out: they would add zeros
+        const uint32_t boff = ((nk - 1) & 1) * kStageBytes;
+        mfma_step_reading<NTF, MORE, A_FORM, B_KS, 1>(f0, f1, fa, boff, boff, acc);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_frags<0, MORE>(f1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (last > 1) {
+            mfma_step_reading<NTF, MORE, A_FORM, B_KS, 2>(f1, f0, fa, boff, boff, acc);
             __builtin_amdgcn_sched_barrier(0);
-            wait_frags<0, MORE>(f1);
+            wait_frags<0, MORE>(f0);
             __builtin_amdgcn_sched_barrier(0);
-            if (last > 1) {
-                mfma_step_reading<NTF, MORE, A_FORM, B_KS, 2>(f1, f0, fa, boff, boff, acc);
-                __builtin_amdgcn_sched_barrier(0);
-                wait_frags<0, MORE>(f0);
-                __builtin_amdgcn_sched_barrier(0);
-                if (last > 2) mfma_step_reading<NTF, MORE, A_FORM, B_KS, 3>(f0, f1, fa, boff, boff, acc);
+            if (last > 2) {
+                mfma_step_reading<NTF, MORE, A_FORM, B_KS, 3>(f0, f1, fa, boff, boff, acc);
                 __builtin_amdgcn_sched_barrier(0);
                 wait_frags<0, MORE>(f1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (last > 3) mfma_step_reading<NTF, MORE, A_FORM, B_KS, 3>(f1, f0, fa, boff, boff, acc);
+                __builtin_amdgcn_sched_barrier(0);
+                wait_frags<0, MORE>(f0);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
     }
+    __builtin_amdgcn_s_barrier();   // every wave has read its last fragments: the buffers may be refilled
+}
+
+// The loop for reductions of one stage that is run whole (see kShortSum).
+template <int NTF, class LB, class LA>
+__device__ __forceinline__ void mma_short(LB& lb, LA& la, char* smem, const FragAddr& fa, Acc& acc) {
+    lb.prepare();
+    la.prepare();
+    __builtin_amdgcn_sched_barrier(0);
+    lb.issue_first(smem);
+    la.issue_first(smem + kRowBytes);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    if constexpr (NTF > 0) {
+        Frags f0, f1;
+        read_frags<NTF, 0, kKs, true, 0>(f0, fa, 0, 0);
+        wait_frags<0, 0>(f0);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_step_reading<NTF, 0, kKs, true, 1>(f0, f1, fa, 0, 0, acc);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_frags<0, 0>(f1);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_step_reading<NTF, 0, kKs, true, 2>(f1, f0, fa, 0, 0, acc);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_frags<0, 0>(f0);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_step_reading<NTF, 0, kKs, true, 3>(f0, f1, fa, 0, 0, acc);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_frags<0, 0>(f1);
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_step_reading<NTF, 0, kKs, true, 3>(f1, f0, fa, 0, 0, acc);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_frags<0, 0>(f0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();   // every wave has read its last fragments: the buffers may be refilled
 }
 
@@ -806,12 +845,13 @@ __device__ __forceinline__ void row_tile_gemm(const Lane& ln, LA& la, int nk, in
     else mma_loop<1, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
 }
 
-// Reductions of up to so many rows run their one stage whole.  Such a pass is bound by memory, by the weights that the row tiles read and
-// the gradients that these tiles write, and quicker tiles crowd the reads out: the tiles alone (a launch a phase) take 2 to 7 % less without their empty
-// sub-steps, the pass takes more.  Backward pass, us, whole / without (tokens, experts of width and inner width; rows an expert): 98, 256 of 2304 x 1024 (3)
-// 1332 / 1369; 33, 64 of 2048 x 1408 (3) 503 / 523; 55, 128 of 2048 x 768 (3) 504 / 527; 133, 80 of 5120 x 1536 (5) 1516 / 1555; 277, 64 of 1280 x 896
-// (26) 230 / 240; but 8192, 128 of 2048 x 768 (512) 1553 / 1531, 1000 (62) 570 / 557, 555, 64 of 2048 x 1408 (52) 553 / 547.  Over 18 shares of 10 layers
-// the pass takes 0 to 6 % more without them (geometric mean 1 to 2.5 %) up to 10 rows, the same at 24 (-4 to +4 %) and 1 % less from 40 rows on.
+// Reductions of up to so many rows run their one stage whole (mma_short), all four fragments of a wave that has any.  Such a pass is bound by memory, by
+// the weights that the row tiles read and the gradients that these tiles write, and quicker tiles crowd the reads out: the tiles alone (a launch a
+// phase) take 2 to 7 % less without their empty sub-steps, the pass takes more.  Backward pass, us, without / whole (tokens, experts of width and inner width; rows an
+// expert): 98, 256 of 2304 x 1024 (3) 1494 / 1448; 33, 64 of 2048 x 1408 (3) 523 / 509; 55, 128 of 2048 x 768 (3) 544 / 523; 133, 80 of 5120 x 1536 (5) 1637 / 1583;
+// 277, 64 of 1280 x 896 (26) 235 / 230; but 555, 64 of 2048 x 1408 (52) 539 / 545, 8192, 128 of 2048 x 768 (512) 1531 / 1553.  Over 18 shares of 10 layers the
+// pass takes 1 to 2 % less with it up to 24 rows an expert (from 2 % more to 5 % less), and the same from 32 on, where few of the experts have no more than
+// 32.  By the loop above, all four of its sub-steps, it took 1 % more than by mma_short; with a wave's own number of fragments 2 % more.
 constexpr int kShortSum = 32;
 // A tile of a weight-gradient GEMM: both operands have k as their memory rows.
 template <class LB, class LA>
@@ -819,7 +859,12 @@ __device__ __forceinline__ void weight_tile_gemm(LB& lb, LA& la, int nk, int row
     zero_acc(acc, false);
     if (nk <= 0) return;   // empty reduction (an expert without rows): the tile is all zeros
     const int ntf = active_row_frags(rows);
-    const int last = rfl(lb.K <= kShortSum ? 4 : ((lb.K - 1) % BK) / 16 + 1);   // sub-steps of the last stage: the rest are zeros
+    if (lb.K <= kShortSum) {
+        if (ntf > 0) mma_short<4>(lb, la, smem, fa, acc);
+        else mma_short<0>(lb, la, smem, fa, acc);
+        return;
+    }
+    const int last = rfl(((lb.K - 1) % BK) / 16 + 1);   // sub-steps of the last stage: the rest are zeros
     if (ntf == 4) mma_loop<4, 0, kKs, true>(lb, la, nk, smem, fa, acc, last);
     else if (ntf == 3) mma_loop<3, 0, kKs, true>(lb, la, nk, smem, fa, acc, last);
     else if (ntf == 2) mma_loop<2, 0, kKs, true>(lb, la, nk, smem, fa, acc, last);
