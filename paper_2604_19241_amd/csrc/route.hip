@@ -83,6 +83,7 @@ static bool topk_alone(const moe_shape_t& s, const Chunks& c) {
         if (s.E > 128 && tokens > kChunkThreads / 32 && n < 96) return true;
         return n < (s.E <= 64 ? 128 : 256) && (tokens > kChunkThreads / 16 || work > 8192);
     }
+    if (c.lng) return true;   // (more than 320 slots of more than 128 experts: past both lines below)
     if (tokens <= kChunkThreads / 64 && (n == 1 || s.E <= 256)) return false;
     if (n == 1) return work * s.k > 13000 || (s.E <= 256 && tokens > 48);
     return n < 128 || (n < 256 && work >= 4096) || (n < 512 && work >= 16384);
@@ -798,8 +799,9 @@ static void launch_rank(const moe_shape_t& s, const Chunks& c, const float* logi
     };
     if constexpr (SEL::kTokens > 0)
         if (c.lng && c.n > 1) return launch(topk_rank_kernel<SEL, false, kLongPieces>);
-    if (c.lng) launch(topk_rank_kernel<SEL, true, kLongPieces>);
-    else if (c.n == 1) launch(topk_rank_kernel<SEL, true, kPieces>);
+    if constexpr (SEL::kTokens != 1)   // (by WaveSelect the top-k of one long chunk is apart)
+        if (c.lng) return launch(topk_rank_kernel<SEL, true, kLongPieces>);
+    if (c.n == 1) launch(topk_rank_kernel<SEL, true, kPieces>);
     else launch(topk_rank_kernel<SEL, false, kPieces>);
 }
 

@@ -279,7 +279,7 @@ def test_route_of_one_chunk(kw):
 @pytest.mark.parametrize("T,E,k,select", [
     (1, 256, 1, "Wave"), (8191, 129, 2, "Wave"), (8192, 129, 2, "Row"), (5, 200, 3, "Wave"), (6, 200, 3, "Row"), (2, 256, 4, "Wave"), (3, 256, 4, "Row"),
     (1, 129, 7, "Wave"), (2, 129, 7, "Row"), (1, 256, 8, "Row"), (1, 256, 9, "Wave"), (64, 129, 1, "Wave"), (100, 129, 1, "Wave"), (256, 129, 5, "Row"),
-    (4993, 144, 5, "Row"), (4992, 144, 5, "Row"), (1, 128, 1, "Row"), (1, 257, 1, "Wave"),
+    (4993, 144, 5, "Row"), (4992, 144, 5, "Row"), (1, 128, 1, "Row"), (1, 257, 1, "Wave"), (320, 257, 1, "Wave"), (321, 257, 1, "Wave"), (321, 129, 1, "Wave"), (21, 129, 16, "Wave"), (64, 1024, 16, "Wave"),
 ])
 def test_route_by_lanes_of_a_token(T, E, k, select):
     import paper_2604_19241_amd as moe
