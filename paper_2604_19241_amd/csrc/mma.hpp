@@ -333,9 +333,18 @@ __device__ __forceinline__ void dma16s(glb_ptr_t base, uint32_t off, char* dst) 
     asm volatile("" : "+s"(base), "+v"(off));   // scalar base + lane offset, not one 64-bit lane address
     __builtin_amdgcn_global_load_lds((glb_void_t*)(base + off), (lds_void_t*)dst, 16, 0, 0);
 }
+// What mma_loop asks of a loader beside issue(), for one that knows its addresses without memory (see KsGatherLoader).
+template <class L>
+struct PlainLoader {
+    __device__ __forceinline__ void prepare() {}
+    __device__ __forceinline__ void prepare_two() {}
+    __device__ __forceinline__ void fetch() {}
+    __device__ __forceinline__ void issue_first(char* dst) { static_cast<L*>(this)->issue(dst); }
+    __device__ __forceinline__ void issue_second(char* dst) { static_cast<L*>(this)->issue(dst); }
+};
 // Rows whose k runs on (weights read transposed): every stage is 128 bytes further along each row, and after `left` more stages
 // in a second matrix of the same layout (W_gate then W_up along k), `delta` bytes on.
-struct KcLoader {
+struct KcLoader : PlainLoader<KcLoader> {
     glb_ptr_t p[4];     // first k of the instruction's eight rows in the stage to come (uniform)
     uint32_t off[2];
     long long delta;
@@ -350,11 +359,6 @@ struct KcLoader {
 #pragma unroll
         for (int i = 0; i < 2; ++i) off[i] = (ln.l >> 3) * ld_bytes + KcGeom::chunk(ln, i) * 16;
     }
-    __device__ __forceinline__ void prepare() {}
-    __device__ __forceinline__ void prepare_two() {}
-    __device__ __forceinline__ void fetch() {}
-    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
-    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + wave_block_off();
         const long long jump = left == 0 ? delta : 0;
@@ -368,7 +372,7 @@ struct KcLoader {
     }
 };
 // The row operand: up to 288 rows, row_of(r) = address of row r's first k (r below `rows`; rows past the last alias it).
-struct RowLoader {
+struct RowLoader : PlainLoader<RowLoader> {
     const char* p[4];
     const char* pm;   // the fifth instruction's
     int n;            // blocks of this wave that hold rows of the tile (wave-uniform); bit 3: the fifth one does too
@@ -382,11 +386,6 @@ struct RowLoader {
         pm = p[0];
         if (n & 8) pm = row_of(min(KcGeom::more_row(ln), rows - 1)) + KcGeom::more_chunk(ln) * 16;
     }
-    __device__ __forceinline__ void prepare() {}
-    __device__ __forceinline__ void prepare_two() {}
-    __device__ __forceinline__ void fetch() {}
-    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
-    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         const int off = wave_block_off();
         char* d = dst + off;
@@ -434,7 +433,7 @@ struct KsGeom {
     static __device__ __forceinline__ int chunk(const Lane& ln, int i) { return ln.l31 ^ ((krow(ln, i) & 3) << 2); }
 };
 // Dense matrix [K, n], K a multiple of 64.
-struct KsLoader {
+struct KsLoader : PlainLoader<KsLoader> {
     glb_ptr_t p[4];     // first k row of the instruction in the stage to come (uniform)
     uint32_t off[2];
     uint32_t step;      // 64 memory rows
@@ -447,11 +446,6 @@ struct KsLoader {
 #pragma unroll
         for (int i = 0; i < 2; ++i) off[i] = ln.hf * ld_bytes + min(first + KsGeom::chunk(ln, i) * 8, n - 8) * 2;
     }
-    __device__ __forceinline__ void prepare() {}
-    __device__ __forceinline__ void prepare_two() {}
-    __device__ __forceinline__ void fetch() {}
-    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
-    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + wave_block_off();
 #pragma unroll
@@ -464,7 +458,7 @@ struct KsLoader {
 // Two such matrices, 128 columns of each (GEMM1: gate, up): two images [64 k][256 B], one behind the other, the chunk c of k row
 // k at c ^ ((k & 3) << 2), in the second with bit 1 turned over as well.  Instructions 0, 1 of a wave move 4 k rows
 // each of the first, 2, 3 of the second.
-struct KsPairLoader {
+struct KsPairLoader : PlainLoader<KsPairLoader> {
     glb_ptr_t p[2];     // this wave's first k row in the stage to come (uniform)
     uint32_t off[2];
     uint32_t ld;
@@ -476,11 +470,6 @@ struct KsPairLoader {
 #pragma unroll
         for (int i = 0; i < 2; ++i) off[i] = e * ld + min(first + (c ^ (2 * i)) * 8, n - 8) * 2;
     }
-    __device__ __forceinline__ void prepare() {}
-    __device__ __forceinline__ void prepare_two() {}
-    __device__ __forceinline__ void fetch() {}
-    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
-    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + (wave_block_off() >> 1);
 #pragma unroll
@@ -499,17 +488,12 @@ __device__ __forceinline__ void lds_zero16(char* dst) {
     asm volatile("ds_write_b128 %0, %1" : : "v"(ad), "v"(zero4()) : "memory");
 }
 
-struct KsTailLoader {
+struct KsTailLoader : PlainLoader<KsTailLoader> {
     __device__ __forceinline__ bool full() const { return true; }   // 4 requests a stage, but the last
     const char* p[2];
     long long ld_bytes;   // one memory row (wave-uniform)
     int k0;               // reduction index of instruction 0's k row in the stage to come
     int K;
-    __device__ __forceinline__ void prepare() {}
-    __device__ __forceinline__ void prepare_two() {}
-    __device__ __forceinline__ void fetch() {}
-    __device__ __forceinline__ void issue_first(char* dst) { issue(dst); }
-    __device__ __forceinline__ void issue_second(char* dst) { issue(dst); }
     __device__ __forceinline__ void issue(char* dst) {
         char* d = dst + wave_block_off();
 #pragma unroll
