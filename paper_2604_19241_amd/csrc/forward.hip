@@ -493,7 +493,8 @@ static int fwd_launch_tiles(FwdParams& p, const moe_opts_t& opts, hipStream_t st
     // Otherwise the counts decide, which only the device has.  But few or small experts never spare the queue enough
     // beside one with more rows, and there is one where the rows are more than kThinRows an expert and all experts are
     // here, or hardly ever none in a part of them with four times as many (the queue takes any counts).  Their launch
-    // without work took 2 us (256 tokens on 8 experts of 512 x 1024 48.3 us, without it 46.3 us).
+    // without work took 2 us (256 tokens on 8 experts of 512 x 1024 48.3 us, without it 46.3 us).  (Where the rule might send experts with medium
+    // rows ahead, in layers of more than 128 experts, thin_may_pay is false only with one width at 64: such a layer keeps the queue for them.)
     const long long enough = (long long)kThinRows * p.s.E * (p.s.e_count == p.s.E ? 1 : 4);
     const bool none_thin = !all_thin && (long long)p.s.T * p.s.k > enough && !thin_may_pay(thin_rule(p.s, kThinRows), p.s);
     p.rule = thin_rule(p.s, all_thin ? INT_MAX : none_thin ? 0 : kThinRows);

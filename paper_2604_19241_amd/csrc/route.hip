@@ -57,14 +57,12 @@ static Chunks chunks_of(const moe_shape_t& s) {
 // 1024 x 64 x 1 18.8 / 6.1, 1024 x 256 x 2 11.6 / 8.4, 2048 x 256 x 4 10.2 / 9.7, 8192 x 64 x 1 10.0 / 8.5.  With 16 keys a lane a launch of its own
 // pays from 33 tokens a chunk on, up to 96 chunks: 256 x 129 x 5 9.95 / 9.55, 512 x 129 x 5 9.97 / 9.12, 4096 x 144 x 5 13.9 / 13.2, 256 x 160 x 7 10.4 / 9.8, but 32 tokens a
 // chunk 256 x 129 x 8 8.0 / 8.7, and 5000 x 129 x 6 13.6 / 14.3, 8192 x 144 x 7 14.1 / 14.8.
-// WaveSelect: up to 16 tokens a wave, one after the other.  Measured when it selected among any number of experts:
-// up to 16 tokens a chunk have a wave each: 1 x 64 experts, 16 tokens 3.4 / 4.8 (tokens x experts x k below);
-// one chunk: 24 x 64 x 8 5.5 / 5.8, 32 x 256 x 1 5.1 / 5.4, 32 x 129 x 1 4.6 / 4.8, but 32 x 256 x 8 8.9 / 6.9, 256 x 1024 x 1 51 / 8, 64 x 129 x 1 6.0 / 5.5,
-// 100 x 129 x 1 7.6 / 5.6;
-// fewer chunks than CUs: 1024 x 128 x 8 10.4 / 9.6, 8192 x 1024 x 1 100 / 17, 4096 x 64 x 8 13.1 / 13.4,
-// 4096 x 256 x 8 16.0 / 15.2; as many: 8192 x 128 x 8 14.7 / 15.7, 8192 x 512 x 8 23.7 / 20.3, 65536 x 64 x 1
-// 21.1 / 19.8, 65536 x 1024 x 1 141 / 81; more, where the chip is full either way: 65536 x 256 x 2 31.4 / 34.8,
-// 32768 x 256 x 8 39.6 / 40.9.
+// WaveSelect: up to 16 tokens a wave, one after the other.  Up to 16 tokens a chunk have a wave each: 16 x 256 x 1 4.0 / 5.1, 16 x 512 x 4 5.7 / 6.4 (but from
+// eight selected of 512 on it is the other way round: 16 x 512 x 16 10.9 / 9.5, 16 x 1024 x 8 11.0 / 9.3);
+// one chunk: 24 x 256 x 1 4.2 / 5.0, 32 x 129 x 2 5.0 / 5.4, 24 x 512 x 1 4.9 / 5.6, but 32 x 512 x 4 8.0 / 6.3, 64 x 129 x 1 6.0 / 5.4, 100 x 129 x 1 7.6 / 5.6,
+// 200 x 1024 x 1 26.6 / 6.5; fewer chunks than CUs: 2000 x 256 x 2 13.8 / 8.5, 1000 x 512 x 8 14.9 / 11.2, 8192 x 512 x 4 20.3 / 16.8; as many: 4096 x 129 x 16
+// 15.6 / 17.1, 8192 x 512 x 8 19.9 / 19.9, 65536 x 1024 x 1 51.8 / 50.5; more, where the chip is full either way: 16384 x 257 x 8 26.4 / 28.1, 65536 x 257 x 2 32.6 / 36.0,
+// but 8192 x 256 x 9 19.7 / 17.9, 8192 x 512 x 10 26.2 / 22.7 (283 and 316 chunks, which stay in one launch).
 constexpr int kTopkGroups = 1 << 16;
 // RowSelect or WaveSelect.  Of 129 to 256 experts RowSelect sorts 16 keys a lane, whatever k; WaveSelect's time is its k rounds.  One or two selected, in batches that
 // are bound by latency, are the faster by WaveSelect, as are the first few tokens with up to 7.  Us of the whole routing, RowSelect / WaveSelect: 1 x 256 x 1
@@ -398,7 +396,8 @@ struct NoSelect {
 // ONE: the batch is a single chunk (a generation step): the ranks are complete, and the same
 // workgroup scans the counts and writes the rows.
 // PIECES: 64-slot pieces of a chunk (a wave's counts of an expert in a piece are at most 64).
-// Two workgroups of 16 waves share a CU: 8 waves a SIMD, up to 64 registers a lane.
+// Two workgroups of 16 waves share a CU: 8 waves a SIMD, up to 64 registers a lane, for which RowSelect<16, 8> puts two away in
+// memory in two of its four forms (with one workgroup a CU 60001 tokens of 256 experts, 8 selected, took 39.6 us for 33.9).
 template <class SEL, bool ONE, int PIECES>
 __global__ void __launch_bounds__(kChunkThreads) __attribute__((amdgpu_waves_per_eu(8)))
 topk_rank_kernel(const float* __restrict__ logits, int T, int E, int k, int per_chunk, int e_start, int e_count,
