@@ -132,6 +132,31 @@ def test_two_blocks_of_rows(rows, d, I):
         assert rel_l2(to_f64(got[0]["o"][:len(own)][at]), o.double().cpu().numpy()) <= REL_L2
 
 
+# The same for some of the experts, several of them a token and no stash: 150 of 200 are here, from the 18th on.
+def test_two_blocks_of_rows_in_a_share():
+    import paper_2604_19241_amd as moe
+    T, d, I, E, k, e_start, ec = 2667, 192, 128, 200, 3, 17, 150
+    dev = {key: v.cuda() for key, v in scaled_inputs(moe_synth.small_config(T=T + 70, d=d, E=E, k=k, I=I, e_start=e_start, e_count=ec), 23, 4.0).items()}
+    logits = torch.rand((T + 70, E), generator=torch.Generator().manual_seed(1)).cuda()
+    logits[T:, e_start + 5] = 2.0   # 70 more tokens for one expert: past 64 rows, with which all are on the work queue
+    got = {}
+    for n in (T, T + 70):
+        shape = moe.make_shape(T=n, d=d, E=E, k=k, I=I, e_start=e_start, e_count=ec)
+        routing = moe.moe_route(shape, logits[:n])
+        most, medium = int(routing.counts.max()), int((routing.counts > 32).sum())
+        say(f"[two blocks] share, {n} tokens, up to {most} rows, {medium} experts with more than 32")
+        assert (most <= 64) == (n == T) and medium > 100
+        saved = moe.alloc_saved(shape, "cuda")
+        for stash in (None, saved):
+            ws = torch.empty(moe.moe_workspace_bytes(shape)["fwd"], dtype=torch.uint8, device="cuda")
+            y = moe.moe_fused_forward(shape, dev["x"][:n], dev["w_gate"], dev["w_up"], dev["w_down"], routing, saved=stash, ws=ws)
+            assert moe.moe_device_status(ws) == 0
+            assert (int(ws.view(torch.int32)[1]) > 0) == (n > T)   # row tiles of the queue
+            got[n, stash is None] = y
+    assert torch.equal(got[T, True], got[T, False])
+    assert torch.equal(got[T, False], got[T + 70, False][:T]) and torch.equal(got[T + 70, True], got[T + 70, False])
+
+
 def us_of_one_row_each(experts, d, I, E=16):
     """The layer for one token on each of so many experts, other ones from call to call."""
     import paper_2604_19241_amd as moe
