@@ -407,7 +407,7 @@ __device__ __forceinline__ void dwd_task(const BwdParams& p, int e, int idx, int
     lb.K = cnt;
     la.init(ln, p.dy, (long long)d * 2, p.row_tok + r0, cnt);
     Acc acc;
-    weight_tile_gemm(lb, la, (cnt + BK - 1) / BK, min(BMAX, I - m0), smem, fa, acc);
+    weight_tile_gemm<!ACC>(lb, la, (cnt + BK - 1) / BK, min(BMAX, I - m0), smem, fa, acc);
     after_mainloop();
     if (SPLIT && !finish_part(p, e, p.mt_dwgu * p.nt_dwgu + mt * p.nt_dwd + nt, wgrad_part(idx), wgrad_parts(idx), acc, s_flag)) return;
     if (ACC) {
@@ -460,7 +460,7 @@ __device__ __forceinline__ void dwgu_task(const BwdParams& p, int e, int idx, in
     la.K = cnt;
     lb.init(ln, p.x, (long long)d * 2, p.row_tok + r0, cnt);
     Acc acc;
-    weight_tile_gemm(lb, la, (cnt + BK - 1) / BK, min(BMAX, d - m0), smem, fa, acc);
+    weight_tile_gemm<!ACC>(lb, la, (cnt + BK - 1) / BK, min(BMAX, d - m0), smem, fa, acc);
     after_mainloop();
     if (SPLIT && !finish_part(p, e, mt * p.nt_dwgu + nt, wgrad_part(idx), wgrad_parts(idx), acc, s_flag)) return;
     if (ACC) {

@@ -683,8 +683,9 @@ __device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, con
     __builtin_amdgcn_s_barrier();   // every wave has read its last fragments: the buffers may be refilled
 }
 
-// The loop for reductions of one stage that is run whole (see kShortSum).
-template <int NTF, class LB, class LA>
+// The loop for reductions of one stage that is run whole, by a wave whose four fragments hold rows (see kShortSum).  The workgroup's other waves run mma_loop:
+// as many barriers for one stage, two.
+template <class LB, class LA>
 __device__ __forceinline__ void mma_short(LB& lb, LA& la, char* smem, const FragAddr& fa, Acc& acc) {
     lb.prepare();
     la.prepare();
@@ -693,27 +694,25 @@ __device__ __forceinline__ void mma_short(LB& lb, LA& la, char* smem, const Frag
     la.issue_first(smem + kRowBytes);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    if constexpr (NTF > 0) {
-        Frags f0, f1;
-        read_frags<NTF, 0, kKs, true, 0>(f0, fa, 0, 0);
-        wait_frags<0, 0>(f0);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_step_reading<NTF, 0, kKs, true, 1>(f0, f1, fa, 0, 0, acc);
-        __builtin_amdgcn_sched_barrier(0);
-        wait_frags<0, 0>(f1);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_step_reading<NTF, 0, kKs, true, 2>(f1, f0, fa, 0, 0, acc);
-        __builtin_amdgcn_sched_barrier(0);
-        wait_frags<0, 0>(f0);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_step_reading<NTF, 0, kKs, true, 3>(f0, f1, fa, 0, 0, acc);
-        __builtin_amdgcn_sched_barrier(0);
-        wait_frags<0, 0>(f1);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_step_reading<NTF, 0, kKs, true, 3>(f1, f0, fa, 0, 0, acc);
-        __builtin_amdgcn_sched_barrier(0);
-        wait_frags<0, 0>(f0);
-    }
+    Frags f0, f1;
+    read_frags<4, 0, kKs, true, 0>(f0, fa, 0, 0);
+    wait_frags<0, 0>(f0);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_step_reading<4, 0, kKs, true, 1>(f0, f1, fa, 0, 0, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_frags<0, 0>(f1);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_step_reading<4, 0, kKs, true, 2>(f1, f0, fa, 0, 0, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_frags<0, 0>(f0);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_step_reading<4, 0, kKs, true, 3>(f0, f1, fa, 0, 0, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_frags<0, 0>(f1);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_step_reading<4, 0, kKs, true, 3>(f1, f0, fa, 0, 0, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_frags<0, 0>(f0);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();   // every wave has read its last fragments: the buffers may be refilled
 }
@@ -829,23 +828,22 @@ __device__ __forceinline__ void row_tile_gemm(const Lane& ln, LA& la, int nk, in
     else mma_loop<1, 0, A_FORM, false>(lb, la, nk, smem, fa, acc);
 }
 
-// Reductions of up to so many rows run their one stage whole (mma_short), all four fragments of a wave that has any.  Such a pass is bound by memory, by
+// Reductions of up to so many rows run their one stage whole (mma_short) where the gradients are written, not added to.  Such a pass is bound by memory, by
 // the weights that the row tiles read and the gradients that these tiles write, and quicker tiles crowd the reads out: the tiles alone (a launch a
 // phase) take 2 to 7 % less without their empty sub-steps, the pass takes more.  Backward pass, us, without / whole (tokens, experts of width and inner width; rows an
-// expert): 98, 256 of 2304 x 1024 (3) 1494 / 1448; 33, 64 of 2048 x 1408 (3) 523 / 509; 55, 128 of 2048 x 768 (3) 544 / 523; 133, 80 of 5120 x 1536 (5) 1637 / 1583;
-// 277, 64 of 1280 x 896 (26) 235 / 230; but 555, 64 of 2048 x 1408 (52) 539 / 545, 8192, 128 of 2048 x 768 (512) 1531 / 1553.  Over 18 shares of 10 layers the
-// pass takes 1 to 2 % less with it up to 24 rows an expert (from 2 % more to 5 % less), and the same from 32 on, where few of the experts have no more than
-// 32.  By the loop above, all four of its sub-steps, it took 1 % more than by mma_short; with a wave's own number of fragments 2 % more.
+// expert): 33, 128 of 2048 x 768 (2) 535 / 525; 64, 256 of 2304 x 1024 (2) 1385 / 1358; 102, 512 of 2048 x 512 (2) 1269 / 1245; 33, 64 of 2048 x 1408 (3) 519 / 509;
+// 107, 64 of 1280 x 896 (10) 235 / 231; but 128, 128 of 1024 x 384 (6) 157 / 159.  Over 18 shares of 10 layers the pass takes 1.5 % less with it from 2 to 10 rows
+// an expert (from 1.5 % more to 2 % less), 1 % less at 24 and the same from 32 on.  With gradients added to fp32 buffers it takes 0.5 % more with it.
+// For other waves, or by the loop above with all of its sub-steps, it costs long reductions 0.3 %: the more code, the slower they are.
 constexpr int kShortSum = 32;
-// A tile of a weight-gradient GEMM: both operands have k as their memory rows.
-template <class LB, class LA>
+// A tile of a weight-gradient GEMM: both operands have k as their memory rows.  SHORT: see kShortSum.
+template <bool SHORT, class LB, class LA>
 __device__ __forceinline__ void weight_tile_gemm(LB& lb, LA& la, int nk, int rows, char* smem, const FragAddr& fa, Acc& acc) {
     zero_acc(acc, false);
     if (nk <= 0) return;   // empty reduction (an expert without rows): the tile is all zeros
     const int ntf = active_row_frags(rows);
-    if (lb.K <= kShortSum) {
-        if (ntf > 0) mma_short<4>(lb, la, smem, fa, acc);
-        else mma_short<0>(lb, la, smem, fa, acc);
+    if (SHORT && lb.K <= kShortSum && ntf == 4) {
+        mma_short(lb, la, smem, fa, acc);
         return;
     }
     const int last = rfl(((lb.K - 1) % BK) / 16 + 1);   // sub-steps of the last stage: the rest are zeros
