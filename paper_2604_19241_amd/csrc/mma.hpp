@@ -511,7 +511,7 @@ struct KsTailLoader : PlainLoader<KsTailLoader> {
 // it, complete by the barrier in between.  init() is called once per tile, after
 // coloff[] is filled.
 // A wave moves 8 rows a stage, and each half of it 4 of them: lane l loads the index for instruction l % 4, and prepare()
-// hands it to the four lanes of its quad (a load for each instruction was four times as many).
+// hands it to the four lanes of its quad (a load for each instruction was four times as many, and 0.2 to 0.4 % slower).
 // prepare() turns the fetched indices into the four source addresses, and the main loop calls
 // it for both loaders before either requests anything: while a DMA is pending the compiler puts
 // a full vmcnt(0) in front of every use of a register that an ordinary load filled (it cannot
@@ -593,9 +593,10 @@ struct KsGatherLoader {
 //                   before issue blocks, which is what one stage has: the second half goes out
 //                   behind a burst of matrix work instead of in front of it; 1 % on the step).
 // Stages 0 and 1 are requested together: stage 1 used to wait for stage 0 to land, and had then only that stage's matrix work to arrive
-// in, once a tile (backward pass of 8192 tokens on 128 experts of 2048 x 768 1617 -> 1591 us).  A reduction over an expert's rows has
-// `last` sub-steps in its last stage: those that hold only zeros were an eighth of the matrix work at 256 rows an expert.  Both together, training
-// steps: 8192 tokens on 128 experts of 2048 x 768 2347 -> 2298 us, Zipf(1.2) 2435 -> 2389, 32 of 256 of 7168 x 2048 2960 -> 2853.
+// in, once a tile.  A reduction over an expert's rows has `last` sub-steps in its last stage: those that hold only zeros were an eighth of the matrix
+// work at 256 rows an expert.  Backward pass, us, before / with both stages together / without the empty sub-steps too: 8192 tokens on 128 experts of 2048 x 768
+// 1570 / 1552 / 1531, 1000 585 / 570 / 557, 4099 on 64 of 2048 x 1408 1165 / 1152 / 1120.  Whole training steps, before / both: 8192 on 128 of 2048 x 768 2288 / 2251,
+// 8001 with Zipf(1.2) routing 2401 / 2376, 8192 on 32 of 256 of 7168 x 2048 2910 / 2825, 60001 on 32 of 256 of 2304 x 1024, added to fp32 gradients, 3181 / 3144.
 template <int NTF, int MORE, int A_FORM, bool B_KS, class LB, class LA>
 __device__ __forceinline__ void mma_loop(LB& lb, LA& la, int nk, char* smem, const FragAddr& fa, Acc& acc, int last = 4) {
     int full = rfl(nk > (B_KS ? 2 : 1) && lb.full());

@@ -109,6 +109,9 @@ struct ThinRule {
     // 76 + 128 557 / 596, 0 + 256 707 / 770; 160 of 5120 x 1536, 144 + 16 1348 / 1300, 46 + 80 1067 / 1150; 256 of 7168 x 2048, 192 + 64 3834 / 3665, 18 + 230
     // 3876 / 4308.  Of 462 batches of 18 layers the estimate sends 322 here, half of them 4 % faster or more, 6 more than 1 % slower (at most 4 %); of the others 17
     // would be more than 1 % faster (at most 7 %).  (At 5.0 and 5.5 TB/s and no time an expert it sent 18 here that were slower, by up to 7 %.)
+    // Beside an expert with more than medium rows the queue keeps them all: 90 batches of five layers with 1 to 32 such experts were 2 % slower
+    // with the medium ones here (512 of 2048 x 512, one with 300 rows, 154 medium 636 / 660; 256 of 2304 x 1024, 8 with 200, 77 medium 675 / 731; 160 of 1024 x 384,
+    // 2 with 100, 48 medium 111 / 118; the best one 139 on the queue, 132 here).
     // Fewer experts would often gain as well (512 tokens on 128 of 1024 x 384, 24 rows each, 96 / 71; 500 on 128 of 2048 x 768, 31 rows,
     // 247 / 232; 250 on 64 of 2048 x 1408, 23 rows, 229 / 202): they keep the choice that is tested for them.
     __device__ __forceinline__ int limit(int few, int medium, int more, int rows) const {
