@@ -98,7 +98,8 @@ def measured_traffic(cfg_name, kernels):
         return None
     for line in lines:
         if "traffic_bytes_per_launch=" in line:
-            found[line.split()[0]] = float(line.split("traffic_bytes_per_launch=")[1].split()[0])
+            # (a workload launches one form of a kernel)
+            found[line.split()[0].split("<")[0]] = float(line.split("traffic_bytes_per_launch=")[1].split()[0])
     return sum(found.get(k, 0.0) for k in kernels) if kernels[-1] in found else None
 
 
