@@ -109,8 +109,8 @@ struct ThinRule {
     // 76 + 128 557 / 596, 0 + 256 707 / 770; 160 of 5120 x 1536, 144 + 16 1348 / 1300, 46 + 80 1067 / 1150; 256 of 7168 x 2048, 192 + 64 3834 / 3665, 18 + 230
     // 3876 / 4308.  Of 462 batches of 18 layers the estimate sends 322 here, half of them 4 % faster or more, 6 more than 1 % slower (at most 4 %); of the others 17
     // would be more than 1 % faster (at most 7 %).  (At 5.0 and 5.5 TB/s and no time an expert it sent 18 here that were slower, by up to 7 %.)
-    // Beside an expert with more than medium rows the queue keeps them all: 90 batches of five layers with 1 to 32 such experts were 2 % slower
-    // with the medium ones here (512 of 2048 x 512, one with 300 rows, 154 medium 636 / 660; 256 of 2304 x 1024, 8 with 200, 77 medium 675 / 731; 160 of 1024 x 384,
+    // Beside an expert with more than medium rows the queue keeps them all: of 90 batches of five layers with 1 to 32 such experts 59 were more than 1 % slower
+    // with the medium ones here, 5 faster, the middle one 2 % slower (512 of 2048 x 512, one with 300 rows, 154 medium 636 / 660; 256 of 2304 x 1024, 8 with 200, 77 medium 675 / 731; 160 of 1024 x 384,
     // 2 with 100, 48 medium 111 / 118; the best one 139 on the queue, 132 here).
     // Fewer experts would often gain as well (512 tokens on 128 of 1024 x 384, 24 rows each, 96 / 71; 500 on 128 of 2048 x 768, 31 rows,
     // 247 / 232; 250 on 64 of 2048 x 1408, 23 rows, 229 / 202): they keep the choice that is tested for them.
@@ -391,7 +391,7 @@ __device__ __forceinline__ void thin_tasks(const ThinParams& p, int first, int c
 // the tasks of one expert share an XCD (its rows are then fetched by one L2); what is left over
 // is spread task by task.
 // kThinAll: every expert is of this path, whatever its rows, and the choices above are left out (one token on 128 experts of 2048 x 768, 8 selected,
-// 31.8 -> 31.2 us).  kThinTwo: experts may have two blocks of rows here.  The code for these costs 0.2 to 0.7 us a launch, 2 % of a
+// 31.5 -> 31.0 us).  kThinTwo: experts may have two blocks of rows here.  The code for these costs 0.2 to 0.7 us a launch, 2 % of a
 // small share's layer, where the rule never sends them here (300 tokens on 16 of 128 of 1024 x 384 20.3 us, with it 21.1; 128 on 16 of 128 of 2048 x 768
 // 36.8 and 37.9; 300 on 8 of 64 of 1280 x 896 52.9 and 53.6).
 enum ThinForm { kThinAll, kThinFew, kThinTwo };
