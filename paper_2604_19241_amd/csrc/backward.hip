@@ -326,6 +326,11 @@ __device__ __forceinline__ void accumulate8(float* q, const f32x16_t& a, int vg)
 // counter is advanced, and the workgroup that finds all other parts already counted adds the
 // `parts` partial tiles in the order of the part index, starting from zero: the sum does not
 // depend on which workgroup adds, nor on the order in which the parts were computed.
+// The adding workgroup is a serial chain at the end of its tile, often of the pass: a part is requested in two halves of 32 loads a lane
+// (64 registers beside the 128 of the sum).  Left to the compiler every load was awaited with the next one or two, some 30 round trips to memory a
+// part.  Backward pass, us, before / so (tokens, experts of width and inner width, rows a part): 2378, 32 of 320 x 256, 8 selected, Zipf(0.6), 256 261 / 180;
+// 4096, 8 of 512 x 1024, 512 190 / 166; 8192, 128 of 2048 x 768, 512 2343 / 2195; 8192, 8 of 256 of 7168 x 2048, 256 1286 / 1168; 16384, 512 of 2048 x 512, 256
+// 7740 / 6320; 60001, 32 of 256 of 2304 x 1024, 1024, added to fp32 gradients 2785 / 2638; 16384, 16 of 128 of 1024 x 384, Zipf(1.2), 256 2035 / 964.
 // Returns whether acc now holds the complete sum (the caller then stores the tile).
 __device__ __forceinline__ bool finish_part(const BwdParams& p, int e, int tile, int part, int parts,
                                             Acc& acc, int* s_flag) {
@@ -367,18 +372,29 @@ __device__ __forceinline__ bool finish_part(const BwdParams& p, int e, int tile,
     for (int j = 0; j < parts; ++j) {
         const char* src = slots + (size_t)j * kPartialTileBytes + lane_off;
 #pragma unroll
-        for (int tf = 0; tf < 4; ++tf)
+        for (int half = 0; half < 2; ++half) {
+            f32x2_t v[2][2][4][2];
 #pragma unroll
-            for (int af = 0; af < 2; ++af)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const char* blk = src + ((tf * 2 + af) * 4 + q) * 1024;
-                    const f32x2_t lo = *(const f32x2_t*)blk, hi = *(const f32x2_t*)(blk + 512);
-                    acc.a[tf][af][4 * q] += lo[0];
-                    acc.a[tf][af][4 * q + 1] += lo[1];
-                    acc.a[tf][af][4 * q + 2] += hi[0];
-                    acc.a[tf][af][4 * q + 3] += hi[1];
-                }
+                for (int af = 0; af < 2; ++af)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const char* blk = src + (((2 * half + t) * 2 + af) * 4 + q) * 1024;
+                        v[t][af][q][0] = *(const f32x2_t*)blk;
+                        v[t][af][q][1] = *(const f32x2_t*)(blk + 512);
+                    }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int af = 0; af < 2; ++af)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc.a[2 * half + t][af][4 * q + i] += v[t][af][q][i >> 1][i & 1];
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     return true;
 }

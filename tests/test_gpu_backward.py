@@ -334,6 +334,41 @@ def test_backward_split_weight_gradient_reduction(split):
         assert torch.equal(acc[key].to(torch.bfloat16), ref[key]), key
 
 
+@pytest.mark.parametrize("rows,split,d,I", [(257, 256, 320, 192), (512, 256, 64, 64), (1300, 256, 64, 320), (4700, 320, 576, 320)])
+def test_split_weight_gradients_are_the_sums_of_their_parts(rows, split, d, I):
+    """The partial tiles of a split reduction, 2 to 15 of them, are added one by one from zero in fp32: bit for bit what calls with the rows of one
+    part each give, added in that order."""
+    import paper_2604_19241_amd as moe
+    say(f"[bwd split] {rows} rows by {split}, {d} x {I}")
+    cfg = moe_synth.small_config(T=rows, d=d, E=2, k=1, I=I)
+    inp = scaled_inputs(cfg, 77, 4.0)
+    inp["logits"][:, 1] = inp["logits"][:, 0] + 1.0     # every token to the second expert, in order
+    keys = ("dw_gate", "dw_up", "dw_down")
+
+    def gradients(first, last, split_rows, dtype):
+        shape = moe.make_shape(**dict(cfg.shape_dict(), T=last - first))
+        dev = {key: (v[first:last].contiguous() if key in ("x", "dy", "logits") else v).cuda() for key, v in inp.items()}
+        routing = moe.moe_route(shape, dev["logits"])
+        assert routing.counts.tolist() == [0, last - first]
+        saved = moe.alloc_saved(shape, "cuda")
+        moe.moe_fused_forward(shape, dev["x"], dev["w_gate"], dev["w_up"], dev["w_down"], routing, saved=saved)
+        opts = moe.make_opts(spin_limit_ms=500, dw_split_rows=split_rows, dw_accumulate=1 if dtype == torch.float32 else 0)
+        out = {"dx": torch.empty_like(dev["x"]), "dtopk_w": None}
+        out.update({key: torch.zeros_like(dev["w_" + key[3:]], dtype=dtype) for key in keys})
+        got = moe.moe_fused_backward(shape, dev["dy"], dev["x"], dev["w_gate"], dev["w_up"], dev["w_down"], routing, saved, opts=opts, out=out,
+                                     want_dtopk_w=False)
+        return {key: got[key].cpu() for key in keys}
+
+    want = {key: 0.0 for key in keys}
+    for first in range(0, rows, split):
+        part = gradients(first, min(first + split, rows), 0, torch.float32)
+        want = {key: want[key] + part[key] for key in keys}
+    added, written = gradients(0, rows, split, torch.float32), gradients(0, rows, split, torch.bfloat16)
+    for key in keys:
+        assert want[key][1].abs().max() > 0 and torch.equal(added[key], want[key]), key
+        assert torch.equal(written[key], want[key].to(torch.bfloat16)), key
+
+
 @pytest.mark.parametrize("d,I", [(65600, 64), (64, 65600)])
 def test_weight_gradients_of_more_than_256_row_tiles(d, I):
     """Every 256 rows of a weight gradient are a task's tile, 257 of them here."""
